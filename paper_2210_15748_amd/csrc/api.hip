@@ -85,6 +85,7 @@ struct dessert_index {
     hipStream_t stream = nullptr;
     void* proj = nullptr;       // device, [L*C][d] int8 or float (library-owned copy)
     void* proj_mfma = nullptr;  // device, MFMA-ordered int8 copy (or null)
+    void* proj_any = nullptr;   // device, copy ordered for the any-shape MFMA kernel (shapes without one of the above; or null)
     uint32_t* remap = nullptr;  // device, [L+1] table of the current score transform in Q16 (library-owned)
     uint32_t remap_max = 0;     // its largest entry
     const uint32_t* q_weights = nullptr;  // caller's, Q16 weights of the query vectors (Sec. 4.2)
@@ -172,7 +173,15 @@ dessert_status_t run_hash(const dessert_index* ix, const void* X, uint64_t n, ui
     if (n == 0) return DESSERT_OK;
     int algo = ix->hash_algo;
     bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)codes % 16 == 0);
-    if (algo == DESSERT_HASH_AUTO) algo = (use_mfma(ix) && aligned) ? DESSERT_HASH_MFMA : DESSERT_HASH_SCALAR;
+    if (algo == DESSERT_HASH_AUTO) {
+        // shapes without a fixed-shape MFMA kernel; its loads take any element's address, its stores are dwords
+        if (ix->proj_any && (uintptr_t)codes % 4 == 0) {
+            HIP_TRY(launch_hash_any(X, ix->cfg.dtype, ix->cfg.proj_kind, n, ix->cfg.d, ix->cfg.L, ix->cfg.C, ix->proj_any, codes,
+                                    ix->stream));
+            return DESSERT_OK;
+        }
+        algo = (use_mfma(ix) && aligned) ? DESSERT_HASH_MFMA : DESSERT_HASH_SCALAR;
+    }
     if (algo == DESSERT_HASH_MFMA) {
         if (!use_mfma(ix))
             return fail(DESSERT_EINVAL, "MFMA hashing needs int8 vectors with +-1 projections or fp16 vectors with "
@@ -585,6 +594,10 @@ dessert_status_t dessert_create(const dessert_config_t* c, dessert_index_t** out
     } else if (e == hipSuccess && is_f16_mfma(*c)) {
         e = hipMalloc(&ix->proj_mfma, mfma_f16_proj_bytes(c->d, c->L));
         if (e == hipSuccess) e = launch_repack_proj_f16((const float*)ix->proj, c->d, c->L, c->C, ix->proj_mfma, ix->stream);
+    } else if (e == hipSuccess && hash_any_supported(c->dtype, c->proj_kind, c->d, c->L, c->C)) {
+        e = hipMalloc(&ix->proj_any, hash_any_proj_bytes(c->dtype, c->proj_kind, c->d, c->L, c->C));
+        if (e == hipSuccess)
+            e = launch_repack_proj_any(ix->proj, c->dtype, c->proj_kind, c->d, c->L, c->C, ix->proj_any, ix->stream);
     }
     if (e == hipSuccess) e = hipMalloc((void**)&ix->remap, SCORE_TABLE_MAX * sizeof(uint32_t));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ix->upload_done, hipEventDisableTiming);
@@ -610,6 +623,7 @@ void dessert_destroy(dessert_index_t* ix) {
     if (ix->build_entry) (void)hipEventDestroy(ix->build_entry);
     if (ix->proj) (void)hipFree(ix->proj);
     if (ix->proj_mfma) (void)hipFree(ix->proj_mfma);
+    if (ix->proj_any) (void)hipFree(ix->proj_any);
     if (ix->remap) (void)hipFree(ix->remap);
     if (ix->dbg_flag) (void)hipFree(ix->dbg_flag);
     if (ix->f_cent) (void)hipFree(ix->f_cent);

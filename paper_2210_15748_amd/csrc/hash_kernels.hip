@@ -611,6 +611,342 @@ hipError_t launch_hash_mfma_f16(const void* X, uint64_t n, uint32_t d, uint32_t 
 }
 
 // ---------------------------------------------------------------------------
+// Hashing on the matrix cores for every other shape: any dimension from one k-step up to HASH_ANY_KS k-steps, any number
+// of tables, up to 16 bits per table, all four pairings of vector and projection type.
+//
+// Same product and lane layout as above (M = projection rows, N = vectors, a lane's 16 accumulators belong to one vector),
+// with three differences that make the shape a run-time value:
+//  - Bits are packed without padding: lane half g owns the tables [g*La, ...) of its vector and their bits are one stream, 16
+//    to an M-tile, cut into codes as they leave.  (A table of 11 bits takes 11 rows, not 16.)  The stream starts anew every
+//    16 tables of a half (a "segment": C tiles), so that a launch with few vectors can give the segments to different
+//    workgroups.
+//  - The k-steps of a row are whole 16-byte fragments at any byte offset; the last one, if d is no multiple of a k-step, is
+//    the window that ends at the row's end, with the elements that the step before has covered set to zero.  So every
+//    load stays inside its row, whatever d is.
+//  - A fragment loop is unrolled KS times with a uniform exit at the shape's own ks_n.
+// fp16 arithmetic (everything but int8 x +-1): each row of R is first scaled by a power of two that brings its largest entry
+// to [1, 2) (a sign does not change), then split in hi + lo/2048 as above (PARTS = 2; +-1 entries are exact in one part).
+// A projection that is not a number gives bit 0, as the comparison p >= 0 does, and an infinite element decides its
+// sign alone: the lo part is clamped to finite values before it joins.
+//
+// All of R stays in LDS when it fits ANY_RESIDENT bytes (two workgroups to a CU); else one tile is multiplied while the next
+// arrives.  Bound: HBM for a few tables, the matrix cores for many.  1.02M fp16 vectors of 200 dimensions, L = 8, C = 11:
+// 17.2 ms on the plain kernel (2.1 TFLOP/s of the method's), 0.130 ms here (3.3 TB/s of 4.8 that a copy reaches).  Against 64-bit
+// projections 2 of 88M bits differ here, 4 on the plain kernel (its fp32 sum is one chain of d additions).
+// The fixed-shape kernels above stay where they exist: int8 2M vectors of 128 dimensions, L = 32, C = 7 take 0.071 ms there and
+// 0.113 ms here; fp16 1M of 256, L = 64, C = 8 0.467 and 0.522 ms.
+constexpr uint32_t HASH_ANY_SEG = 16;            // tables of a lane half per segment
+constexpr size_t ANY_RESIDENT = 80 * 1024;
+
+struct HashAnyShape {
+    uint32_t d, L, C;
+    uint32_t La;          // tables of lane half 0 (half 1 has the other L - La <= La)
+    uint32_t ks;          // k-steps of a row
+    uint32_t segs, tiles; // segments, and M-tiles in all
+};
+
+template <bool F16>
+struct AnyAcc { typedef v16i type; };
+template <>
+struct AnyAcc<true> { typedef v16f type; };
+
+// XT: element type of the vectors; F16: fp16 arithmetic (else int8); KS >= shape.ks; NT n-tiles of 32 vectors per wave
+template <typename XT, bool F16, int PARTS, int KS, int NT>
+__global__ __launch_bounds__(256, 2) void hash_mfma_any_kernel(const XT* __restrict__ X, uint64_t n, HashAnyShape sh,
+                                                               const v4i* __restrict__ Rp, uint8_t* __restrict__ codes,
+                                                               uint32_t seg_first_step, uint32_t resident) {
+    constexpr int E = F16 ? 8 : 16;          // elements of a lane's fragment
+    constexpr int XB = E * (int)sizeof(XT);  // their bytes in memory (8 for int8 vectors in fp16 arithmetic)
+    typedef typename AnyAcc<F16>::type Acc;
+    extern __shared__ v4i sR[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 31, g = lane >> 5;
+    const uint32_t frags = PARTS * sh.ks;    // of 64 lanes each, per tile
+    const uint32_t cw = sh.C <= 8 ? 1 : 2, row_bytes = sh.L * cw;
+    const uint32_t cmask = (1u << sh.C) - 1u;
+    const uint32_t full = sh.d / (2 * E);    // whole k-steps
+    const uint32_t mine = g ? sh.L - sh.La : sh.La;   // tables of this lane half
+
+    auto copy_tile = [&](uint32_t tile, uint32_t slot) {  // whole waves; lane i lands 16*i bytes further
+        for (uint32_t f = (uint32_t)wave; f < frags; f += 4)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Rp + ((size_t)tile * frags + f) * 64 + lane),
+                                             (__attribute__((address_space(3))) void*)&sR[((size_t)slot * frags + f) * 64], 16, 0, 0);
+    };
+    // elements of the last, overlapping window that the whole k-steps have not covered
+    const int tail_base = (int)sh.d - 2 * E + g * E - (int)(full * 2 * E);   // window element e is new if tail_base + e >= 0
+    const bool has_tail = full * 2 * E != sh.d;
+
+    // grid.y > 1: segments are dealt round-robin (seg_first_step = grid.y), else this workgroup does all of them
+    const uint32_t seg0 = seg_first_step ? blockIdx.y : 0, seg_step = seg_first_step ? seg_first_step : 1;
+    if (resident) {
+        for (uint32_t t = 0; t < sh.tiles; ++t) copy_tile(t, t);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    const uint64_t block_vecs = 4 * 32 * NT;
+    const uint64_t n_blocks = (n + block_vecs - 1) / block_vecs;
+    for (uint64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+        const uint64_t v0 = blk * block_vecs + (uint64_t)wave * 32 * NT;
+        uint32_t slot = 0;
+        if (!resident) {
+            __syncthreads();   // every wave is done with both buffers
+            copy_tile(seg0 * sh.C, 0);
+        }
+        v4i b[NT][KS];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            uint64_t v = v0 + nt * 32 + col;
+            if (v >= n) v = n - 1;
+            const XT* row = X + v * sh.d + g * E;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint32_t at = (uint32_t)ks < full ? ks * 2 * E : sh.d - 2 * E;   // uniform, inside the row
+                XT raw[E];
+                __builtin_memcpy(raw, row + at, XB);
+                if constexpr (F16 && sizeof(XT) == 1) {
+                    v8h h;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) h[e] = (_Float16)(short)raw[e];
+                    __builtin_memcpy(&b[nt][ks], &h, 16);
+                } else {
+                    __builtin_memcpy(&b[nt][ks], raw, 16);
+                }
+            }
+            if (has_tail) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    if ((uint32_t)ks == full) {
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            uint32_t keep = 0;
+#pragma unroll
+                            for (int e = 0; e < E / 4; ++e)
+                                if (tail_base + w * (E / 4) + e >= 0) keep |= (E == 16 ? 0xFFu : 0xFFFFu) << (e * (E == 16 ? 8 : 16));
+                            b[nt][ks][w] &= (int)keep;
+                        }
+                    }
+            }
+        }
+        for (uint32_t seg = seg0; seg < sh.segs; seg += seg_step) {
+            const uint32_t seg_tables = sh.La - seg * HASH_ANY_SEG < HASH_ANY_SEG ? sh.La - seg * HASH_ANY_SEG : HASH_ANY_SEG;
+            const uint32_t tile0 = seg * sh.C;
+            const uint32_t seg_tiles = (seg_tables * sh.C + 15) / 16;
+            uint32_t buf[NT], word[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) buf[nt] = word[nt] = 0;
+            uint32_t nbits = 0, pos = 0, done = 0;   // bits waiting in buf, bit position in word, codes cut off so far
+            for (uint32_t t = 0; t < seg_tiles; ++t) {
+                const v4i* tile = sR + (size_t)(resident ? tile0 + t : slot) * frags * 64;
+                if (!resident) {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of the tile has landed
+                    __syncthreads();                                    // everyone's has, and nobody reads the other buffer any more
+                    const bool more = t + 1 < seg_tiles;
+                    if (more || seg + seg_step < sh.segs) copy_tile(more ? tile0 + t + 1 : (seg + seg_step) * sh.C, slot ^ 1);
+                    slot ^= 1;
+                }
+                Acc acc[PARTS][NT];
+#pragma unroll
+                for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[p][nt][r] = 0;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    if ((uint32_t)ks < sh.ks) {
+#pragma unroll
+                        for (int p = 0; p < PARTS; ++p) {
+                            const v4i a = tile[((uint32_t)p * sh.ks + ks) * 64 + lane];
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) {
+                                if constexpr (F16)
+                                    acc[p][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a),
+                                                                                       __builtin_bit_cast(v8h, b[nt][ks]), acc[p][nt], 0, 0, 0);
+                                else
+                                    acc[p][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[nt][ks], acc[p][nt], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    uint32_t neg = 0;
+#pragma unroll
+                    for (int r = 15; r >= 0; --r) {
+                        uint32_t bits;
+                        if constexpr (F16) {
+                            float p = acc[0][nt][r];
+                            if constexpr (PARTS == 2)
+                                p = __builtin_fmaf(__builtin_amdgcn_fmed3f(acc[PARTS - 1][nt][r], -1e30f, 1e30f), 1.0f / 2048.0f, p);
+                            bits = __float_as_uint(__builtin_fmaxf(p, -1.0f));   // not a number: negative
+                        } else {
+                            bits = (uint32_t)acc[0][nt][r];
+                        }
+                        neg = __builtin_amdgcn_alignbit(neg, bits, 31);
+                    }
+                    buf[nt] |= (~neg & 0xFFFFu) << nbits;   // fewer than C <= 16 bits were waiting
+                }
+                nbits += 16;
+                while (nbits >= sh.C && done < seg_tables) {   // the same for the whole grid
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        word[nt] |= (buf[nt] & cmask) << pos;
+                        buf[nt] >>= sh.C;
+                    }
+                    nbits -= sh.C;
+                    pos += 8 * cw;
+                    ++done;
+                    if (pos == 32) {   // tables are owned in whole dwords of codes
+                        const uint32_t first = seg * HASH_ANY_SEG + done - 4 / cw;   // the dword's first table in this half
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) {
+                            const uint64_t v = v0 + nt * 32 + col;
+                            if (v < n && first < mine)
+                                *(uint32_t*)(codes + v * row_bytes + ((g ? sh.La : 0u) + first) * cw) = word[nt];
+                            word[nt] = 0;
+                        }
+                        pos = 0;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Re-ordered matrix: [tiles][PARTS][ks][64 lanes][16 bytes].  One workgroup per tile: the scale of each of its 32 rows first.
+template <typename RT, bool F16, int PARTS>
+__global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restrict__ R, HashAnyShape sh, void* __restrict__ Rp) {
+    constexpr uint32_t E = F16 ? 8 : 16;
+    __shared__ float scale[32];
+    __shared__ uint32_t row_of[32];   // row of R, all ones: no such table
+    const uint32_t tile = blockIdx.x, seg = tile / sh.C, tid = threadIdx.x;
+    if (tid < 32) {
+        const uint32_t i = tid, g = (i >> 2) & 1, r = 4 * (i >> 3) + (i & 3);   // accumulator r of lane half g
+        const uint32_t bit = (tile - seg * sh.C) * 16 + r;                     // of the segment's stream
+        const uint32_t j = seg * HASH_ANY_SEG + bit / sh.C, c = bit % sh.C;
+        const bool have = bit / sh.C < HASH_ANY_SEG && j < (g ? sh.L - sh.La : sh.La);
+        const uint32_t row = have ? ((g ? sh.La : 0u) + j) * sh.C + c : 0xFFFFFFFFu;
+        row_of[i] = row;
+        float s = 1.0f;
+        if constexpr (F16) {
+            float top = 0.0f;
+            if (have)
+                for (uint32_t k = 0; k < sh.d; ++k) {
+                    const float a = __builtin_fabsf((float)R[(size_t)row * sh.d + k]);
+                    if (a < __builtin_inff() && a > top) top = a;
+                }
+            if (top > 0.0f) {
+                int e = (int)((__float_as_uint(top) >> 23) & 0xFF) - 127;   // a subnormal row is scaled as far as 2^126 goes
+                e = e < -126 ? -126 : e;
+                s = __builtin_ldexpf(1.0f, -e);
+            }
+        }
+        scale[i] = s;
+    }
+    __syncthreads();
+    const uint32_t total = PARTS * sh.ks * 64 * E;
+    for (uint32_t idx = tid; idx < total; idx += 256) {
+        const uint32_t e = idx % E, l = (idx / E) & 63, ks = (idx / E / 64) % sh.ks, part = idx / E / 64 / sh.ks;
+        const uint32_t row = row_of[l & 31];
+        // element of the row: whole k-steps, then the window that ends at d, whose covered elements count nothing
+        const uint32_t full = sh.d / (2 * E), in = (l >> 5) * E + e;
+        const uint32_t k = ks < full ? ks * 2 * E + in : sh.d - 2 * E + in;
+        const bool have = row != 0xFFFFFFFFu && (ks < full || k >= full * 2 * E);
+        if constexpr (F16) {
+            const float x = have ? (float)R[(size_t)row * sh.d + k] * scale[l & 31] : 0.0f;
+            const _Float16 hi = (_Float16)x;
+            const float rest = (x - (float)hi) * 2048.0f;
+            const _Float16 lo = (rest - rest == 0.0f) ? (_Float16)rest : (_Float16)0.0f;   // an entry that is not finite: hi alone
+            ((_Float16*)Rp)[(size_t)tile * total + idx] = part ? lo : hi;
+        } else {
+            ((int8_t*)Rp)[(size_t)tile * total + idx] = have ? (int8_t)R[(size_t)row * sh.d + k] : (int8_t)0;
+        }
+    }
+}
+
+// dtype / proj_kind as in dessert.h (0: int8 / +-1, 1: fp16 / Gaussian)
+static bool any_is_f16(uint32_t dtype, uint32_t proj_kind) { return dtype != 0 || proj_kind != 0; }
+static uint32_t any_parts(uint32_t proj_kind) { return proj_kind == 0 ? 1 : 2; }
+static HashAnyShape any_shape(uint32_t dtype, uint32_t d, uint32_t L, uint32_t C, uint32_t proj_kind) {
+    HashAnyShape s{};
+    const uint32_t kstep = any_is_f16(dtype, proj_kind) ? 16 : 32;
+    s.d = d; s.L = L; s.C = C;
+    s.La = C <= 8 ? 4 * ((L + 7) / 8) : L / 2;   // whole dwords of codes: 4 one-byte codes, 2 of 16 bits
+    s.ks = (d + kstep - 1) / kstep;
+    s.segs = (s.La + HASH_ANY_SEG - 1) / HASH_ANY_SEG;
+    s.tiles = (s.segs - 1) * C + ((s.La - (s.segs - 1) * HASH_ANY_SEG) * C + 15) / 16;   // a full segment: C tiles
+    return s;
+}
+
+bool hash_any_supported(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C) {
+    const uint32_t kstep = any_is_f16(dtype, proj_kind) ? 16 : 32;
+    return d >= kstep && d <= HASH_ANY_MAX_D && L >= 4 && L % 4 == 0 && L <= 128 && C >= 1 && C <= 16;
+}
+
+size_t hash_any_proj_bytes(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C) {
+    const HashAnyShape s = any_shape(dtype, d, L, C, proj_kind);
+    return (size_t)s.tiles * any_parts(proj_kind) * s.ks * 1024;
+}
+
+hipError_t launch_repack_proj_any(const void* R, uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C, void* Rp,
+                                  hipStream_t stream) {
+    if (!hash_any_supported(dtype, proj_kind, d, L, C)) return hipErrorInvalidValue;
+    const HashAnyShape s = any_shape(dtype, d, L, C, proj_kind);
+    const dim3 grid(s.tiles), block(256);
+    if (!any_is_f16(dtype, proj_kind))
+        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, false, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp);
+    else if (proj_kind == 0)
+        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, true, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp);
+    else
+        hipLaunchKernelGGL((repack_proj_any_kernel<float, true, 2>), grid, block, 0, stream, (const float*)R, s, Rp);
+    return hipGetLastError();
+}
+
+template <typename XT, bool F16, int PARTS, int KS, int NT>
+static hipError_t launch_any_t(const void* X, uint64_t n, const HashAnyShape& s, const void* Rp, uint8_t* codes, hipStream_t stream) {
+    auto kern = hash_mfma_any_kernel<XT, F16, PARTS, KS, NT>;
+    static hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 2 * KS * 1024 > (int)ANY_RESIDENT ? 2 * 2 * KS * 1024 : (int)ANY_RESIDENT);
+    if (attr != hipSuccess) return attr;
+    const size_t tile_bytes = (size_t)PARTS * s.ks * 1024, all = tile_bytes * s.tiles;
+    const uint64_t block_vecs = 4 * 32 * NT;
+    uint64_t blocks = (n + block_vecs - 1) / block_vecs;
+    // few vectors: the segments go to different workgroups (a workgroup then walks over C tiles instead of all)
+    const uint32_t gy = (s.segs > 1 && blocks < 256) ? s.segs : 1;
+    const bool resident = gy == 1 && all <= ANY_RESIDENT && blocks > 512;   // short runs would wait for tiles they use once
+    if (blocks > 2048) blocks = 2048;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, gy), dim3(256), resident ? all : 2 * tile_bytes, stream, (const XT*)X, n, s,
+                       (const v4i*)Rp, codes, gy > 1 ? gy : 0u, resident ? 1u : 0u);
+    return hipGetLastError();
+}
+
+template <typename XT, bool F16, int PARTS>
+static hipError_t launch_any_ks(const void* X, uint64_t n, const HashAnyShape& s, const void* Rp, uint8_t* codes, hipStream_t stream) {
+    // two n-tiles per wave while their fragments leave room for the accumulators of two waves per SIMD
+    if (s.ks <= 4) return launch_any_t<XT, F16, PARTS, 4, 2>(X, n, s, Rp, codes, stream);
+    if (s.ks <= 8) return launch_any_t<XT, F16, PARTS, 8, 2>(X, n, s, Rp, codes, stream);
+    if constexpr (F16) {
+        if (s.ks <= 13) return launch_any_t<XT, F16, PARTS, 13, 2>(X, n, s, Rp, codes, stream);
+        if (s.ks <= 16) return launch_any_t<XT, F16, PARTS, 16, 2>(X, n, s, Rp, codes, stream);
+        if (s.ks <= 24) return launch_any_t<XT, F16, PARTS, 24, 1>(X, n, s, Rp, codes, stream);
+    } else {
+        if (s.ks <= 12) return launch_any_t<XT, F16, PARTS, 12, 2>(X, n, s, Rp, codes, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_hash_any(const void* X, uint32_t dtype, uint32_t proj_kind, uint64_t n, uint32_t d, uint32_t L, uint32_t C,
+                           const void* Rp, uint8_t* codes, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    if (!hash_any_supported(dtype, proj_kind, d, L, C) || (uintptr_t)codes % 4) return hipErrorInvalidValue;
+    const HashAnyShape s = any_shape(dtype, d, L, C, proj_kind);
+    if (dtype == 0)
+        return proj_kind == 0 ? launch_any_ks<int8_t, false, 1>(X, n, s, Rp, codes, stream)
+                              : launch_any_ks<int8_t, true, 2>(X, n, s, Rp, codes, stream);
+    return proj_kind == 0 ? launch_any_ks<_Float16, true, 1>(X, n, s, Rp, codes, stream)
+                          : launch_any_ks<_Float16, true, 2>(X, n, s, Rp, codes, stream);
+}
+
+// ---------------------------------------------------------------------------
 // Plain streaming read (measurement aid): what HBM delivers to a kernel that does nothing but
 // read, for comparison with the 8 TB/s nameplate and with the scoring kernel's rate.
 __global__ __launch_bounds__(256) void read_probe_kernel(const v4i* __restrict__ p, size_t n16, int* sink) {

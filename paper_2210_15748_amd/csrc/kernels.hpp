@@ -31,6 +31,16 @@ bool hash_mfma_f16_supported(uint32_t d, uint32_t L, uint32_t C);
 hipError_t launch_hash_mfma_f16(const void* X, uint64_t n, uint32_t d, uint32_t L, uint32_t C, const void* Rp,
                                 uint8_t* codes, hipStream_t stream);
 
+// The matrix-core kernel for the other shapes: any L and C, d from one k-step (32 for int8 x +-1, else 16) to HASH_ANY_MAX_D,
+// every pairing of types (dtype, proj_kind as in dessert.h).  codes 4-byte aligned; X at any element's address.
+constexpr uint32_t HASH_ANY_MAX_D = 384;
+bool hash_any_supported(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C);
+size_t hash_any_proj_bytes(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C);
+hipError_t launch_repack_proj_any(const void* R, uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C, void* Rp,
+                                  hipStream_t stream);
+hipError_t launch_hash_any(const void* X, uint32_t dtype, uint32_t proj_kind, uint64_t n, uint32_t d, uint32_t L, uint32_t C,
+                           const void* Rp, uint8_t* codes, hipStream_t stream);
+
 // One thread per (vector, table); any d, L, C <= 16.  dtype/proj_kind as in dessert.h.  Codes are one byte
 // per table for C <= 8, else two.
 hipError_t launch_hash_scalar(const void* X, uint32_t dtype, uint64_t n, uint32_t d, const void* R, uint32_t proj_kind,

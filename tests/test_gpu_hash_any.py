@@ -1,0 +1,100 @@
+"""The any-shape matrix-core hashing kernel (DESSERT_HASH_AUTO where no fixed-shape kernel exists) against the CPU oracle and
+against the plain kernel (DESSERT_HASH_SCALAR)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2210_15748_amd as dz
+from oracle import oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def both(xt, pk, X, R, L, Cb):
+    ix = dz.create(X.shape[1], L, Cb, dtype=dz.I8 if xt == "i8" else dz.F16,
+                   proj_kind=dz.PROJ_RADEMACHER_I8 if pk == "pm1" else dz.PROJ_GAUSSIAN_F32, proj=torch.from_numpy(R).to(DEV))
+    Xd = torch.from_numpy(X).to(DEV)
+    auto = dz.hash(ix, Xd).cpu().numpy()
+    dz.set_algo(ix, dz.HASH_SCALAR)
+    return auto, dz.hash(ix, Xd).cpu().numpy()
+
+
+def i8_inputs(rng, n, d, P):
+    X = rng.integers(-127, 128, (n, d)).astype(np.int8)
+    X[0] = 0
+    return X, (rng.integers(0, 2, (P, d)) * 2 - 1).astype(np.int8)
+
+
+# d: one k-step of 32, either side of whole k-steps, the largest.  L, C: tables that divide unevenly over the two lane halves
+# (12, 20, 28), several segments of 16 tables a half (36, 96, 100), code bits that straddle M-tiles, one-byte and 16-bit codes.
+# n: a lone vector, either side of a wave's 64 and of a workgroup's 256 vectors
+@pytest.mark.parametrize("d,L,Cb,n", [(32, 20, 5, 1), (33, 4, 1, 63), (47, 12, 7, 65), (63, 28, 8, 255), (96, 24, 6, 257), (100, 96, 3, 300),
+                                      (127, 100, 4, 333), (200, 8, 11, 1000), (255, 36, 9, 129), (300, 48, 16, 70), (383, 24, 13, 31),
+                                      (384, 128, 8, 140), (200, 16, 5, 140_003)])
+def test_i8_any_shape_bit_exact(d, L, Cb, n):
+    print("[case]", d, L, Cb, n, flush=True)
+    rng = np.random.default_rng(d * 7 + L)
+    X, R = i8_inputs(rng, n, d, L * Cb)
+    auto, scalar = both("i8", "pm1", X, R, L, Cb)
+    assert np.array_equal(auto, scalar)
+    if n <= 1000:
+        want = orc.hash_i8(X, R, L, Cb)
+        assert np.array_equal(auto, want)
+
+
+# fp32 sums of exact products: a sign may differ from the 64-bit one only where the projection is within the rounding of the
+# sum, at most (d + 2^3) * 2^-24 * sum |r_i x_i| with any order of adding, plus 2^-23 of every |r_i x_i| for the two-part matrix
+@pytest.mark.parametrize("xt,pk", [("f16", "gauss"), ("f16", "pm1"), ("i8", "gauss")])
+@pytest.mark.parametrize("d,L,Cb,n", [(16, 8, 8, 33), (17, 12, 3, 500), (50, 24, 11, 300), (200, 8, 11, 70_001), (200, 96, 5, 257), (255, 20, 7, 100),
+                                      (300, 24, 12, 1000), (384, 4, 16, 65)])
+def test_fp_any_shape_signs_within_rounding(xt, pk, d, L, Cb, n):
+    print("[case]", xt, pk, d, L, Cb, n, flush=True)
+    rng = np.random.default_rng(d + L * Cb)
+    if xt == "i8":
+        X = rng.integers(-127, 128, (n, d)).astype(np.int8)
+    else:
+        X = (rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float16)
+    X[0] = 0
+    R = (rng.integers(0, 2, (L * Cb, d)) * 2 - 1).astype(np.int8) if pk == "pm1" else rng.standard_normal((L * Cb, d)).astype(np.float32)
+    if pk == "gauss":
+        R[1] *= 1e-12          # rows far from unit scale, and an all-zero one: the sign does not depend on a row's scale
+        R[2] *= 1e12
+        R[3] = 0
+    auto, _ = both(xt, pk, X, R, L, Cb)
+    X64, R64 = X.astype(np.float64), R.astype(np.float64)
+    p = X64 @ R64.T
+    bound = ((d + 8) * 2.0 ** -24 + 2.0 ** -23) * (np.abs(X64) @ np.abs(R64).T)
+    bits = ((auto.astype(np.int64)[:, :, None] >> np.arange(Cb)) & 1).reshape(n, L * Cb)
+    diff = bits != (p >= 0)
+    assert auto.astype(np.int64).max() < (1 << Cb)
+    assert np.all(np.abs(p)[diff] <= bound[diff])
+    assert diff.mean() <= 1e-4
+
+
+def test_fp_any_shape_infinite_and_nan_elements_as_the_plain_kernel():
+    """Rows with infinities (their sign decides), opposed infinities and NaN (not >= 0: bit 0), and neighbours that must
+    not see them, at a dimension whose last k-step overlaps the one before."""
+    rng = np.random.default_rng(5)
+    for d in (50, 200):
+        X = (rng.standard_normal((300, d)) / np.sqrt(d)).astype(np.float16)
+        X[3, 5], X[4, d - 1], X[5, 0] = np.inf, -np.inf, np.nan
+        X[8, 1], X[8, d - 2] = np.inf, np.inf
+        R = rng.standard_normal((24 * 7, d)).astype(np.float32)
+        auto, scalar = both("f16", "gauss", X, R, 24, 7)
+        special = [3, 4, 5, 8]
+        assert np.array_equal(auto[special], scalar[special])
+        assert (auto != scalar).mean() <= 1e-4
+
+
+def test_any_shape_at_unaligned_vector_addresses():
+    """Vectors that start at an odd element: the kernel's loads take any element's address."""
+    rng = np.random.default_rng(6)
+    d, L, Cb, n = 100, 24, 6, 300
+    X, R = i8_inputs(rng, n, d, L * Cb)
+    ix = dz.create(d, L, Cb, proj=torch.from_numpy(R).to(DEV))
+    room = torch.zeros(n * d + 16, dtype=torch.int8, device=DEV)
+    for shift in (1, 2, 7):
+        v = room[shift:shift + n * d].view(n, d)
+        v.copy_(torch.from_numpy(X).to(DEV))
+        assert np.array_equal(dz.hash(ix, v).cpu().numpy(), orc.hash_i8(X, R, L, Cb))
