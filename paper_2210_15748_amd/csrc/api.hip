@@ -439,16 +439,19 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     int algo = ix->score_algo;
     // sigma = mean has a mask-table form for phi = identity only (sums of counts), and for documents short enough
     const bool mean_on_masklut = sa.sigma_mean && sa.phi_identity && ix->max_len <= MASKLUT_MEAN_MAX_LEN;
-    if (algo == DESSERT_SCORE_AUTO && sa.sigma_mean && !mean_on_masklut) algo = DESSERT_SCORE_BYTECMP;
-    // the mask-table kernel lets idle lanes read code row 0, so it needs a non-empty code array
-    if (algo == DESSERT_SCORE_AUTO || ix->n_vectors == 0)
-        algo = (score_masklut_supported(ix->cfg.L, ix->cfg.C) && ix->n_vectors) ? DESSERT_SCORE_MASKLUT
-                                                                                : DESSERT_SCORE_BYTECMP;
+    // the mask-table kernels let idle lanes read code row 0, so they need a non-empty code array
+    bool any_tables = false;   // the mask-table kernel for any number of tables
+    if (algo == DESSERT_SCORE_AUTO || ix->n_vectors == 0) {
+        const bool fixed = score_masklut_supported(ix->cfg.L, ix->cfg.C) && (!sa.sigma_mean || mean_on_masklut);
+        any_tables = ix->n_vectors && !fixed && bt.max_scored <= (1ull << 29) && score_maskany_supported(ix->cfg.L, ix->cfg.C) &&
+                     (!sa.sigma_mean || score_maskany_mean_fits(ix->max_len, ix->remap_max));
+        algo = (ix->n_vectors && fixed) ? DESSERT_SCORE_MASKLUT : DESSERT_SCORE_BYTECMP;
+    }
     // Query preparation: the query codes and, for the mask-table kernel with long candidate lists, each list's slots
     // grouped by document id range (with fewer than 8 lists the one workgroup per list of the grouping costs more
     // than the scoring gains).  The grouping rides in the hashing launch when that is the int8 MFMA kernel.
     CandOrderArgs oa{};
-    bool grouping = algo == DESSERT_SCORE_MASKLUT && score_masklut_supported(ix->cfg.L, ix->cfg.C) &&
+    bool grouping = (any_tables || (algo == DESSERT_SCORE_MASKLUT && score_masklut_supported(ix->cfg.L, ix->cfg.C))) &&
                     cand_ids && B >= 8 && bt.max_scored >= score_order_min() && order_space(ix, B, bt.total_scored);
     if (grouping) {
         const uint32_t fused_ranges = hash_mfma_fused_ranges(ix->cfg.d, ix->cfg.L, ix->cfg.C);
@@ -469,6 +472,8 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
             return fail(DESSERT_EINVAL, "mask-table scoring needs L in {8,16,32,64,128} (C <= 8), or L = 8 with C <= 11, "
                                         "L = 16 with C <= 10, L = 32 with C = 9");
         HIP_TRY(launch_score_masklut(sa, ix->stream, ix->last_score_kernel, sizeof(ix->last_score_kernel)));
+    } else if (any_tables) {
+        HIP_TRY(launch_score_maskany(sa, ix->stream, ix->last_score_kernel, sizeof(ix->last_score_kernel)));
     } else if (algo == DESSERT_SCORE_BYTECMP) {
         HIP_TRY(launch_score_bytecmp(sa, ix->stream, ix->last_score_kernel, sizeof(ix->last_score_kernel)));
     } else {

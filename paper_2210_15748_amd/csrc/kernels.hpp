@@ -106,6 +106,11 @@ bool score_masklut_supported(uint32_t L, uint32_t C);
 // longest document (in vectors) for which the mask-table kernel can form sigma = mean (32-bit numerators)
 constexpr uint64_t MASKLUT_MEAN_MAX_LEN = 65535;
 hipError_t launch_score_masklut(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
+// The same method at any number of tables whose masks (4 * L * 2^C bytes) fit 128 KB of LDS, for every transform; sigma = mean
+// when score_maskany_mean_fits(longest document, largest phi).  The fixed-size kernel above is the faster one where it exists.
+bool score_maskany_supported(uint32_t L, uint32_t C);
+bool score_maskany_mean_fits(uint64_t max_len, uint32_t phi_max);
+hipError_t launch_score_maskany(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
 
 // ---- candidate filter (Sec. 5 "Filtering") ---------------------------------------------
 bool filter_supported(uint32_t d);

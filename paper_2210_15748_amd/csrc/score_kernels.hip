@@ -776,6 +776,358 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     }
 }
 
+// ---------------------------------------------------------------------------
+// The mask-table method at any number of tables, and for sigma = mean of any phi: what would otherwise be the code-compare
+// kernel's work, at one comparison per dword and query vector.  (Callers tell the two families apart by how
+// dessert_last_score_kernel's text begins, hence this kernel's name.)
+//
+// Tables are taken 16 at a time: their masks go through carry-save adders into the planes of weight 1, 2, 4, 8 and the
+// carry of weight 16 ripples into the planes above (15 full adders and 4 half adders for 16 tables, against 1.9
+// operations per table of a tree whose size is fixed at compile time); a group of fewer tables takes the adders of 8 and 4.
+//   MEAN = false   sigma = max, as in the kernel above (raw counts, a tabulated phi, weights).
+//   MEAN = true    sigma = mean of phi(count): phi is not linear in the planes, so the counts of the 32 query vectors are
+//                  turned from planes to bytes (an 8 x 8 bit transposition in three steps, 48 operations), looked up in LDS one by
+//                  one and added to 32 sums per lane; a document's eight lanes add theirs by halves, four query vectors left to
+//                  each.  The host lets this form run when (longest document) * (largest phi) fits 32 bits.
+// NG = groups of 16 tables (an upper bound; the loops leave at the shape's own number), CW = bytes per code, 2^cb entries per
+// table.  Table and phi table lie in dynamic LDS.  Bound: vector ALU (two operations for an address, 2.4 for the count, and
+// per query vector 4 with MEAN).  Measured against the code-compare kernel:
+// mean of the sigmoid, L = 32, C = 7, 8 query sets x 20 000 documents 5.04 -> 0.147 ms; raw counts, L = 96, C = 4, 4 sets of 48 vectors
+// x 68 576 documents 75.3 -> 0.94 ms; Eq. 1 with weights, L = 48, C = 6, 12 sets of 8 x 5479 0.84 -> 0.079 ms.
+constexpr uint32_t MASKANY_MAX_TABLE = 128 * 1024;
+
+struct MaskanyLaunch {
+    uint32_t cb;               // log2 of a table's entries
+    uint32_t docs_per_block, gy_linear, gz;
+};
+
+__device__ inline void full_add(uint32_t& sum, uint32_t x, uint32_t y, uint32_t& carry) {
+    const uint32_t s = sum;
+    sum = xor3(s, x, y);
+    carry = maj3(s, x, y);
+}
+template <int FROM>
+__device__ inline void ripple(uint32_t (&p)[8], uint32_t carry) {   // planes FROM.. += carry
+#pragma unroll
+    for (int i = FROM; i < 8; ++i) {
+        const uint32_t x = p[i];
+        p[i] = x ^ carry;
+        carry &= x;
+    }
+}
+__device__ inline uint32_t add4(uint32_t (&p)[8], const uint32_t* m) {   // four masks; returns the carry of weight 4
+    uint32_t c0, c1, d;
+    full_add(p[0], m[0], m[1], c0);
+    full_add(p[0], m[2], m[3], c1);
+    full_add(p[1], c0, c1, d);
+    return d;
+}
+__device__ inline uint32_t add8(uint32_t (&p)[8], const uint32_t* m) {
+    const uint32_t d0 = add4(p, m), d1 = add4(p, m + 4);
+    uint32_t e;
+    full_add(p[2], d0, d1, e);
+    return e;
+}
+__device__ inline void add16(uint32_t (&p)[8], const uint32_t* m) {
+    const uint32_t e0 = add8(p, m), e1 = add8(p, m + 8);
+    uint32_t f;
+    full_add(p[3], e0, e1, f);
+    ripple<4>(p, f);
+}
+
+// p[i] = bit i of 32 values  ->  byte k of p[j] = value 8 * k + j
+__device__ inline void planes_to_bytes(uint32_t (&p)[8]) {
+    auto step = [&](int i, int j, int s, uint32_t keep) {   // exchange the s-wide fields: high fields of p[i] with low fields of p[j]
+        const uint32_t a = p[i], b = p[j];
+        p[i] = select3(keep, a, b << s);
+        p[j] = select3(keep, a >> s, b);
+    };
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) step(i, i + 1, 1, 0x55555555u);
+#pragma unroll
+    for (int i = 0; i < 8; i += 4)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) step(i + j, i + j + 2, 2, 0x33333333u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) step(i, i + 4, 4, 0x0F0F0F0Fu);
+}
+
+template <int NG, int CW, bool MEAN>
+__global__ __launch_bounds__(1024) void score_bytecmp_kernel_masks(ScoreArgs a, MaskanyLaunch ml) {
+    extern __shared__ uint32_t any_lds[];   // masks [L][2^cb], then phi [L+1]
+    __shared__ LutBlockMeta meta;
+    constexpr int G = 8;                    // lanes per document
+    constexpr int WG16 = 4 * CW;            // dwords of 16 codes
+    const uint32_t T = blockDim.x;
+    const uint32_t L = a.L, LW = L * CW / 4, row_bytes = L * CW;
+    const uint32_t lut_words = L << ml.cb, gz = ml.gz;
+    uint32_t* phi = any_lds + lut_words;
+
+    // as in the kernel above: linear grid with the XCD-aware decode, chunk groups
+    uint32_t bx_idx, by_idx;
+    if (ml.gy_linear) {
+        const uint32_t xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+        by_idx = j % ml.gy_linear;
+        bx_idx = (j / ml.gy_linear) * 8 + xcd;
+    } else {
+        bx_idx = blockIdx.x;
+        by_idx = blockIdx.y;
+    }
+    const uint32_t cz = by_idx % gz, b = by_idx / gz;
+    const Span sp = query_span(a, b);
+    const uint64_t first = (uint64_t)bx_idx * ml.docs_per_block;
+    if (first >= sp.count) return;
+    const uint32_t ndocs = (uint32_t)(first + ml.docs_per_block < sp.count ? ml.docs_per_block : sp.count - first);
+    const uint32_t q_lo = q_begin(a, b), q_len = q_begin(a, b + 1) - q_lo;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, sub = lane & (G - 1), grp = lane / G;
+
+    auto build_table = [&](uint32_t c0) {   // masks of the query vectors c0 .. c0+31; the table has been cleared
+        const uint32_t n_ent = (q_len - c0 < 32 ? q_len - c0 : 32u) * L;
+        for (uint32_t i = tid; i < n_ent; i += T) {
+            const uint32_t q = i / L, t = i - q * L;
+            const size_t at = (size_t)(q_lo + c0) * L + i;
+            const uint32_t h = CW == 1 ? (uint32_t)a.qcodes[at] : (uint32_t)((const uint16_t*)a.qcodes)[at];
+            atomicOr(&any_lds[(t << ml.cb) + h], 1u << q);
+        }
+    };
+    const bool have_doc = tid < ndocs;
+    uint64_t my_id = 0;
+    uint32_t my_slot = 0;
+    if (have_doc) {
+        const uint64_t pos = first + tid;
+        my_slot = (uint32_t)(a.order ? a.order[sp.base + pos] : pos);
+        my_id = a.cand_ids ? a.cand_ids[sp.base + my_slot] : pos;
+    }
+    for (uint32_t i = tid; i < lut_words; i += T) any_lds[i] = 0;
+    if constexpr (MEAN)
+        for (uint32_t i = tid; i <= L; i += T) phi[i] = a.remap[i];
+    for (uint32_t i = tid; i < LUT_BINS; i += T) meta.bin[i] = 0;
+    if (tid == 0) meta.next = 0;
+    const bool empty_slot = a.cand_ids && my_id == 0xFFFFFFFFull;   // kept as a document of no vectors with start ~0
+    uint64_t my_lo = ~0ull, my_hi = ~0ull;
+    if (have_doc && !empty_slot) {
+        my_lo = a.offsets[my_id];
+        my_hi = a.offsets[my_id + 1];
+    }
+    __syncthreads();
+    const uint32_t c_first = cz * 32;
+    if (c_first < q_len) build_table(c_first);
+    uint32_t my_class = 0;
+    if (have_doc) {
+        const uint32_t m = (uint32_t)(my_hi - my_lo);
+        meta.lo[tid] = my_lo;
+        meta.m[tid] = m;
+        meta.slot[tid] = a.order ? my_slot : (uint32_t)(first + tid);
+        const uint32_t rounds = (m + G - 1) / G;
+        my_class = rounds < LUT_BINS ? LUT_BINS - 1 - rounds : 0;   // class 0 = longest
+        atomicAdd(&meta.bin[my_class], 1u);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        const uint32_t c = meta.bin[lane];
+        uint32_t incl = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(incl, off, 64);
+            if ((int)lane >= off) incl += o;
+        }
+        meta.bin[lane] = incl - c;
+    }
+    __syncthreads();
+    if (have_doc) meta.order[atomicAdd(&meta.bin[my_class], 1u)] = (uint16_t)tid;
+
+    for (uint32_t c0 = c_first; c0 < q_len; c0 += gz * 32) {
+        if (c0 != c_first) {
+            __syncthreads();   // the previous chunk's readers are done
+            for (uint32_t i = tid; i < lut_words; i += T) any_lds[i] = 0;
+            if (tid == 0) meta.next = 0;
+            __syncthreads();
+            build_table(c0);
+        }
+        __syncthreads();       // table and `order` complete
+        for (;;) {
+            uint32_t claim = 0;
+            if (lane == 0) claim = atomicAdd(&meta.next, 64u / G);
+            claim = __builtin_amdgcn_readfirstlane(claim);
+            if (claim >= ndocs) break;
+            const uint32_t slot = claim + grp;
+            const bool valid = slot < ndocs;
+            const uint32_t doc = valid ? meta.order[slot] : 0;
+            const uint32_t m = valid ? meta.m[doc] : 0;
+            const uint64_t lo = m ? meta.lo[doc] : 0;   // lanes with nothing to do read row 0 (the index holds a vector)
+            const uint32_t last_j = m ? m - 1 : 0;
+            const uint8_t* doc_codes = a.codes + lo * row_bytes;
+            auto row_of = [&](uint32_t j) {   // row j of the document, past its end the last one
+                return (const uint32_t*)(doc_codes + (size_t)(j < last_j ? j : last_j) * row_bytes);
+            };
+            auto load_group = [&](const uint32_t* row, int gi, uint32_t (&dst)[WG16]) {   // its codes of tables 16 gi .. 16 gi + 15
+#pragma unroll
+                for (int w = 0; w < WG16; w += 4) {
+                    const uint32_t at = gi * WG16 + w;
+                    if (at + 4 <= LW) {
+                        __builtin_memcpy(&dst[w], row + at, 16);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (at + i < LW) dst[w + i] = row[at + i];
+                    }
+                }
+            };
+            uint32_t mx[8], sum[MEAN ? 32 : 1];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) mx[p] = 0;
+#pragma unroll
+            for (int i = 0; i < (MEAN ? 32 : 1); ++i) sum[i] = 0;
+
+            uint32_t dw[WG16], ahead[WG16];   // the group at hand, and the one that is on its way meanwhile
+            auto process = [&](const uint32_t* row, const uint32_t* next_row, bool counts) {
+                uint32_t cnt[8];
+#pragma unroll
+                for (int p = 0; p < 8; ++p) cnt[p] = 0;
+                const char* lds_bytes = reinterpret_cast<const char*>(any_lds);
+                const uint32_t tstep = 4u << ml.cb;
+#pragma unroll
+                for (int gi = 0; gi < NG; ++gi) {
+                    if ((uint32_t)gi * 16 < L) {
+                        const uint32_t here = L - gi * 16 < 16 ? L - gi * 16 : 16;   // 4, 8, 12 or 16 tables
+                        if (gi + 1 < NG && (uint32_t)(gi + 1) * 16 < L) load_group(row, gi + 1, ahead);
+                        else load_group(next_row, 0, ahead);
+                        uint32_t msk[16];
+                        auto read = [&](int t0, int nt) {
+#pragma unroll
+                            for (int t = t0; t < t0 + nt; ++t) {
+                                const uint32_t code = CW == 1 ? (dw[t / 4] >> (8 * (t % 4))) & 0xFFu
+                                                              : (dw[t / 2] >> (16 * (t % 2))) & 0xFFFFu;
+                                msk[t] = *(const uint32_t*)(lds_bytes + (code * 4 + (uint32_t)(gi * 16 + t) * tstep));
+                            }
+                        };
+                        if (here == 16) {
+                            read(0, 16);
+                            add16(cnt, msk);
+                        } else {
+                            if (here >= 8) {
+                                read(0, 8);
+                                ripple<3>(cnt, add8(cnt, msk));
+                            }
+                            if (here == 4) {
+                                read(0, 4);
+                                ripple<2>(cnt, add4(cnt, msk));
+                            } else if (here == 12) {
+                                read(8, 4);
+                                ripple<2>(cnt, add4(cnt, msk + 8));
+                            }
+                        }
+#pragma unroll
+                        for (int w = 0; w < WG16; ++w) dw[w] = ahead[w];
+                    }
+                }
+                if constexpr (!MEAN) {
+                    planes_max<8>(mx, cnt);
+                } else {
+                    const uint32_t keep = counts ? ~0u : 0u;   // rows past the document's end count 0, and phi(0) = 0
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) cnt[p] &= keep;
+                    planes_to_bytes(cnt);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) sum[4 * j + k] += phi[(cnt[j] >> (8 * k)) & 0xFFu];   // query vector 8 k + j
+                }
+            };
+            const uint32_t* row = row_of(sub);
+            load_group(row, 0, dw);
+            for (uint32_t j = sub;;) {
+                const uint32_t* next_row = row_of(j + G);
+                process(row, next_row, j < m);
+                row = next_row;
+                j += G;
+                if (!__any(j - sub < m)) break;
+            }
+            int32_t score = 0;
+            if constexpr (!MEAN) {
+                if (m == 0) {
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) mx[p] = 0;
+                }
+                uint32_t o[8];
+#pragma unroll
+                for (int p = 0; p < 8; ++p) o[p] = dpp_mov<0x141>(mx[p]);   // row_half_mirror
+                planes_max<8>(mx, o);
+#pragma unroll
+                for (int p = 0; p < 8; ++p) o[p] = dpp_mov<0xB1>(mx[p]);    // quad_perm [1,0,3,2]
+                planes_max<8>(mx, o);
+#pragma unroll
+                for (int p = 0; p < 8; ++p) o[p] = dpp_mov<0x4E>(mx[p]);    // quad_perm [2,3,0,1]
+                planes_max<8>(mx, o);
+                if (!a.remap) {
+#pragma unroll
+                    for (int p = 7; p >= 0; --p) score = 2 * score + __builtin_popcount(mx[p]);
+                } else {
+                    planes_to_bytes(mx);
+                    uint32_t mine = 0;   // word `sub`: query vectors sub, sub + 8, sub + 16, sub + 24
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) mine = sub == (uint32_t)j ? mx[j] : mine;
+                    uint32_t part = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t q = sub + 8 * k;
+                        uint32_t term = a.remap[(mine >> (8 * k)) & 0xFFu];   // remap[0] = 0, and absent query vectors have maximum 0
+                        if (a.q_weights && c0 + q < q_len) term = (uint32_t)(((uint64_t)a.q_weights[q_lo + c0 + q] * term + 32768) >> 16);
+                        part += term;
+                    }
+                    part += dpp_mov<0x141>(part);
+                    part += dpp_mov<0xB1>(part);
+                    part += dpp_mov<0x4E>(part);
+                    score = (int32_t)part;
+                }
+            } else {
+                // the eight lanes' sums: a lane keeps one half of the query vectors and takes the partner's sums of that half,
+                // then a quarter, an eighth: sum[0..3] = query vectors sub + 8 k in the end
+                const bool h4 = sub >= 4, h2 = (sub & 2) != 0, h1 = (sub & 1) != 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t x = h4 ? sum[i + 16] : sum[i], y = h4 ? sum[i] : sum[i + 16];
+                    sum[i] = x + dpp_mov<0x141>(y);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t x = h2 ? sum[i + 8] : sum[i], y = h2 ? sum[i] : sum[i + 8];
+                    sum[i] = x + dpp_mov<0x4E>(y);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t x = h1 ? sum[i + 4] : sum[i], y = h1 ? sum[i] : sum[i + 4];
+                    sum[i] = x + dpp_mov<0xB1>(y);
+                }
+                uint32_t part = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t q = sub + 8 * k;
+                    uint32_t term = m ? (sum[k] + m / 2) / m : 0u;
+                    if (a.q_weights && c0 + q < q_len) term = (uint32_t)(((uint64_t)a.q_weights[q_lo + c0 + q] * term + 32768) >> 16);
+                    part += term;
+                }
+                part += dpp_mov<0x141>(part);
+                part += dpp_mov<0xB1>(part);
+                part += dpp_mov<0x4E>(part);
+                score = (int32_t)part;
+            }
+            if (valid && sub == 0) {
+                int32_t* dst = a.scores + sp.base + meta.slot[doc];
+                if (m == 0 && meta.lo[doc] == ~0ull) {
+                    if (c0 == 0) *dst = -1;   // empty candidate slot
+                } else if (gz > 1) {
+                    if (score) atomicAdd(dst, score);
+                } else if (c0 == 0) {
+                    *dst = score;
+                } else {
+                    *dst += score;
+                }
+            }
+        }
+    }
+}
+
 // Stand-alone form of the candidate grouping (cand_order.hpp): one workgroup per list.
 constexpr uint32_t ORDER_THREADS = 512, ORDER_MAX_RANGES = 4096;
 __global__ __launch_bounds__(ORDER_THREADS) void cand_order_kernel(CandOrderArgs a) {
@@ -969,6 +1321,79 @@ hipError_t launch_score_masklut(const ScoreArgs& a, hipStream_t stream, char* de
     DESSERT_LUT_CASE(32, 9, 2)
 #undef DESSERT_LUT_CASE
     return hipErrorInvalidValue;
+}
+
+bool score_maskany_supported(uint32_t L, uint32_t C) {
+    return L >= 4 && L <= 128 && L % 4 == 0 && C >= 1 && C <= 16 && ((size_t)L << C) * 4 <= MASKANY_MAX_TABLE;
+}
+
+bool score_maskany_mean_fits(uint64_t max_len, uint32_t phi_max) {   // 32-bit sums, and the rounding term added to them
+    return max_len <= 0x7fffffffull && max_len * phi_max + max_len / 2 <= 0xffffffffull;
+}
+
+template <int NG, int CW>
+static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+    const size_t table = ((size_t)a.L << a.C) * 4, lds = table + ((size_t)a.L + 1) * 4;
+    // as many waves share a table as keep several workgroups on a CU: 160 KB of LDS hold six tables of up to 24 KB (four waves
+    // each), three of up to 48 KB (eight), one of 128 KB (sixteen)
+    const uint32_t T = table <= 24 * 1024 ? 256 : table <= 48 * 1024 ? 512 : 1024;
+    const uint32_t wave_docs = T / 64 * 8;   // one run of 8 documents per wave
+    uint32_t dpb = LUT_DOCS;
+    while (dpb > wave_docs && ((a.max_scored + dpb - 1) / dpb) * a.n_queries < 4096) dpb /= 2;
+    const uint64_t bx = (a.max_scored + dpb - 1) / dpb;
+    if (bx > 0x7fffffffull || a.n_queries > 65535) return hipErrorInvalidValue;
+    // long query sets on a small grid: chunks of 32 query vectors dealt to gz workgroups that add into zeroed scores
+    const uint32_t chunks = (a.max_q_len + 31) / 32;
+    uint32_t gz = 1;
+    if (chunks > 1 && bx * a.n_queries < 1024) {
+        gz = (uint32_t)((1024 + bx * a.n_queries - 1) / (bx * a.n_queries));
+        if (gz > chunks) gz = chunks;
+        if (gz < 2) gz = 2;
+    }
+    uint64_t gy = (uint64_t)a.n_queries * gz;
+    if (gy > 65535) {
+        gz = 1;
+        gy = a.n_queries;
+    }
+    if (gz > 1) {
+        hipError_t e = launch_fill_zero(a.scores, a.cand_ids ? a.total_scored : (uint64_t)a.n_queries * a.n_docs, stream);
+        if (e != hipSuccess) return e;
+    }
+    MaskanyLaunch ml{a.C, dpb, 0, gz};
+    dim3 grid((unsigned)bx, (unsigned)gy);
+    if (a.cand_ids == nullptr || a.order != nullptr) {   // the groups of a block of documents back to back on one XCD
+        const uint64_t total = (bx + 7) / 8 * 8 * gy;
+        if (total * T <= 0xffffffffull) {
+            grid = dim3((unsigned)total);
+            ml.gy_linear = (uint32_t)gy;
+        }
+    }
+    if (desc) snprintf(desc, desc_len, "score_bytecmp_kernel_masks<%d, %d, %s>", NG, CW, a.sigma_mean ? "true" : "false");
+    auto kern = a.sigma_mean ? score_bytecmp_kernel_masks<NG, CW, true> : score_bytecmp_kernel_masks<NG, CW, false>;
+    static hipError_t a0 = hipFuncSetAttribute((const void*)score_bytecmp_kernel_masks<NG, CW, false>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, MASKANY_MAX_TABLE + 1024);
+    static hipError_t a1 = hipFuncSetAttribute((const void*)score_bytecmp_kernel_masks<NG, CW, true>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, MASKANY_MAX_TABLE + 1024);
+    if (a0 != hipSuccess) return a0;
+    if (a1 != hipSuccess) return a1;
+    hipLaunchKernelGGL(kern, grid, dim3(T), lds, stream, a, ml);
+    return hipGetLastError();
+}
+
+hipError_t launch_score_maskany(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+    if (desc && desc_len) desc[0] = 0;
+    if (a.n_queries == 0 || a.max_scored == 0) return hipSuccess;
+    if (!score_maskany_supported(a.L, a.C) || a.code_bytes != (a.C > 8 ? 2u : 1u)) return hipErrorInvalidValue;
+    if ((a.sigma_mean || a.q_weights) && !a.remap) return hipErrorInvalidValue;
+    if (a.code_bytes == 1) {
+        if (a.L <= 16) return launch_maskany_t<1, 1>(a, stream, desc, desc_len);
+        if (a.L <= 32) return launch_maskany_t<2, 1>(a, stream, desc, desc_len);
+        if (a.L <= 64) return launch_maskany_t<4, 1>(a, stream, desc, desc_len);
+        return launch_maskany_t<8, 1>(a, stream, desc, desc_len);
+    }
+    if (a.L <= 16) return launch_maskany_t<1, 2>(a, stream, desc, desc_len);
+    if (a.L <= 32) return launch_maskany_t<2, 2>(a, stream, desc, desc_len);
+    return launch_maskany_t<4, 2>(a, stream, desc, desc_len);   // 64 tables of 512 entries fill the largest table
 }
 
 }  // namespace dessert
