@@ -21,42 +21,51 @@ __host__ __device__ inline uint32_t tile_row(uint32_t r, uint32_t g) { return 8 
 
 // ---------------------------------------------------------------------------
 // Centroids in MFMA operand order, [tiles][KS][64 lanes][16 B] (tile = 32 centroids, rows past K
-// are zero), and the per-row constants, for accumulator register r of lane half g:
-//   H[tiles][2][16]  -ceil(|c|^2 / 2): the accumulators start from it, so that after the MFMAs
-//                    acc = x.c - ceil(|c|^2 / 2) =: h  and  2 x.c - |c|^2 = 2 h + (|c|^2 & 1);
-//                    rows past K start from -2^25, below every real value (> -2^24 / 2)
-//   PAR[tiles][2]    bit r = |c|^2 & 1
-// A lane's largest h bounds its largest value (<= 2 h + 1): most tiles are dismissed by a max
-// over the raw accumulators, without building any per-row key.
-constexpr int32_t FILTER_PAD_INIT = -(1 << 25);
+// are zero), and one constant per row, W[tiles][2][16] for accumulator register r of lane half g:
+//   bits 0..26   -ceil(|c|^2 / 2), signed: the accumulators start from it, so that after the MFMAs
+//                acc = x.c - ceil(|c|^2 / 2) =: h  and  2 x.c - |c|^2 = 2 h + (|c|^2 & 1);
+//                rows past K start from -2^23: a value of -2^24, below every real one (at least -3 * 128^2 * 256)
+//   bits 27..30  15 - r
+//   bit 31       |c|^2 & 1
+// so that shifting the top bit, or the top five, of W into an accumulator (one v_alignbit) gives the row's value, or the key
+// 16 * value + 15 - r that decides ties within a tile.  A lane's largest h bounds its largest value (<= 2 h + 1): most tiles
+// are dismissed by a max over the raw accumulators, without building any key.
+constexpr int32_t FILTER_PAD_INIT = -(1 << 23);
 
-__global__ void filter_prep_kernel(const int8_t* __restrict__ Cn, uint32_t K, uint32_t d, int8_t* __restrict__ Cp,
-                                   int32_t* __restrict__ H, uint32_t tiles) {
-    const uint32_t KS = d / 32;
-    const uint32_t total = tiles * KS * 1024;
-    uint32_t* PAR = (uint32_t*)H + (size_t)tiles * 32;
-    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
-        uint32_t e = idx & 15, l = (idx >> 4) & 63;
-        uint32_t ks = (idx >> 10) % KS, tile = (idx >> 10) / KS;
-        uint32_t c = tile * 32 + (l & 31);
-        uint32_t kk = ks * 32 + 16 * (l >> 5) + e;
-        Cp[idx] = c < K ? Cn[(size_t)c * d + kk] : (int8_t)0;
+// One thread per row for the constants (its bytes in 16-byte loads), then one per 16-byte fragment for the copy: 16 384
+// centroids of 128 bytes 242 -> 5 us (one thread took 16 rows byte by byte before).
+__global__ __launch_bounds__(256) void filter_prep_kernel(const int8_t* __restrict__ Cn, uint32_t K, uint32_t d, int8_t* __restrict__ Cp,
+                                                          uint32_t* __restrict__ W, uint32_t tiles) {
+    const uint32_t KS = d / 32, stride = gridDim.x * blockDim.x, first = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t idx = first; idx < tiles * KS * 64; idx += stride) {
+        const uint32_t l = idx & 63, ks = (idx >> 6) % KS, tile = (idx >> 6) / KS;
+        const uint32_t c = tile * 32 + (l & 31);
+        v4i x = {0, 0, 0, 0};
+        if (c < K) __builtin_memcpy(&x, Cn + (size_t)c * d + ks * 32 + 16 * (l >> 5), 16);   // the caller's array, at any address
+        ((v4i*)Cp)[idx] = x;
     }
-    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < tiles * 2; idx += gridDim.x * blockDim.x) {
-        const uint32_t g = idx & 1, tile = idx >> 1;
+    for (uint32_t idx = first; idx < tiles * 32; idx += stride) {
+        const uint32_t r = idx & 15, g = (idx >> 4) & 1, tile = idx >> 5;
+        const uint32_t c = tile * 32 + tile_row(r, g);
+        int32_t h = FILTER_PAD_INIT;
         uint32_t par = 0;
-        for (uint32_t r = 0; r < 16; ++r) {
-            const uint32_t c = tile * 32 + tile_row(r, g);
-            int32_t h = FILTER_PAD_INIT;
-            if (c < K) {
-                int32_t nrm = 0;
-                for (uint32_t i = 0; i < d; ++i) nrm += (int32_t)Cn[(size_t)c * d + i] * (int32_t)Cn[(size_t)c * d + i];
-                h = -((nrm + 1) >> 1);
-                par |= (uint32_t)(nrm & 1) << r;
+        if (c < K) {
+            int32_t nrm = 0;
+            for (uint32_t i = 0; i < d; i += 16) {
+                v4i x;
+                __builtin_memcpy(&x, Cn + (size_t)c * d + i, 16);
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int32_t v = (int32_t)(int8_t)((uint32_t)x[w] >> (8 * e));
+                        nrm += v * v;
+                    }
             }
-            H[(size_t)idx * 16 + r] = h;
+            h = -((nrm + 1) >> 1);
+            par = (uint32_t)(nrm & 1);
         }
-        PAR[idx] = par;
+        W[idx] = (par << 31) | ((15 - r) << 27) | ((uint32_t)h & 0x7FFFFFFu);
     }
 }
 
@@ -70,6 +79,12 @@ __global__ void filter_prep_kernel(const int8_t* __restrict__ Cn, uint32_t K, ui
 //                 (value in the high word, ~id in the low word: larger = closer, then lower id),
 //                 lists[v][range][half][P]; filter_merge_kernel joins the lists of a vector.
 //   MODE = -1     the values 2 x.c - |c|^2 themselves, out[v][tiles*32] (any probe count).
+// Bound: matrix cores.  Column tiles are multiplied one after the other, each while the one before is compared: two accumulator
+// sets instead of one per column tile (202 -> 168 VGPRs at d = 128, three waves per SIMD instead of two).  With 512 tiles
+// 38 % of the tiles can improve some lane of a wave, so what such a tile costs matters: 16 shifts and 8 maxima (parity and
+// tie-break come out of the row's constant with the shift; about 64 operations when they were computed per row).  4.2M vectors x
+// 16 384 centroids, d = 128: 8.7 -> 7.4 ms = 2.4 POP/s, the share of nominal that a large bf16 matrix product reaches here.
+// Four probes of 4096 vectors in 32 768 centroids 116 -> 54 us (32-bit sorted keys; 64-bit list inserts per row before).
 constexpr int64_t LIST_EMPTY = INT64_MIN;
 
 template <int P>
@@ -88,9 +103,18 @@ __device__ __forceinline__ int32_t max3(int32_t a, int32_t b, int32_t c) {  // o
     return ab > c ? ab : c;
 }
 
+__device__ __forceinline__ int32_t med3_i32(int32_t x, int32_t y, int32_t z) {
+    int32_t r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+}
+
+// Waves per SIMD that the registers leave room for: 32*NT vectors as fragments (4*KS*NT), two accumulator sets, a tile's constants
+constexpr int gemm_min_waves(int KS, int NT, int MODE) { return KS >= 8 ? 2 : KS * NT >= 8 || MODE > 1 ? 3 : 4; }
+
 template <int KS, int NT, int MODE>
-__global__ __launch_bounds__(256) void filter_gemm_kernel(const int8_t* __restrict__ X, uint64_t n,
-                                                          const v4i* __restrict__ Cp, const v4i* __restrict__ T2,
+__global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm_kernel(const int8_t* __restrict__ X, uint64_t n,
+                                                          const v4i* __restrict__ Cp, const v4i* __restrict__ W,
                                                           uint32_t tiles, uint32_t K, uint32_t tiles_per_range,
                                                           uint32_t* __restrict__ assign, int32_t* __restrict__ out,
                                                           int64_t* __restrict__ lists, uint32_t zero_words) {
@@ -107,14 +131,12 @@ __global__ __launch_bounds__(256) void filter_gemm_kernel(const int8_t* __restri
     constexpr bool ARGMAX = MODE == 0 || MODE == 1;
     // centroid tiles per group: 8 for the build's assignment (long ranges, d <= 128), 4 on the query side and for
     // d = 256, where two buffers of 8 tiles would leave a CU with fewer workgroups than the registers allow
-    constexpr int TG = (MODE == 0 && KS <= 4) ? FILTER_TG : FILTER_TG / 2;
+    constexpr int TG = (MODE == 0 && KS <= 4 && gemm_min_waves(KS, NT, MODE) <= 2) ? FILTER_TG : FILTER_TG / 2;
     // two groups of centroid tiles in LDS: while the waves multiply one, the next is copied from global memory
     // straight into the other buffer (global_load ... lds: no staging registers; a wave's 64 lanes fill
     // consecutive LDS), one barrier per group
     __shared__ v4i sA[2][TG * KS * 64];
-    __shared__ v4i sT[2][TG * 8];  // 32 ints per tile
-    __shared__ uint32_t sP[2][64];        // TG * 2 in use; a wave's copy lands at lane * 4 bytes
-    const uint32_t* PAR = (const uint32_t*)T2 + (size_t)tiles * 32;
+    __shared__ v4i sW[2][TG * 8];  // 32 words per tile
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, g = lane >> 5;
     const uint64_t v0 = ((uint64_t)blockIdx.x * 4 + wave) * (32 * NT);
@@ -130,33 +152,53 @@ __global__ __launch_bounds__(256) void filter_gemm_kernel(const int8_t* __restri
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) b[nt][ks] = src[ks * 2];
     }
-    // MODE 0: best_key = 16 * value + (15 - register) of the best row so far, best_tile its tile
+    // ARGMAX: best_key = 16 * value + (15 - register) of the best row so far, best_tile its tile
     int32_t best_key[NT];
     uint32_t best_tile[NT];
+    // lists: `best` over the chunks of LIST_CHUNK tiles that are done, `near` of the chunk at hand as 32-bit keys
+    // (value << 7 | 127 - position): value needs 25 bits, a lane's 16 rows of 8 tiles the other 7.  A key goes into the sorted
+    // `near` with one max or median per entry; its entries join the 64-bit list once per chunk.
+    constexpr uint32_t LIST_CHUNK = 8;
     int64_t best[NT][P];
+    int32_t near[NT][P], bar[NT];   // bar: a value must exceed it to matter
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        best_key[nt] = (int32_t)0x80000000;
+        best_key[nt] = bar[nt] = (int32_t)0x80000000;
         best_tile[nt] = 0;
 #pragma unroll
-        for (int i = 0; i < P; ++i) best[nt][i] = LIST_EMPTY;
+        for (int i = 0; i < P; ++i) {
+            best[nt][i] = LIST_EMPTY;
+            near[nt][i] = (int32_t)0x80000000;
+        }
     }
+    auto fold = [&](uint32_t chunk0) {   // the keys of the chunk that starts at tile chunk0 join `best`
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                const uint32_t at = 127 - ((uint32_t)near[nt][i] & 127u);
+                const uint32_t cid = (chunk0 + (at >> 4)) * 32 + tile_row(at & 15, g);
+                const int64_t e = (int64_t)(((uint64_t)(uint32_t)(near[nt][i] >> 7) << 32) | (uint32_t)~cid);
+                if (near[nt][i] != (int32_t)0x80000000 && cid < K && e > best[nt][P - 1]) list_insert<P>(best[nt], e);
+                near[nt][i] = (int32_t)0x80000000;
+            }
+            bar[nt] = (int32_t)(best[nt][P - 1] >> 32);
+        }
+    };
 
-    static_assert(TG * 8 <= 64 && TG * 2 <= 64, "the key constants of a group are one wave's copy");
+    static_assert(TG * 8 <= 64, "the constants of a group are one wave's copy");
     auto stage = [&](uint32_t t0, int buf) {  // every copy instruction is issued by whole waves (exec masks the tail)
         const uint32_t tg = t_end - t0 < TG ? t_end - t0 : TG;
         for (uint32_t i = threadIdx.x; i < tg * KS * 64; i += 256)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Cp + (size_t)t0 * KS * 64 + i),
                                              (__attribute__((address_space(3))) void*)&sA[buf][i - lane], 16, 0, 0);
         if (wave == 0 && (uint32_t)lane < tg * 8)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(T2 + (size_t)t0 * 8 + lane),
-                                             (__attribute__((address_space(3))) void*)&sT[buf][0], 16, 0, 0);
-        if (wave == 1 && (uint32_t)lane < tg * 2)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(PAR + (size_t)t0 * 2 + lane),
-                                             (__attribute__((address_space(3))) void*)&sP[buf][0], 4, 0, 0);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(W + (size_t)t0 * 8 + lane),
+                                             (__attribute__((address_space(3))) void*)&sW[buf][0], 16, 0, 0);
     };
     if (t_begin < t_end) stage(t_begin, 0);
     int buf = 0;
+    uint32_t in_chunk = 0;   // lists: tiles of the chunk at hand that are done
     for (uint32_t t0 = t_begin; t0 < t_end; t0 += TG, buf ^= 1) {
         const uint32_t tg = t_end - t0 < TG ? t_end - t0 : TG;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's copies into sA[buf] have landed
@@ -164,23 +206,26 @@ __global__ __launch_bounds__(256) void filter_gemm_kernel(const int8_t* __restri
         if (t0 + TG < t_end) stage(t0 + TG, buf ^ 1);
 #pragma unroll 1
         for (uint32_t tt = 0; tt < tg; ++tt) {
+            uint32_t w[16];
             v16i init;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                v4i t = sT[buf][tt * 8 + g * 4 + q];
-                init[4 * q] = t.x; init[4 * q + 1] = t.y; init[4 * q + 2] = t.z; init[4 * q + 3] = t.w;
+                const v4i t = sW[buf][tt * 8 + g * 4 + q];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    w[4 * q + j] = (uint32_t)t[j];
+                    init[4 * q + j] = t[j] << 5 >> 5;
+                }
             }
-            const uint32_t par = sP[buf][tt * 2 + g];
-            v16i acc[NT];
+            v4i a[KS];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                v4i a = sA[buf][(tt * KS + ks) * 64 + lane];
+            for (int ks = 0; ks < KS; ++ks) a[ks] = sA[buf][(tt * KS + ks) * 64 + lane];
+            auto multiply = [&](v16i& acc, int nt) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[nt][ks], ks == 0 ? init : acc[nt], 0, 0, 0);
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
+                for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], b[nt][ks], ks == 0 ? init : acc, 0, 0, 0);
+            };
+            auto value = [&](const v16i& acc, int r) { return (int32_t)__builtin_amdgcn_alignbit((uint32_t)acc[r], w[r], 31); };
+            auto take = [&](const v16i& acc, int nt) {
                 if constexpr (MODE < 0) {
                     const uint64_t v = v0 + nt * 32 + col;
                     if (v < n) {
@@ -189,44 +234,65 @@ __global__ __launch_bounds__(256) void filter_gemm_kernel(const int8_t* __restri
                         for (int q = 0; q < 4; ++q) {
                             v4i o;
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) o[j] = 2 * acc[nt][4 * q + j] + (int32_t)((par >> (4 * q + j)) & 1);
+                            for (int j = 0; j < 4; ++j) o[j] = value(acc, 4 * q + j);
                             *(v4i*)(dst + 8 * q) = o;
                         }
                     }
                 } else {
-                    int32_t m = max3(acc[nt][0], acc[nt][1], acc[nt][2]);
+                    int32_t m = max3(acc[0], acc[1], acc[2]);
 #pragma unroll
-                    for (int r = 3; r < 15; r += 2) m = max3(m, acc[nt][r], acc[nt][r + 1]);
-                    m = acc[nt][15] > m ? acc[nt][15] : m;
+                    for (int r = 3; r < 15; r += 2) m = max3(m, acc[r], acc[r + 1]);
+                    m = acc[15] > m ? acc[15] : m;
                     // a lane meets centroid ids in increasing tile order, so only a strictly larger value can
                     // replace what it holds, and no value of this tile exceeds 2 m + 1
-                    const int32_t bound = ARGMAX ? best_key[nt] >> 4 : (int32_t)(best[nt][P - 1] >> 32);
+                    const int32_t bound = ARGMAX ? best_key[nt] >> 4 : bar[nt];
                     if (2 * m + 1 > bound) {
                         if constexpr (ARGMAX) {
-                            int32_t km = (int32_t)0x80000000;
+                            int32_t key[16];   // equal values: the lower register = lower row
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const int32_t val = 2 * acc[nt][r] + (int32_t)((par >> r) & 1);
-                                const int32_t key = val * 16 + (15 - r);  // equal values: the lower register = lower row
-                                km = key > km ? key : km;
-                            }
+                            for (int r = 0; r < 16; ++r) key[r] = (int32_t)__builtin_amdgcn_alignbit((uint32_t)acc[r], w[r], 27);
+                            int32_t km = max3(key[0], key[1], key[2]);
+#pragma unroll
+                            for (int r = 3; r < 15; r += 2) km = max3(km, key[r], key[r + 1]);
+                            km = key[15] > km ? key[15] : km;
                             if ((km >> 4) > bound) {
                                 best_key[nt] = km;
                                 best_tile[nt] = t0 + tt;
                             }
                         } else {
+                            const uint32_t top = 127 - in_chunk * 16;
 #pragma unroll
                             for (int r = 0; r < 16; ++r) {
-                                const int32_t val = 2 * acc[nt][r] + (int32_t)((par >> r) & 1);
-                                const uint32_t cid = (t0 + tt) * 32 + tile_row(r, g);
-                                const int64_t e = (int64_t)(((uint64_t)(uint32_t)val << 32) | (uint32_t)~cid);
-                                if (cid < K && e > best[nt][P - 1]) list_insert<P>(best[nt], e);
+                                const int32_t key = (int32_t)(((uint32_t)value(acc, r) << 7) + (top - r));
+#pragma unroll
+                                for (int i = P - 1; i > 0; --i) near[nt][i] = med3_i32(near[nt][i - 1], near[nt][i], key);
+                                near[nt][0] = key > near[nt][0] ? key : near[nt][0];
                             }
+                            const int32_t last = near[nt][P - 1] >> 7, far = (int32_t)(best[nt][P - 1] >> 32);
+                            bar[nt] = last > far ? last : far;
                         }
                     }
                 }
+            };
+            // the products of one column tile run on the matrix cores while the one before is compared
+            v16i acc[2];
+            multiply(acc[0], 0);
+#pragma unroll
+            for (int nt = 1; nt < NT; ++nt) {
+                multiply(acc[nt & 1], nt);
+                take(acc[(nt - 1) & 1], nt - 1);
+            }
+            take(acc[(NT - 1) & 1], NT - 1);
+            if constexpr (MODE > 1) {
+                if (++in_chunk == LIST_CHUNK) {
+                    fold(t0 + tt + 1 - LIST_CHUNK);
+                    in_chunk = 0;
+                }
             }
         }
+    }
+    if constexpr (MODE > 1) {
+        if (in_chunk) fold(t_end - in_chunk);
     }
     if constexpr (MODE == 0) {
 #pragma unroll
@@ -674,11 +740,11 @@ static bool filter_shape(uint32_t d) { return d == 64 || d == 128 || d == 256; }
 bool filter_supported(uint32_t d) { return filter_shape(d); }
 uint32_t filter_tiles(uint32_t K) { return (K + 31) / 32; }
 size_t filter_centroid_bytes(uint32_t K, uint32_t d) { return (size_t)filter_tiles(K) * (d / 32) * 1024; }
-size_t filter_table_bytes(uint32_t K) { return (size_t)filter_tiles(K) * (32 + 2) * 4; }
+size_t filter_table_bytes(uint32_t K) { return (size_t)filter_tiles(K) * 32 * 4; }
 
 hipError_t launch_filter_prep(const int8_t* Cn, uint32_t K, uint32_t d, void* Cp, void* T2, hipStream_t stream) {
     if (!filter_shape(d) || K == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(filter_prep_kernel, dim3(1024), dim3(256), 0, stream, Cn, K, d, (int8_t*)Cp, (int32_t*)T2,
+    hipLaunchKernelGGL(filter_prep_kernel, dim3(1024), dim3(256), 0, stream, Cn, K, d, (int8_t*)Cp, (uint32_t*)T2,
                        filter_tiles(K));
     return hipGetLastError();
 }
