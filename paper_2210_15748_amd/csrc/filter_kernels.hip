@@ -345,32 +345,57 @@ __global__ __launch_bounds__(256) void filter_merge1_kernel(const int64_t* __res
     if (lane == 0) probe_ids[v] = best == LIST_EMPTY ? 0xFFFFFFFFu : ~(uint32_t)best;
 }
 
-// one thread per vector: the `probe` best entries of its per_vec list entries, closest first
+// the `probe` best entries of a vector's per_vec list entries, closest first: one wave per vector.  Lanes stride over the
+// entries and keep sorted lists of their own, then the wave's largest head is taken P times (entries differ: they end in their
+// centroid's id).  Bound: the round trips of one pass over the entries; 4096 vectors x 512 entries, 4 probes: 96 -> 7 us
+// (one thread walked a vector's entries before, uncoalesced and with 16 workgroups in all).
 template <int P>
 __global__ __launch_bounds__(256) void filter_merge_kernel(const int64_t* __restrict__ lists, uint64_t n,
                                                            uint32_t per_vec, uint32_t probe,
                                                            uint32_t* __restrict__ probe_ids) {
-    const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t v = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (v >= n) return;
     int64_t best[P];
 #pragma unroll
     for (int i = 0; i < P; ++i) best[i] = LIST_EMPTY;
     const int64_t* src = lists + v * per_vec;
-    for (uint32_t i = 0; i < per_vec; ++i) {
-        const int64_t e = src[i];
-        if (e > best[P - 1]) list_insert<P>(best, e);
+    constexpr uint32_t U = 4;   // loads in flight
+    for (uint32_t i = lane; i < per_vec; i += 64 * U) {
+        int64_t e[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) e[u] = i + 64 * u < per_vec ? src[i + 64 * u] : LIST_EMPTY;
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+            if (e[u] > best[P - 1]) list_insert<P>(best, e[u]);
     }
 #pragma unroll
-    for (int i = 0; i < P; ++i)
-        if ((uint32_t)i < probe) probe_ids[v * probe + i] = best[i] == LIST_EMPTY ? 0xFFFFFFFFu : ~(uint32_t)best[i];
+    for (int i = 0; i < P; ++i) {
+        int64_t top = best[0];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const int64_t other = __shfl_xor((long long)top, o, 64);
+            top = other > top ? other : top;
+        }
+        if (lane == 0 && (uint32_t)i < probe) probe_ids[v * probe + i] = top == LIST_EMPTY ? 0xFFFFFFFFu : ~(uint32_t)top;
+        if (best[0] == top) {   // the lane that holds it moves up
+#pragma unroll
+            for (int j = 0; j + 1 < P; ++j) best[j] = best[j + 1];
+            best[P - 1] = LIST_EMPTY;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
-// Inverted index.  One wave per document; a vector is the first of its document with its
-// centroid if no earlier vector of the document has the same one (a bucket holds a document
-// once).  A document goes to sub-bucket c*S + (doc >> sub_shift) of its centroid c.  FILL = false counts
+// Inverted index.  One wave per document; a vector counts if it is the one that puts its centroid into the document's set
+// (a bucket holds a document once).  A document goes to sub-bucket c*S + (doc >> sub_shift) of its centroid c.  FILL = false counts
 // sub-bucket sizes; FILL = true writes document ids at sub_off[...] + (atomic cursor), so the order inside
 // a sub-bucket is unspecified.
+// The set is an open-addressing table in LDS, per wave, when the document has at most DOC_SET_MAX vectors: some three
+// compare-and-swap round trips per 64 vectors.  Longer documents compare each vector with all before it by lane broadcast, 64 of them
+// per 64 vectors and chunk, as all documents did before: 60 000 documents of 70 vectors, 16 384 centroids 231 -> 199 us counting,
+// 238 -> 201 us filling.  Bound now: the counters' atomics, 4.1M to random places at 20 G/s.
+constexpr uint32_t DOC_SET = 512, DOC_SET_MAX = 384, DOC_SET_EMPTY = 0xFFFFFFFFu;
 template <bool FILL>
 __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __restrict__ assign,
                                                             const uint64_t* __restrict__ doc_off, uint64_t n_docs,
@@ -378,9 +403,46 @@ __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __re
                                                             uint32_t* __restrict__ size_or_cursor,
                                                             const uint32_t* __restrict__ sub_off,
                                                             uint32_t* __restrict__ bucket_docs) {
+    __shared__ uint4 sets[4][DOC_SET / 4];
     const uint32_t lane = threadIdx.x & 63;
+    uint4* set4 = sets[threadIdx.x >> 6];
+    uint32_t* set = (uint32_t*)set4;
+    auto enter = [&](uint64_t doc, uint32_t c) {
+        const uint32_t sub = c * S + (uint32_t)(doc >> sub_shift);
+        uint32_t pos = atomicAdd(&size_or_cursor[sub], 1u);
+        if constexpr (FILL) bucket_docs[sub_off[sub] + pos] = (uint32_t)doc;
+    };
     for (uint64_t doc = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); doc < n_docs; doc += (uint64_t)gridDim.x * 4) {
         const uint64_t lo = doc_off[doc], hi = doc_off[doc + 1];
+        if (hi - lo <= DOC_SET_MAX) {
+            const uint32_t m = (uint32_t)(hi - lo);
+            uint32_t log_slots = 7;   // at least a third of the slots stays free
+            while (log_slots < 9 && (1u << log_slots) * 3 < m * 4) ++log_slots;
+            const uint32_t slots = 1u << log_slots;
+            for (uint32_t i = lane; i < slots / 4; i += 64) set4[i] = uint4{DOC_SET_EMPTY, DOC_SET_EMPTY, DOC_SET_EMPTY, DOC_SET_EMPTY};
+            uint32_t next = lane < m ? assign[lo + lane] : 0;
+            // a wave's LDS operations execute in order; the fences keep the compiler from moving them
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t j0 = 0; j0 < m; j0 += 64) {
+                const uint32_t c = next;
+                if (j0 + 64 + lane < m) next = assign[lo + j0 + 64 + lane];
+                bool pending = j0 + lane < m, first = false;
+                uint32_t at = (c * 0x9E3779B1u) >> (32 - log_slots);
+                while (__any(pending)) {   // ends: a free slot lies behind every start
+                    if (pending) {
+                        const uint32_t old = atomicCAS(&set[at], DOC_SET_EMPTY, c);
+                        first = old == DOC_SET_EMPTY;
+                        pending = !first && old != c;
+                        at = (at + 1) & (slots - 1);
+                    }
+                }
+                if (first) enter(doc, c);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            continue;
+        }
         for (uint64_t j0 = lo; j0 < hi; j0 += 64) {  // 64 vectors of the document per pass, one per lane
             const bool valid = j0 + lane < hi;
             const uint32_t c = valid ? assign[j0 + lane] : 0xFFFFFFFFu;
@@ -393,45 +455,84 @@ __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __re
                     if (v == c && (e0 < j0 || e < lane)) first = false;
                 }
             }
-            if (first) {
-                const uint32_t sub = c * S + (uint32_t)(doc >> sub_shift);
-                uint32_t pos = atomicAdd(&size_or_cursor[sub], 1u);
-                if constexpr (FILL) bucket_docs[sub_off[sub] + pos] = (uint32_t)doc;
-            }
+            if (first) enter(doc, c);
         }
     }
 }
 
-// exclusive scan of size[0..K) into off[0..K], one workgroup; size is zeroed for reuse as cursors
-__global__ __launch_bounds__(1024) void filter_scan_kernel(uint32_t* __restrict__ size, uint32_t K,
-                                                           uint32_t* __restrict__ off) {
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < K; base += 1024) {
-        const uint32_t i = base + tid;
-        const uint32_t x = i < K ? size[i] : 0;
-        uint32_t incl = x;
+// Exclusive scan of size[0..K) into off[0..K]; size is zeroed for reuse as cursors.  Three launches: workgroup i adds up its
+// SCAN_PART entries and leaves the sum in off[i * SCAN_PART], one workgroup scans those sums where they lie, workgroup i scans
+// its entries from there on.  (One workgroup walked over all entries before, 1.1 us per 1024: 37 us for 32 768, 2.3 ms for 2M.)
+constexpr uint32_t SCAN_THREADS = 256, SCAN_PART = SCAN_THREADS * 16;
+// inclusive prefix sum over the workgroup's threads; wsum: SCAN_THREADS / 64 words, free again after the call's last barrier
+__device__ inline uint32_t scan_threads(uint32_t x, uint32_t* wsum) {
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = x;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            uint32_t y = __shfl_up(incl, o, 64);
-            if ((int)lane >= o) incl += y;
-        }
-        if (lane == 63) wsum[wave] = incl;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if ((int)lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    for (uint32_t w = 0; w < wave; ++w) incl += wsum[w];
+    __syncthreads();
+    return incl;
+}
+__device__ inline uint32_t scan_load16(const uint32_t* size, uint32_t first, uint32_t K, uint32_t (&x)[16]) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i) {
+        x[i] = first + i < K ? size[first + i] : 0;
+        sum += x[i];
+    }
+    return sum;
+}
+__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_sums_kernel(const uint32_t* __restrict__ size, uint32_t K,
+                                                                        uint32_t* __restrict__ off) {
+    __shared__ uint32_t wsum[SCAN_THREADS / 64];
+    uint32_t x[16];
+    const uint32_t sum = scan_load16(size, blockIdx.x * SCAN_PART + threadIdx.x * 16, K, x);
+    const uint32_t incl = scan_threads(sum, wsum);
+    if (threadIdx.x == SCAN_THREADS - 1) off[(size_t)blockIdx.x * SCAN_PART] = incl;
+}
+__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_parts_kernel(uint32_t* __restrict__ off, uint32_t parts, uint32_t K) {
+    __shared__ uint32_t wsum[SCAN_THREADS / 64];
+    __shared__ uint32_t last;
+    uint32_t carry = 0;
+    for (uint32_t p0 = 0; p0 < parts; p0 += SCAN_THREADS) {
+        const uint32_t p = p0 + threadIdx.x;
+        const uint32_t x = p < parts ? off[(size_t)p * SCAN_PART] : 0;
+        const uint32_t incl = scan_threads(x, wsum);
+        if (p < parts) off[(size_t)p * SCAN_PART] = carry + incl - x;
+        if (threadIdx.x == SCAN_THREADS - 1) last = incl;
         __syncthreads();
-        uint32_t before = carry;
-        for (uint32_t w = 0; w < wave; ++w) before += wsum[w];
-        if (i < K) {
-            off[i] = before + incl - x;
-            size[i] = 0;
-        }
-        __syncthreads();
-        if (tid == 1023) carry = before + incl;
+        carry += last;
         __syncthreads();
     }
-    if (tid == 0) off[K] = carry;
+    if (threadIdx.x == 0) off[K] = carry;
+}
+__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_kernel(uint32_t* __restrict__ size, uint32_t K,
+                                                                   uint32_t* __restrict__ off) {
+    __shared__ uint32_t wsum[SCAN_THREADS / 64];
+    uint32_t x[16];
+    const uint32_t first = blockIdx.x * SCAN_PART + threadIdx.x * 16;
+    const uint32_t base = off[(size_t)blockIdx.x * SCAN_PART];   // read by all before scan_threads' barriers, rewritten after them
+    const uint32_t sum = scan_load16(size, first, K, x);
+    uint32_t run = base + scan_threads(sum, wsum) - sum;
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i)
+        if (first + i < K) {
+            off[first + i] = run;
+            size[first + i] = 0;
+            run += x[i];
+        }
+}
+static void launch_filter_scan(uint32_t* size, uint32_t K, uint32_t* off, hipStream_t stream) {   // K >= 1
+    const uint32_t parts = (K + SCAN_PART - 1) / SCAN_PART;
+    hipLaunchKernelGGL(filter_scan_sums_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, off);
+    hipLaunchKernelGGL(filter_scan_parts_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, off, parts, K);
+    hipLaunchKernelGGL(filter_scan_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, off);
 }
 
 // bucket_off[c] = sub_off[c*S] for c = 0..K: the caller-visible bucket starts
@@ -815,13 +916,13 @@ hipError_t launch_filter_probe_lists(const int8_t* X, uint64_t n, uint32_t d, ui
     if (pl.ranges == 0 || probe > K || pl.width != list_width(probe)) return hipErrorInvalidValue;
     hipError_t e;
     const uint32_t per_vec = pl.ranges * 2 * pl.width;
-    const dim3 mgrid((unsigned)((n + 255) / 256)), mblock(256);
+    const dim3 mgrid((unsigned)((n + 3) / 4)), mblock(256);
     switch (pl.width) {
         case 1:
             e = pl.nt == 2 ? launch_gemm<2, 1>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
                            : launch_gemm<1, 1>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(filter_merge1_kernel, dim3((unsigned)((n + 3) / 4)), mblock, 0, stream, lists, n, per_vec, probe_ids);
+            hipLaunchKernelGGL(filter_merge1_kernel, mgrid, mblock, 0, stream, lists, n, per_vec, probe_ids);
             break;
         case 2:
             e = pl.nt == 2 ? launch_gemm<2, 2>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
@@ -871,7 +972,7 @@ hipError_t launch_filter_buckets(const uint32_t* assign, const uint64_t* doc_off
     hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)zb), dim3(256), 0, stream, (int32_t*)cursor, KS);
     hipLaunchKernelGGL(filter_bucket_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, assign, doc_off, n_docs,
                        sp.S, sp.sub_shift, cursor, sub_off, bucket_docs);
-    hipLaunchKernelGGL(filter_scan_kernel, dim3(1), dim3(1024), 0, stream, cursor, (uint32_t)KS, sub_off);
+    launch_filter_scan(cursor, (uint32_t)KS, sub_off, stream);
     hipLaunchKernelGGL(filter_bucket_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, assign, doc_off, n_docs,
                        sp.S, sp.sub_shift, cursor, sub_off, bucket_docs);
     hipLaunchKernelGGL(filter_bucket_starts_kernel, dim3(K / 256 + 1), dim3(256), 0, stream, sub_off, K, sp.S, bucket_off);

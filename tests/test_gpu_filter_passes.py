@@ -1,0 +1,77 @@
+"""The passes around the filter's GEMM where their paths branch: bucket building for documents either side of the LDS set's limits,
+scans over several parts, merges of the per-range lists, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2210_15748_amd as dz
+from oracle import oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def index(rng, lens, d=64, L=8, Cb=4):
+    X = rng.integers(-127, 128, (int(lens.sum()), d)).astype(np.int8)
+    R = (rng.integers(0, 2, (L * Cb, d)) * 2 - 1).astype(np.int8)
+    ix = dz.create(d, L, Cb, proj=torch.from_numpy(R).to(DEV))
+    dz.build_index(ix, torch.from_numpy(X).to(DEV), lens)
+    return ix, X
+
+
+def buckets_equal(starts, docs, want_starts, want_docs):
+    assert np.array_equal(starts, want_starts)
+    for c in range(len(starts) - 1):
+        assert np.array_equal(np.sort(docs[starts[c]:starts[c + 1]]), np.sort(want_docs[starts[c]:starts[c + 1]])), c
+
+
+# few centroids: nearly every vector of a document repeats one; many: nearly none does.  Lengths either side of the set's three sizes
+# (96, 192 and 384 vectors fill 3/4 of 128, 256 and 512 slots), of whole passes of 64 and of the fall-back
+@pytest.mark.parametrize("K", [1, 2, 33, 700, 5000])
+def test_buckets_of_documents_of_every_length_class(K):
+    print("[case]", K, flush=True)
+    rng = np.random.default_rng(K)
+    lens = np.array([0, 1, 63, 64, 65, 95, 96, 97, 128, 129, 191, 192, 193, 256, 257, 383, 384, 385, 449, 1000, 0] + [5] * 40)
+    ix, X = index(rng, lens)
+    C = X[rng.permutation(X.shape[0])[:K]].copy() if K <= X.shape[0] else rng.integers(-127, 128, (K, 64)).astype(np.int8)
+    assign, starts, docs = (t.cpu().numpy() for t in dz.filter_build(ix, torch.from_numpy(C).to(DEV), torch.from_numpy(X).to(DEV)))
+    want = orc.assign_centroids(X, C)
+    assert np.array_equal(assign.view(np.uint32), want)
+    ws, wd = orc.inverted_index(want, np.concatenate([[0], np.cumsum(lens)]), K)
+    buckets_equal(starts.view(np.uint32).astype(np.int64), docs.view(np.uint32), np.asarray(ws, dtype=np.int64), np.asarray(wd))
+
+
+# the scan's parts hold 4096 entries: one part, exactly full, one more entry, several parts
+@pytest.mark.parametrize("K", [4095, 4096, 4097, 20_000])
+def test_bucket_starts_over_several_scan_parts(K):
+    rng = np.random.default_rng(K)
+    lens = rng.integers(0, 30, 1500)
+    ix, X = index(rng, lens)
+    C = rng.integers(-127, 128, (K, 64)).astype(np.int8)
+    assign, starts, docs = (t.cpu().numpy() for t in dz.filter_build(ix, torch.from_numpy(C).to(DEV), torch.from_numpy(X).to(DEV)))
+    ws, wd = orc.inverted_index(assign.view(np.uint32), np.concatenate([[0], np.cumsum(lens)]), K)
+    buckets_equal(starts.view(np.uint32).astype(np.int64), docs.view(np.uint32), np.asarray(ws, dtype=np.int64), np.asarray(wd))
+
+
+# probes 2, 3, 4, 5 and 8 (every list width, full or not); centroids that repeat (ties to the lower id); tiles of one chunk of eight,
+# a chunk and one tile, several ranges; the values themselves decide at the end of a chunk
+@pytest.mark.parametrize("K", [9, 32, 256, 257, 290, 3000])
+@pytest.mark.parametrize("probe", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_probes_with_ties_over_chunks(d, probe, K):
+    print("[case]", d, probe, K, flush=True)
+    rng = np.random.default_rng(K + probe)
+    lens = rng.integers(1, 12, 400)
+    ix, X = index(rng, lens, d=d)
+    C = rng.integers(-127, 128, (K, d)).astype(np.int8)
+    C[rng.integers(0, K, K // 3)] = C[0]                        # a third of the centroids equal
+    C[K - 1] = -128
+    q_lens = np.array([5, 40, 1], dtype=np.int64)
+    Q = np.concatenate([X[rng.integers(0, X.shape[0], 44)], C[:1], np.full((1, d), 127, np.int8)])
+    assign, starts, docs = (t.cpu().numpy() for t in dz.filter_build(ix, torch.from_numpy(C).to(DEV), torch.from_numpy(X).to(DEV)))
+    ids, counts = dz.filter_query(ix, torch.from_numpy(Q).to(DEV), q_lens, probe, 60)
+    qo = np.concatenate([[0], np.cumsum(q_lens)])
+    for b in range(len(q_lens)):
+        want_ids, want_counts = orc.filter_query(Q[qo[b]:qo[b + 1]], C, starts.view(np.uint32), docs.view(np.uint32), len(lens), probe, 60)
+        assert np.array_equal(counts.cpu().numpy()[b], want_counts)
+        assert np.array_equal(ids.cpu().numpy()[b], want_ids)
