@@ -937,7 +937,7 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
 
 namespace {
 struct KmeansWorkspace {
-    size_t assign, sums, counts, cent, table, total;
+    size_t assign, sums, counts, cent, table, least, order, total;   // least: what a call cannot do without
 };
 KmeansWorkspace carve_kmeans(uint32_t d, uint64_t n, uint32_t K) {
     KmeansWorkspace w{};
@@ -947,6 +947,8 @@ KmeansWorkspace carve_kmeans(uint32_t d, uint64_t n, uint32_t K) {
     w.counts = p; p += align_up((size_t)K * 4, 256);
     w.cent = p;   p += align_up(filter_centroid_bytes(K, d), 256);
     w.table = p;  p += align_up(filter_table_bytes(K), 256);
+    w.least = p;   // a workspace without the rest is accepted too
+    w.order = p;  p += align_up(((size_t)n + K) * 4, 256);
     w.total = p;
     return w;
 }
@@ -969,7 +971,7 @@ dessert_status_t dessert_filter_kmeans(const dessert_index_t* ix, const int8_t* 
     if ((uintptr_t)sample_dev % 16 || (uintptr_t)workspace_dev % 256)
         return fail(DESSERT_EINVAL, "sample_dev must be 16-byte and workspace_dev 256-byte aligned");
     const KmeansWorkspace w = carve_kmeans(ix->cfg.d, n_sample, n_centroids);
-    if (workspace_bytes < w.total)
+    if (workspace_bytes < w.least)
         return fail(DESSERT_EINVAL, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, w.total);
     DeviceGuard guard(ix->cfg.device);
     if (!guard.ok) return fail(DESSERT_EHIP, "hipSetDevice(%d) failed", ix->cfg.device);
@@ -980,7 +982,8 @@ dessert_status_t dessert_filter_kmeans(const dessert_index_t* ix, const int8_t* 
         HIP_TRY(launch_filter_assign(sample_dev, n_sample, ix->cfg.d, n_centroids, ws + w.cent, ws + w.table, assign,
                                      ix->stream));
         HIP_TRY(launch_kmeans_update(sample_dev, n_sample, ix->cfg.d, assign, n_centroids, (int32_t*)(ws + w.sums),
-                                     (uint32_t*)(ws + w.counts), centroids_dev, ix->stream));
+                                     (uint32_t*)(ws + w.counts), centroids_dev,
+                                     workspace_bytes >= w.total ? (uint32_t*)(ws + w.order) : nullptr, ix->stream));
     }
     return DESSERT_OK;
 }

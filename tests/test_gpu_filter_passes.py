@@ -75,3 +75,28 @@ def test_probes_with_ties_over_chunks(d, probe, K):
         want_ids, want_counts = orc.filter_query(Q[qo[b]:qo[b + 1]], C, starts.view(np.uint32), docs.view(np.uint32), len(lens), probe, 60)
         assert np.array_equal(counts.cpu().numpy()[b], want_counts)
         assert np.array_equal(ids.cpu().numpy()[b], want_ids)
+
+
+# n: less than a group's positions, either side of a workgroup's 1024, several workgroups; one cluster for all, clusters that span
+# groups and workgroups, most clusters empty.  The smaller workspace of a caller that knows only the older size takes the other path
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("n,K", [(1, 3), (15, 1), (63, 7), (1023, 5), (1024, 1), (1025, 40), (5000, 900), (3000, 20_000)])
+def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
+    print("[case]", d, n, K, flush=True)
+    rng = np.random.default_rng(d + n + K)
+    pool = rng.integers(-128, 128, (6, d))
+    X = np.clip(pool[rng.integers(0, 6, n)] + rng.integers(-9, 10, (n, d)), -128, 127).astype(np.int8)
+    C = rng.integers(-128, 128, (K, d)).astype(np.int8)
+    C[: min(K, n)] = X[: min(K, n)]
+    R = (rng.integers(0, 2, (8 * 4, d)) * 2 - 1).astype(np.int8)
+    ix = dz.create(d, 8, 4, proj=torch.from_numpy(R).to(DEV))
+    Xd = torch.from_numpy(X).to(DEV)
+    want = orc.kmeans(X, C, 2)
+    want = want[0] if isinstance(want, tuple) else want
+    assert np.array_equal(dz.filter_kmeans(ix, Xd, torch.from_numpy(C).to(DEV), 2).cpu().numpy(), want)
+    full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
+    order = ((n + K) * 4 + 255) // 256 * 256
+    cent = torch.from_numpy(C).to(DEV)
+    ws = torch.empty(full - order, dtype=torch.uint8, device=DEV)
+    assert dz.lib().dessert_filter_kmeans(ix.handle, Xd.data_ptr(), n, cent.data_ptr(), K, 2, ws.data_ptr(), ws.numel()) == dz.OK
+    assert np.array_equal(cent.cpu().numpy(), want)
