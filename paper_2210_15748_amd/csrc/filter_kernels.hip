@@ -687,6 +687,61 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
         const uint32_t left = (pairs - p0 + WAVES - 1) / WAVES;
         const uint32_t n_ranges = left < 64 ? left : 64;
         constexpr int U = 8;  // elements per lane per trip
+        // Count a trip's ids (0xFFFFFFFF: none) and queue the documents that are hit for the first time: all counter updates are
+        // in flight together, and the wave takes its queue slots with one atomic per trip.
+        auto count = [&](const uint32_t (&id)[U]) {
+            uint32_t old[U], local[U];
+            bool hit[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                local[u] = id[u] - doc0;  // wraps to a large value for ids below the slab
+                hit[u] = id[u] != 0xFFFFFFFFu && local[u] < here;
+                old[u] = hit[u] ? atomicAdd(&cnt[local[u] / PER], 1u << ((local[u] % PER) * BITS)) : 0u;
+            }
+            uint64_t fm[U];
+            uint32_t found = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                fm[u] = __ballot(hit[u] && ((old[u] >> ((local[u] % PER) * BITS)) & MASK) == 0);
+                found += (uint32_t)__builtin_popcountll(fm[u]);
+            }
+            if (found == 0) return;
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&q_count, found);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t pos = base + (uint32_t)__builtin_popcountll(fm[u] & ((1ull << lane) - 1));
+                if (((fm[u] >> lane) & 1) && pos < FILTER_QUEUE) queue[pos] = (QT)local[u];
+                base += (uint32_t)__builtin_popcountll(fm[u]);
+            }
+        };
+        // Ranges of 24 and more elements on average (a few thousand documents per bucket): a load takes one range, 64 elements of it at
+        // most, and its bounds are wave-uniform; a long range comes back for its rest.  Shorter ranges are read as one concatenated
+        // run, where finding an element's range costs some nine operations per range and element.  (128 query sets of 128 probed
+        // buckets, 65 elements per bucket and slab: 275 -> 176 us, together with the batched counting; one set of 32: 12.2 -> 9.6 us.)
+        if (total >= 24 * n_ranges) {
+            uint32_t j = 0, off = 0;   // next range, and what is done of it
+            while (j < n_ranges) {
+                uint32_t id[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    id[u] = 0xFFFFFFFFu;
+                    if (j < n_ranges) {
+                        const uint32_t lo_j = (uint32_t)__builtin_amdgcn_readlane((int)lo_l, (int)j);
+                        const uint32_t n_j = (uint32_t)__builtin_amdgcn_readlane((int)n_l, (int)j);
+                        if (off + lane < n_j) id[u] = bucket_docs[(size_t)lo_j + off + lane];
+                        off += 64;
+                        if (off >= n_j) {
+                            off = 0;
+                            ++j;
+                        }
+                    }
+                }
+                count(id);
+            }
+            continue;
+        }
         for (uint32_t f0 = 0; f0 < total; f0 += 64 * U) {
             uint32_t id[U];
 #pragma unroll
@@ -704,26 +759,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
                 }
                 id[u] = addr != 0xFFFFFFFFu ? bucket_docs[addr] : 0xFFFFFFFFu;
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t local = id[u] - doc0;  // wraps to a large value for ids below the slab
-                const bool hit = id[u] != 0xFFFFFFFFu && local < here;
-                bool first = false;
-                if (hit) {
-                    const uint32_t sh = (local % PER) * BITS;
-                    const uint32_t old = atomicAdd(&cnt[local / PER], 1u << sh);
-                    first = ((old >> sh) & MASK) == 0;
-                }
-                // documents hit for the first time go to the queue: one LDS atomic per wave
-                const uint64_t fm = __ballot(first);
-                if (fm) {
-                    uint32_t base = 0;
-                    if (lane == (uint32_t)__builtin_ctzll(fm)) base = atomicAdd(&q_count, (uint32_t)__builtin_popcountll(fm));
-                    base = (uint32_t)__builtin_amdgcn_readlane((int)base, __builtin_ctzll(fm));
-                    const uint32_t pos = base + (uint32_t)__builtin_popcountll(fm & ((1ull << lane) - 1));
-                    if (first && pos < FILTER_QUEUE) queue[pos] = (QT)local;
-                }
-            }
+            count(id);
         }
     }
     __syncthreads();
