@@ -236,6 +236,7 @@ Workspace carve(const dessert_index* ix, uint32_t B, uint64_t total_q, uint64_t 
 struct Batch {
     std::vector<uint32_t> q_off;
     uint64_t total_q = 0, total_scored = 0, max_scored = 0;
+    uint64_t chunks = 0, chunk_pairs = 0;   // of 32 query vectors, summed over the sets
     uint32_t max_q_len = 0;
     uint32_t q_uniform = 0;      // common query-set length, 0 if they differ
     uint64_t cand_uniform = 0;   // common candidate-list length, 0 if they differ (or no candidates)
@@ -282,6 +283,8 @@ dessert_status_t check_batch(const dessert_index* ix, const void* q_vectors, con
         if (nxt > 0xFFFFFFFFull) return fail(DESSERT_EINVAL, "more than 2^32-1 query vectors");
         out->q_off[b + 1] = (uint32_t)nxt;
         if (q_lengths[b] > out->max_q_len) out->max_q_len = q_lengths[b];
+        out->chunks += (q_lengths[b] + 31) / 32;
+        out->chunk_pairs += (q_lengths[b] + 31) / 64;
     }
     out->total_q = out->q_off[B];
     out->q_uniform = q_lengths[0];
@@ -323,6 +326,8 @@ dessert_status_t check_uniform_batch(const dessert_index* ix, const void* q_vect
     if ((uint64_t)q_len * B > 0xFFFFFFFFull) return fail(DESSERT_EINVAL, "more than 2^32-1 query vectors");
     out->total_q = (uint64_t)q_len * B;
     out->max_q_len = out->q_uniform = q_len;
+    out->chunks = (uint64_t)B * ((q_len + 31) / 32);
+    out->chunk_pairs = (uint64_t)B * ((q_len + 31) / 64);
     if (cand_ids) {
         if (cand_len == 0) return fail(DESSERT_EINVAL, "cand_length = 0 with candidate ids given");
         out->max_scored = out->cand_uniform = cand_len;
@@ -428,6 +433,9 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     sa.codes = ix->codes; sa.offsets = ix->offsets; sa.n_docs = ix->n_docs;
     sa.L = ix->cfg.L; sa.C = ix->cfg.C; sa.code_bytes = code_width(ix->cfg);
     sa.qcodes = qcodes; sa.q_off = d_q_off; sa.q_uniform = bt.q_uniform; sa.n_queries = B; sa.max_q_len = bt.max_q_len;
+    sa.chunks = bt.chunks;
+    // DESSERT_SCORE_MASKLUT stays with the single-chunk forms (the cross-check)
+    sa.chunk_pairs = ix->score_algo == DESSERT_SCORE_AUTO ? bt.chunk_pairs : 0;
     sa.cand_ids = cand_ids; sa.cand_off = cand_ids ? d_cand_off : nullptr; sa.cand_uniform = cand_ids ? bt.cand_uniform : 0;
     sa.max_scored = bt.max_scored; sa.total_scored = bt.total_scored; sa.n_vectors = ix->n_vectors; sa.scores = scores;
     sa.remap = ix->transform != DESSERT_SCORE_RAW_COUNTS ? ix->remap : nullptr;

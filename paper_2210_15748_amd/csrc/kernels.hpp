@@ -63,6 +63,7 @@ struct ScoreArgs {
     uint32_t q_uniform;         // != 0: every query set has this many vectors (q_off[b] = b * q_uniform)
     uint32_t n_queries;
     uint32_t max_q_len;
+    uint64_t chunks, chunk_pairs;  // chunks of 32 query vectors in all sets together, and pairs of chunks of one set (launch heuristics only)
     const uint32_t* cand_ids;   // dev or nullptr
     const uint64_t* cand_off;   // dev [B+1] (candidate mode); unused when cand_uniform != 0
     uint64_t cand_uniform;      // != 0: every candidate list has this many ids

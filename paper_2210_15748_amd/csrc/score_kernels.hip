@@ -5,6 +5,7 @@
 #include "kernels.hpp"
 
 #include <cstdio>
+#include <type_traits>
 
 namespace dessert {
 
@@ -267,6 +268,7 @@ constexpr int masklut_min_waves(int L, int CB, int CW, int W, int REMAP) {
     return 1;
 }
 constexpr uint32_t LUT_BINS = 64;   // length classes for the in-block ordering
+constexpr uint32_t MASKLUT_CHUNK_PAIRS = 1u << 31;  // flag in the kernel's gz argument
 
 // Per-workgroup bookkeeping, in static LDS beside the mask table.
 struct LutBlockMeta {
@@ -299,6 +301,11 @@ struct LutBlockMeta {
 // of P+15 planes; the lanes of a document add theirs over DPP, each lane un-slices its share of the query vectors and
 // forms (65536/L * S + floor(m/2)) / m.  Needs documents shorter than 65536 vectors (32-bit numerators).
 // CW = bytes per table code (1: C <= 8, 2: wider codes); CB = bits of a table index (2^CB entries per table).
+// Chunk pairs (W = 2, one query set per workgroup): the two masks of an entry are those of two successive chunks of the same
+// set, for sets of more than 32 vectors: the codes are read once for 64 query vectors, with one address and one 8-byte LDS read per
+// table, and one sum is stored.  The last chunk of an odd number runs a loop that uses the first masks only.
+// 64 lists of 4096 of 300 000 documents, 48 vectors: L = 32, C = 7 214 -> 184 us, C = 8 253 -> 181, L = 16, C = 8 160 -> 115; 1000
+// documents of 256 vectors against 16 sets of 256, L = 8, C = 9: 68 -> 38 us (LDS-bound: half the reads).
 // gz = chunk groups: with gz > 1 the 32-vector chunks of a query set are dealt round-robin to gz
 // workgroups, which add their partial sums into the (pre-zeroed) scores with integer atomics.
 // (SPLIT = false: gz is 1.)
@@ -339,7 +346,10 @@ template <int L, int CB, int CW, int REMAP, int W, bool SPLIT>
 __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L, CB, CW, W, REMAP)) void score_masklut_kernel(ScoreArgs a, uint32_t docs_per_block, uint32_t gy_linear,
                                                             uint32_t gz_arg) {
     constexpr bool ROT = masklut_rotated(L, CB, CW, W);
-    const uint32_t gz = SPLIT ? gz_arg : 1u;
+    // chunk pairs: W = 2, but both masks of an entry belong to one query set, to its chunks c and c + 1 of 32 vectors
+    const bool chunk_pairs = W == 2 && (SPLIT || (gz_arg & MASKLUT_CHUNK_PAIRS) != 0);
+    const uint32_t gz = SPLIT ? gz_arg & ~MASKLUT_CHUNK_PAIRS : 1u;
+    const uint32_t chunk_step = chunk_pairs ? 64u : 32u;
     constexpr int T = masklut_threads(L, CB, CW, W);
     constexpr int LW = L * CW / 4;  // dwords per code row
     constexpr int STRIDE = 1 << CB;
@@ -371,17 +381,19 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     }
     const uint32_t cz = SPLIT ? by_idx % gz : 0u;  // chunk group
     if constexpr (SPLIT) by_idx /= gz;
-    const uint32_t b0 = by_idx * W;     // first query set of this workgroup
-    const Span sp = query_span(a, b0);  // W > 1: every set scores the same documents
+    const uint32_t b0 = chunk_pairs ? by_idx : by_idx * W;  // first query set of this workgroup
+    const Span sp = query_span(a, b0);  // two sets: both score the same documents
     const uint64_t first = (uint64_t)bx_idx * docs_per_block;
     if (first >= sp.count) return;
     const uint32_t ndocs = (uint32_t)((first + docs_per_block < sp.count) ? docs_per_block : sp.count - first);
     uint32_t q_lo[W], q_len[W], max_len = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const bool have = b0 + w < a.n_queries;
-        q_lo[w] = have ? q_begin(a, b0 + w) : 0;
-        q_len[w] = have ? q_begin(a, b0 + w + 1) - q_lo[w] : 0;
+        const uint32_t b = chunk_pairs ? b0 : b0 + w, skip = chunk_pairs ? 32u * w : 0u;
+        const bool have = b < a.n_queries;
+        q_lo[w] = have ? q_begin(a, b) + skip : 0;
+        const uint32_t end = have ? q_begin(a, b + 1) : 0;
+        q_len[w] = end > q_lo[w] ? end - q_lo[w] : 0;
         max_len = q_len[w] > max_len ? q_len[w] : max_len;
     }
     const uint32_t lane = threadIdx.x & 63;
@@ -391,7 +403,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     // ---- prologue: where each document lives, the length-class ordering, and the first chunk's mask
     // table.  Global loads are issued first and used late, so the dependent chain candidate id ->
     // offsets runs while the table is zeroed and the query codes arrive.
-    const uint32_t c_first = cz * 32;  // first chunk of 32 query vectors taken by this workgroup
+    const uint32_t c_first = cz * chunk_step;  // first chunk of 32 query vectors taken by this workgroup
     auto chunk_len = [&](int w, uint32_t c0) { return c0 >= q_len[w] ? 0u : (q_len[w] - c0 < 32 ? q_len[w] - c0 : 32u); };
     auto query_code = [&](int w, uint32_t c0, uint32_t i) {  // entry i = (q, t) of the chunk: the code of q in table t
         const size_t at = (size_t)(q_lo[w] + c0) * L + i;
@@ -505,7 +517,8 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
         for (int k = 0; k < LW; ++k) asm volatile("" : "+v"(rot_posc[k]));
         asm volatile("" : "+v"(rot_swap));
     }
-    for (uint32_t c0 = c_first; c0 < max_len; c0 += gz * 32) {  // chunks of 32 query vectors
+    for (uint32_t c0 = c_first; c0 < max_len; c0 += gz * chunk_step) {  // chunks of 32 query vectors
+        const bool second = W == 2 && c0 < q_len[W - 1];  // the entries' second masks are in use
         if (c0 != c_first) {  // the first chunk's table was built above
             __syncthreads();  // previous chunk's readers are done
             zero_table();
@@ -573,7 +586,8 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
             };
             // one round: the table reads of this lane's vector, the carry-save count and the running maximum (or sum).
             // row = the lane's row of the document in this round before clamping: only rows 0 .. m-1 count towards a sum
-            auto process = [&](const uint32_t (&dw)[LW], int32_t row) {
+            auto process = [&](const uint32_t (&dw)[LW], int32_t row, auto masks) {
+                constexpr int NW = decltype(masks)::value;
                 const char* lut_bytes = reinterpret_cast<const char*>(lut);
                 uint32_t off[L];  // byte offset of x's entry within each table
 #pragma unroll
@@ -592,7 +606,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                         off[2 * w + 1] = half_shl<1>(dw[w], entry_shift);
                     }
                 }
-                uint32_t msk[W][L];
+                uint32_t msk[NW][L];
 #pragma unroll
                 for (int t = 0; t < L; ++t) {
                     if constexpr (ROT) {
@@ -602,11 +616,11 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     } else {
                         uint2 e = *(const uint2*)(lut_bytes + t * STRIDE * 8 + off[t]);
                         msk[0][t] = e.x;
-                        msk[1][t] = e.y;
+                        if constexpr (NW == 2) msk[1][t] = e.y;
                     }
                 }
 #pragma unroll
-                for (int w = 0; w < W; ++w) {
+                for (int w = 0; w < NW; ++w) {
                     uint32_t cnt[P];
                     csa_planes<L>(msk[w], cnt);
                     if constexpr (!MEAN) {
@@ -622,7 +636,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     if (++rounds_in_sum1 == 16) {   // the same for every lane of the wave
                         rounds_in_sum1 = 0;
 #pragma unroll
-                        for (int w = 0; w < W; ++w) {
+                        for (int w = 0; w < NW; ++w) {
                             planes_add<P2, P1>(sum2[w], sum1[w]);
 #pragma unroll
                             for (int p = 0; p < P1; ++p) sum1[w][p] = 0;
@@ -641,16 +655,17 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
             // code buffers used in turn (the loop body is one round per buffer), so no register copies;
             // DEPTH rounds of codes are in flight while a round is processed
             constexpr int DEPTH = (W == 1 && LW <= 8) ? 2 : 1;
+            auto rounds = [&](auto masks) {
             if constexpr (DEPTH == 1) {
                 uint32_t buf_a[LW], buf_b[LW];
                 load_codes(clamped(j < 0 ? 0 : j), buf_a);
                 for (;;) {
                     load_codes(clamped(j + G), buf_b);
-                    process(buf_a, j);
+                    process(buf_a, j, masks);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + G), buf_a);
-                    process(buf_b, j);
+                    process(buf_b, j, masks);
                     j += G;
                     if (!__any(j < j_end)) break;
                 }
@@ -660,19 +675,27 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                 load_codes(clamped(j + G), buf_b);
                 for (;;) {
                     load_codes(clamped(j + 2 * G), buf_c);
-                    process(buf_a, j);
+                    process(buf_a, j, masks);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + 2 * G), buf_a);
-                    process(buf_b, j);
+                    process(buf_b, j, masks);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + 2 * G), buf_b);
-                    process(buf_c, j);
+                    process(buf_c, j, masks);
                     j += G;
                     if (!__any(j < j_end)) break;
                 }
             }
+            };
+            if constexpr (W == 2) {  // a loop of its own where only the first masks are in use (a set's odd last chunk, an odd last set)
+                if (second) rounds(std::integral_constant<int, 2>{});
+                else rounds(std::integral_constant<int, 1>{});
+            } else {
+                rounds(std::integral_constant<int, 1>{});
+            }
+            int32_t first_score = 0;
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 int32_t score = 0;
@@ -758,10 +781,18 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     part += dpp_mov<0x4E>(part);
                     score = (int32_t)part;
                 }
-                if (valid && sub == 0 && b0 + w < a.n_queries && c0 < q_len[w]) {
-                    // W > 1 implies every set scores every document: set b0+w starts at (b0+w)*n_docs
-                    int32_t* dst = a.scores + (W == 1 ? sp.base + meta.slot[doc] : (uint64_t)(b0 + w) * a.n_docs + first + doc);
-                    if (W == 1 && m == 0 && meta.lo[doc] == ~0ull) {
+                if (W == 2 && chunk_pairs) {
+                    if (w == 0) {
+                        first_score = score;
+                        continue;
+                    }
+                    score += first_score;
+                }
+                const bool one_set = W == 1 || chunk_pairs;
+                if (valid && sub == 0 && (one_set || (b0 + w < a.n_queries && c0 < q_len[w]))) {
+                    // two sets: each scores every document, set b0+w starts at (b0+w)*n_docs
+                    int32_t* dst = a.scores + (one_set ? sp.base + meta.slot[doc] : (uint64_t)(b0 + w) * a.n_docs + first + doc);
+                    if (one_set && m == 0 && meta.lo[doc] == ~0ull) {
                         if (c0 == 0) *dst = -1;  // empty candidate slot
                     } else if (SPLIT) {
                         if (score) atomicAdd(dst, score);
@@ -1224,6 +1255,11 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     constexpr size_t PAIR_BYTES = (size_t)L * (1u << CB) * 8;
     constexpr bool PAIR_OK = PAIR_BYTES <= 32 * 1024 || (L <= 32 && PAIR_BYTES <= 64 * 1024);
     bool pair = PAIR_OK && a.cand_ids == nullptr && a.n_queries >= 2 && !a.sigma_mean;  // the mean form takes one set per workgroup
+    // chunk pairs where sets are not paired: measured against a pass over one chunk, a pass over two costs 1.72 and one that uses
+    // only the first masks 1.4 (8-byte entries, and at 32 tables not the rotated order): not for batches of mostly short sets or of
+    // three chunks each
+    const bool chunk_pairs_pay = PAIR_OK && !a.sigma_mean &&
+                                 172 * a.chunk_pairs + 140 * (a.chunks - 2 * a.chunk_pairs) < 97 * a.chunks;
     // documents per workgroup: at most LUT_DOCS; fewer when that would leave the 256 CUs short of
     // workgroups, but at least 64 (32 = one run of 8 documents for each of the four waves when the
     // documents are long: about 4096 vectors per workgroup keep the table build amortised)
@@ -1244,8 +1280,30 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     // long query sets on a grid that is still small: split the 32-vector chunks over gz workgroups
     const uint32_t chunks = (a.max_q_len + 31) / 32;
     uint32_t gz = 1;
-    if (chunks > 1 && bx * gy < 2048) {
-        pair = false;  // the split kernels take one query set per workgroup
+    bool cp = false;
+    if (chunk_pairs_pay && (!pair || bx * gy < 2048)) {
+        // one query set per workgroup and, when that leaves the chip short of workgroups, its pairs of chunks split over gz of them.
+        // Not when even that is a small grid (one short list): then single chunks split, twice the workgroups
+        constexpr uint32_t cp_threads = PAIR_OK ? masklut_threads(L, CB, CW, 2) : 256;
+        constexpr uint32_t cp_docs = cp_threads / 64 * (L <= 32 ? 16 : 8);   // a run of documents for every wave
+        uint32_t d2 = LUT_DOCS;
+        while (d2 > cp_docs && ((a.max_scored + d2 - 1) / d2) * a.n_queries < 4096) d2 /= 2;
+        const uint64_t bx2 = (a.max_scored + d2 - 1) / d2;
+        const uint32_t units = (chunks + 1) / 2;
+        if (bx2 * a.n_queries * units * (cp_threads / 256) >= 1024) {
+            cp = true;
+            pair = false;
+            dpb = d2;
+            bx = bx2;
+            gy = a.n_queries;
+            if (units > 1 && bx * gy < 2048) {
+                gz = (uint32_t)((2048 + bx * gy - 1) / (bx * gy));
+                if (gz > units) gz = units;
+            }
+        }
+    }
+    if (!cp && chunks > 1 && bx * gy < 2048) {
+        pair = false;  // single chunks of one query set per workgroup
         gy = a.n_queries;
         gz = (uint32_t)((2048 + bx * gy - 1) / (bx * gy));
         if (gz > chunks) gz = chunks;
@@ -1273,10 +1331,20 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     const int remap = a.sigma_mean ? (a.q_weights ? 4 : 3) : a.q_weights ? 2 : a.remap ? 1 : 0;
     // the instantiation as a profiler prints it
     if (desc)
-        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, remap, pair ? 2 : 1,
+        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, remap, (pair || cp) ? 2 : 1,
                  gz > 1 ? "true" : "false");
     using Kernel = void (*)(ScoreArgs, uint32_t, uint32_t, uint32_t);
     if constexpr (PAIR_OK) {
+        if (cp) {
+            const Kernel kern3 = gz > 1 ? (remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, true>
+                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, true>
+                                                        : score_masklut_kernel<L, CB, CW, 0, 2, true>)
+                                        : (remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, false>
+                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, false>
+                                                        : score_masklut_kernel<L, CB, CW, 0, 2, false>);
+            hipLaunchKernelGGL(kern3, grid, dim3(masklut_threads(L, CB, CW, 2)), 0, stream, a, dpb, gy_linear, gz | MASKLUT_CHUNK_PAIRS);
+            return hipGetLastError();
+        }
         if (pair) {
             const Kernel kern2 = remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, false>
                                  : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, false>
