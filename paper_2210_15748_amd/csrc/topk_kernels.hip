@@ -54,6 +54,112 @@ __global__ __launch_bounds__(T) void topk_scores_kernel(TopkArgs a, KeyPlan plan
     }
 }
 
+// A few results from a short slice (k <= TOPK_FEW, at most 4096 scores, 32-bit keys): no histogram.  A lane holds eight keys in
+// descending order; a round takes the largest head of the wave (six DPP maxima) and moves the lane that held it up, so a wave's
+// k best of its 512 scores are k rounds with no barrier between them; the waves' lists meet in LDS once, where every key's place
+// in the result is counted.  Bound: latency of the load and of k rounds of some 100 cycles; the selection above has some twenty
+// barriers.  Whole searches of one list of 4096 ids: k = 1 26.3 -> 23.2 us, 10 27.6 -> 25.2, 16 28.7 -> 26.1, 24 28.4 -> 27.9, 32 29.4 -> 30.3 (64
+// lists of 4096: k = 10 120.8 -> 117.8, 32 122.4 -> 123.0): taken up to 16 results.
+constexpr uint32_t TOPK_FEW = 16, TOPK_FEW_KEYS = 8, TOPK_FEW_WAVES = 8;   // results; keys per lane; waves of a workgroup at most
+// largest x of the wave, in every lane
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+    auto step = [](uint32_t v, uint32_t o) { return v > o ? v : o; };
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true));   // row_shr 1, 2, 4, 8
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true));
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true));
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true));
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, true));   // row_bcast 15, 31
+    x = step(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, true));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+// k <= 64 rounds over the lanes' descending lists: lane i ends with the i-th largest key of the wave (0: fewer than that)
+template <int N>
+__device__ __forceinline__ uint32_t wave_take_best(uint32_t (&key)[N], uint32_t k) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t mine = 0;
+    for (uint32_t i = 0; i < k;) {
+        const uint32_t top = wave_max_u32(key[0]);
+        const bool held = key[0] == top;
+        uint64_t holders = __ballot(held);   // more than one: an id listed twice, or no keys left
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t stays = key[j], follows = j + 1 < N ? key[j + 1 < N ? j + 1 : j] : 0u;
+            key[j] = held ? follows : stays;
+        }
+        mine = lane == i ? top : mine;
+        ++i;
+        for (holders &= holders - 1; holders && i < k; holders &= holders - 1, ++i) mine = lane == i ? top : mine;
+    }
+    return mine;
+}
+
+__global__ __launch_bounds__(TOPK_FEW_WAVES * 64) void topk_few_kernel(TopkArgs a, uint32_t id_bits, uint32_t slices) {
+    __shared__ uint32_t best[TOPK_FEW_WAVES][TOPK_FEW + 1];   // a list per wave; the odd row length keeps rows apart in the banks
+    const uint32_t b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    uint64_t base, count;
+    if (a.cand_ids) {
+        base = a.cand_uniform ? (uint64_t)b * a.cand_uniform : a.cand_off[b];
+        count = a.cand_uniform ? a.cand_uniform : a.cand_off[b + 1] - base;
+    } else {
+        base = (uint64_t)b * a.n_docs;
+        count = a.n_docs;
+    }
+    const uint64_t per = (count + slices - 1) / slices;
+    const uint64_t lo = (uint64_t)s * per < count ? (uint64_t)s * per : count;
+    const uint32_t n = (uint32_t)((lo + per < count ? lo + per : count) - lo);   // at most 8 * blockDim.x
+    ScoreKeysT<uint32_t> keys{a.scores + base + lo, a.cand_ids ? a.cand_ids + base + lo : nullptr, lo, id_bits};
+    uint32_t key[TOPK_FEW_KEYS];
+#pragma unroll
+    for (uint32_t u = 0; u < TOPK_FEW_KEYS; ++u) {
+        uint32_t got[1];
+        keys.load(tid + u * blockDim.x, n, got);
+        key[u] = got[0];
+    }
+    auto order = [&](int i, int j) {
+        const uint32_t x = key[i], y = key[j];
+        key[i] = x > y ? x : y;
+        key[j] = x > y ? y : x;
+    };
+    // Batcher's odd-even merge sort of eight
+    order(0, 1); order(2, 3); order(4, 5); order(6, 7);
+    order(0, 2); order(1, 3); order(4, 6); order(5, 7);
+    order(1, 2); order(5, 6);
+    order(0, 4); order(1, 5); order(2, 6); order(3, 7);
+    order(2, 4); order(3, 5);
+    order(1, 2); order(3, 4); order(5, 6);
+    auto result = [&](uint32_t i, uint32_t top) {
+        if (slices == 1)
+            write_result(top, id_bits, a.out_ids + (size_t)b * a.k + i, a.out_scores + (size_t)b * a.k + i);
+        else
+            a.partial[((size_t)b * slices + s) * a.k + i] = top;
+    };
+    const uint32_t k = a.k, mine = wave_take_best(key, k);
+    if (waves == 1) {
+        if (lane < k) result(lane, mine);
+        return;
+    }
+    if (lane < k) best[wave][lane] = mine;
+    __syncthreads();
+    // a key's place in the result = its place in its own list plus the keys of each other list that rank before it (of equal
+    // keys the lower wave's): eight lanes per key, one list each
+    const uint32_t other = tid & 7, keys_in_all = waves * k, per_pass = blockDim.x / 8;
+    for (uint32_t e0 = 0; e0 < keys_in_all; e0 += per_pass) {
+        const uint32_t e = e0 + tid / 8, w = e / k, i = e - w * k;
+        const bool have = e < keys_in_all;
+        const uint32_t x = have ? best[w][i] : 0u;
+        uint32_t before = 0;
+        if (have && other < waves && other != w)
+            for (uint32_t j = 0; j < k; ++j) {
+                const uint32_t o = best[other][j];
+                before += (o > x || (o == x && other < w)) ? 1u : 0u;
+            }
+        before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x111, 0xF, 0xF, true);   // lane 7 and 15 of a row: sum over eight
+        before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x112, 0xF, 0xF, true);
+        before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x114, 0xF, 0xF, true);
+        if (have && other == 7 && i + before < k) result(i + before, x);
+    }
+}
+
 __global__ __launch_bounds__(TOPK_THREADS) void topk_merge_kernel(TopkArgs a, KeyPlan plan, uint32_t slices,
                                                                   uint32_t kpad) {
     extern __shared__ uint64_t sorted[];
@@ -304,6 +410,11 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t stream) {
     }
     const bool fit32 = keys_fit_32(a.max_score, a.n_docs ? a.n_docs - 1 : 0);
     const dim3 grid(slices, a.n_queries);
+    const uint64_t slice_len = (a.max_scored + slices - 1) / slices;
+    if (fit32 && a.k <= TOPK_FEW && slice_len <= 4096) {   // 512 scores per wave
+        const uint32_t waves = slice_len <= 512 ? 1 : (uint32_t)((slice_len + 511) / 512);
+        hipLaunchKernelGGL(topk_few_kernel, grid, dim3(64 * waves), 0, stream, a, plan.id_bits, slices);
+    } else
     // every slice short enough to stay in the registers of the wider workgroup (see topk_scores_kernel)
     if ((a.max_scored + slices - 1) / slices <= (uint64_t)TOPK_THREADS_SHORT * 4) {
         if (fit32)
