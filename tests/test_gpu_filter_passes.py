@@ -100,3 +100,24 @@ def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
     ws = torch.empty(full - order, dtype=torch.uint8, device=DEV)
     assert dz.lib().dessert_filter_kmeans(ix.handle, Xd.data_ptr(), n, cent.data_ptr(), K, 2, ws.data_ptr(), ws.numel()) == dz.OK
     assert np.array_equal(cent.cpu().numpy(), want)
+
+
+# few vectors (up to 160 000, or 80 000 at d = 256): either side of a workgroup's 64 and 128 vectors and of the sizes that change the
+# form; fewer centroid tiles than waves, one more than waves, many; centroids that repeat across waves (ties to the lower id)
+@pytest.mark.parametrize("d,n,K", [(64, 1, 1), (64, 63, 33), (64, 65, 520), (128, 64, 257), (128, 129, 4000), (256, 100, 300), (256, 1000, 31),
+                                   (64, 32_769, 513), (128, 32_770, 700), (128, 160_000, 90), (128, 160_001, 90), (256, 80_001, 70)])
+def test_closest_centroid_of_few_vectors(d, n, K):
+    print("[case]", d, n, K, flush=True)
+    rng = np.random.default_rng(n + K)
+    lens = np.full((n + 6) // 7, 7)
+    lens[-1] = n - 7 * (len(lens) - 1)
+    ix, X = index(rng, lens, d=d)
+    C = rng.integers(-127, 128, (K, d)).astype(np.int8)
+    if K > 4:
+        C[rng.integers(0, K, K // 2)] = C[K - 1]
+        X[: n // 2] = C[K - 1]                                # their closest centroid stands in many tiles
+        dz.build_index(ix, torch.from_numpy(X).to(DEV), lens)
+    assign, _, _ = dz.filter_build(ix, torch.from_numpy(C).to(DEV), torch.from_numpy(X).to(DEV))
+    got = assign.cpu().numpy().view(np.uint32)
+    pick = np.unique(np.concatenate([np.arange(min(n, 200)), np.arange(max(0, n - 200), n), rng.integers(0, n, 1000)]))
+    assert np.array_equal(got[pick], orc.assign_centroids(X[pick], C).astype(np.uint32))
