@@ -916,7 +916,7 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
         ix->f_alloc_sub = 0;
         hipError_t e = hipMalloc(&ix->f_cent, filter_centroid_bytes(n_centroids, ix->cfg.d));
         if (e == hipSuccess) e = hipMalloc(&ix->f_table, filter_table_bytes(n_centroids));
-        if (e == hipSuccess) e = hipMalloc((void**)&ix->f_cursor, n_sub * 4);
+        if (e == hipSuccess) e = hipMalloc((void**)&ix->f_cursor, filter_cursor_bytes(n_sub));
         if (e == hipSuccess) e = hipMalloc((void**)&ix->f_sub_off, (n_sub + 1) * 4);
         if (e != hipSuccess) return fail(DESSERT_ENOMEM, "hipMalloc(filter state): %s", hipGetErrorString(e));
         ix->f_alloc_K = n_centroids;
@@ -956,7 +956,7 @@ KmeansWorkspace carve_kmeans(uint32_t d, uint64_t n, uint32_t K) {
     w.cent = p;   p += align_up(filter_centroid_bytes(K, d), 256);
     w.table = p;  p += align_up(filter_table_bytes(K), 256);
     w.least = p;   // a workspace without the rest is accepted too
-    w.order = p;  p += align_up(((size_t)n + K) * 4, 256);
+    w.order = p;  p += align_up((size_t)(n ? n : 1) * 4, 256);
     w.total = p;
     return w;
 }

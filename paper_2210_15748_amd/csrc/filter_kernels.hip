@@ -495,12 +495,20 @@ __global__ __launch_bounds__(256) void filter_merge_kernel(const int64_t* __rest
 // The set is an open-addressing table in LDS, per wave, when the document has at most DOC_SET_MAX vectors: some three
 // compare-and-swap round trips per 64 vectors.  Longer documents compare each vector with all before it by lane broadcast, 64 of them
 // per 64 vectors and chunk, as all documents did before: 60 000 documents of 70 vectors, 16 384 centroids 231 -> 199 us counting,
-// 238 -> 201 us filling.  Bound now: the counters' atomics, 4.1M to random places at 20 G/s.
+// 238 -> 201 us filling.  Bound now: the counters' atomics, 4.1M to random places at 20 G/s.  Few counters would share
+// lines, and atomics to one line wait for each other (4.5 G/s over 932 counters in 59 lines): up to COUNTER_WORDS words counter i
+// lies at word i << spread, a line of its own if they are few enough: 648 000 vectors, 932 centroids 145 -> 40 us a pass.
+constexpr uint64_t COUNTER_WORDS = 65536;
+static uint32_t counter_spread(uint64_t counters) {
+    uint32_t spread = 0;
+    while (spread < 4 && (counters << (spread + 1)) <= COUNTER_WORDS) ++spread;
+    return spread;
+}
 constexpr uint32_t DOC_SET = 512, DOC_SET_MAX = 384, DOC_SET_EMPTY = 0xFFFFFFFFu;
 template <bool FILL>
 __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __restrict__ assign,
                                                             const uint64_t* __restrict__ doc_off, uint64_t n_docs,
-                                                            uint32_t S, uint32_t sub_shift,
+                                                            uint32_t S, uint32_t sub_shift, uint32_t spread,
                                                             uint32_t* __restrict__ size_or_cursor,
                                                             const uint32_t* __restrict__ sub_off,
                                                             uint32_t* __restrict__ bucket_docs) {
@@ -510,7 +518,7 @@ __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __re
     uint32_t* set = (uint32_t*)set4;
     auto enter = [&](uint64_t doc, uint32_t c) {
         const uint32_t sub = c * S + (uint32_t)(doc >> sub_shift);
-        uint32_t pos = atomicAdd(&size_or_cursor[sub], 1u);
+        uint32_t pos = atomicAdd(&size_or_cursor[(size_t)sub << spread], 1u);
         if constexpr (FILL) bucket_docs[sub_off[sub] + pos] = (uint32_t)doc;
     };
     for (uint64_t doc = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6); doc < n_docs; doc += (uint64_t)gridDim.x * 4) {
@@ -580,20 +588,20 @@ __device__ inline uint32_t scan_threads(uint32_t x, uint32_t* wsum) {
     __syncthreads();
     return incl;
 }
-__device__ inline uint32_t scan_load16(const uint32_t* size, uint32_t first, uint32_t K, uint32_t (&x)[16]) {
+__device__ inline uint32_t scan_load16(const uint32_t* size, uint32_t first, uint32_t K, uint32_t spread, uint32_t (&x)[16]) {
     uint32_t sum = 0;
 #pragma unroll
     for (uint32_t i = 0; i < 16; ++i) {
-        x[i] = first + i < K ? size[first + i] : 0;
+        x[i] = first + i < K ? size[(size_t)(first + i) << spread] : 0;
         sum += x[i];
     }
     return sum;
 }
-__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_sums_kernel(const uint32_t* __restrict__ size, uint32_t K,
+__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_sums_kernel(const uint32_t* __restrict__ size, uint32_t K, uint32_t spread,
                                                                         uint32_t* __restrict__ off) {
     __shared__ uint32_t wsum[SCAN_THREADS / 64];
     uint32_t x[16];
-    const uint32_t sum = scan_load16(size, blockIdx.x * SCAN_PART + threadIdx.x * 16, K, x);
+    const uint32_t sum = scan_load16(size, blockIdx.x * SCAN_PART + threadIdx.x * 16, K, spread, x);
     const uint32_t incl = scan_threads(sum, wsum);
     if (threadIdx.x == SCAN_THREADS - 1) off[(size_t)blockIdx.x * SCAN_PART] = incl;
 }
@@ -613,27 +621,27 @@ __global__ __launch_bounds__(SCAN_THREADS) void filter_scan_parts_kernel(uint32_
     }
     if (threadIdx.x == 0) off[K] = carry;
 }
-__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_kernel(uint32_t* __restrict__ size, uint32_t K,
+__global__ __launch_bounds__(SCAN_THREADS) void filter_scan_kernel(uint32_t* __restrict__ size, uint32_t K, uint32_t spread,
                                                                    uint32_t* __restrict__ off) {
     __shared__ uint32_t wsum[SCAN_THREADS / 64];
     uint32_t x[16];
     const uint32_t first = blockIdx.x * SCAN_PART + threadIdx.x * 16;
     const uint32_t base = off[(size_t)blockIdx.x * SCAN_PART];   // read by all before scan_threads' barriers, rewritten after them
-    const uint32_t sum = scan_load16(size, first, K, x);
+    const uint32_t sum = scan_load16(size, first, K, spread, x);
     uint32_t run = base + scan_threads(sum, wsum) - sum;
 #pragma unroll
     for (uint32_t i = 0; i < 16; ++i)
         if (first + i < K) {
             off[first + i] = run;
-            size[first + i] = 0;
+            size[(size_t)(first + i) << spread] = 0;
             run += x[i];
         }
 }
-static void launch_filter_scan(uint32_t* size, uint32_t K, uint32_t* off, hipStream_t stream) {   // K >= 1
+static void launch_filter_scan(uint32_t* size, uint32_t K, uint32_t spread, uint32_t* off, hipStream_t stream) {   // K >= 1
     const uint32_t parts = (K + SCAN_PART - 1) / SCAN_PART;
-    hipLaunchKernelGGL(filter_scan_sums_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, off);
+    hipLaunchKernelGGL(filter_scan_sums_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off);
     hipLaunchKernelGGL(filter_scan_parts_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, off, parts, K);
-    hipLaunchKernelGGL(filter_scan_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, off);
+    hipLaunchKernelGGL(filter_scan_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off);
 }
 
 // bucket_off[c] = sub_off[c*S] for c = 0..K: the caller-visible bucket starts
@@ -926,19 +934,20 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
 // workspace of the older, smaller size) every coordinate is added to the sums by itself, as it always was before.
 // Bound: the vectors are read once, whole lines; 524 288 vectors of 128 dimensions, 16 384 centroids: 796 -> 117 us
 // for the update's five kernels (67M atomics before, 1.1M now and the two per vector of the sort, at 20 G/s).
-__global__ __launch_bounds__(256) void kmeans_count_kernel(const uint32_t* __restrict__ assign, uint64_t n, uint32_t* __restrict__ counts) {
+// While the vectors are ordered the sums' memory holds the counters, a centroid's at word c << spread (see COUNTER_WORDS).
+__global__ __launch_bounds__(256) void kmeans_count_kernel(const uint32_t* __restrict__ assign, uint64_t n, uint32_t spread, uint32_t* counters) {
     const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < n) atomicAdd(counts + assign[v], 1u);
+    if (v < n) atomicAdd(counters + ((size_t)assign[v] << spread), 1u);
 }
-// start of a centroid's run = sum of the counts before it (one workgroup; the counts stay, and so do the entries of cursor past K)
-__global__ __launch_bounds__(1024) void kmeans_starts_kernel(const uint32_t* __restrict__ counts, uint32_t K, uint32_t* __restrict__ cursor) {
+// a centroid's counter becomes the start of its run = the sum of the counts before it; the counts are kept (one workgroup)
+__global__ __launch_bounds__(1024) void kmeans_starts_kernel(uint32_t* counters, uint32_t K, uint32_t spread, uint32_t* __restrict__ counts) {
     __shared__ uint32_t wsum[16];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t carry = 0;
     for (uint32_t base = 0; base < K; base += 1024 * 16) {
         uint32_t x[16];
         const uint32_t first = base + tid * 16;
-        const uint32_t sum = scan_load16(counts, first, K, x);
+        const uint32_t sum = scan_load16(counters, first, K, spread, x);
         uint32_t incl = sum;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -956,27 +965,29 @@ __global__ __launch_bounds__(1024) void kmeans_starts_kernel(const uint32_t* __r
 #pragma unroll
         for (uint32_t i = 0; i < 16; ++i)
             if (first + i < K) {
-                cursor[first + i] = run;
+                counters[(size_t)(first + i) << spread] = run;
+                counts[first + i] = x[i];
                 run += x[i];
             }
         carry += all;
         __syncthreads();
     }
 }
-__global__ __launch_bounds__(256) void kmeans_order_kernel(const uint32_t* __restrict__ assign, uint64_t n, uint32_t* __restrict__ cursor,
-                                                           uint32_t* __restrict__ order) {
+__global__ __launch_bounds__(256) void kmeans_order_kernel(const uint32_t* __restrict__ assign, uint64_t n, uint32_t spread,
+                                                           uint32_t* counters, uint32_t* __restrict__ order) {
     const uint64_t v = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < n) order[atomicAdd(cursor + assign[v], 1u)] = (uint32_t)v;
+    if (v < n) order[atomicAdd(counters + ((size_t)assign[v] << spread), 1u)] = (uint32_t)v;
 }
-// LR = d / 4 lanes take a vector, four coordinates each; a group of LR lanes walks over KM_PIECES * LR consecutive
-// positions of the order and adds to the sums where the centroid changes.
-constexpr int KM_PIECES = 4;
+// LR = d / 4 lanes take a vector, four coordinates each; a group of LR lanes walks over pieces * LR consecutive
+// positions of the order and adds to the sums where the centroid changes.  (More pieces: fewer runs cut in two; fewer: more
+// workgroups.  14 000 vectors of 15 000 centroids take 63 us with four pieces, in 14 workgroups, 20 with one.)
 template <int LR>
 __global__ __launch_bounds__(256) void kmeans_runs_kernel(const int8_t* __restrict__ X, uint64_t n, const uint32_t* __restrict__ assign,
-                                                          const uint32_t* __restrict__ order, int32_t* __restrict__ sums) {
+                                                          const uint32_t* __restrict__ order, uint32_t pieces,
+                                                          int32_t* __restrict__ sums) {
     constexpr uint32_t D = LR * 4;
     const uint32_t l = threadIdx.x & (LR - 1), group_lane = (threadIdx.x & 63) & ~(LR - 1);
-    const uint64_t p0 = ((uint64_t)blockIdx.x * (256 / LR) + threadIdx.x / LR) * (KM_PIECES * LR);
+    const uint64_t p0 = ((uint64_t)blockIdx.x * (256 / LR) + threadIdx.x / LR) * (pieces * LR);
     int32_t acc[4] = {0, 0, 0, 0};
     uint32_t at = 0xFFFFFFFFu;   // the run's centroid
     auto flush = [&]() {
@@ -987,7 +998,7 @@ __global__ __launch_bounds__(256) void kmeans_runs_kernel(const int8_t* __restri
             acc[i] = 0;
         }
     };
-    for (int piece = 0; piece < KM_PIECES; ++piece) {
+    for (uint32_t piece = 0; piece < pieces; ++piece) {
         const uint64_t p = p0 + (uint64_t)piece * LR;
         if (!__any(p < n)) break;   // the groups of a wave stay together for the lane exchanges
         const uint32_t have = p >= n ? 0u : n - p < LR ? (uint32_t)(n - p) : (uint32_t)LR;
@@ -1055,19 +1066,27 @@ hipError_t launch_kmeans_update(const int8_t* X, uint64_t n, uint32_t d, const u
                                 int32_t* sums, uint32_t* counts, int8_t* Cn, uint32_t* order, hipStream_t stream) {
     if (d % 4 || K == 0 || (uint64_t)K * d > 0x7fffffffull) return hipErrorInvalidValue;
     const uint64_t cells = (uint64_t)K * d;
-    hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)((cells + 2047) / 2048)), dim3(256), 0, stream, sums, cells);
-    hipLaunchKernelGGL(filter_zero_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, (int32_t*)counts, (uint64_t)K);
+    auto zero = [&](void* p, uint64_t words) {
+        hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)((words + 2047) / 2048)), dim3(256), 0, stream, (int32_t*)p, words);
+    };
     if (n && order && filter_shape(d)) {
-        uint32_t* cursor = order + n;
+        const uint32_t spread = counter_spread(K);   // K << 4 words fit the sums: d is at least 64
         const dim3 per_vector((unsigned)((n + 255) / 256)), block(256);
-        hipLaunchKernelGGL(kmeans_count_kernel, per_vector, block, 0, stream, assign, n, counts);
-        hipLaunchKernelGGL(kmeans_starts_kernel, dim3(1), dim3(1024), 0, stream, counts, K, cursor);
-        hipLaunchKernelGGL(kmeans_order_kernel, per_vector, block, 0, stream, assign, n, cursor, order);
-        const dim3 runs((unsigned)((n + 256 * KM_PIECES - 1) / (256 * KM_PIECES)));   // a workgroup walks over 256 * KM_PIECES positions
-        if (d == 64) hipLaunchKernelGGL(kmeans_runs_kernel<16>, runs, block, 0, stream, X, n, assign, order, sums);
-        else if (d == 128) hipLaunchKernelGGL(kmeans_runs_kernel<32>, runs, block, 0, stream, X, n, assign, order, sums);
-        else hipLaunchKernelGGL(kmeans_runs_kernel<64>, runs, block, 0, stream, X, n, assign, order, sums);
-    } else if (n) {
+        zero(sums, (uint64_t)K << spread);
+        hipLaunchKernelGGL(kmeans_count_kernel, per_vector, block, 0, stream, assign, n, spread, (uint32_t*)sums);
+        hipLaunchKernelGGL(kmeans_starts_kernel, dim3(1), dim3(1024), 0, stream, (uint32_t*)sums, K, spread, counts);
+        hipLaunchKernelGGL(kmeans_order_kernel, per_vector, block, 0, stream, assign, n, spread, (uint32_t*)sums, order);
+        zero(sums, cells);
+        const uint32_t pieces = n >= (1u << 19) ? 4 : n >= (1u << 17) ? 2 : 1;   // 512 workgroups where there are enough vectors
+        const dim3 runs((unsigned)((n + 256 * pieces - 1) / (256 * pieces)));    // a workgroup walks over 256 * pieces positions
+        if (d == 64) hipLaunchKernelGGL(kmeans_runs_kernel<16>, runs, block, 0, stream, X, n, assign, order, pieces, sums);
+        else if (d == 128) hipLaunchKernelGGL(kmeans_runs_kernel<32>, runs, block, 0, stream, X, n, assign, order, pieces, sums);
+        else hipLaunchKernelGGL(kmeans_runs_kernel<64>, runs, block, 0, stream, X, n, assign, order, pieces, sums);
+    } else {
+        zero(sums, cells);
+        zero(counts, K);
+    }
+    if (n && !(order && filter_shape(d))) {
         const uint64_t blocks = (n * (d / 4) + 255) / 256;
         if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
         hipLaunchKernelGGL(kmeans_accumulate_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, assign, sums,
@@ -1217,6 +1236,8 @@ FilterSubPlan filter_sub_plan(uint64_t n_docs, uint32_t K) {
     }
 }
 
+size_t filter_cursor_bytes(uint64_t n_sub) { return (size_t)(n_sub << counter_spread(n_sub)) * 4; }
+
 hipError_t launch_filter_buckets(const uint32_t* assign, const uint64_t* doc_off, uint64_t n_docs, uint32_t K,
                                  FilterSubPlan sp, uint32_t* cursor, uint32_t* sub_off, uint32_t* bucket_off,
                                  uint32_t* bucket_docs, hipStream_t stream) {
@@ -1225,14 +1246,15 @@ hipError_t launch_filter_buckets(const uint32_t* assign, const uint64_t* doc_off
     if (blocks == 0) blocks = 1;
     const uint64_t KS = (uint64_t)K * sp.S;
     if (KS > 0x7fffffffull) return hipErrorInvalidValue;
-    uint64_t zb = (KS + 255) / 256;
+    const uint32_t spread = counter_spread(KS);
+    uint64_t zb = ((KS << spread) + 255) / 256;
     if (zb > 65536) zb = 65536;
-    hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)zb), dim3(256), 0, stream, (int32_t*)cursor, KS);
+    hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)zb), dim3(256), 0, stream, (int32_t*)cursor, KS << spread);
     hipLaunchKernelGGL(filter_bucket_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, assign, doc_off, n_docs,
-                       sp.S, sp.sub_shift, cursor, sub_off, bucket_docs);
-    launch_filter_scan(cursor, (uint32_t)KS, sub_off, stream);
+                       sp.S, sp.sub_shift, spread, cursor, sub_off, bucket_docs);
+    launch_filter_scan(cursor, (uint32_t)KS, spread, sub_off, stream);
     hipLaunchKernelGGL(filter_bucket_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, assign, doc_off, n_docs,
-                       sp.S, sp.sub_shift, cursor, sub_off, bucket_docs);
+                       sp.S, sp.sub_shift, spread, cursor, sub_off, bucket_docs);
     hipLaunchKernelGGL(filter_bucket_starts_kernel, dim3(K / 256 + 1), dim3(256), 0, stream, sub_off, K, sp.S, bucket_off);
     return hipGetLastError();
 }

@@ -125,7 +125,7 @@ hipError_t launch_filter_distances(const int8_t* X, uint64_t n, uint32_t d, uint
                                    int32_t* out /*[n][filter_tiles(K)*32]*/, hipStream_t stream);
 // Update step of Lloyd's k-means: per-cluster coordinate sums and counts of the assigned vectors, then the rounded means
 // written over Cn [K][d] (clusters without vectors keep their centroid).  sums [K][d] i32, counts [K] u32 are scratch, and so is
-// order [n + K] u32 (or nullptr: the sums are then made without ordering the vectors by cluster, which is slower).
+// order [n] u32 (or nullptr: the sums are then made without ordering the vectors by cluster, which is slower).
 hipError_t launch_kmeans_update(const int8_t* X, uint64_t n, uint32_t d, const uint32_t* assign, uint32_t K,
                                 int32_t* sums, uint32_t* counts, int8_t* Cn, uint32_t* order, hipStream_t stream);
 // Probe selection inside the GEMM for probe <= FILTER_LIST_MAX (ranges = 0: not applicable, use the
@@ -149,8 +149,9 @@ struct FilterSubPlan {
     uint32_t sub_shift;  // log2 of the documents per sub-bucket range
 };
 FilterSubPlan filter_sub_plan(uint64_t n_docs, uint32_t K);
+size_t filter_cursor_bytes(uint64_t n_sub);   // of launch_filter_buckets' scratch for n_sub = K*S sub-buckets
 hipError_t launch_filter_buckets(const uint32_t* assign, const uint64_t* doc_off, uint64_t n_docs, uint32_t K,
-                                 FilterSubPlan sp, uint32_t* cursor /*[K*S] scratch*/, uint32_t* sub_off /*[K*S+1]*/,
+                                 FilterSubPlan sp, uint32_t* cursor /*filter_cursor_bytes(K*S) scratch*/, uint32_t* sub_off /*[K*S+1]*/,
                                  uint32_t* bucket_off /*[K+1]*/, uint32_t* bucket_docs, hipStream_t stream);
 hipError_t launch_filter_probe(const int32_t* dist, uint64_t total_q, uint32_t K, uint32_t probe, uint32_t* probe_ids,
                                hipStream_t stream);

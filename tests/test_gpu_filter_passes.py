@@ -95,7 +95,7 @@ def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
     want = want[0] if isinstance(want, tuple) else want
     assert np.array_equal(dz.filter_kmeans(ix, Xd, torch.from_numpy(C).to(DEV), 2).cpu().numpy(), want)
     full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
-    order = ((n + K) * 4 + 255) // 256 * 256
+    order = (n * 4 + 255) // 256 * 256
     cent = torch.from_numpy(C).to(DEV)
     ws = torch.empty(full - order, dtype=torch.uint8, device=DEV)
     assert dz.lib().dessert_filter_kmeans(ix.handle, Xd.data_ptr(), n, cent.data_ptr(), K, 2, ws.data_ptr(), ws.numel()) == dz.OK
