@@ -1404,7 +1404,11 @@ static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char*
     const size_t table = ((size_t)a.L << a.C) * 4, lds = table + ((size_t)a.L + 1) * 4;
     // as many waves share a table as keep several workgroups on a CU: 160 KB of LDS hold six tables of up to 24 KB (four waves
     // each), three of up to 48 KB (eight), one of 128 KB (sixteen)
-    const uint32_t T = table <= 24 * 1024 ? 256 : table <= 48 * 1024 ? 512 : 1024;
+    uint32_t T = table <= 24 * 1024 ? 256 : table <= 48 * 1024 ? 512 : 1024;
+    // a small batch: more workgroups matter more than what a CU could hold of them (2 sets x 1452 documents, 48 KB table 52.3 -> 48.7 us
+    // a search); not from half the CUs on (3 sets of 39 vectors x 2846, L = 96: 95 -> 117) and not with the tables that leave a CU
+    // one workgroup anyway (8 sets x 5000, 96 KB table 151 -> 176)
+    if (T == 512 && ((a.max_scored + 63) / 64) * a.n_queries * ((a.max_q_len + 31) / 32) < 128) T = 256;
     const uint32_t wave_docs = T / 64 * 8;   // one run of 8 documents per wave
     uint32_t dpb = LUT_DOCS;
     while (dpb > wave_docs && ((a.max_scored + dpb - 1) / dpb) * a.n_queries < 4096) dpb /= 2;
