@@ -26,6 +26,8 @@ uint32_t topk_slices(uint64_t max_scored, uint32_t n_queries) {
 // slice is longer than that (candidate lists): the phases of such a selection are short chains of LDS round trips and
 // barriers, which sixteen waves get through sooner than eight (17 -> 14 us for 256 lists of 4096); on long slices the
 // wider workgroup is slower (0.90 -> 1.20 ms on 8M documents).
+// Slices of 4097 to 16 384 scores with 32-bit keys: 1024 threads, U = 16, so that these too are read once and stay in registers (114
+// VGPRs); per search, one list of 8192, k = 10 31.7 -> 30.0 us, k = 1000 43.5 -> 40.0; 64 lists of 16 384, k = 1000 250.5 -> 246.1.
 constexpr uint32_t TOPK_THREADS_SHORT = 1024;
 template <typename KT, int T, int U>
 __global__ __launch_bounds__(T) void topk_scores_kernel(TopkArgs a, KeyPlan plan, uint32_t slices, uint32_t kpad) {
@@ -326,6 +328,8 @@ static hipError_t allow_large_k() {  // large k: opt in to more dynamic LDS (the
                                                hipFuncAttributeMaxDynamicSharedMemorySize, TOPK_KMAX * 8);
     static hipError_t a9 = hipFuncSetAttribute((const void*)topk_scores_kernel<uint32_t, TOPK_THREADS_SHORT, 4>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, TOPK_KMAX * 8);
+    static hipError_t a11 = hipFuncSetAttribute((const void*)topk_scores_kernel<uint32_t, TOPK_THREADS_SHORT, 16>,
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, TOPK_KMAX * 8);
     static hipError_t a10 = hipFuncSetAttribute((const void*)topk_scores_kernel<uint64_t, TOPK_THREADS_SHORT, 4>,
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, TOPK_KMAX * 8);
     static hipError_t a2 = hipFuncSetAttribute((const void*)topk_merge_kernel,
@@ -343,7 +347,7 @@ static hipError_t allow_large_k() {  // large k: opt in to more dynamic LDS (the
     static hipError_t a8 = hipFuncSetAttribute((const void*)topk_lists_plan_kernel<uint32_t>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, TOPK_KMAX * 8);
     return a0 != hipSuccess ? a0 : a1 != hipSuccess ? a1 : a2 != hipSuccess ? a2 : a3 != hipSuccess ? a3 : a4 != hipSuccess ? a4
-           : a5 != hipSuccess ? a5 : a6 != hipSuccess ? a6 : a7 != hipSuccess ? a7 : a8 != hipSuccess ? a8 : a9 != hipSuccess ? a9 : a10;
+           : a5 != hipSuccess ? a5 : a6 != hipSuccess ? a6 : a7 != hipSuccess ? a7 : a8 != hipSuccess ? a8 : a9 != hipSuccess ? a9 : a11 != hipSuccess ? a11 : a10;
 }
 
 hipError_t launch_topk_lists(const uint64_t* lists, uint64_t list_stride, const uint32_t* counts, uint32_t n_queries,
@@ -423,6 +427,9 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t stream) {
         else
             hipLaunchKernelGGL((topk_scores_kernel<uint64_t, TOPK_THREADS_SHORT, 4>), grid, dim3(TOPK_THREADS_SHORT), lds, stream, a, plan,
                                slices, kpad);
+    } else if (fit32 && slice_len <= (uint64_t)TOPK_THREADS_SHORT * 16) {
+        hipLaunchKernelGGL((topk_scores_kernel<uint32_t, TOPK_THREADS_SHORT, 16>), grid, dim3(TOPK_THREADS_SHORT), lds, stream, a, plan, slices,
+                           kpad);
     } else {
         if (fit32)
             hipLaunchKernelGGL((topk_scores_kernel<uint32_t, TOPK_THREADS, 8>), grid, dim3(TOPK_THREADS), lds, stream, a, plan, slices, kpad);

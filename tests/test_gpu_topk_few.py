@@ -63,3 +63,28 @@ def test_few_results_of_many_slices():
         ids, sc = (t.cpu().numpy() for t in dz.search(ix, torch.from_numpy(Q).to(DEV), [7], k))
         want_ids, want_sc = orc.topk(orc.scores(dc, np.arange(N + 1), qc), k)
         assert np.array_equal(ids[0], want_ids) and np.array_equal(sc[0], want_sc)
+
+
+@pytest.mark.parametrize("k", [17, 1000, 5000])
+def test_lists_that_stay_in_registers(k):
+    """Lists either side of 4096 and of 16 384 scores, the lengths at which the selection changes its workgroup."""
+    rng = np.random.default_rng(k)
+    d, L, Cb, N = 64, 4, 2, 20_000
+    X = rng.integers(-127, 128, (N, d)).astype(np.int8)
+    ix = dz.create(d, L, Cb, seed=3)
+    R = dz.get_projection(ix).cpu().numpy()
+    dz.build_index(ix, torch.from_numpy(X).to(DEV), np.ones(N, dtype=np.int64))
+    Q = rng.integers(-127, 128, (6, d)).astype(np.int8)
+    dc, qc = orc.hash_i8(X, R, L, Cb), orc.hash_i8(Q, R, L, Cb)
+    score = orc.scores(dc, np.arange(N + 1), qc[:2])
+    for n in (4096, 4097, 8191, 16384, 16385):
+        print("[case]", n, k, flush=True)
+        lists = [rng.integers(0, N, n), rng.integers(0, N, n // 2), rng.integers(0, N, 3)]
+        co = np.concatenate([[0], np.cumsum([len(c) for c in lists])])
+        flat = torch.from_numpy(np.concatenate(lists).astype(np.int32)).to(DEV)
+        ids, sc = (t.cpu().numpy() for t in dz.search(ix, torch.from_numpy(np.concatenate([Q[:2]] * 3)).to(DEV), [2, 2, 2], k, cand_ids=flat, cand_offsets=co))
+        for b, c in enumerate(lists):
+            order = np.lexsort((c, -score[c].astype(np.int64)))[:k]
+            want_ids, want_sc = np.full(k, 0xFFFFFFFF, np.uint32), np.full(k, -1, np.int32)
+            want_ids[:len(order)], want_sc[:len(order)] = c[order], score[c][order]
+            assert np.array_equal(ids[b], want_ids) and np.array_equal(sc[b], want_sc), (n, b)
