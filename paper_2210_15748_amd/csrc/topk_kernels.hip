@@ -28,6 +28,8 @@ uint32_t topk_slices(uint64_t max_scored, uint32_t n_queries) {
 // wider workgroup is slower (0.90 -> 1.20 ms on 8M documents).
 // Slices of 4097 to 16 384 scores with 32-bit keys: 1024 threads, U = 16, so that these too are read once and stay in registers (114
 // VGPRs); per search, one list of 8192, k = 10 31.7 -> 30.0 us, k = 1000 43.5 -> 40.0; 64 lists of 16 384, k = 1000 250.5 -> 246.1.
+// Not with more workgroups than CUs, where the narrower ones share a CU better (64 query sets x 12 slices of 8334 scores, k = 100:
+// 1269 -> 1285 us a search).
 constexpr uint32_t TOPK_THREADS_SHORT = 1024;
 template <typename KT, int T, int U>
 __global__ __launch_bounds__(T) void topk_scores_kernel(TopkArgs a, KeyPlan plan, uint32_t slices, uint32_t kpad) {
@@ -427,7 +429,7 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t stream) {
         else
             hipLaunchKernelGGL((topk_scores_kernel<uint64_t, TOPK_THREADS_SHORT, 4>), grid, dim3(TOPK_THREADS_SHORT), lds, stream, a, plan,
                                slices, kpad);
-    } else if (fit32 && slice_len <= (uint64_t)TOPK_THREADS_SHORT * 16) {
+    } else if (fit32 && slice_len <= (uint64_t)TOPK_THREADS_SHORT * 16 && (uint64_t)slices * a.n_queries <= 256) {
         hipLaunchKernelGGL((topk_scores_kernel<uint32_t, TOPK_THREADS_SHORT, 16>), grid, dim3(TOPK_THREADS_SHORT), lds, stream, a, plan, slices,
                            kpad);
     } else {
