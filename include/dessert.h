@@ -133,7 +133,7 @@ dessert_status_t dessert_set_algo(dessert_index_t *index, int hash_algo, int sco
  *     round(65536 * phi); the mean of a document of m vectors is the integer (sum + floor(m/2)) / m, 0 for an
  *     empty document; the score is the sum over the query vectors.  Needs |Q| <= 16383.  MEAN_IDENTITY has a
  *     mask-table form (L a power of two, documents of at most 65535 vectors: with phi the identity the mean comes
- *     from sums of collision counts); the other MEAN transforms run on the code-compare kernel only.
+ *     from sums of collision counts); the other MEAN transforms have none (DESSERT_SCORE_AUTO runs them on a kernel of their own).
  * Applies to later dessert_search / dessert_scores calls. */
 enum {
     DESSERT_SCORE_RAW_COUNTS = 0,

@@ -932,7 +932,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
 // The sample's vectors are first ordered by centroid (a counting sort of their numbers), so that a vector's coordinates are added in
 // registers to those of the same centroid's other vectors and only whole runs reach memory.  Without room for the order (a
 // workspace of the older, smaller size) every coordinate is added to the sums by itself, as it always was before.
-// Bound: the vectors are read once, whole lines; 524 288 vectors of 128 dimensions, 16 384 centroids: 796 -> 117 us
+// Bound: the vectors are read once, whole lines; 524 288 vectors of 128 dimensions, 16 384 centroids: 796 -> 128 us
 // for the update's five kernels (67M atomics before, 1.1M now and the two per vector of the sort, at 20 G/s).
 // While the vectors are ordered the sums' memory holds the counters, a centroid's at word c << spread (see COUNTER_WORDS).
 __global__ __launch_bounds__(256) void kmeans_count_kernel(const uint32_t* __restrict__ assign, uint64_t n, uint32_t spread, uint32_t* counters) {
