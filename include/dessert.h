@@ -105,7 +105,8 @@ typedef struct {
 
 /* Create a handle: validates the configuration, copies (or generates) the
  * projection matrix into library-owned device memory.  The hash functions
- * f_1..f_L of Sec. 3 are fixed from here on. */
+ * f_1..f_L of Sec. 3 are fixed from here on.  With a Gaussian matrix the call may wait for the stream (the matrix is looked over
+ * once, to choose the hashing kernel). */
 dessert_status_t dessert_create(const dessert_config_t *config, dessert_index_t **out);
 void dessert_destroy(dessert_index_t *index);
 

@@ -607,10 +607,24 @@ dessert_status_t dessert_create(const dessert_config_t* c, dessert_index_t** out
     } else if (e == hipSuccess && is_f16_mfma(*c)) {
         e = hipMalloc(&ix->proj_mfma, mfma_f16_proj_bytes(c->d, c->L));
         if (e == hipSuccess) e = launch_repack_proj_f16((const float*)ix->proj, c->d, c->L, c->C, ix->proj_mfma, ix->stream);
-    } else if (e == hipSuccess && hash_any_supported(c->dtype, c->proj_kind, c->d, c->L, c->C)) {
-        e = hipMalloc(&ix->proj_any, hash_any_proj_bytes(c->dtype, c->proj_kind, c->d, c->L, c->C));
+    } else if (e == hipSuccess && hash_any_supported(c->dtype, c->proj_kind, c->d, c->L, c->C) &&
+               !(hash_any_rounds(c->proj_kind) && stream_capturing(ix))) {   // the answer below cannot be waited for in a capture
+        const bool rounds = hash_any_rounds(c->proj_kind);
+        const size_t bytes = align_up(hash_any_proj_bytes(c->dtype, c->proj_kind, c->d, c->L, c->C), 16);
+        uint32_t lost = 0;
+        e = hipMalloc(&ix->proj_any, bytes + sizeof(lost));
+        uint32_t* lost_dev = rounds ? (uint32_t*)((char*)ix->proj_any + bytes) : nullptr;
+        if (e == hipSuccess && rounds) e = hipMemsetAsync(lost_dev, 0, sizeof(lost), ix->stream);
         if (e == hipSuccess)
-            e = launch_repack_proj_any(ix->proj, c->dtype, c->proj_kind, c->d, c->L, c->C, ix->proj_any, ix->stream);
+            e = launch_repack_proj_any(ix->proj, c->dtype, c->proj_kind, c->d, c->L, c->C, ix->proj_any, lost_dev, ix->stream);
+        if (e == hipSuccess && rounds) {   // a matrix whose rows span too much stays with the plain kernel
+            e = hipMemcpyAsync(&lost, lost_dev, sizeof(lost), hipMemcpyDeviceToHost, ix->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(ix->stream);
+            if (e == hipSuccess && lost) {
+                (void)hipFree(ix->proj_any);
+                ix->proj_any = nullptr;
+            }
+        }
     }
     if (e == hipSuccess) e = hipMalloc((void**)&ix->remap, SCORE_TABLE_MAX * sizeof(uint32_t));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ix->upload_done, hipEventDisableTiming);

@@ -625,9 +625,13 @@ hipError_t launch_hash_mfma_f16(const void* X, uint64_t n, uint32_t d, uint32_t 
 //    load stays inside its row, whatever d is.
 //  - A fragment loop is unrolled KS times with a uniform exit at the shape's own ks_n.
 // fp16 arithmetic (everything but int8 x +-1): each row of R is first scaled by a power of two that brings its largest entry
-// to [1, 2) (a sign does not change), then split in hi + lo/2048 as above (PARTS = 2; +-1 entries are exact in one part).
+// to [2^14, 2^15) (a sign does not change), then split in hi + lo/4096 (PARTS = 2; +-1 entries are exact in one part).  At that
+// scale both parts of an entry are normal fp16 numbers down to 2^-28 of the row's largest, and the two hold it to 2^-23 of
+// itself; below that it is off by up to 2^-51 of the row's largest.  Vectors may be zero wherever a row is large, so a matrix
+// with an entry that is off by more than 2^-22 of itself stays with the plain kernel (the repacking reports it; of
+// Gaussian matrices with 786 432 entries one in several hundred has such an entry).
 // A projection that is not a number gives bit 0, as the comparison p >= 0 does, and an infinite element decides its
-// sign alone: the lo part is clamped to finite values before it joins.
+// sign alone: hi is never 0 for an entry that is not, and the lo part is clamped to finite values before it joins.
 //
 // All of R stays in LDS when it fits ANY_RESIDENT bytes (two workgroups to a CU); else one tile is multiplied while the next
 // arrives.  Bound: HBM for a few tables, the matrix cores for many.  1.02M fp16 vectors of 200 dimensions, L = 8, C = 11:
@@ -637,6 +641,8 @@ hipError_t launch_hash_mfma_f16(const void* X, uint64_t n, uint32_t d, uint32_t 
 // 0.113 ms here; fp16 1M of 256, L = 64, C = 8 0.467 and 0.522 ms.
 constexpr uint32_t HASH_ANY_SEG = 16;            // tables of a lane half per segment
 constexpr size_t ANY_RESIDENT = 80 * 1024;
+constexpr int ANY_ROW_EXP = 14;                  // of a scaled row's largest entry; 2^15 * 65504 * 384 is far inside fp32
+constexpr float ANY_LO_SCALE = 4096.0f;          // hi is off by 2^3 at most: lo stays below 2^15
 
 struct HashAnyShape {
     uint32_t d, L, C;
@@ -777,7 +783,7 @@ __global__ __launch_bounds__(256, 2) void hash_mfma_any_kernel(const XT* __restr
                         if constexpr (F16) {
                             float p = acc[0][nt][r];
                             if constexpr (PARTS == 2)
-                                p = __builtin_fmaf(__builtin_amdgcn_fmed3f(acc[PARTS - 1][nt][r], -1e30f, 1e30f), 1.0f / 2048.0f, p);
+                                p = __builtin_fmaf(__builtin_amdgcn_fmed3f(acc[PARTS - 1][nt][r], -1e30f, 1e30f), 1.0f / ANY_LO_SCALE, p);
                             bits = __float_as_uint(__builtin_fmaxf(p, -1.0f));   // not a number: negative
                         } else {
                             bits = (uint32_t)acc[0][nt][r];
@@ -814,10 +820,12 @@ __global__ __launch_bounds__(256, 2) void hash_mfma_any_kernel(const XT* __restr
 }
 
 // Re-ordered matrix: [tiles][PARTS][ks][64 lanes][16 bytes].  One workgroup per tile: the scale of each of its 32 rows first.
+// *lost (PARTS = 2) becomes 1 if an entry is off by more than 2^-22 of itself.
 template <typename RT, bool F16, int PARTS>
-__global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restrict__ R, HashAnyShape sh, void* __restrict__ Rp) {
+__global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restrict__ R, HashAnyShape sh, void* __restrict__ Rp,
+                                                              uint32_t* __restrict__ lost) {
     constexpr uint32_t E = F16 ? 8 : 16;
-    __shared__ float scale[32];
+    __shared__ int scale[32];         // exponent
     __shared__ uint32_t row_of[32];   // row of R, all ones: no such table
     const uint32_t tile = blockIdx.x, seg = tile / sh.C, tid = threadIdx.x;
     if (tid < 32) {
@@ -827,7 +835,7 @@ __global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restri
         const bool have = bit / sh.C < HASH_ANY_SEG && j < (g ? sh.L - sh.La : sh.La);
         const uint32_t row = have ? ((g ? sh.La : 0u) + j) * sh.C + c : 0xFFFFFFFFu;
         row_of[i] = row;
-        float s = 1.0f;
+        int s = 0;
         if constexpr (F16) {
             float top = 0.0f;
             if (have)
@@ -835,11 +843,7 @@ __global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restri
                     const float a = __builtin_fabsf((float)R[(size_t)row * sh.d + k]);
                     if (a < __builtin_inff() && a > top) top = a;
                 }
-            if (top > 0.0f) {
-                int e = (int)((__float_as_uint(top) >> 23) & 0xFF) - 127;   // a subnormal row is scaled as far as 2^126 goes
-                e = e < -126 ? -126 : e;
-                s = __builtin_ldexpf(1.0f, -e);
-            }
+            if (top > 0.0f) s = ANY_ROW_EXP - ilogbf(top);
         }
         scale[i] = s;
     }
@@ -853,10 +857,16 @@ __global__ __launch_bounds__(256) void repack_proj_any_kernel(const RT* __restri
         const uint32_t k = ks < full ? ks * 2 * E + in : sh.d - 2 * E + in;
         const bool have = row != 0xFFFFFFFFu && (ks < full || k >= full * 2 * E);
         if constexpr (F16) {
-            const float x = have ? (float)R[(size_t)row * sh.d + k] * scale[l & 31] : 0.0f;
-            const _Float16 hi = (_Float16)x;
-            const float rest = (x - (float)hi) * 2048.0f;
+            const float entry = have ? (float)R[(size_t)row * sh.d + k] : 0.0f;
+            const float x = ldexpf(entry, scale[l & 31]);
+            _Float16 hi = (_Float16)x;
+            if ((float)hi == 0.0f && entry != 0.0f) hi = (_Float16)(entry > 0.0f ? 0x1p-24f : -0x1p-24f);
+            const float rest = (x - (float)hi) * ANY_LO_SCALE;
             const _Float16 lo = (rest - rest == 0.0f) ? (_Float16)rest : (_Float16)0.0f;   // an entry that is not finite: hi alone
+            if constexpr (PARTS == 2) {
+                const double exact = ldexp((double)entry, scale[l & 31]), off = ((double)(float)hi + (double)(float)lo / ANY_LO_SCALE) - exact;
+                if (fabs(off) > fabs(exact) * 0x1p-22) *lost = 1;   // (not for infinities: off is not a number or 0)
+            }
             ((_Float16*)Rp)[(size_t)tile * total + idx] = part ? lo : hi;
         } else {
             ((int8_t*)Rp)[(size_t)tile * total + idx] = have ? (int8_t)R[(size_t)row * sh.d + k] : (int8_t)0;
@@ -888,17 +898,19 @@ size_t hash_any_proj_bytes(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint3
     return (size_t)s.tiles * any_parts(proj_kind) * s.ks * 1024;
 }
 
+bool hash_any_rounds(uint32_t proj_kind) { return any_parts(proj_kind) == 2; }
+
 hipError_t launch_repack_proj_any(const void* R, uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C, void* Rp,
-                                  hipStream_t stream) {
-    if (!hash_any_supported(dtype, proj_kind, d, L, C)) return hipErrorInvalidValue;
+                                  uint32_t* lost, hipStream_t stream) {
+    if (!hash_any_supported(dtype, proj_kind, d, L, C) || (hash_any_rounds(proj_kind) && !lost)) return hipErrorInvalidValue;
     const HashAnyShape s = any_shape(dtype, d, L, C, proj_kind);
     const dim3 grid(s.tiles), block(256);
     if (!any_is_f16(dtype, proj_kind))
-        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, false, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp);
+        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, false, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp, lost);
     else if (proj_kind == 0)
-        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, true, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp);
+        hipLaunchKernelGGL((repack_proj_any_kernel<int8_t, true, 1>), grid, block, 0, stream, (const int8_t*)R, s, Rp, lost);
     else
-        hipLaunchKernelGGL((repack_proj_any_kernel<float, true, 2>), grid, block, 0, stream, (const float*)R, s, Rp);
+        hipLaunchKernelGGL((repack_proj_any_kernel<float, true, 2>), grid, block, 0, stream, (const float*)R, s, Rp, lost);
     return hipGetLastError();
 }
 

@@ -36,8 +36,11 @@ hipError_t launch_hash_mfma_f16(const void* X, uint64_t n, uint32_t d, uint32_t 
 constexpr uint32_t HASH_ANY_MAX_D = 384;
 bool hash_any_supported(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C);
 size_t hash_any_proj_bytes(uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C);
+bool hash_any_rounds(uint32_t proj_kind);   // the re-ordered matrix may hold entries rounded
+// lost: device word (needed if hash_any_rounds), set to 1 if an entry is off by more than 2^-22 of itself: the matrix is for
+// launch_hash_scalar then; left as it is otherwise.
 hipError_t launch_repack_proj_any(const void* R, uint32_t dtype, uint32_t proj_kind, uint32_t d, uint32_t L, uint32_t C, void* Rp,
-                                  hipStream_t stream);
+                                  uint32_t* lost, hipStream_t stream);
 hipError_t launch_hash_any(const void* X, uint32_t dtype, uint32_t proj_kind, uint64_t n, uint32_t d, uint32_t L, uint32_t C,
                            const void* Rp, uint8_t* codes, hipStream_t stream);
 

@@ -98,3 +98,42 @@ def test_any_shape_at_unaligned_vector_addresses():
         v = room[shift:shift + n * d].view(n, d)
         v.copy_(torch.from_numpy(X).to(DEV))
         assert np.array_equal(dz.hash(ix, v).cpu().numpy(), orc.hash_i8(X, R, L, Cb))
+
+
+# Rows of which half the entries lie `span` below the largest, and vectors that are zero where a row is large: the sums of the small
+# entries alone.  Down to 2^-28 the two parts hold an entry to 2^-23 of itself; matrices that span more are for the plain kernel
+@pytest.mark.parametrize("xt", ["f16", "i8"])
+@pytest.mark.parametrize("span", [1e-3, 1e-6, 2.0 ** -27, 1e-10, 1e-12, 1e-30])
+def test_rows_of_wide_range_keep_their_small_entries(xt, span):
+    print("[case]", xt, span, flush=True)
+    rng = np.random.default_rng(11)
+    d, L, Cb, n = 100, 24, 7, 2000
+    X = np.zeros((n, d), np.int8 if xt == "i8" else np.float16)
+    X[:, d // 2:] = rng.integers(-127, 128, (n, d - d // 2)) if xt == "i8" else rng.standard_normal((n, d - d // 2))
+    R = rng.uniform(1, 2, (L * Cb, d)).astype(np.float32) * rng.choice([-1, 1], (L * Cb, d))
+    R[:, d // 2:] *= span
+    R = R.astype(np.float32)
+    auto, _ = both(xt, "gauss", X, R, L, Cb)
+    X64, R64 = X.astype(np.float64), R.astype(np.float64)
+    p = X64 @ R64.T
+    bound = ((d + 8) * 2.0 ** -24 + 2.0 ** -22) * (np.abs(X64) @ np.abs(R64).T)
+    bits = ((auto.astype(np.int64)[:, :, None] >> np.arange(Cb)) & 1).reshape(n, L * Cb)
+    diff = bits != (p >= 0)
+    assert np.all(np.abs(p)[diff] <= bound[diff])
+    assert diff.mean() <= 1e-4
+
+
+def test_infinite_elements_against_entries_far_below_the_largest():
+    """A lone infinite element decides the sign of every bit whose entry is not zero, however small beside its row: powers of
+    two, which the two parts hold exactly."""
+    rng = np.random.default_rng(12)
+    d, L, Cb = 50, 24, 7
+    R = (2.0 ** rng.integers(-40, 1, (L * Cb, d)) * rng.choice([-1, 1], (L * Cb, d))).astype(np.float32)
+    X = rng.standard_normal((2 * d, d)).astype(np.float16)
+    X[np.arange(d), np.arange(d)] = np.inf
+    X[d + np.arange(d), np.arange(d)] = -np.inf
+    auto, scalar = both("f16", "gauss", X, R, L, Cb)
+    want = (np.concatenate([R.T, -R.T]) > 0).astype(np.int64)       # [2 d][L C]
+    bits = ((auto.astype(np.int64)[:, :, None] >> np.arange(Cb)) & 1).reshape(2 * d, L * Cb)
+    assert np.array_equal(bits, want)
+    assert np.array_equal(auto, scalar)
