@@ -336,8 +336,10 @@ dessert_status_t dessert_probe_read_bandwidth(const void *buf_dev, size_t bytes,
 
 /* Measurement and test aid: the scoring kernel instantiation that the handle's most recent dessert_search /
  * dessert_scores / dessert_search_noalloc call launched, spelled as a profiler's kernel trace prints it (e.g.
- * "score_masklut_kernel<32, 7, 1, 0, 1, false>": tables, index bits, bytes per code, score transform form, query sets
- * per workgroup, chunks split over workgroups); "" if nothing was launched.  Lets a caller pair a run with the
+ * "score_masklut_kernel<32, 7, 1, 0, 1, false>": tables, index bits, bytes per code, form, masks per table entry, chunks
+ * split over workgroups).  The form is 0 raw counts, 1 tabulated maximum, 2 weighted, 3 mean, 4 weighted mean; two masks are
+ * those of two query sets, or with the forms 5, 6, 7 (0, 1, 2 over chunk pairs) of two chunks of 32 vectors of one set.
+ * "" if nothing was launched.  Lets a caller pair a run with the
  * profiler summary of the same kernel.  The string lives in the handle. */
 const char *dessert_last_score_kernel(const dessert_index_t *index);
 

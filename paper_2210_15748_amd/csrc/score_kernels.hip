@@ -268,7 +268,7 @@ constexpr int masklut_min_waves(int L, int CB, int CW, int W, int REMAP) {
     return 1;
 }
 constexpr uint32_t LUT_BINS = 64;   // length classes for the in-block ordering
-constexpr uint32_t MASKLUT_CHUNK_PAIRS = 1u << 31;  // flag in the kernel's gz argument
+constexpr int MASKLUT_CHUNK_PAIRS = 5;  // REMAP of the raw form over chunk pairs (see the kernel)
 
 // Per-workgroup bookkeeping, in static LDS beside the mask table.
 struct LutBlockMeta {
@@ -301,9 +301,11 @@ struct LutBlockMeta {
 // of P+15 planes; the lanes of a document add theirs over DPP, each lane un-slices its share of the query vectors and
 // forms (65536/L * S + floor(m/2)) / m.  Needs documents shorter than 65536 vectors (32-bit numerators).
 // CW = bytes per table code (1: C <= 8, 2: wider codes); CB = bits of a table index (2^CB entries per table).
-// Chunk pairs (W = 2, one query set per workgroup): the two masks of an entry are those of two successive chunks of the same
-// set, for sets of more than 32 vectors: the codes are read once for 64 query vectors, with one address and one 8-byte LDS read per
-// table, and one sum is stored.  The last chunk of an odd number runs a loop that uses the first masks only.
+// 5 / 6 / 7 = the forms 0 / 1 / 2 over chunk pairs (W = 2, one query set per workgroup): the two masks of an entry are those of
+// two successive chunks of the same set, for sets of more than 32 vectors: the codes are read once for 64 query vectors, with one
+// address and one 8-byte LDS read per table, and one sum is stored.  The last chunk of an odd number runs a loop that uses the first
+// masks only.  (Instantiations of their own: with the choice made at run time the forms for two sets lost 3 to 11 % where
+// documents or query sets are short, L = 64, C = 6, 16 000 documents of one vector, 64 sets of 8: 118 -> 129 us.)
 // 64 lists of 4096 of 300 000 documents, 48 vectors: L = 32, C = 7 214 -> 184 us, C = 8 253 -> 181, L = 16, C = 8 160 -> 115; 1000
 // documents of 256 vectors against 16 sets of 256, L = 8, C = 9: 68 -> 38 us (LDS-bound: half the reads).
 // gz = chunk groups: with gz > 1 the 32-vector chunks of a query set are dealt round-robin to gz
@@ -347,17 +349,19 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                                                             uint32_t gz_arg) {
     constexpr bool ROT = masklut_rotated(L, CB, CW, W);
     // chunk pairs: W = 2, but both masks of an entry belong to one query set, to its chunks c and c + 1 of 32 vectors
-    const bool chunk_pairs = W == 2 && (SPLIT || (gz_arg & MASKLUT_CHUNK_PAIRS) != 0);
-    const uint32_t gz = SPLIT ? gz_arg & ~MASKLUT_CHUNK_PAIRS : 1u;
-    const uint32_t chunk_step = chunk_pairs ? 64u : 32u;
+    constexpr bool chunk_pairs = REMAP >= MASKLUT_CHUNK_PAIRS;
+    constexpr int FORM = chunk_pairs ? REMAP - MASKLUT_CHUNK_PAIRS : REMAP;
+    static_assert(!chunk_pairs || (W == 2 && FORM <= 2), "chunk pairs: two masks per entry, sigma = max");
+    const uint32_t gz = SPLIT ? gz_arg : 1u;
+    constexpr uint32_t chunk_step = chunk_pairs ? 64u : 32u;
     constexpr int T = masklut_threads(L, CB, CW, W);
     constexpr int LW = L * CW / 4;  // dwords per code row
     constexpr int STRIDE = 1 << CB;
     constexpr int P = ilog2_ceil(L + 1);  // planes needed for counts 0..L
     constexpr int G = (W == 2 && L <= 32) ? 4 : 8;
     constexpr int DOCS_PER_WAVE = 64 / G;
-    constexpr bool MEAN = REMAP >= 3;
-    constexpr bool WEIGHTED = REMAP == 2 || REMAP == 4;
+    constexpr bool MEAN = FORM >= 3;
+    constexpr bool WEIGHTED = FORM == 2 || FORM == 4;
     constexpr int P1 = P + 4;    // planes of the 16-round accumulator: 16 * L < 2^(P+4)
     constexpr int P2 = P + 15;   // planes of the document's accumulator: S <= L * m < 2^(P-1) * 2^16
     // static LDS: the table sits at a link-time constant address, so t*STRIDE*4*W folds into the
@@ -389,11 +393,15 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     uint32_t q_lo[W], q_len[W], max_len = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        const uint32_t b = chunk_pairs ? b0 : b0 + w, skip = chunk_pairs ? 32u * w : 0u;
-        const bool have = b < a.n_queries;
-        q_lo[w] = have ? q_begin(a, b) + skip : 0;
-        const uint32_t end = have ? q_begin(a, b + 1) : 0;
-        q_len[w] = end > q_lo[w] ? end - q_lo[w] : 0;
+        if constexpr (chunk_pairs) {
+            q_lo[w] = q_begin(a, b0) + 32 * w;
+            const uint32_t end = q_begin(a, b0 + 1);
+            q_len[w] = end > q_lo[w] ? end - q_lo[w] : 0;
+        } else {
+            const bool have = b0 + w < a.n_queries;
+            q_lo[w] = have ? q_begin(a, b0 + w) : 0;
+            q_len[w] = have ? q_begin(a, b0 + w + 1) - q_lo[w] : 0;
+        }
         max_len = q_len[w] > max_len ? q_len[w] : max_len;
     }
     const uint32_t lane = threadIdx.x & 63;
@@ -518,7 +526,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
         asm volatile("" : "+v"(rot_swap));
     }
     for (uint32_t c0 = c_first; c0 < max_len; c0 += gz * chunk_step) {  // chunks of 32 query vectors
-        const bool second = W == 2 && c0 < q_len[W - 1];  // the entries' second masks are in use
+        const bool second = chunk_pairs && c0 < q_len[W - 1];  // false: a set's odd last chunk, the entries' first masks alone
         if (c0 != c_first) {  // the first chunk's table was built above
             __syncthreads();  // previous chunk's readers are done
             zero_table();
@@ -586,7 +594,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
             };
             // one round: the table reads of this lane's vector, the carry-save count and the running maximum (or sum).
             // row = the lane's row of the document in this round before clamping: only rows 0 .. m-1 count towards a sum
-            auto process = [&](const uint32_t (&dw)[LW], int32_t row, auto masks) {
+            auto process = [&](const uint32_t (&dw)[LW], int32_t row, auto masks) {  // masks: how many of an entry's are in use
                 constexpr int NW = decltype(masks)::value;
                 const char* lut_bytes = reinterpret_cast<const char*>(lut);
                 uint32_t off[L];  // byte offset of x's entry within each table
@@ -655,17 +663,34 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
             // code buffers used in turn (the loop body is one round per buffer), so no register copies;
             // DEPTH rounds of codes are in flight while a round is processed
             constexpr int DEPTH = (W == 1 && LW <= 8) ? 2 : 1;
-            auto rounds = [&](auto masks) {
-            if constexpr (DEPTH == 1) {
+            constexpr std::integral_constant<int, W> every{};
+            if constexpr (chunk_pairs) {   // the loop of DEPTH 1 twice: a branch inside it would part the reads of an entry's two masks
+                auto rounds = [&](auto masks) {
+                    uint32_t buf_a[LW], buf_b[LW];
+                    load_codes(clamped(j), buf_a);
+                    for (;;) {
+                        load_codes(clamped(j + G), buf_b);
+                        process(buf_a, j, masks);
+                        j += G;
+                        if (!__any(j < j_end)) break;
+                        load_codes(clamped(j + G), buf_a);
+                        process(buf_b, j, masks);
+                        j += G;
+                        if (!__any(j < j_end)) break;
+                    }
+                };
+                if (second) rounds(every);
+                else rounds(std::integral_constant<int, 1>{});
+            } else if constexpr (DEPTH == 1) {
                 uint32_t buf_a[LW], buf_b[LW];
                 load_codes(clamped(j < 0 ? 0 : j), buf_a);
                 for (;;) {
                     load_codes(clamped(j + G), buf_b);
-                    process(buf_a, j, masks);
+                    process(buf_a, j, every);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + G), buf_a);
-                    process(buf_b, j, masks);
+                    process(buf_b, j, every);
                     j += G;
                     if (!__any(j < j_end)) break;
                 }
@@ -675,25 +700,18 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                 load_codes(clamped(j + G), buf_b);
                 for (;;) {
                     load_codes(clamped(j + 2 * G), buf_c);
-                    process(buf_a, j, masks);
+                    process(buf_a, j, every);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + 2 * G), buf_a);
-                    process(buf_b, j, masks);
+                    process(buf_b, j, every);
                     j += G;
                     if (!__any(j < j_end)) break;
                     load_codes(clamped(j + 2 * G), buf_b);
-                    process(buf_c, j, masks);
+                    process(buf_c, j, every);
                     j += G;
                     if (!__any(j < j_end)) break;
                 }
-            }
-            };
-            if constexpr (W == 2) {  // a loop of its own where only the first masks are in use (a set's odd last chunk, an odd last set)
-                if (second) rounds(std::integral_constant<int, 2>{});
-                else rounds(std::integral_constant<int, 1>{});
-            } else {
-                rounds(std::integral_constant<int, 1>{});
             }
             int32_t first_score = 0;
 #pragma unroll
@@ -719,7 +737,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     for (int p = 0; p < P; ++p) o[p] = dpp_mov<0x4E>(mx[w][p]);   // quad_perm [2,3,0,1]
                     planes_max<P>(mx[w], o);
                 }
-                if constexpr (REMAP == 0) {
+                if constexpr (FORM == 0) {
 #pragma unroll
                     for (int p = P - 1; p >= 0; --p) score = 2 * score + __builtin_popcount(mx[w][p]);
                 } else if constexpr (!MEAN) {
@@ -781,14 +799,14 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     part += dpp_mov<0x4E>(part);
                     score = (int32_t)part;
                 }
-                if (W == 2 && chunk_pairs) {
+                if constexpr (chunk_pairs) {
                     if (w == 0) {
                         first_score = score;
                         continue;
                     }
                     score += first_score;
                 }
-                const bool one_set = W == 1 || chunk_pairs;
+                constexpr bool one_set = W == 1 || chunk_pairs;
                 if (valid && sub == 0 && (one_set || (b0 + w < a.n_queries && c0 < q_len[w]))) {
                     // two sets: each scores every document, set b0+w starts at (b0+w)*n_docs
                     int32_t* dst = a.scores + (one_set ? sp.base + meta.slot[doc] : (uint64_t)(b0 + w) * a.n_docs + first + doc);
@@ -1331,18 +1349,19 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     const int remap = a.sigma_mean ? (a.q_weights ? 4 : 3) : a.q_weights ? 2 : a.remap ? 1 : 0;
     // the instantiation as a profiler prints it
     if (desc)
-        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, remap, (pair || cp) ? 2 : 1,
-                 gz > 1 ? "true" : "false");
+        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, cp ? MASKLUT_CHUNK_PAIRS + remap : remap,
+                 (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
     using Kernel = void (*)(ScoreArgs, uint32_t, uint32_t, uint32_t);
     if constexpr (PAIR_OK) {
         if (cp) {
-            const Kernel kern3 = gz > 1 ? (remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, true>
-                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, true>
-                                                        : score_masklut_kernel<L, CB, CW, 0, 2, true>)
-                                        : (remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, false>
-                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, false>
-                                                        : score_masklut_kernel<L, CB, CW, 0, 2, false>);
-            hipLaunchKernelGGL(kern3, grid, dim3(masklut_threads(L, CB, CW, 2)), 0, stream, a, dpb, gy_linear, gz | MASKLUT_CHUNK_PAIRS);
+            constexpr int CP = MASKLUT_CHUNK_PAIRS;
+            const Kernel kern3 = gz > 1 ? (remap == 2   ? score_masklut_kernel<L, CB, CW, CP + 2, 2, true>
+                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, CP + 1, 2, true>
+                                                        : score_masklut_kernel<L, CB, CW, CP, 2, true>)
+                                        : (remap == 2   ? score_masklut_kernel<L, CB, CW, CP + 2, 2, false>
+                                           : remap == 1 ? score_masklut_kernel<L, CB, CW, CP + 1, 2, false>
+                                                        : score_masklut_kernel<L, CB, CW, CP, 2, false>);
+            hipLaunchKernelGGL(kern3, grid, dim3(masklut_threads(L, CB, CW, 2)), 0, stream, a, dpb, gy_linear, gz);
             return hipGetLastError();
         }
         if (pair) {

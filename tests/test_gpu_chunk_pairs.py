@@ -17,7 +17,7 @@ EMPTY = 0xFFFFFFFF
 def launched(ix):
     m = re.fullmatch(r"score_masklut_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), (true|false)>", dz.last_score_kernel(ix))
     assert m, dz.last_score_kernel(ix)
-    return int(m.group(5)), m.group(6) == "true"
+    return int(m.group(5)), m.group(6) == "true", int(m.group(4))
 
 
 # every shape whose paired table fits.  Query sets of 33, 63, 64, 65, 96, 97 and 128 vectors: full and nearly empty second chunks, odd and
@@ -59,9 +59,10 @@ def test_chunk_pairs(L, Cb, mode, form):
     for algo in (dz.SCORE_AUTO, dz.SCORE_MASKLUT):
         dz.set_algo(ix, dz.HASH_AUTO, algo)
         got[algo] = dz.scores(ix, torch.from_numpy(Q).to(DEV), q_lens, cand_ids=flat, cand_offsets=co).cpu().numpy().reshape(-1)
-        W, split = launched(ix)
+        W, split, remap = launched(ix)
         if algo == dz.SCORE_AUTO:
             assert W == 2 and split == (mode != "lists"), dz.last_score_kernel(ix)
+            assert remap == 5 + ["raw", "eq1", "weighted"].index(form)   # instantiations of their own, told from pairs of sets
         else:
             assert W == 1
     assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_MASKLUT])
