@@ -1273,11 +1273,22 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     constexpr size_t PAIR_BYTES = (size_t)L * (1u << CB) * 8;
     constexpr bool PAIR_OK = PAIR_BYTES <= 32 * 1024 || (L <= 32 && PAIR_BYTES <= 64 * 1024);
     bool pair = PAIR_OK && a.cand_ids == nullptr && a.n_queries >= 2 && !a.sigma_mean;  // the mean form takes one set per workgroup
-    // chunk pairs where sets are not paired: measured against a pass over one chunk, a pass over two costs 1.72 and one that uses
-    // only the first masks 1.4 (8-byte entries, and at 32 tables not the rotated order): not for batches of mostly short sets or of
-    // three chunks each
-    const bool chunk_pairs_pay = PAIR_OK && !a.sigma_mean &&
-                                 172 * a.chunk_pairs + 140 * (a.chunks - 2 * a.chunk_pairs) < 97 * a.chunks;
+    // Chunk pairs where sets are not paired.  Measured against a pass over one chunk, a pass over two costs at most 1.72 and one that
+    // uses only the first masks 1.4 (8-byte entries, and at 32 tables not the rotated order), with tables of 64 KB 1.6: not for
+    // batches of mostly short sets or of three chunks each, nor of five with such tables (L = 32, C = 8, 64 lists of 2000, 160
+    // vectors: 258 -> 278 us).  Scoring, single chunks -> pairs, where the form as a whole decides:
+    //   64 tables: the single form is the rotated one with half the LDS, and 64 lists of 2000, 33 to 256 vectors, take 162 -> 188 to
+    //     594 -> 760 us: never;
+    //   32 tables, C <= 5: few codes, so the single form's reads of one bank often share an address.  Every document for 64 sets of
+    //     256 vectors 339 -> 355 us, 8 lists of 4096, 128 vectors 48 -> 52, but 64 lists of 2000, 256 vectors 0.84 of the time: lists only,
+    //     from 1536 workgroups on;
+    //   8 tables, C = 10 (16-byte rows): 64 lists of 2000, 64 vectors 0.84 of the time, 256 lists 1.05: lists in small batches.
+    constexpr bool CHUNK_PAIRS_OK = PAIR_OK && L <= 32;
+    constexpr uint32_t first_masks_only = PAIR_BYTES == 64 * 1024 && (L == 32 || L == 8) ? 160 : 140;
+    const bool few_codes = L == 32 && a.C <= 5;
+    const bool chunk_pairs_pay = CHUNK_PAIRS_OK && !a.sigma_mean && !(few_codes && !a.cand_ids) &&
+                                 !(L == 8 && CB == 10 && a.cand_ids && a.total_scored >= (1u << 18)) &&
+                                 172 * a.chunk_pairs + first_masks_only * (a.chunks - 2 * a.chunk_pairs) < 97 * a.chunks;
     // documents per workgroup: at most LUT_DOCS; fewer when that would leave the 256 CUs short of
     // workgroups, but at least 64 (32 = one run of 8 documents for each of the four waves when the
     // documents are long: about 4096 vectors per workgroup keep the table build amortised)
@@ -1302,13 +1313,13 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     if (chunk_pairs_pay && (!pair || bx * gy < 2048)) {
         // one query set per workgroup and, when that leaves the chip short of workgroups, its pairs of chunks split over gz of them.
         // Not when even that is a small grid (one short list): then single chunks split, twice the workgroups
-        constexpr uint32_t cp_threads = PAIR_OK ? masklut_threads(L, CB, CW, 2) : 256;
+        constexpr uint32_t cp_threads = CHUNK_PAIRS_OK ? masklut_threads(L, CB, CW, 2) : 256;
         constexpr uint32_t cp_docs = cp_threads / 64 * (L <= 32 ? 16 : 8);   // a run of documents for every wave
         uint32_t d2 = LUT_DOCS;
         while (d2 > cp_docs && ((a.max_scored + d2 - 1) / d2) * a.n_queries < 4096) d2 /= 2;
         const uint64_t bx2 = (a.max_scored + d2 - 1) / d2;
         const uint32_t units = (chunks + 1) / 2;
-        if (bx2 * a.n_queries * units * (cp_threads / 256) >= 1024) {
+        if (bx2 * a.n_queries * units * (cp_threads / 256) >= (few_codes ? 1536 : 1024)) {
             cp = true;
             pair = false;
             dpb = d2;
@@ -1352,7 +1363,7 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
         snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, cp ? MASKLUT_CHUNK_PAIRS + remap : remap,
                  (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
     using Kernel = void (*)(ScoreArgs, uint32_t, uint32_t, uint32_t);
-    if constexpr (PAIR_OK) {
+    if constexpr (CHUNK_PAIRS_OK) {
         if (cp) {
             constexpr int CP = MASKLUT_CHUNK_PAIRS;
             const Kernel kern3 = gz > 1 ? (remap == 2   ? score_masklut_kernel<L, CB, CW, CP + 2, 2, true>
@@ -1364,6 +1375,8 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
             hipLaunchKernelGGL(kern3, grid, dim3(masklut_threads(L, CB, CW, 2)), 0, stream, a, dpb, gy_linear, gz);
             return hipGetLastError();
         }
+    }
+    if constexpr (PAIR_OK) {
         if (pair) {
             const Kernel kern2 = remap == 2   ? score_masklut_kernel<L, CB, CW, 2, 2, false>
                                  : remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 2, false>

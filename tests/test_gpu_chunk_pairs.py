@@ -20,6 +20,12 @@ def launched(ix):
     return int(m.group(5)), m.group(6) == "true", int(m.group(4))
 
 
+def paired(L, Cb, mode):
+    """Whether the batches below are for chunk pairs: not with 64 tables (the single form is the rotated one), and with 32 tables of up to
+    5 bits only for lists that make 1536 workgroups."""
+    return L < 64 and not (L == 32 and Cb <= 5 and mode != "lists")
+
+
 # every shape whose paired table fits.  Query sets of 33, 63, 64, 65, 96, 97 and 128 vectors: full and nearly empty second chunks, odd and
 # even chunk counts; some of at most 32 among them.  Lists with empty slots, repeats, one of no ids and lengths that end inside a block;
 # documents of no vectors
@@ -61,8 +67,9 @@ def test_chunk_pairs(L, Cb, mode, form):
         got[algo] = dz.scores(ix, torch.from_numpy(Q).to(DEV), q_lens, cand_ids=flat, cand_offsets=co).cpu().numpy().reshape(-1)
         W, split, remap = launched(ix)
         if algo == dz.SCORE_AUTO:
-            assert W == 2 and split == (mode != "lists"), dz.last_score_kernel(ix)
-            assert remap == 5 + ["raw", "eq1", "weighted"].index(form)   # instantiations of their own, told from pairs of sets
+            assert W == (2 if paired(L, Cb, mode) else 1) and (W == 1 or split == (mode != "lists")), dz.last_score_kernel(ix)
+            # instantiations of their own, told from pairs of sets
+            assert remap == (5 if W == 2 else 0) + ["raw", "eq1", "weighted"].index(form)
         else:
             assert W == 1
     assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_MASKLUT])
@@ -78,3 +85,29 @@ def test_chunk_pairs(L, Cb, mode, form):
         want = orc.scores_general(dc, off, qc, orc.PHI_SIGMOID, orc.SIGMA_MAX, weights=w[qo[b]:qo[b + 1]], doc_ids=sel)
     mine = got[dz.SCORE_AUTO].reshape(len(q_lens), -1)[b] if co is None else got[dz.SCORE_AUTO][co[b]:co[b + 1]]
     assert np.array_equal(mine, want if co is None else np.where(cands[b] == EMPTY, -1, want))
+
+
+# Where chunk pairs are the slower form although the paired table fits: 64 tables; 32 tables with few codes unless many lists; five chunks
+# with tables of 64 KB; 16-byte rows of 8 tables in large batches of lists; three chunks
+@pytest.mark.parametrize("L,Cb,q,n_sets,n_cand,want", [(64, 6, 64, 64, 1000, False), (64, 4, 128, 12, 0, False), (32, 4, 128, 64, 0, False),
+                                                       (32, 5, 128, 8, 4096, False), (32, 4, 64, 64, 1600, True), (32, 6, 128, 64, 0, True),
+                                                       (32, 8, 160, 64, 500, False), (32, 8, 128, 64, 500, True), (8, 10, 160, 64, 500, False),
+                                                       (8, 10, 64, 64, 1000, True), (8, 10, 64, 256, 1100, False), (8, 9, 64, 256, 1100, True),
+                                                       (16, 8, 96, 64, 500, False), (16, 8, 160, 64, 500, True)])
+def test_which_batches_take_chunk_pairs(L, Cb, q, n_sets, n_cand, want):
+    print("[case]", L, Cb, q, n_sets, n_cand, flush=True)
+    rng = np.random.default_rng(q)
+    lens = rng.integers(1, 5, 2000)
+    ix = dz.create(64, L, Cb, seed=2)
+    dz.build_index(ix, torch.from_numpy(rng.integers(-127, 128, (int(lens.sum()), 64)).astype(np.int8)).to(DEV), lens)
+    Q = torch.from_numpy(rng.integers(-127, 128, (n_sets * q, 64)).astype(np.int8)).to(DEV)
+    kw = {}
+    if n_cand:
+        kw = dict(cand_ids=torch.from_numpy(rng.integers(0, 2000, n_sets * n_cand).astype(np.int32)).to(DEV),
+                  cand_offsets=np.arange(n_sets + 1) * n_cand)
+    got = {}
+    for algo in (dz.SCORE_AUTO, dz.SCORE_MASKLUT):
+        dz.set_algo(ix, dz.HASH_AUTO, algo)
+        got[algo] = dz.scores(ix, Q, np.full(n_sets, q), **kw).cpu().numpy()
+        assert (launched(ix)[2] >= 5) == (want and algo == dz.SCORE_AUTO), dz.last_score_kernel(ix)
+    assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_MASKLUT])
