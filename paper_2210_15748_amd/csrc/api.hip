@@ -452,7 +452,7 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     if (algo == DESSERT_SCORE_AUTO || ix->n_vectors == 0) {
         const bool fixed = score_masklut_supported(ix->cfg.L, ix->cfg.C) && (!sa.sigma_mean || mean_on_masklut);
         any_tables = ix->n_vectors && !fixed && bt.max_scored <= (1ull << 29) && score_maskany_supported(ix->cfg.L, ix->cfg.C) &&
-                     (!sa.sigma_mean || score_maskany_mean_fits(ix->max_len, ix->remap_max));
+                     (!sa.sigma_mean || score_maskany_mean_fits(ix->max_len, ix->remap_max)) && score_maskany_pays(sa);
         algo = (ix->n_vectors && fixed) ? DESSERT_SCORE_MASKLUT : DESSERT_SCORE_BYTECMP;
     }
     // Query preparation: the query codes and, for the mask-table kernel with long candidate lists, each list's slots

@@ -114,6 +114,7 @@ hipError_t launch_score_masklut(const ScoreArgs& a, hipStream_t stream, char* de
 // when score_maskany_mean_fits(longest document, largest phi).  The fixed-size kernel above is the faster one where it exists.
 bool score_maskany_supported(uint32_t L, uint32_t C);
 bool score_maskany_mean_fits(uint64_t max_len, uint32_t phi_max);
+bool score_maskany_pays(const ScoreArgs& a);   // the faster one of it and launch_score_bytecmp, as far as sizes tell
 hipError_t launch_score_maskany(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
 
 // ---- candidate filter (Sec. 5 "Filtering") ---------------------------------------------

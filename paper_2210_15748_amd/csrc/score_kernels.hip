@@ -4,6 +4,8 @@
 // Scores are raw integer counts (no division by L, no remap of Eq. 1).
 #include "kernels.hpp"
 
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -1431,12 +1433,37 @@ bool score_maskany_mean_fits(uint64_t max_len, uint32_t phi_max) {   // 32-bit s
     return max_len <= 0x7fffffffull && max_len * phi_max + max_len / 2 <= 0xffffffffull;
 }
 
+// waves that share a table: as many as keep several workgroups on a CU: 160 KB of LDS hold six tables of up to 24 KB (four waves
+// each), three of up to 48 KB (eight), one of 128 KB (sixteen)
+static uint32_t maskany_threads(size_t table) { return table <= 24 * 1024 ? 256 : table <= 48 * 1024 ? 512 : 1024; }
+
+// The mask table takes 32 query vectors at the cost of one and gives a document eight lanes; the code-compare kernel takes query
+// vectors one by one and gives a document a wave.  So the latter is the faster one for a few query vectors, the more so the fewer
+// or the longer the documents are.  Mean of the sigmoid, L = 4, 20 documents, code-compare against mask table: one query vector,
+// documents of 3000 14 us and 281; four, documents of 600 13 and 62; 64 sets of 8, documents of 120 16 and 38 (L = 8, C = 12).  On the
+// other side 8 sets of 32 x 20 000 documents, L = 32 5040 and 147; raw counts, 64 sets of one vector x 1500 documents of
+// 120 and L = 96 888 and 350.  The rule compares estimates in ns, fitted to both kernels' times over nine (L, C), 1 to 8000 documents of
+// 1 to 3000 vectors and 1 to 64 sets of 1 to 64 (2656 pairs of times: slower by more than 10 % in 2 % of them, at worst 2.3 times).
+bool score_maskany_pays(const ScoreArgs& a) {
+    const double m = a.n_docs ? (double)((a.n_vectors + a.n_docs - 1) / a.n_docs) : 1.0;   // mean of the index, also for lists
+    const double docs = (double)a.total_scored, q = a.max_q_len;
+    const size_t table = ((size_t)a.L << a.C) * 4;
+    // code-compare: a round trip per dword of a row and 64 vectors, for each query vector; waves beyond three per SIMD take turns, and
+    // rows of many dwords then drop out of L1 between two of their dwords
+    const double steps = std::ceil(m / 64), row = a.L * a.code_bytes / 4;
+    const double cmp_doc = steps * (95 * row + 30) + 400;
+    const double cmp_ns = q * (cmp_doc * std::max(1.0, docs / 2816) + steps * row * row * docs / 1024);
+    // mask table: cleared and built, then a wave takes eight documents, eight vectors of each at a time (chunks side by side)
+    const double waves = std::ceil(q / 32) * std::max((double)a.n_queries, docs / 8);
+    const double mask_run = std::ceil(m / 8) * (24.0 * a.L + (a.sigma_mean ? 500 : 250)) + 700;
+    const double mask_ns = 270 + 170.0 * (table / 4) / maskany_threads(table) + mask_run * std::max(1.0, waves / 3072);
+    return mask_ns <= cmp_ns;
+}
+
 template <int NG, int CW>
 static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
     const size_t table = ((size_t)a.L << a.C) * 4, lds = table + ((size_t)a.L + 1) * 4;
-    // as many waves share a table as keep several workgroups on a CU: 160 KB of LDS hold six tables of up to 24 KB (four waves
-    // each), three of up to 48 KB (eight), one of 128 KB (sixteen)
-    uint32_t T = table <= 24 * 1024 ? 256 : table <= 48 * 1024 ? 512 : 1024;
+    uint32_t T = maskany_threads(table);
     // a small batch: more workgroups matter more than what a CU could hold of them (2 sets x 1452 documents, 48 KB table 52.3 -> 48.7 us
     // a search); not from half the CUs on (3 sets of 39 vectors x 2846, L = 96: 95 -> 117) and not with the tables that leave a CU
     // one workgroup anyway (8 sets x 5000, 96 KB table 151 -> 176)

@@ -99,7 +99,7 @@ def test_mean_falls_back_where_32_bit_sums_do_not_fit():
     """phi(1) = e - 1 in Q16 is 112609: 38 140 of them and the rounding term 19 070 are below 2^32, 38 141 and 19 070 are not."""
     for m, masks in ((38140, True), (38141, False)):
         lens = np.array([5, m, 3])
-        q_lens = np.array([3], dtype=np.int64)
+        q_lens = np.array([40], dtype=np.int64)                # enough query vectors for the mask table where it can be taken
         rng, ix, X, Q, R = case(m, 32, 4, lens, q_lens)
         X[5:] = X[5]                                          # every vector of the long document collides in every table
         Q[:] = X[5]
@@ -110,3 +110,26 @@ def test_mean_falls_back_where_32_bit_sums_do_not_fit():
         dc, qc = orc.hash_i8(X, R, 32, 4), orc.hash_i8(Q, R, 32, 4)
         want = orc.scores_general(dc, np.concatenate([[0], np.cumsum(lens)]), qc, orc.PHI_EXPM1, orc.SIGMA_MEAN, eq1_C=4)
         assert np.array_equal(got, want)
+
+
+# A few query vectors against few or long documents are for the code-compare kernel (a wave per document, query vectors one by one),
+# more of them for the mask table (eight lanes per document, 32 query vectors at once)
+@pytest.mark.parametrize("L,Cb,N,m,n_sets,q,transform,masks",
+                         [(4, 4, 20, 3000, 1, 1, dz.SCORE_MEAN_SIGMOID_Q16, False), (4, 4, 20, 600, 1, 4, dz.SCORE_MEAN_SIGMOID_Q16, False),
+                          (4, 4, 20, 600, 1, 64, dz.SCORE_MEAN_SIGMOID_Q16, True), (96, 8, 200, 1, 1, 1, dz.SCORE_RAW_COUNTS, False),
+                          (96, 8, 1500, 120, 64, 8, dz.SCORE_RAW_COUNTS, True), (128, 7, 1500, 120, 64, 1, dz.SCORE_MEAN_EXPM1_Q16, True),
+                          (12, 7, 1500, 30, 8, 16, dz.SCORE_RAW_COUNTS, True), (64, 9, 20, 120, 8, 2, dz.SCORE_RAW_COUNTS, False)])
+def test_which_kernel_takes_a_few_query_vectors(L, Cb, N, m, n_sets, q, transform, masks):
+    print("[case]", L, Cb, N, m, n_sets, q, transform, flush=True)
+    rng = np.random.default_rng(L + N)
+    ix = dz.create(64, L, Cb, seed=4)
+    dz.build_index(ix, torch.from_numpy(rng.integers(-127, 128, (N * m, 64)).astype(np.int8)).to(DEV), np.full(N, m))
+    Q = torch.from_numpy(rng.integers(-127, 128, (n_sets * q, 64)).astype(np.int8)).to(DEV)
+    dz.set_score_transform(ix, transform)
+    got = {}
+    for algo in (dz.SCORE_AUTO, dz.SCORE_BYTECMP):
+        dz.set_algo(ix, dz.HASH_AUTO, algo)
+        got[algo] = dz.scores(ix, Q, np.full(n_sets, q)).cpu().numpy()
+        mask_kernel = dz.last_score_kernel(ix).startswith("score_bytecmp_kernel_masks<")
+        assert mask_kernel == (masks and algo == dz.SCORE_AUTO), dz.last_score_kernel(ix)
+    assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_BYTECMP])
