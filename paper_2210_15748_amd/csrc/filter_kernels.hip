@@ -1135,8 +1135,12 @@ static hipError_t launch_gemm(const int8_t* X, uint64_t n, uint32_t d, uint32_t 
 hipError_t launch_filter_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
                                 uint32_t* assign, hipStream_t stream) {
     // measured over n, K = 1024 .. 16 384: at d = 128 and 16 384 centroids 30 000 vectors 211 us per k-means round instead of
-    // 455, 120 000 383 instead of 447, 250 000 655 instead of 590; at d = 256 60 000 515 instead of 702, 120 000 832 instead of 699
-    if (n && n <= (d <= 128 ? 160000u : 80000u)) {
+    // 455, 120 000 383 instead of 447, 250 000 655 instead of 590; at d = 256 60 000 515 instead of 702, 120 000 832 instead of 699.
+    // With many vectors, where the kernel above comes near to filling the chip, it takes centroids enough to keep the waves in work:
+    // d = 128, 120 000 vectors, 256 centroids 121 -> 134 us, 1024 116 -> 122, 1536 115 -> 116, 2048 120 -> 118; d = 256, 79 000 vectors, 256
+    // 134 -> 149, 1536 117 -> 118, 2048 130 -> 127; d = 64 and fewer vectors are no slower at any K (60 000, d = 128, 256: 114 -> 117).
+    const bool many = (d == 128 && n > 65536) || (d == 256 && n > 49152);
+    if (n && n <= (d <= 128 ? 160000u : 80000u) && (!many || K >= 1536)) {
         const uint32_t tiles = filter_tiles(K);
         const bool wide = n > 32 * 1024 && d <= 128;   // 128 vectors per workgroup where that still gives every CU one
         const dim3 grid((unsigned)((n + (wide ? 127 : 63)) / (wide ? 128 : 64)));

@@ -103,9 +103,12 @@ def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
 
 
 # few vectors (up to 160 000, or 80 000 at d = 256): either side of a workgroup's 64 and 128 vectors and of the sizes that change the
-# form; fewer centroid tiles than waves, one more than waves, many; centroids that repeat across waves (ties to the lower id)
+# form; fewer centroid tiles than waves, one more than waves, many; centroids that repeat across waves (ties to the lower id); many
+# vectors of few centroids, which take the general kernel
 @pytest.mark.parametrize("d,n,K", [(64, 1, 1), (64, 63, 33), (64, 65, 520), (128, 64, 257), (128, 129, 4000), (256, 100, 300), (256, 1000, 31),
-                                   (64, 32_769, 513), (128, 32_770, 700), (128, 160_000, 90), (128, 160_001, 90), (256, 80_001, 70)])
+                                   (64, 32_769, 513), (128, 32_770, 700), (128, 160_000, 90), (128, 160_001, 90), (256, 80_001, 70),
+                                   (128, 65_536, 100), (128, 65_537, 1535), (128, 65_537, 1536), (128, 160_000, 1601), (256, 49_152, 40),
+                                   (256, 49_153, 1500), (256, 50_001, 1537)])
 def test_closest_centroid_of_few_vectors(d, n, K):
     print("[case]", d, n, K, flush=True)
     rng = np.random.default_rng(n + K)
