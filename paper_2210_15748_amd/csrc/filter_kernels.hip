@@ -931,7 +931,8 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
 // in integers.  The assignment step is the GEMM above; the kernels below are the update step.
 // The sample's vectors are first ordered by centroid (a counting sort of their numbers), so that a vector's coordinates are added in
 // registers to those of the same centroid's other vectors and only whole runs reach memory.  Without room for the order (a
-// workspace of the older, smaller size) every coordinate is added to the sums by itself, as it always was before.
+// workspace of the older, smaller size), and for a few vectors per centroid in a small sample, every coordinate is added to the
+// sums by itself.
 // Bound: the vectors are read once, whole lines; 524 288 vectors of 128 dimensions, 16 384 centroids: 796 -> 128 us
 // for the update's five kernels (67M atomics before, 1.1M now and the two per vector of the sort, at 20 G/s).
 // While the vectors are ordered the sums' memory holds the counters, a centroid's at word c << spread (see COUNTER_WORDS).
@@ -1069,7 +1070,11 @@ hipError_t launch_kmeans_update(const int8_t* X, uint64_t n, uint32_t d, const u
     auto zero = [&](void* p, uint64_t words) {
         hipLaunchKernelGGL(filter_zero_kernel, dim3((unsigned)((words + 2047) / 2048)), dim3(256), 0, stream, (int32_t*)p, words);
     };
-    if (n && order && filter_shape(d)) {
+    // The order's three more launches and its walks over runs pay where runs are long or many: from n = 370 sqrt(K) vectors on, the line
+    // at which a round takes the same time either way for K = 1 to 8192 at d = 64, 128 and 256.  (K = 64 to 512, n = 200 to 1500:
+    // 20 -> 41 and 25 -> 44 us with the order; K = 32 at d = 128, n = 1500 27 -> 30, n = 3000 39 -> 33, n = 100 000 821 -> 324.)
+    const bool ordered = n && order && filter_shape(d) && n * n >= 140000ull * K;
+    if (ordered) {
         const uint32_t spread = counter_spread(K);   // K << 4 words fit the sums: d is at least 64
         const dim3 per_vector((unsigned)((n + 255) / 256)), block(256);
         zero(sums, (uint64_t)K << spread);
@@ -1086,7 +1091,7 @@ hipError_t launch_kmeans_update(const int8_t* X, uint64_t n, uint32_t d, const u
         zero(sums, cells);
         zero(counts, K);
     }
-    if (n && !(order && filter_shape(d))) {
+    if (n && !ordered) {
         const uint64_t blocks = (n * (d / 4) + 255) / 256;
         if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
         hipLaunchKernelGGL(kmeans_accumulate_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, assign, sums,

@@ -77,10 +77,12 @@ def test_probes_with_ties_over_chunks(d, probe, K):
         assert np.array_equal(ids.cpu().numpy()[b], want_ids)
 
 
-# n: less than a group's positions, either side of a workgroup's 1024, several workgroups; one cluster for all, clusters that span
-# groups and workgroups, most clusters empty.  The smaller workspace of a caller that knows only the older size takes the other path
+# n: less than a group's positions, either side of a workgroup's 256 (the form for fewer than 2^17 vectors), several workgroups; one
+# cluster for all, clusters that span groups and workgroups, most clusters empty; either side of n = 370 sqrt(K), below which the vectors
+# are not ordered.  The smaller workspace of a caller that knows only the older size takes the unordered path always
 @pytest.mark.parametrize("d", [64, 128, 256])
-@pytest.mark.parametrize("n,K", [(1, 3), (15, 1), (63, 7), (1023, 5), (1024, 1), (1025, 40), (5000, 900), (3000, 20_000)])
+@pytest.mark.parametrize("n,K", [(1, 3), (15, 1), (63, 7), (1023, 5), (1024, 1), (1025, 40), (5000, 900), (3000, 20_000),
+                                 (374, 1), (375, 1), (1058, 8), (1059, 8), (1500, 7), (6000, 40), (11_300, 900)])
 def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
     print("[case]", d, n, K, flush=True)
     rng = np.random.default_rng(d + n + K)
@@ -100,6 +102,39 @@ def test_kmeans_update_with_and_without_room_for_the_order(d, n, K):
     ws = torch.empty(full - order, dtype=torch.uint8, device=DEV)
     assert dz.lib().dessert_filter_kmeans(ix.handle, Xd.data_ptr(), n, cent.data_ptr(), K, 2, ws.data_ptr(), ws.numel()) == dz.OK
     assert np.array_equal(cent.cpu().numpy(), want)
+
+
+# Samples of 2^17 and more take two pieces per group of lanes, from 2^19 on four: runs that go on from piece to piece, groups whose later
+# pieces lie past the sample's end, waves of which one group has work left; against the path that adds every coordinate by itself
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("n,K", [(131_071, 3), (131_072, 90), (131_077, 1), (131_077, 5000), (524_287, 70), (524_365, 4), (524_365, 20_000)])
+def test_kmeans_update_of_large_samples(d, n, K):
+    print("[case]", d, n, K, flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + n + K)
+    ix = dz.create(d, 8, 4, seed=1)
+    pool = torch.randint(-120, 121, (50, d), generator=g, device=DEV)
+    X = (pool[torch.randint(0, 50, (n,), generator=g, device=DEV)] + torch.randint(-8, 9, (n, d), generator=g, device=DEV)).clamp(-128, 127).to(torch.int8)
+    C = X[torch.randperm(n, generator=g, device=DEV)[:K]].contiguous()
+    full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
+    order = (n * 4 + 255) // 256 * 256
+    got = []
+    for nbytes in (full, full - order):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        cent = C.clone()
+        assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 1, ws.data_ptr(), nbytes) == dz.OK
+        got.append(cent.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+    # and the rounded means of a few clusters, from the assignments of the oracle's definition
+    if K <= 100:
+        first = torch.arange(K, device=DEV)                                  # ties to the lower id
+        near = lambda x: (128 * (2 * x @ C.double().T - (C.double() ** 2).sum(1)) - first).argmax(1)
+        assign = torch.cat([near(x.double()) for x in X.split(16384)]).cpu().numpy()
+        Xh = X.cpu().numpy().astype(np.int64)
+        for c in range(min(K, 5)):
+            mine = Xh[assign == c]
+            want = (2 * mine.sum(0) + len(mine)) // (2 * len(mine)) if len(mine) else C[c].cpu().numpy()
+            assert np.array_equal(got[0][c], want), c
 
 
 # few vectors (up to 160 000, or 80 000 at d = 256): either side of a workgroup's 64 and 128 vectors and of the sizes that change the
