@@ -571,7 +571,8 @@ __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __re
 
 // Exclusive scan of size[0..K) into off[0..K]; size is zeroed for reuse as cursors.  Three launches: workgroup i adds up its
 // SCAN_PART entries and leaves the sum in off[i * SCAN_PART], one workgroup scans those sums where they lie, workgroup i scans
-// its entries from there on.  (One workgroup walked over all entries before, 1.1 us per 1024: 37 us for 32 768, 2.3 ms for 2M.)
+// its entries from there on.  (One workgroup walked over all entries before, 1.1 us per 1024: 37 us for 32 768, 2.3 ms for 2M.)  One
+// part needs the last of the three alone: with all of them the filter over one centroid and 10 documents took 71 -> 79 us to build.
 constexpr uint32_t SCAN_THREADS = 256, SCAN_PART = SCAN_THREADS * 16;
 // inclusive prefix sum over the workgroup's threads; wsum: SCAN_THREADS / 64 words, free again after the call's last barrier
 __device__ inline uint32_t scan_threads(uint32_t x, uint32_t* wsum) {
@@ -622,13 +623,15 @@ __global__ __launch_bounds__(SCAN_THREADS) void filter_scan_parts_kernel(uint32_
     if (threadIdx.x == 0) off[K] = carry;
 }
 __global__ __launch_bounds__(SCAN_THREADS) void filter_scan_kernel(uint32_t* __restrict__ size, uint32_t K, uint32_t spread,
-                                                                   uint32_t* __restrict__ off) {
+                                                                   uint32_t* __restrict__ off, uint32_t alone) {
     __shared__ uint32_t wsum[SCAN_THREADS / 64];
     uint32_t x[16];
     const uint32_t first = blockIdx.x * SCAN_PART + threadIdx.x * 16;
-    const uint32_t base = off[(size_t)blockIdx.x * SCAN_PART];   // read by all before scan_threads' barriers, rewritten after them
+    const uint32_t base = alone ? 0u : off[(size_t)blockIdx.x * SCAN_PART];   // read by all before scan_threads' barriers, rewritten after them
     const uint32_t sum = scan_load16(size, first, K, spread, x);
-    uint32_t run = base + scan_threads(sum, wsum) - sum;
+    const uint32_t incl = scan_threads(sum, wsum);
+    if (alone && threadIdx.x == SCAN_THREADS - 1) off[K] = incl;
+    uint32_t run = base + incl - sum;
 #pragma unroll
     for (uint32_t i = 0; i < 16; ++i)
         if (first + i < K) {
@@ -639,9 +642,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void filter_scan_kernel(uint32_t* __r
 }
 static void launch_filter_scan(uint32_t* size, uint32_t K, uint32_t spread, uint32_t* off, hipStream_t stream) {   // K >= 1
     const uint32_t parts = (K + SCAN_PART - 1) / SCAN_PART;
-    hipLaunchKernelGGL(filter_scan_sums_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off);
-    hipLaunchKernelGGL(filter_scan_parts_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, off, parts, K);
-    hipLaunchKernelGGL(filter_scan_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off);
+    if (parts > 1) {
+        hipLaunchKernelGGL(filter_scan_sums_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off);
+        hipLaunchKernelGGL(filter_scan_parts_kernel, dim3(1), dim3(SCAN_THREADS), 0, stream, off, parts, K);
+    }
+    hipLaunchKernelGGL(filter_scan_kernel, dim3(parts), dim3(SCAN_THREADS), 0, stream, size, K, spread, off, parts == 1 ? 1u : 0u);
 }
 
 // bucket_off[c] = sub_off[c*S] for c = 0..K: the caller-visible bucket starts
