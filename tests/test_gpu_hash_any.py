@@ -28,7 +28,8 @@ def i8_inputs(rng, n, d, P):
 
 # d: one k-step of 32, either side of whole k-steps, the largest.  L, C: tables that divide unevenly over the two lane halves
 # (12, 20, 28), several segments of 16 tables a half (36, 96, 100), code bits that straddle M-tiles, one-byte and 16-bit codes.
-# n: a lone vector, either side of a wave's 64 and of a workgroup's 256 vectors
+# n: a lone vector, either side of a wave's 32 and of a workgroup's 128 vectors (one n-tile per wave, up to 65 536 vectors by segments); the
+# next test has the two-tile forms
 @pytest.mark.parametrize("d,L,Cb,n", [(32, 20, 5, 1), (33, 4, 1, 63), (47, 12, 7, 65), (63, 28, 8, 255), (96, 24, 6, 257), (100, 96, 3, 300),
                                       (127, 100, 4, 333), (200, 8, 11, 1000), (255, 36, 9, 129), (300, 48, 16, 70), (383, 24, 13, 31),
                                       (384, 128, 8, 140), (200, 16, 5, 140_003)])
@@ -43,11 +44,30 @@ def test_i8_any_shape_bit_exact(d, L, Cb, n):
         assert np.array_equal(auto, want)
 
 
+# Two n-tiles per wave, from 65 537 vectors (times segments) on: either side of that line, ragged ends of a wave's 64 and a workgroup's 256
+# vectors, every step of KS; beyond 131 072 vectors all of R in LDS where it fits 80 KB, a tile at a time where it does not.  All rows
+# against the plain kernel, the first and the last workgroups' against the oracle
+@pytest.mark.parametrize("d,L,Cb,n", [(64, 12, 7, 65_536), (64, 12, 7, 65_537), (128, 24, 6, 65_600), (200, 20, 5, 65_793), (384, 16, 3, 65_599),
+                                      (96, 40, 8, 32_769), (100, 36, 9, 40_003), (47, 12, 7, 140_003), (255, 100, 4, 131_137), (300, 96, 7, 140_001)])
+def test_i8_two_tiles_per_wave(d, L, Cb, n):
+    print("[case]", d, L, Cb, n, flush=True)
+    rng = np.random.default_rng(d + n)
+    X, R = i8_inputs(rng, n, d, L * Cb)
+    auto, scalar = both("i8", "pm1", X, R, L, Cb)
+    assert np.array_equal(auto, scalar)
+    for part in (slice(0, 300), slice(n - 300, n)):
+        assert np.array_equal(auto[part], orc.hash_i8(X[part], R, L, Cb))
+
+
 # fp32 sums of exact products: a sign may differ from the 64-bit one only where the projection is within the rounding of the
 # sum, at most (d + 2^3) * 2^-24 * sum |r_i x_i| with any order of adding, plus 2^-23 of every |r_i x_i| for the two-part matrix
 @pytest.mark.parametrize("xt,pk", [("f16", "gauss"), ("f16", "pm1"), ("i8", "gauss")])
 @pytest.mark.parametrize("d,L,Cb,n", [(16, 8, 8, 33), (17, 12, 3, 500), (50, 24, 11, 300), (200, 8, 11, 70_001), (200, 96, 5, 257), (255, 20, 7, 100),
-                                      (300, 24, 12, 1000), (384, 4, 16, 65)])
+                                      (300, 24, 12, 1000), (384, 4, 16, 65),
+                                      # two n-tiles per wave at every step of KS, with ragged ends
+                                      (50, 24, 11, 65_537), (100, 8, 7, 65_793), (200, 12, 3, 65_599), (250, 8, 5, 65_600), (384, 4, 6, 65_601),
+                                      # beyond 131 072 vectors: all of R in LDS where it fits, a tile at a time where it does not
+                                      (200, 8, 11, 140_003), (50, 12, 4, 131_073), (250, 24, 6, 131_137)])
 def test_fp_any_shape_signs_within_rounding(xt, pk, d, L, Cb, n):
     print("[case]", xt, pk, d, L, Cb, n, flush=True)
     rng = np.random.default_rng(d + L * Cb)
