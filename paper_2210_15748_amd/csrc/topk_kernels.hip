@@ -58,7 +58,7 @@ __global__ __launch_bounds__(T) void topk_scores_kernel(TopkArgs a, KeyPlan plan
     }
 }
 
-// A few results from a short slice (k <= TOPK_FEW, at most 4096 scores, 32-bit keys): no histogram.  A lane holds eight keys in
+// A few results from a short list (k <= TOPK_FEW, at most 4096 scores, 32-bit keys; such lists are never cut into slices): no histogram.  A lane holds eight keys in
 // descending order; a round takes the largest head of the wave (six DPP maxima) and moves the lane that held it up, so a wave's
 // k best of its 512 scores are k rounds with no barrier between them; the waves' lists meet in LDS once, where every key's place
 // in the result is counted.  Bound: latency of the load and of k rounds of some 100 cycles; the selection above has some twenty
@@ -97,9 +97,9 @@ __device__ __forceinline__ uint32_t wave_take_best(uint32_t (&key)[N], uint32_t 
     return mine;
 }
 
-__global__ __launch_bounds__(TOPK_FEW_WAVES * 64) void topk_few_kernel(TopkArgs a, uint32_t id_bits, uint32_t slices) {
+__global__ __launch_bounds__(TOPK_FEW_WAVES * 64) void topk_few_kernel(TopkArgs a, uint32_t id_bits) {
     __shared__ uint32_t best[TOPK_FEW_WAVES][TOPK_FEW + 1];   // a list per wave; the odd row length keeps rows apart in the banks
-    const uint32_t b = blockIdx.y, s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
     uint64_t base, count;
     if (a.cand_ids) {
         base = a.cand_uniform ? (uint64_t)b * a.cand_uniform : a.cand_off[b];
@@ -108,10 +108,8 @@ __global__ __launch_bounds__(TOPK_FEW_WAVES * 64) void topk_few_kernel(TopkArgs 
         base = (uint64_t)b * a.n_docs;
         count = a.n_docs;
     }
-    const uint64_t per = (count + slices - 1) / slices;
-    const uint64_t lo = (uint64_t)s * per < count ? (uint64_t)s * per : count;
-    const uint32_t n = (uint32_t)((lo + per < count ? lo + per : count) - lo);   // at most 8 * blockDim.x
-    ScoreKeysT<uint32_t> keys{a.scores + base + lo, a.cand_ids ? a.cand_ids + base + lo : nullptr, lo, id_bits};
+    const uint32_t n = (uint32_t)count;   // at most 8 * blockDim.x
+    ScoreKeysT<uint32_t> keys{a.scores + base, a.cand_ids ? a.cand_ids + base : nullptr, 0, id_bits};
     uint32_t key[TOPK_FEW_KEYS];
 #pragma unroll
     for (uint32_t u = 0; u < TOPK_FEW_KEYS; ++u) {
@@ -132,10 +130,7 @@ __global__ __launch_bounds__(TOPK_FEW_WAVES * 64) void topk_few_kernel(TopkArgs 
     order(2, 4); order(3, 5);
     order(1, 2); order(3, 4); order(5, 6);
     auto result = [&](uint32_t i, uint32_t top) {
-        if (slices == 1)
-            write_result(top, id_bits, a.out_ids + (size_t)b * a.k + i, a.out_scores + (size_t)b * a.k + i);
-        else
-            a.partial[((size_t)b * slices + s) * a.k + i] = top;
+        write_result(top, id_bits, a.out_ids + (size_t)b * a.k + i, a.out_scores + (size_t)b * a.k + i);
     };
     const uint32_t k = a.k, mine = wave_take_best(key, k);
     if (waves == 1) {
@@ -417,9 +412,9 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t stream) {
     const bool fit32 = keys_fit_32(a.max_score, a.n_docs ? a.n_docs - 1 : 0);
     const dim3 grid(slices, a.n_queries);
     const uint64_t slice_len = (a.max_scored + slices - 1) / slices;
-    if (fit32 && a.k <= TOPK_FEW && slice_len <= 4096) {   // 512 scores per wave
+    if (fit32 && a.k <= TOPK_FEW && slices == 1 && slice_len <= 4096) {   // 512 scores per wave
         const uint32_t waves = slice_len <= 512 ? 1 : (uint32_t)((slice_len + 511) / 512);
-        hipLaunchKernelGGL(topk_few_kernel, grid, dim3(64 * waves), 0, stream, a, plan.id_bits, slices);
+        hipLaunchKernelGGL(topk_few_kernel, dim3(a.n_queries), dim3(64 * waves), 0, stream, a, plan.id_bits);
     } else
     // every slice short enough to stay in the registers of the wider workgroup (see topk_scores_kernel)
     if ((a.max_scored + slices - 1) / slices <= (uint64_t)TOPK_THREADS_SHORT * 4) {

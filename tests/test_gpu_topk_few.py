@@ -1,5 +1,5 @@
-"""The selection of a few results (k <= 16) from slices of at most 4096 scores against the oracle: list lengths either side of a wave's 512
-and of a workgroup's 4096 scores, lists shorter than k, heavy ties, repeated ids, empty slots, several slices."""
+"""The selection of a few results (k <= 16) from lists of at most 4096 scores against the oracle: list lengths either side of a wave's 512
+and of a workgroup's 4096 scores, lists shorter than k, heavy ties, repeated ids, empty slots; the longer lists beside them."""
 import numpy as np
 import pytest
 import torch
@@ -49,8 +49,9 @@ def test_few_results(N, lens_of_lists, k):
         assert np.array_equal(ids[b], want_ids) and np.array_equal(sc[b], want_sc), b
 
 
-def test_few_results_of_many_slices():
-    """One query set over 40 000 documents: slices of at most 4096 scores, merged."""
+def test_few_results_of_a_list_cut_into_slices():
+    """One query set over 40 000 documents: four slices of 10 000, a list that the selection of a few results leaves to the general
+    one and its merge."""
     rng = np.random.default_rng(1)
     d, L, Cb, N = 64, 8, 3, 40_000
     X = rng.integers(-127, 128, (N, d)).astype(np.int8)
