@@ -15,7 +15,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 
 static bool filter_shape(uint32_t d) { return d == 64 || d == 128 || d == 256; }
 
-constexpr int FILTER_TG = 8;           // centroid tiles per LDS group (the kernel may take half of it)
+constexpr int FILTER_TG = 4;           // centroid tiles per LDS group
+constexpr int FILTER_RANGE_TILES = 8;  // ranges of the query side are whole multiples of it
 constexpr int32_t FILTER_BIAS = 1 << 24;  // 2 x.c - |c|^2 lies in (-2^24, 2^24) for int8 vectors up to d = 256
 
 // accumulator register r of lane half g holds tile row 8*(r/4) + 4*g + r%4
@@ -84,7 +85,8 @@ __global__ __launch_bounds__(256) void filter_prep_kernel(const int8_t* __restri
 // Bound: matrix cores.  Column tiles are multiplied one after the other, each while the one before is compared: two accumulator
 // sets instead of one per column tile (202 -> 168 VGPRs at d = 128, three waves per SIMD instead of two).  With 512 tiles
 // 38 % of the tiles can improve some lane of a wave, so what such a tile costs matters: 16 shifts and 8 maxima (parity and
-// tie-break come out of the row's constant with the shift; about 64 operations when they were computed per row).  4.2M vectors x
+// tie-break come out of the row's constant with the shift; about 64 operations when they were computed per row).  (Held to three
+// waves the d = 128 build of MODE 0 spills three registers, 16 bytes of scratch per lane; the figures are with them.)  4.2M vectors x
 // 16 384 centroids, d = 128: 8.7 -> 7.4 ms = 2.4 POP/s, the share of nominal that a large bf16 matrix product reaches here.
 // Four probes of 4096 vectors in 32 768 centroids 116 -> 54 us (32-bit sorted keys; 64-bit list inserts per row before).
 constexpr int64_t LIST_EMPTY = INT64_MIN;
@@ -131,9 +133,8 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
     // a list of one entry is an argmax: MODE = 1 keeps the 32-bit running key of MODE = 0 (no 64-bit list
     // inserts in the loop) and forms its list entry at the end
     constexpr bool ARGMAX = MODE == 0 || MODE == 1;
-    // centroid tiles per group: 8 for the build's assignment (long ranges, d <= 128), 4 on the query side and for
-    // d = 256, where two buffers of 8 tiles would leave a CU with fewer workgroups than the registers allow
-    constexpr int TG = (MODE == 0 && KS <= 4 && gemm_min_waves(KS, NT, MODE) <= 2) ? FILTER_TG : FILTER_TG / 2;
+    // centroid tiles per group: two buffers of 8 would leave a CU with fewer workgroups than the registers allow
+    constexpr int TG = FILTER_TG;
     // two groups of centroid tiles in LDS: while the waves multiply one, the next is copied from global memory
     // straight into the other buffer (global_load ... lds: no staging registers; a wave's 64 lanes fill
     // consecutive LDS), one barrier per group
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(256) void filter_bucket_kernel(const uint32_t* __re
         const uint64_t lo = doc_off[doc], hi = doc_off[doc + 1];
         if (hi - lo <= DOC_SET_MAX) {
             const uint32_t m = (uint32_t)(hi - lo);
-            uint32_t log_slots = 7;   // at least a third of the slots stays free
+            uint32_t log_slots = 7;   // at least a quarter of the slots stays free
             while (log_slots < 9 && (1u << log_slots) * 3 < m * 4) ++log_slots;
             const uint32_t slots = 1u << log_slots;
             for (uint32_t i = lane; i < slots / 4; i += 64) set4[i] = uint4{DOC_SET_EMPTY, DOC_SET_EMPTY, DOC_SET_EMPTY, DOC_SET_EMPTY};
@@ -691,7 +692,7 @@ __global__ void filter_zero_kernel(int32_t* __restrict__ p, uint64_t n) {
 // [slab * slab_docs, +slab_docs) and keeps one counter per document in LDS (W bytes each, packed into
 // 32-bit words; a count never exceeds the number of probed buckets, which the host bounds by the
 // counter range).  It reads, of every bucket its query set probes, the sub-buckets that overlap its slab
-// (a wave takes its buckets' ranges as one concatenated run, so all its loads are in flight together),
+// (long ranges 64 elements to a load, eight loads in flight; short ones as one concatenated run, see below),
 // counts the ids that fall into the slab, and remembers each document at its first hit in a queue.  Then
 // one key (count, id) in the top-k key format per queued document goes to the query set's list;
 // cursor[b] ends as the number of distinct documents hit.  The order inside a list is unspecified.
@@ -1181,19 +1182,20 @@ FilterProbePlan filter_probe_plan(uint64_t n, uint32_t K, uint32_t probe) {
     FilterProbePlan pl{};
     if (probe == 0 || probe > FILTER_LIST_MAX || n == 0) return pl;  // ranges = 0: use the distance matrix
     const uint32_t tiles = filter_tiles(K);
-    const uint32_t groups = (tiles + FILTER_TG - 1) / FILTER_TG;
+    const uint32_t groups = (tiles + FILTER_RANGE_TILES - 1) / FILTER_RANGE_TILES;
     // more vectors per workgroup halve the centroid bytes staged through LDS per vector
     pl.nt = n >= 4096 ? 2 : 1;
     const uint64_t blocks = (n + 128 * pl.nt - 1) / (128 * pl.nt);
     uint64_t want = (2048 + blocks - 1) / blocks;  // aim at ~2048 workgroups
     if (want > groups) want = groups;
     // a few query vectors alone (one query set): the launch is a chain of global -> LDS stages per workgroup, so more,
-    // shorter ranges cut its latency; the merge of a vector's lists is wave-wide for one probe, a thread's loop otherwise
+    // shorter ranges cut its latency.  With more probes the merge has as many times the entries to read: 65 536 centroids, 512
+    // ranges instead of 128 for one set of 32 vectors, d = 128, 2 probes 43.8 -> 41.2 us a filter query, 8 probes 97.9 -> 104.7
     const uint64_t cap = blocks <= 4 ? (probe == 1 ? 512 : 128) : 64;
     if (want > cap) want = cap;
     if (want < 1) want = 1;
     const uint32_t per = (groups + (uint32_t)want - 1) / (uint32_t)want;
-    pl.tiles_per_range = per * FILTER_TG;
+    pl.tiles_per_range = per * FILTER_RANGE_TILES;
     pl.ranges = (tiles + pl.tiles_per_range - 1) / pl.tiles_per_range;
     pl.width = list_width(probe);
     pl.list_bytes = (size_t)n * pl.ranges * 2 * pl.width * 8;
