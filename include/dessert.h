@@ -132,9 +132,10 @@ dessert_status_t dessert_set_algo(dessert_index_t *index, int hash_algo, int sco
  *     vectors is the maximum (MAX) or the mean (MEAN) of phi(count / L), with phi(x) = x (IDENTITY),
  *     e^x - 1 (EXPM1) or 1/(1+e^-x) - 1/2 (SIGMOID).  phi is tabulated for the L+1 counts as
  *     round(65536 * phi); the mean of a document of m vectors is the integer (sum + floor(m/2)) / m, 0 for an
- *     empty document; the score is the sum over the query vectors.  Needs |Q| <= 16383.  MEAN_IDENTITY has a
- *     mask-table form (L a power of two, documents of at most 65535 vectors: with phi the identity the mean comes
- *     from sums of collision counts); the other MEAN transforms have none (DESSERT_SCORE_AUTO runs them on a kernel of their own).
+ *     empty document; the score is the sum over the query vectors.  Needs |Q| <= 16383.  Of the MEAN
+ *     transforms DESSERT_SCORE_MASKLUT takes MEAN_IDENTITY only (L a power of two, documents of at most 65535 vectors: with
+ *     phi the identity the mean comes from sums of collision counts).  DESSERT_SCORE_AUTO takes them all, on the mask-table kernel for any number
+ *     of tables where its table fits and 32 bits hold the sums, else on the code-compare kernel.
  * Applies to later dessert_search / dessert_scores calls. */
 enum {
     DESSERT_SCORE_RAW_COUNTS = 0,
@@ -339,6 +340,9 @@ dessert_status_t dessert_probe_read_bandwidth(const void *buf_dev, size_t bytes,
  * "score_masklut_kernel<32, 7, 1, 0, 1, false>": tables, index bits, bytes per code, form, masks per table entry, chunks
  * split over workgroups).  The form is 0 raw counts, 1 tabulated maximum, 2 weighted, 3 mean, 4 weighted mean; two masks are
  * those of two query sets, or with the forms 5, 6, 7 (0, 1, 2 over chunk pairs) of two chunks of 32 vectors of one set.
+ * "score_bytecmp_kernel<1>" (bytes per code) is the code-compare kernel.  "score_bytecmp_kernel_masks<2, 1, true>" (groups of 16 tables,
+ * bytes per code, mean) is the mask-table kernel for any number of tables: it compares no codes, and its name begins as it does
+ * because programs tell the calls that score_masklut_kernel does not take by that beginning.
  * "" if nothing was launched.  Lets a caller pair a run with the
  * profiler summary of the same kernel.  The string lives in the handle. */
 const char *dessert_last_score_kernel(const dessert_index_t *index);

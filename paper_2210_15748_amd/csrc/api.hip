@@ -445,7 +445,7 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
                        (ix->cfg.L & (ix->cfg.L - 1)) == 0) ? 1u : 0u;
     sa.q_weights = ix->q_weights;
     int algo = ix->score_algo;
-    // sigma = mean has a mask-table form for phi = identity only (sums of counts), and for documents short enough
+    // in the fixed-size mask-table kernel sigma = mean has a form for phi = identity only (sums of counts), and for documents short enough
     const bool mean_on_masklut = sa.sigma_mean && sa.phi_identity && ix->max_len <= MASKLUT_MEAN_MAX_LEN;
     // the mask-table kernels let idle lanes read code row 0, so they need a non-empty code array
     bool any_tables = false;   // the mask-table kernel for any number of tables
@@ -474,8 +474,8 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     if (timed) { HIP_TRY(hipEventRecord(tsp->ev[1], ix->stream)); tsp->hash = true; }
     if (algo == DESSERT_SCORE_MASKLUT) {
         if (sa.sigma_mean && !mean_on_masklut)
-            return fail(DESSERT_EINVAL, "of the MEAN score transforms only MEAN_IDENTITY has a mask-table form (documents of at "
-                                        "most 65535 vectors); the others run on the code-compare kernel only");
+            return fail(DESSERT_EINVAL, "of the MEAN score transforms DESSERT_SCORE_MASKLUT has MEAN_IDENTITY only (L a power of two, "
+                                        "documents of at most 65535 vectors); DESSERT_SCORE_AUTO and the code-compare kernel take the others");
         if (!score_masklut_supported(ix->cfg.L, ix->cfg.C))
             return fail(DESSERT_EINVAL, "mask-table scoring needs L in {8,16,32,64,128} (C <= 8), or L = 8 with C <= 11, "
                                         "L = 16 with C <= 10, L = 32 with C = 9");

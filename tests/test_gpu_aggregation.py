@@ -68,6 +68,8 @@ def test_aggregations_match_oracle(transform, weighted, L, Cb, algo):
     Qd = torch.from_numpy(Q).to(DEV)
     got = dz.scores(ix, Qd, q_lens).cpu().numpy()
     assert dz.last_score_kernel(ix).startswith("score_masklut_kernel" if want_masklut else "score_bytecmp_kernel"), dz.last_score_kernel(ix)
+    if not want_masklut:      # the mask-table kernel for any number of tables under AUTO, code compares where they are asked for
+        assert dz.last_score_kernel(ix).startswith("score_bytecmp_kernel_masks<" if algo == dz.SCORE_AUTO else "score_bytecmp_kernel<")
     for b in range(len(q_lens)):
         assert np.array_equal(got[b], ref(b)), b
     # candidate lists with an empty slot, then top-k
