@@ -1189,7 +1189,7 @@ FilterProbePlan filter_probe_plan(uint64_t n, uint32_t K, uint32_t probe) {
     uint64_t want = (2048 + blocks - 1) / blocks;  // aim at ~2048 workgroups
     if (want > groups) want = groups;
     // a few query vectors alone (one query set): the launch is a chain of global -> LDS stages per workgroup, so more,
-    // shorter ranges cut its latency.  With more probes the merge has as many times the entries to read: 65 536 centroids, 512
+    // shorter ranges cut its latency.  With more probes the merge has as many times the entries to read: 65 536 centroids, 256
     // ranges instead of 128 for one set of 32 vectors, d = 128, 2 probes 43.8 -> 41.2 us a filter query, 8 probes 97.9 -> 104.7
     const uint64_t cap = blocks <= 4 ? (probe == 1 ? 512 : 128) : 64;
     if (want > cap) want = cap;
