@@ -809,7 +809,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     score += first_score;
                 }
                 constexpr bool one_set = W == 1 || chunk_pairs;
-                if (valid && sub == 0 && (one_set || (b0 + w < a.n_queries && c0 < q_len[w]))) {
+                if (valid && sub == 0 && (chunk_pairs || (b0 + w < a.n_queries && c0 < q_len[w]))) {
                     // two sets: each scores every document, set b0+w starts at (b0+w)*n_docs
                     int32_t* dst = a.scores + (one_set ? sp.base + meta.slot[doc] : (uint64_t)(b0 + w) * a.n_docs + first + doc);
                     if (one_set && m == 0 && meta.lo[doc] == ~0ull) {
