@@ -1284,13 +1284,19 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     //   32 tables, C <= 5: few codes, so the single form's reads of one bank often share an address.  Every document for 64 sets of
     //     256 vectors 339 -> 355 us, 8 lists of 4096, 128 vectors 48 -> 52, but 64 lists of 2000, 256 vectors 0.84 of the time: lists only,
     //     from 1536 workgroups on;
-    //   8 tables, C = 10 (16-byte rows): 64 lists of 2000, 64 vectors 0.84 of the time, 256 lists 1.05: lists in small batches.
+    //   8 tables, C = 10 (16-byte rows): 64 lists of 2000, 64 vectors 0.84 of the time, 256 lists 1.05: lists in small batches;
+    //   weights: with four lanes per document a lane weighs eight query vectors of each mask, so a pass over two chunks costs up to
+    //     1.8 and one over the first masks 1.5 (64 lists of 2000, 160 vectors, L = 16, C = 6 132 -> 159 us); with 64-entry tables no
+    //     lists (L = 32, 8 of 4096, 128 vectors 55 -> 64), with 32 tables of 128 entries from 1536 workgroups on (60 -> 66).
     constexpr bool CHUNK_PAIRS_OK = PAIR_OK && L <= 32;
     constexpr uint32_t first_masks_only = PAIR_BYTES == 64 * 1024 && (L == 32 || L == 8) ? 160 : 140;
-    const bool few_codes = L == 32 && a.C <= 5;
+    const bool few_codes = L == 32 && a.C <= 5, weighted = a.q_weights != nullptr;
+    const uint64_t two_cost = weighted ? 178 : 172, one_cost = weighted && first_masks_only < 150 ? 150 : first_masks_only;
     const bool chunk_pairs_pay = CHUNK_PAIRS_OK && !a.sigma_mean && !(few_codes && !a.cand_ids) &&
                                  !(L == 8 && CB == 10 && a.cand_ids && a.total_scored >= (1u << 18)) &&
-                                 172 * a.chunk_pairs + first_masks_only * (a.chunks - 2 * a.chunk_pairs) < 97 * a.chunks;
+                                 !(weighted && CB == 6 && a.cand_ids) &&
+                                 two_cost * a.chunk_pairs + one_cost * (a.chunks - 2 * a.chunk_pairs) < 97 * a.chunks;
+    const uint32_t pairs_min_grid = few_codes || (weighted && L == 32 && CB <= 7) ? 1536 : 1024;
     // documents per workgroup: at most LUT_DOCS; fewer when that would leave the 256 CUs short of
     // workgroups, but at least 64 (32 = one run of 8 documents for each of the four waves when the
     // documents are long: about 4096 vectors per workgroup keep the table build amortised)
@@ -1321,7 +1327,7 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
         while (d2 > cp_docs && ((a.max_scored + d2 - 1) / d2) * a.n_queries < 4096) d2 /= 2;
         const uint64_t bx2 = (a.max_scored + d2 - 1) / d2;
         const uint32_t units = (chunks + 1) / 2;
-        if (bx2 * a.n_queries * units * (cp_threads / 256) >= (few_codes ? 1536 : 1024)) {
+        if (bx2 * a.n_queries * units * (cp_threads / 256) >= pairs_min_grid) {
             cp = true;
             pair = false;
             dpb = d2;

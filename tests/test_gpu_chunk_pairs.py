@@ -20,9 +20,12 @@ def launched(ix):
     return int(m.group(5)), m.group(6) == "true", int(m.group(4))
 
 
-def paired(L, Cb, mode):
-    """Whether the batches below are for chunk pairs: not with 64 tables (the single form is the rotated one), and with 32 tables of up to
-    5 bits only for lists that make 1536 workgroups."""
+def paired(L, Cb, mode, form):
+    """Whether the batches below are for chunk pairs: not with 64 tables (the single form is the rotated one), with 32 tables of up to
+    5 bits only for lists that make 1536 workgroups; with weights no lists at up to 6 bits, and with 32 tables of 7 bits 1536
+    workgroups."""
+    if form == "weighted" and (Cb <= 6 and mode != "all split" or L == 32 and Cb <= 7 and mode == "lists split"):
+        return False
     return L < 64 and not (L == 32 and Cb <= 5 and mode != "lists")
 
 
@@ -67,7 +70,7 @@ def test_chunk_pairs(L, Cb, mode, form):
         got[algo] = dz.scores(ix, torch.from_numpy(Q).to(DEV), q_lens, cand_ids=flat, cand_offsets=co).cpu().numpy().reshape(-1)
         W, split, remap = launched(ix)
         if algo == dz.SCORE_AUTO:
-            assert W == (2 if paired(L, Cb, mode) else 1) and (W == 1 or split == (mode != "lists")), dz.last_score_kernel(ix)
+            assert W == (2 if paired(L, Cb, mode, form) else 1) and (W == 1 or split == (mode != "lists")), dz.last_score_kernel(ix)
             # instantiations of their own, told from pairs of sets
             assert remap == (5 if W == 2 else 0) + ["raw", "eq1", "weighted"].index(form)
         else:
