@@ -94,6 +94,7 @@ struct dessert_index {
     void* f_cent = nullptr;
     void* f_table = nullptr;
     uint32_t* f_cursor = nullptr;
+    void* f_groups = nullptr;                 // scratch of assignments by groups of centroids; nullptr: they are not tried
     uint32_t* f_sub_off = nullptr;   // [K*S+1] sub-bucket starts (library-owned)
     FilterSubPlan f_sub{1, 15};
     uint32_t f_K = 0;
@@ -657,6 +658,7 @@ void dessert_destroy(dessert_index_t* ix) {
     if (ix->f_table) (void)hipFree(ix->f_table);
     if (ix->f_cursor) (void)hipFree(ix->f_cursor);
     if (ix->f_sub_off) (void)hipFree(ix->f_sub_off);
+    if (ix->f_groups) (void)hipFree(ix->f_groups);
     if (ix->h_offsets) (void)hipHostFree(ix->h_offsets);
     for (auto& slot : ix->slots)
         for (auto& ev : slot.ev)
@@ -924,6 +926,8 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
         if (ix->f_table) (void)hipFree(ix->f_table);
         if (ix->f_cursor) (void)hipFree(ix->f_cursor);
         if (ix->f_sub_off) (void)hipFree(ix->f_sub_off);
+        if (ix->f_groups) (void)hipFree(ix->f_groups);
+        ix->f_groups = nullptr;
         ix->f_cent = ix->f_table = nullptr;
         ix->f_cursor = ix->f_sub_off = nullptr;
         ix->f_alloc_K = 0;
@@ -933,13 +937,17 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
         if (e == hipSuccess) e = hipMalloc((void**)&ix->f_cursor, filter_cursor_bytes(n_sub));
         if (e == hipSuccess) e = hipMalloc((void**)&ix->f_sub_off, (n_sub + 1) * 4);
         if (e != hipSuccess) return fail(DESSERT_ENOMEM, "hipMalloc(filter state): %s", hipGetErrorString(e));
+        if (filter_groups_pay_from(n_centroids) && hipMalloc(&ix->f_groups, filter_group_bytes(n_centroids, ix->cfg.d)) != hipSuccess) {
+            ix->f_groups = nullptr;   // the build does without
+            (void)hipGetLastError();
+        }
         ix->f_alloc_K = n_centroids;
         ix->f_alloc_sub = n_sub;
     }
     ix->f_sub = sub;
     HIP_TRY(launch_filter_prep(centroids_dev, n_centroids, ix->cfg.d, ix->f_cent, ix->f_table, ix->stream));
     HIP_TRY(launch_filter_assign((const int8_t*)vectors_dev, ix->n_vectors, ix->cfg.d, n_centroids, ix->f_cent,
-                                 ix->f_table, assign_dev, ix->stream));
+                                 ix->f_table, assign_dev, ix->f_groups, bucket_docs_dev, ix->stream));
     HIP_TRY(launch_filter_buckets(assign_dev, ix->offsets, ix->n_docs, n_centroids, ix->f_sub, ix->f_cursor, ix->f_sub_off,
                                   bucket_offsets_dev, bucket_docs_dev, ix->stream));
     {   // the largest bucket bounds how many documents one query set can hit (sizes the query workspace)
@@ -959,7 +967,7 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
 
 namespace {
 struct KmeansWorkspace {
-    size_t assign, sums, counts, cent, table, least, order, total;   // least: what a call cannot do without
+    size_t assign, sums, counts, cent, table, least, order, ordered, groups, total;   // least: what a call cannot do without
 };
 KmeansWorkspace carve_kmeans(uint32_t d, uint64_t n, uint32_t K) {
     KmeansWorkspace w{};
@@ -971,6 +979,8 @@ KmeansWorkspace carve_kmeans(uint32_t d, uint64_t n, uint32_t K) {
     w.table = p;  p += align_up(filter_table_bytes(K), 256);
     w.least = p;   // a workspace without the rest is accepted too
     w.order = p;  p += align_up((size_t)(n ? n : 1) * 4, 256);
+    w.ordered = p;
+    w.groups = p; p += filter_groups_try(n, d, K) ? align_up(filter_group_bytes(K, d), 256) : 0;
     w.total = p;
     return w;
 }
@@ -1001,11 +1011,12 @@ dessert_status_t dessert_filter_kmeans(const dessert_index_t* ix, const int8_t* 
     uint32_t* assign = (uint32_t*)(ws + w.assign);
     for (uint32_t it = 0; it < iterations; ++it) {
         HIP_TRY(launch_filter_prep(centroids_dev, n_centroids, ix->cfg.d, ws + w.cent, ws + w.table, ix->stream));
+        // the list of an assignment by groups lies where the order of the update step goes afterwards
         HIP_TRY(launch_filter_assign(sample_dev, n_sample, ix->cfg.d, n_centroids, ws + w.cent, ws + w.table, assign,
-                                     ix->stream));
+                                     workspace_bytes >= w.total ? ws + w.groups : nullptr, (uint32_t*)(ws + w.order), ix->stream));
         HIP_TRY(launch_kmeans_update(sample_dev, n_sample, ix->cfg.d, assign, n_centroids, (int32_t*)(ws + w.sums),
                                      (uint32_t*)(ws + w.counts), centroids_dev,
-                                     workspace_bytes >= w.total ? (uint32_t*)(ws + w.order) : nullptr, ix->stream));
+                                     workspace_bytes >= w.ordered ? (uint32_t*)(ws + w.order) : nullptr, ix->stream));
     }
     return DESSERT_OK;
 }

@@ -5,22 +5,16 @@
 // "Closest" is the squared Euclidean distance with ties to the lower centroid id.  Since
 // |x|^2 is common to all centroids, argmin_k |x - c_k|^2 = argmax_k (2 x.c_k - |c_k|^2): the
 // dense part is an int8 GEMM (vectors x centroids) on v_mfma_i32_32x32x32_i8, exact in int32.
+#include "filter_common.hpp"
 #include "kernels.hpp"
 #include "topk_select.hpp"
 
 namespace dessert {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-
 static bool filter_shape(uint32_t d) { return d == 64 || d == 128 || d == 256; }
 
-constexpr int FILTER_TG = 4;           // centroid tiles per LDS group
 constexpr int FILTER_RANGE_TILES = 8;  // ranges of the query side are whole multiples of it
 constexpr int32_t FILTER_BIAS = 1 << 24;  // 2 x.c - |c|^2 lies in (-2^24, 2^24) for int8 vectors up to d = 256
-
-// accumulator register r of lane half g holds tile row 8*(r/4) + 4*g + r%4
-__host__ __device__ inline uint32_t tile_row(uint32_t r, uint32_t g) { return 8 * (r / 4) + 4 * g + (r % 4); }
 
 // ---------------------------------------------------------------------------
 // Centroids in MFMA operand order, [tiles][KS][64 lanes][16 B] (tile = 32 centroids, rows past K
@@ -33,8 +27,6 @@ __host__ __device__ inline uint32_t tile_row(uint32_t r, uint32_t g) { return 8 
 // so that shifting the top bit, or the top five, of W into an accumulator (one v_alignbit) gives the row's value, or the key
 // 16 * value + 15 - r that decides ties within a tile.  A lane's largest h bounds its largest value (<= 2 h + 1): most tiles
 // are dismissed by a max over the raw accumulators, without building any key.
-constexpr int32_t FILTER_PAD_INIT = -(1 << 23);
-
 // One thread per row for the constants (its bytes in 16-byte loads), then one per 16-byte fragment for the copy: 16 384
 // centroids of 128 bytes 242 -> 5 us (one thread took 16 rows byte by byte before).
 __global__ __launch_bounds__(256) void filter_prep_kernel(const int8_t* __restrict__ Cn, uint32_t K, uint32_t d, int8_t* __restrict__ Cp,
@@ -102,28 +94,36 @@ __device__ __forceinline__ void list_insert(int64_t (&best)[P], int64_t x) {
     }
 }
 
-__device__ __forceinline__ int32_t max3(int32_t a, int32_t b, int32_t c) {  // one v_max3_i32
-    const int32_t ab = a > b ? a : b;
-    return ab > c ? ab : c;
-}
-
-__device__ __forceinline__ int32_t med3_i32(int32_t x, int32_t y, int32_t z) {
-    int32_t r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
-    return r;
-}
-
 // Waves per SIMD that the registers leave room for: 32*NT vectors as fragments (4*KS*NT), two accumulator sets, a tile's constants
 constexpr int gemm_min_waves(int KS, int NT, int MODE) { return KS >= 8 ? 2 : KS * NT >= 8 || MODE > 1 ? 3 : 4; }
 
-template <int KS, int NT, int MODE>
+// What an assignment by groups (filter_groups.hip) leaves to the kernels that compare with every centroid: the vectors of its list, or all of
+// them where the groups do not pay.  Two launches share it, whichever suits the number that is known on the device only: one takes up to
+// `few` vectors, one more than that; the other ends at once.
+struct Rest {
+    const GroupCtl* ctl;   // nullptr: all n vectors, no list
+    const uint32_t* list;
+    uint32_t few;
+};
+// The vectors to do; false: none for this launch.  list becomes nullptr where it is not to be used.
+__device__ __forceinline__ bool rest_of(Rest& rest, uint32_t K, bool many, uint64_t& n) {
+    const GroupCtl c = *rest.ctl;
+    if (groups_pay(c, K)) n = c.rest;
+    else rest.list = nullptr;
+    return n != 0 && (n > rest.few) == many;
+}
+
+template <int KS, int NT, int MODE, bool REST = false>
 __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm_kernel(const int8_t* __restrict__ X, uint64_t n,
                                                           const v4i* __restrict__ Cp, const v4i* __restrict__ W,
                                                           uint32_t tiles, uint32_t K, uint32_t tiles_per_range,
                                                           uint32_t* __restrict__ assign, int32_t* __restrict__ out,
-                                                          int64_t* __restrict__ lists, uint32_t zero_words) {
+                                                          int64_t* __restrict__ lists, uint32_t zero_words, Rest rest) {
     constexpr int D = KS * 32;
     constexpr int P = MODE > 0 ? MODE : 1;
+    if constexpr (REST) {
+        if (!rest_of(rest, K, true, n) || (uint64_t)blockIdx.x * (128 * NT) >= n) return;   // the same for the whole workgroup
+    }
     // list modes do not write `assign`: there it names zero_words words that the first workgroup clears for the kernel
     // that follows (the counting kernel's list lengths), which saves a launch on the single-query path
     if constexpr (MODE > 0) {
@@ -151,6 +151,7 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
     for (int nt = 0; nt < NT; ++nt) {
         uint64_t v = v0 + nt * 32 + col;
         if (v >= n) v = n - 1;
+        if (REST && rest.list) v = rest.list[v];
         const v4i* src = (const v4i*)(X + v * D + g * 16);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) b[nt][ks] = src[ks * 2];
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
             uint32_t oc = (uint32_t)__shfl_xor((int)c, 32, 64);
             if (oval > val || (oval == val && oc < c)) c = oc;
             const uint64_t v = v0 + nt * 32 + col;
-            if (g == 0 && v < n) assign[v] = c;
+            if (g == 0 && v < n) assign[REST && rest.list ? rest.list[v] : v] = c;
         }
     } else if constexpr (MODE > 0) {
 #pragma unroll
@@ -333,11 +334,15 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
 // registers, the next tile on its way while one is multiplied: a tile has one reader in the workgroup, so LDS would bring
 // nothing.  No barrier until the waves' winners meet.  Bound: L2 to registers (the centroids once per 32*NT vectors).
 // A k-means round of 12 000 vectors, 16 384 centroids, d = 128: 461 -> 177 us.
-template <int KS, int NT, int WAVES>
+template <int KS, int NT, int WAVES, bool REST = false>
 __global__ __launch_bounds__(WAVES * 64) void filter_assign_few_kernel(const int8_t* __restrict__ X, uint64_t n,
                                                                                 const v4i* __restrict__ Cp, const v4i* __restrict__ W,
-                                                                                uint32_t tiles, uint32_t* __restrict__ assign) {
+                                                                                uint32_t tiles, uint32_t K, uint32_t* __restrict__ assign,
+                                                                                Rest rest) {
     constexpr int D = KS * 32;
+    if constexpr (REST) {
+        if (!rest_of(rest, K, false, n) || (uint64_t)blockIdx.x * (32 * NT) >= n) return;   // the same for the whole workgroup
+    }
     __shared__ int32_t s_val[WAVES][32 * NT];
     __shared__ uint32_t s_id[WAVES][32 * NT];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -348,6 +353,7 @@ __global__ __launch_bounds__(WAVES * 64) void filter_assign_few_kernel(const int
     for (int nt = 0; nt < NT; ++nt) {
         uint64_t v = v0 + nt * 32 + col;
         if (v >= n) v = n - 1;
+        if (REST && rest.list) v = rest.list[v];
         const v4i* src = (const v4i*)(X + v * D + g * 16);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) b[nt][ks] = src[ks * 2];
@@ -423,7 +429,7 @@ __global__ __launch_bounds__(WAVES * 64) void filter_assign_few_kernel(const int
                 c = oc;
             }
         }
-        if (v0 + i < n) assign[v0 + i] = c;
+        if (v0 + i < n) assign[REST && rest.list ? rest.list[v0 + i] : v0 + i] = c;
     }
 }
 
@@ -1133,37 +1139,73 @@ static hipError_t launch_gemm(const int8_t* X, uint64_t n, uint32_t d, uint32_t 
         return hipErrorInvalidValue;  // every range must hold at least one tile and together they cover all
     dim3 grid((unsigned)blocks, ranges), block(256);
     if (d == 64)
-        hipLaunchKernelGGL((filter_gemm_kernel<2, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words);
+        hipLaunchKernelGGL((filter_gemm_kernel<2, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words, Rest{});
     else if (d == 128)
-        hipLaunchKernelGGL((filter_gemm_kernel<4, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words);
+        hipLaunchKernelGGL((filter_gemm_kernel<4, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words, Rest{});
     else if (d == 256)
-        hipLaunchKernelGGL((filter_gemm_kernel<8, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words);
+        hipLaunchKernelGGL((filter_gemm_kernel<8, NT, MODE>), grid, block, 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K, tiles_per_range, assign, out, lists, zero_words, Rest{});
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
+// up to so many vectors the kernel whose waves split the centroids is the faster one
+static uint32_t assign_few_max(uint32_t d) { return d <= 128 ? 160000u : 80000u; }
+
+template <int KS, int NT, int WAVES, bool REST>
+static void launch_few(const int8_t* X, uint64_t n, uint32_t K, const void* Cp, const void* T2, uint32_t* assign, Rest rest, hipStream_t stream) {
+    const uint64_t most = REST && rest.few < n ? rest.few : n;   // vectors that the launch may have to do
+    hipLaunchKernelGGL((filter_assign_few_kernel<KS, NT, WAVES, REST>), dim3((unsigned)((most + 32 * NT - 1) / (32 * NT))), dim3(WAVES * 64), 0, stream, X, n,
+                       (const v4i*)Cp, (const v4i*)T2, filter_tiles(K), K, assign, rest);
+}
+
+template <int KS>
+static hipError_t launch_rest(const int8_t* X, uint64_t n, uint32_t K, const void* Cp, const void* T2, uint32_t* assign, Rest rest, hipStream_t stream) {
+    const uint64_t blocks = (n + 511) / 512;
+    if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
+    launch_few<KS, 2, KS == 8 ? 8 : 16, true>(X, n, K, Cp, T2, assign, rest, stream);
+    const uint32_t tiles = filter_tiles(K);
+    hipLaunchKernelGGL((filter_gemm_kernel<KS, 4, 0, true>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, K,
+                       tiles, assign, nullptr, nullptr, 0u, rest);
+    return hipGetLastError();
+}
+
+// Assignment by groups (filter_groups.hip) saves the more the more centroids there are to a group and the more vectors there are to pay
+// for the eight launches.  Measured where it helps, vectors around 1024 centres (time of a k-means round against the comparison with
+// every centroid, first and later rounds): d = 128, K = 4096, 500 000 vectors 0.94, 1.05; 1.5M 0.66, 0.71; K = 6000, 170 000 0.77, 0.76;
+// K = 8192, 170 000 0.67, 0.68; K = 16 384, 500 000 0.37, 0.37, 1.5M 0.26, 0.24; K = 3000, 1.5M 1.14, 1.06.  d = 64 and 256 lie on the same line in
+// n * d: 500 000 vectors, K = 6000 0.98, 0.66 and 0.55, 0.53.  Where it does not help, vectors from all directions, the launches that find
+// that out cost 40 to 60 us (130 at d = 256, K = 16 384): 500 000 vectors, d = 128, K = 8192 1.08, K = 16 384 1.05.
+bool filter_groups_pay_from(uint32_t K) { return K >= 4096; }
+bool filter_groups_try(uint64_t n, uint32_t d, uint32_t K) {
+    return filter_shape(d) && n > assign_few_max(d) && n <= 0xFFFFFFFFull && filter_groups_pay_from(K) && n >= 8ull * K &&
+           (double)n * d * (K - 3300) >= 1e11;
+}
+
 hipError_t launch_filter_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
-                                uint32_t* assign, hipStream_t stream) {
+                                uint32_t* assign, void* groups, uint32_t* list, hipStream_t stream) {
+    if (groups && list && filter_groups_try(n, d, K)) {
+        const hipError_t e = launch_group_assign(X, n, d, K, Cp, T2, groups, assign, list, stream);
+        if (e != hipSuccess) return e;
+        const Rest rest{(const GroupCtl*)groups, list, 65536};
+        if (d == 64) return launch_rest<2>(X, n, K, Cp, T2, assign, rest, stream);
+        if (d == 128) return launch_rest<4>(X, n, K, Cp, T2, assign, rest, stream);
+        return launch_rest<8>(X, n, K, Cp, T2, assign, rest, stream);
+    }
     // measured over n, K = 1024 .. 16 384: at d = 128 and 16 384 centroids 30 000 vectors 211 us per k-means round instead of
     // 455, 120 000 383 instead of 447, 250 000 655 instead of 590; at d = 256 60 000 515 instead of 702, 120 000 832 instead of 699.
     // With many vectors, where the kernel above comes near to filling the chip, it takes centroids enough to keep the waves in work:
     // d = 128, 120 000 vectors, 256 centroids 121 -> 134 us, 1024 116 -> 122, 1536 115 -> 116, 2048 120 -> 118; d = 256, 79 000 vectors, 256
     // 134 -> 149, 1536 117 -> 118, 2048 130 -> 127; d = 64 and fewer vectors are no slower at any K (60 000, d = 128, 256: 114 -> 117).
     const bool many = (d == 128 && n > 65536) || (d == 256 && n > 49152);
-    if (n && n <= (d <= 128 ? 160000u : 80000u) && (!many || K >= 1536)) {
-        const uint32_t tiles = filter_tiles(K);
+    if (n && n <= assign_few_max(d) && (!many || K >= 1536)) {
         const bool wide = n > 32 * 1024 && d <= 128;   // 128 vectors per workgroup where that still gives every CU one
-        const dim3 grid((unsigned)((n + (wide ? 127 : 63)) / (wide ? 128 : 64)));
-#define DESSERT_FEW(KS_, NT_, WV_) \
-    hipLaunchKernelGGL((filter_assign_few_kernel<KS_, NT_, WV_>), grid, dim3(WV_ * 64), 0, stream, X, n, (const v4i*)Cp, (const v4i*)T2, tiles, assign)
-        if (d == 64 && wide) DESSERT_FEW(2, 4, 8);
-        else if (d == 64) DESSERT_FEW(2, 2, 16);
-        else if (d == 128 && wide) DESSERT_FEW(4, 4, 8);
-        else if (d == 128) DESSERT_FEW(4, 2, 16);
-        else if (d == 256) DESSERT_FEW(8, 2, 8);
+        if (d == 64 && wide) launch_few<2, 4, 8, false>(X, n, K, Cp, T2, assign, Rest{}, stream);
+        else if (d == 64) launch_few<2, 2, 16, false>(X, n, K, Cp, T2, assign, Rest{}, stream);
+        else if (d == 128 && wide) launch_few<4, 4, 8, false>(X, n, K, Cp, T2, assign, Rest{}, stream);
+        else if (d == 128) launch_few<4, 2, 16, false>(X, n, K, Cp, T2, assign, Rest{}, stream);
+        else if (d == 256) launch_few<8, 2, 8, false>(X, n, K, Cp, T2, assign, Rest{}, stream);
         else return hipErrorInvalidValue;
-#undef DESSERT_FEW
         return hipGetLastError();
     }
     return launch_gemm<4, 0>(X, n, d, K, Cp, T2, 1, filter_tiles(K), assign, nullptr, nullptr, stream);

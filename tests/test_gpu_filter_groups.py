@@ -1,0 +1,103 @@
+"""Assignment by groups of centroids (large filter_build and filter_kmeans calls): the same closest centroid, bit for bit, as comparing every
+vector with every centroid, whatever the data look like; ties go to the lower centroid id."""
+import math
+
+import pytest
+import torch
+
+import paper_2210_15748_amd as dz
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def vectors(n, d, centres, g, spread=0.3):
+    v = torch.randn(n, d, generator=g, device=DEV)
+    if centres is not None:
+        v = centres[torch.randint(0, centres.shape[0], (n,), generator=g, device=DEV)] + spread / math.sqrt(d) * v
+    v = v / v.norm(dim=1, keepdim=True)
+    return (v * 127).round_().clamp_(-127, 127).to(torch.int8)
+
+
+def closest(X, C):
+    """argmin |x - c|^2, lowest id among equals.  Sums of products of int8 values stay below 2^24: exact in fp32 in any order."""
+    Ct, norm = C.float().t().contiguous(), (C.int() ** 2).sum(1)
+    ids = torch.arange(C.shape[0], device=DEV, dtype=torch.int32)
+    out = torch.empty(X.shape[0], dtype=torch.int32, device=DEV)
+    for lo in range(0, X.shape[0], 8192):
+        value = 2 * (X[lo:lo + 8192].float() @ Ct).int() - norm[None, :]
+        best = value.max(dim=1, keepdim=True).values
+        out[lo:lo + 8192] = torch.where(value == best, ids[None, :], C.shape[0]).min(dim=1).values
+    return out
+
+
+def handle(d, n):
+    ix = dz.create(d, 8, 4, proj=torch.ones(32, d, dtype=torch.int8, device=DEV))
+    lens = [64] * (n // 64) + ([n % 64] if n % 64 else [])
+    codes = torch.zeros(n, 8, dtype=torch.uint8, device=DEV)
+    off = torch.zeros(len(lens) + 1, dtype=torch.int64, device=DEV)
+    off[1:] = torch.cumsum(torch.tensor(lens, device=DEV), 0)
+    dz.attach_index(ix, codes, off, 64)
+    return ix
+
+
+# clusters: most vectors need one group.  partly: 45 % of the vectors lie where no centroid does, a list long enough for the kernel for
+# many vectors.  all directions / one point: groups are of no use (too near to each other; one group of everything).  wide: groups around
+# centroids that are their own only members, next to a few large ones; duplicates: equal centroids, in and out of order.
+KINDS = ["clusters", "partly", "all directions", "one point", "wide", "duplicates"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("d,K,n", [(128, 8192, 170_000), (64, 8223, 320_003), (256, 8200, 82_001), (128, 16_385, 200_000)])
+def test_assignment_by_groups(kind, d, K, n):
+    say(f"assignment by groups: {kind} d={d} K={K} n={n}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1000 * KINDS.index(kind) + d + K)
+    centres = torch.randn(700, d, generator=g, device=DEV) / math.sqrt(d)
+    X = vectors(n, d, None if kind == "all directions" else centres, g)
+    pick = torch.randint(0, n, (K,), generator=g, device=DEV)
+    C = X[pick].clone()
+    if kind == "partly":
+        X[: int(0.45 * n)] = vectors(int(0.45 * n), d, torch.randn(900, d, generator=g, device=DEV) / math.sqrt(d), g)
+        X = X[torch.randperm(n, generator=g, device=DEV)].contiguous()
+    elif kind == "one point":
+        C[:] = C[0]
+        C[K // 2] = X[5]
+    elif kind == "wide":
+        C[K // 2:] = vectors(K - K // 2, d, centres[:5], g, spread=0.6)
+        C[: K // 16] = vectors(K // 16, d, None, g)
+    elif kind == "duplicates":
+        C[K // 2:] = C[torch.randint(0, K // 2, (K - K // 2,), generator=g, device=DEV)]
+    ix = handle(d, n)
+    assign, starts, docs = dz.filter_build(ix, C, X)
+    want = closest(X, C)
+    assert torch.equal(assign, want), f"{int((assign != want).sum())} of {n} vectors"
+    # the buckets are made from it, over the array that held the list of vectors left over
+    pairs = torch.unique(assign.long() * (n // 64 + 1) + torch.arange(n, device=DEV) // 64)
+    assert torch.equal(torch.bincount(pairs // (n // 64 + 1), minlength=K), starts[1:].long() - starts[:-1].long())
+    total = int(starts[-1])
+    got = torch.repeat_interleave(torch.arange(K, device=DEV), starts[1:].long() - starts[:-1].long()) * (n // 64 + 1) + docs[:total].long()
+    assert torch.equal(torch.sort(got).values, pairs)
+
+
+@pytest.mark.parametrize("d,K,n", [(128, 8192, 170_000), (64, 8223, 320_003), (256, 8200, 82_001)])
+def test_kmeans_with_and_without_room_for_groups(d, K, n):
+    say(f"k-means by groups: d={d} K={K} n={n}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + K)
+    X = vectors(n, d, torch.randn(500, d, generator=g, device=DEV) / math.sqrt(d), g)
+    start = X[torch.randint(0, n, (K,), generator=g, device=DEV)].contiguous()
+    ix = handle(d, 64)
+    full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
+    assert full > 4 * n + K * d, "the workspace has no room for groups: these sizes do not reach them"
+    got = []
+    for nbytes in (full, full - 256):   # a workspace without room for the groups is accepted
+        ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+        cent = start.clone()
+        assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 3, ws.data_ptr(), nbytes) == dz.OK
+        got.append(cent)
+    assert torch.equal(got[0], got[1])
