@@ -435,8 +435,9 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     sa.L = ix->cfg.L; sa.C = ix->cfg.C; sa.code_bytes = code_width(ix->cfg);
     sa.qcodes = qcodes; sa.q_off = d_q_off; sa.q_uniform = bt.q_uniform; sa.n_queries = B; sa.max_q_len = bt.max_q_len;
     sa.chunks = bt.chunks;
-    // DESSERT_SCORE_MASKLUT stays with the single-chunk forms (the cross-check)
+    // DESSERT_SCORE_MASKLUT stays with single chunks and at most two sets per workgroup (the cross-check)
     sa.chunk_pairs = ix->score_algo == DESSERT_SCORE_AUTO ? bt.chunk_pairs : 0;
+    sa.four_sets = ix->score_algo == DESSERT_SCORE_AUTO;
     sa.cand_ids = cand_ids; sa.cand_off = cand_ids ? d_cand_off : nullptr; sa.cand_uniform = cand_ids ? bt.cand_uniform : 0;
     sa.max_scored = bt.max_scored; sa.total_scored = bt.total_scored; sa.n_vectors = ix->n_vectors; sa.scores = scores;
     sa.remap = ix->transform != DESSERT_SCORE_RAW_COUNTS ? ix->remap : nullptr;

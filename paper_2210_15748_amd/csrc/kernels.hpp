@@ -67,6 +67,7 @@ struct ScoreArgs {
     uint32_t n_queries;
     uint32_t max_q_len;
     uint64_t chunks, chunk_pairs;  // chunks of 32 query vectors in all sets together, and pairs of chunks of one set (launch heuristics only)
+    bool four_sets;             // workgroups may take four query sets
     const uint32_t* cand_ids;   // dev or nullptr
     const uint64_t* cand_off;   // dev [B+1] (candidate mode); unused when cand_uniform != 0
     uint64_t cand_uniform;      // != 0: every candidate list has this many ids

@@ -210,6 +210,33 @@ __device__ inline void planes_add(uint32_t* acc, const uint32_t* b) {
     }
 }
 
+__device__ inline void full_add(uint32_t& sum, uint32_t x, uint32_t y, uint32_t& carry) {
+    const uint32_t s = sum;
+    sum = xor3(s, x, y);
+    carry = maj3(s, x, y);
+}
+template <int FROM>
+__device__ inline void ripple(uint32_t (&p)[8], uint32_t carry) {   // planes FROM.. += carry
+#pragma unroll
+    for (int i = FROM; i < 8; ++i) {
+        const uint32_t x = p[i];
+        p[i] = x ^ carry;
+        carry &= x;
+    }
+}
+__device__ inline uint32_t add4(uint32_t (&p)[8], const uint32_t* m) {   // four masks; returns the carry of weight 4
+    uint32_t c0, c1, d;
+    full_add(p[0], m[0], m[1], c0);
+    full_add(p[0], m[2], m[3], c1);
+    full_add(p[1], c0, c1, d);
+    return d;
+}
+__device__ inline uint32_t add8(uint32_t (&p)[8], const uint32_t* m) {
+    const uint32_t d0 = add4(p, m), d1 = add4(p, m + 4);
+    uint32_t e;
+    full_add(p[2], d0, d1, e);
+    return e;
+}
 template <int CTRL>
 __device__ inline uint32_t dpp_mov(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
@@ -260,24 +287,27 @@ constexpr bool masklut_rotated(int L, int CB, int CW, int W) { return (L == 64 |
 // Bytes of LDS the table takes: rows of the rotated order are 256 bytes (64 slots) also with 32 tables.
 constexpr int masklut_table_bytes(int L, int CB, int CW, int W) { return masklut_rotated(L, CB, CW, W) ? (64 << CB) * 4 : (L << CB) * 4 * W; }
 constexpr int masklut_threads(int L, int CB, int CW, int W) {
-    return (masklut_table_bytes(L, CB, CW, W) >= 32 * 1024 &&
+    return W == 4 || (masklut_table_bytes(L, CB, CW, W) >= 32 * 1024 &&
             (L <= 16 || L >= 128 || masklut_table_bytes(L, CB, CW, W) >= 64 * 1024)) ? 512 : 256;
 }
 // Waves per SIMD the register allocation must allow: the rotated form (L = 64) keeps 24 more per-lane
 // constants and would otherwise drop from 4 to 3.
 constexpr int masklut_min_waves(int L, int CB, int CW, int W, int REMAP) {
     if (L == 64 && CW == 1 && W == 1 && REMAP < 3) return 4;
+    if (W == 4) return 4;
     return 1;
 }
+constexpr int masklut_docs(int W) { return W == 4 ? 2 * (int)LUT_DOCS : (int)LUT_DOCS; }   // four sets: eight waves, see launch_masklut_t
 constexpr uint32_t LUT_BINS = 64;   // length classes for the in-block ordering
 constexpr int MASKLUT_CHUNK_PAIRS = 5;  // REMAP of the raw form over chunk pairs (see the kernel)
 
 // Per-workgroup bookkeeping, in static LDS beside the mask table.
+template <uint32_t DOCS = LUT_DOCS>
 struct LutBlockMeta {
-    uint64_t lo[LUT_DOCS];      // first code row of each document of the block
-    uint32_t m[LUT_DOCS];       // its length
-    uint32_t slot[LUT_DOCS];    // its slot within the query set's candidate list (= output position)
-    uint16_t order[LUT_DOCS];   // documents ordered longest class first
+    uint64_t lo[DOCS];          // first code row of each document of the block
+    uint32_t m[DOCS];           // its length
+    uint32_t slot[DOCS];        // its slot within the query set's candidate list (= output position)
+    uint16_t order[DOCS];       // documents ordered longest class first
     uint32_t bin[LUT_BINS];     // counting sort by length class
     uint32_t next;              // next unclaimed position in `order`
 };
@@ -360,7 +390,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     constexpr int LW = L * CW / 4;  // dwords per code row
     constexpr int STRIDE = 1 << CB;
     constexpr int P = ilog2_ceil(L + 1);  // planes needed for counts 0..L
-    constexpr int G = (W == 2 && L <= 32) ? 4 : 8;
+    constexpr int G = (W >= 2 && L <= 32) ? 4 : 8;
     constexpr int DOCS_PER_WAVE = 64 / G;
     constexpr bool MEAN = FORM >= 3;
     constexpr bool WEIGHTED = FORM == 2 || FORM == 4;
@@ -370,7 +400,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     // immediate offset of each ds_read and the only per-read address arithmetic is one shift
     constexpr int LUT_WORDS = masklut_table_bytes(L, CB, CW, W) / 4;
     __shared__ __attribute__((aligned(256))) uint32_t lut[LUT_WORDS];  // [t][h][w]; ROT: [h][pos(t)]
-    __shared__ LutBlockMeta meta;
+    __shared__ LutBlockMeta<masklut_docs(W)> meta;
 
     // Which (document block, query-set group) this workgroup takes.  When every set scores every
     // document (gy_linear != 0) the grid is linear and decoded so that the groups of one document
@@ -406,6 +436,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
         }
         max_len = q_len[w] > max_len ? q_len[w] : max_len;
     }
+    static_assert(masklut_docs(W) <= T, "a thread looks up one document");
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t sub = lane & (G - 1);  // lane within the document's group
     const uint32_t grp = lane / G;        // group within the wave
@@ -493,7 +524,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     __syncthreads();
     if (have_doc) meta.order[atomicAdd(&meta.bin[my_class], 1u)] = (uint16_t)threadIdx.x;
 
-    const uint32_t entry_shift = W == 1 ? 2 : 3;  // log2 of the bytes per table entry
+    const uint32_t entry_shift = W == 1 ? 2 : W == 2 ? 3 : 4;  // log2 of the bytes per table entry
     // ROT: lane-dependent table order (see above)
     uint32_t rot_sel[4], rot_posc[ROT ? LW : 1], rot_quarter[ROT ? LW / 4 : 1], rot_swap = 0;
     if constexpr (ROT) {
@@ -654,11 +685,88 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     }
                 }
             };
+            // The same for four sets: four tables at a time, the next four's masks on their way (all at once would take 4 * L registers).
+            // The registers of a quad of codes take the next round's once their last table is addressed.
+            auto process_four = [&](uint32_t (&dw)[LW], int32_t next_row) {
+                const char* lut_bytes = reinterpret_cast<const char*>(lut);
+                constexpr int QUAD = LW < 4 ? LW : 4;
+                const uint8_t* next_codes = doc_codes + (uint32_t)next_row * (uint32_t)(L * CW);
+                uint32_t planes[4][8], fours[4], eights[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) planes[w][p] = 0;
+                v4i e[2][4];
+                auto read = [&](int g) {
+                    uint32_t at[4];
+                    if constexpr (CW == 1) {
+                        at[0] = byte_shl<0>(dw[g], entry_shift);
+                        at[1] = byte_shl<1>(dw[g], entry_shift);
+                        at[2] = byte_shl<2>(dw[g], entry_shift);
+                        at[3] = byte_shl<3>(dw[g], entry_shift);
+                    } else {
+                        at[0] = half_shl<0>(dw[2 * g], entry_shift);
+                        at[1] = half_shl<1>(dw[2 * g], entry_shift);
+                        at[2] = half_shl<0>(dw[2 * g + 1], entry_shift);
+                        at[3] = half_shl<1>(dw[2 * g + 1], entry_shift);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) e[g & 1][t] = *(const v4i*)(lut_bytes + (4 * g + t) * STRIDE * 16 + at[t]);
+                    if ((g + 1) * CW % QUAD == 0) {
+                        const int q0 = (g + 1) * CW - QUAD;
+                        if constexpr (QUAD == 4) {
+                            const v4i v = *(const v4i*)(next_codes + q0 * 4);
+                            dw[q0] = v.x; dw[q0 + 1] = v.y; dw[q0 + 2] = v.z; dw[q0 + 3] = v.w;
+                        } else {
+                            const uint2 v = *(const uint2*)next_codes;
+                            dw[0] = v.x; dw[1] = v.y;
+                        }
+                    }
+                };
+                read(0);
+#pragma unroll
+                for (int g = 0; g < L / 4; ++g) {
+                    if (g + 1 < L / 4) read(g + 1);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        uint32_t m4[4], up;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) m4[t] = (uint32_t)e[g & 1][t][w];
+                        uint32_t carry = add4(planes[w], m4);
+                        if (g % 2 == 0) {
+                            fours[w] = carry;
+                            continue;
+                        }
+                        full_add(planes[w][2], fours[w], carry, up);
+                        if (L == 8) {
+                            planes[w][3] = up;
+                            continue;
+                        }
+                        if (g % 4 == 1) {
+                            eights[w] = up;
+                            continue;
+                        }
+                        carry = up;
+                        full_add(planes[w][3], eights[w], carry, up);
+                        if (L == 16 || g % 8 == 3) {
+                            planes[w][4] = up;
+                            continue;
+                        }
+                        planes[w][5] = planes[w][4] & up;
+                        planes[w][4] ^= up;
+                    }
+                    // keeps the additions of a group before the reads of the group after the next
+                    asm volatile("" : "+v"(planes[0][0]), "+v"(planes[1][0]), "+v"(planes[2][0]), "+v"(planes[3][0]), "+v"(planes[0][1]),
+                                 "+v"(planes[1][1]), "+v"(planes[2][1]), "+v"(planes[3][1]) : : "memory");
+                }
+#pragma unroll
+                for (int w = 0; w < 4; ++w) planes_max<P>(mx[w], planes[w]);
+            };
             // a round's G rows start on a 128-byte line of the code array (rows before the document's
             // first clamp to it), so the rows of one round are whole lines and no line is requested
             // by two rounds.  Not in the paired form: it streams the code array in order and is bound by
             // arithmetic, so it starts at the document's first row and computes no clamped rows in front
-            constexpr uint32_t ROWS_PER_LINE = W == 2 ? 1 : 128 / (L * CW) < 1 ? 1 : (128 / (L * CW) > G ? G : 128 / (L * CW));
+            constexpr uint32_t ROWS_PER_LINE = W >= 2 ? 1 : 128 / (L * CW) < 1 ? 1 : (128 / (L * CW) > G ? G : 128 / (L * CW));
             int32_t j = (int32_t)sub - (int32_t)((uint32_t)lo & (ROWS_PER_LINE - 1));  // this lane's row in the round at hand
             const int32_t j_end = (int32_t)m + (int32_t)sub;  // rounds run while j - sub < m
             auto clamped = [&](int32_t jj) { return jj < (int32_t)last_j ? jj : (int32_t)last_j; };
@@ -666,7 +774,14 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
             // DEPTH rounds of codes are in flight while a round is processed
             constexpr int DEPTH = (W == 1 && LW <= 8) ? 2 : 1;
             constexpr std::integral_constant<int, W> every{};
-            if constexpr (chunk_pairs) {   // the loop of DEPTH 1 twice: a branch inside it would part the reads of an entry's two masks
+            if constexpr (W == 4) {
+                uint32_t codes[LW];
+                load_codes(clamped(j), codes);
+                do {
+                    process_four(codes, clamped(j + G));
+                    j += G;
+                } while (__any(j < j_end));
+            } else if constexpr (chunk_pairs) {   // the loop of DEPTH 1 twice: a branch inside it would part the reads of an entry's two masks
                 auto rounds = [&](auto masks) {
                     uint32_t buf_a[LW], buf_b[LW];
                     load_codes(clamped(j), buf_a);
@@ -852,33 +967,6 @@ struct MaskanyLaunch {
     uint32_t docs_per_block, gy_linear, gz;
 };
 
-__device__ inline void full_add(uint32_t& sum, uint32_t x, uint32_t y, uint32_t& carry) {
-    const uint32_t s = sum;
-    sum = xor3(s, x, y);
-    carry = maj3(s, x, y);
-}
-template <int FROM>
-__device__ inline void ripple(uint32_t (&p)[8], uint32_t carry) {   // planes FROM.. += carry
-#pragma unroll
-    for (int i = FROM; i < 8; ++i) {
-        const uint32_t x = p[i];
-        p[i] = x ^ carry;
-        carry &= x;
-    }
-}
-__device__ inline uint32_t add4(uint32_t (&p)[8], const uint32_t* m) {   // four masks; returns the carry of weight 4
-    uint32_t c0, c1, d;
-    full_add(p[0], m[0], m[1], c0);
-    full_add(p[0], m[2], m[3], c1);
-    full_add(p[1], c0, c1, d);
-    return d;
-}
-__device__ inline uint32_t add8(uint32_t (&p)[8], const uint32_t* m) {
-    const uint32_t d0 = add4(p, m), d1 = add4(p, m + 4);
-    uint32_t e;
-    full_add(p[2], d0, d1, e);
-    return e;
-}
 __device__ inline void add16(uint32_t (&p)[8], const uint32_t* m) {
     const uint32_t e0 = add8(p, m), e1 = add8(p, m + 8);
     uint32_t f;
@@ -906,7 +994,7 @@ __device__ inline void planes_to_bytes(uint32_t (&p)[8]) {
 template <int NG, int CW, bool MEAN>
 __global__ __launch_bounds__(1024) void score_bytecmp_kernel_masks(ScoreArgs a, MaskanyLaunch ml) {
     extern __shared__ uint32_t any_lds[];   // masks [L][2^cb], then phi [L+1]
-    __shared__ LutBlockMeta meta;
+    __shared__ LutBlockMeta<> meta;
     constexpr int G = 8;                    // lanes per document
     constexpr int WG16 = 4 * CW;            // dwords of 16 codes
     const uint32_t T = blockDim.x;
@@ -1267,6 +1355,22 @@ bool score_masklut_supported(uint32_t L, uint32_t C) {
     return (L == 8 && C <= 11) || (L == 16 && C <= 10) || (L == 32 && C == 9);
 }
 
+// workgroups of the forms for one, two and four sets that a CU holds at a time
+template <int L, int CB, int CW, int W>
+static uint32_t masklut_resident() {
+    constexpr size_t PAIR_BYTES = (size_t)L * (1u << CB) * 8;
+    if constexpr (W == 1 || (W == 2 && (PAIR_BYTES <= 32 * 1024 || (L <= 32 && PAIR_BYTES <= 64 * 1024))) || (W == 4 && L <= 32 && PAIR_BYTES <= 32 * 1024)) {
+        static const uint32_t n = [] {
+            int at_a_time = 0;
+            const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&at_a_time, (const void*)score_masklut_kernel<L, CB, CW, 0, W, false>,
+                                                                              masklut_threads(L, CB, CW, W), 0);
+            return e == hipSuccess && at_a_time > 0 ? (uint32_t)at_a_time : 2u;
+        }();
+        return n;
+    }
+    return 2;
+}
+
 template <int L, int CB, int CW>
 static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
     // two query sets per workgroup when every document is scored for every set and the paired table (8 bytes per entry)
@@ -1346,6 +1450,32 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
         if (gz > chunks) gz = chunks;
         if (gz < 2) gz = 2;
     }
+    // Four query sets per workgroup where even those make a large grid: one address and one 16-byte LDS read serve 128 query vectors, a
+    // lane-operation in eleven less, and 16-byte reads of random entries conflict less (eight lanes to a pass).  A workgroup takes up to 512
+    // documents: half the tables to build, and documents that share a wave are more alike in length.  64 sets of 32 x 100 000 documents,
+    // L = 32, C = 7: 1270 -> 1200 us a search with blocks of 256 documents, 1168 with larger ones.  A pass over four
+    // sets costs 1.82 of one over two, so not where the last workgroup's sets would be missing (5, 6, 9, 10 ... sets), nor for
+    // sets of unequal numbers of chunks, where all four would wait for the longest.
+    constexpr bool FOUR_OK = L <= 32 && PAIR_BYTES <= 32 * 1024;
+    const bool four = FOUR_OK && pair && a.four_sets && !a.q_weights && a.chunks == (uint64_t)chunks * a.n_queries &&
+                      (a.n_queries + 3) / 4 * 91 <= (a.n_queries + 1) / 2 * 50 &&
+                      (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * ((a.n_queries + 3) / 4) >= 256;
+    if (four) gy = (a.n_queries + 3) / 4;
+    // Every document scored: as many documents per workgroup as make whole rounds over the chip, where the smallest blocks did (to have
+    // 4096 workgroups) or the largest, and the chip then waited for a last round that few of them fill (12.2 rounds take as long as
+    // 13).  A search over 60 000 documents for 5 sets, L = 32, C = 7 133 -> 107 us, C = 8 182 -> 114; 30 000 for 33 sets, L = 16, C = 9
+    // 300 -> 157, L = 64, C = 6 533 -> 455; 5000 for 62, L = 128, C = 6 575 -> 433.  Lists with 128 tables too (64 of 4096, C = 6 548 -> 420), other lists
+    // not: they are bound by gathered reads, which small blocks spread better, and lists of unequal length make no rounds.
+    if ((!a.cand_ids || L == 128) && gz == 1 && !cp && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= 128) {
+        // slots: of an XCD, which takes every 8th block (below)
+        const uint64_t slots = 32ull * (four ? masklut_resident<L, CB, CW, 4>() : pair ? masklut_resident<L, CB, CW, 2>() : masklut_resident<L, CB, CW, 1>());
+        const uint64_t docs_max = masklut_docs(four ? 4 : 1);
+        uint64_t rounds = ((a.max_scored + docs_max - 1) / docs_max * gy + 8 * slots - 1) / (8 * slots), most;
+        while ((most = rounds * slots / gy * 8) == 0 || (a.max_scored + most - 1) / most > docs_max) ++rounds;
+        const uint32_t docs_min = four && dpb_min < 128 ? 128 : dpb_min;
+        dpb = std::max((uint32_t)((a.max_scored + most - 1) / most), docs_min);
+        bx = (a.max_scored + dpb - 1) / dpb;
+    }
     const uint64_t gyz = (uint64_t)gy * gz;
     if (gyz > 65535) return hipErrorInvalidValue;
     if (gz > 1) {  // partial sums are added into the scores
@@ -1369,7 +1499,7 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     // the instantiation as a profiler prints it
     if (desc)
         snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, cp ? MASKLUT_CHUNK_PAIRS + remap : remap,
-                 (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
+                 four ? 4 : (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
     using Kernel = void (*)(ScoreArgs, uint32_t, uint32_t, uint32_t);
     if constexpr (CHUNK_PAIRS_OK) {
         if (cp) {
@@ -1381,6 +1511,13 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
                                            : remap == 1 ? score_masklut_kernel<L, CB, CW, CP + 1, 2, false>
                                                         : score_masklut_kernel<L, CB, CW, CP, 2, false>);
             hipLaunchKernelGGL(kern3, grid, dim3(masklut_threads(L, CB, CW, 2)), 0, stream, a, dpb, gy_linear, gz);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (FOUR_OK) {
+        if (four) {
+            const Kernel kern4 = remap == 1 ? score_masklut_kernel<L, CB, CW, 1, 4, false> : score_masklut_kernel<L, CB, CW, 0, 4, false>;
+            hipLaunchKernelGGL(kern4, grid, dim3(masklut_threads(L, CB, CW, 4)), 0, stream, a, dpb, gy_linear, 1u);
             return hipGetLastError();
         }
     }
