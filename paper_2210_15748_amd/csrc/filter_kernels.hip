@@ -789,6 +789,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
         }
     };
     uint32_t lo_l, n_l;
+    bool full = false;   // this wave has seen the queue overflow
     bounds(wave, lo_l, n_l);
     for (uint32_t i = tid; i < words; i += T) cnt[i] = 0;
     if (tid == 0) q_count = 0;
@@ -817,6 +818,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
                 hit[u] = id[u] != 0xFFFFFFFFu && local[u] < here;
                 old[u] = hit[u] ? atomicAdd(&cnt[local[u] / PER], 1u << ((local[u] % PER) * BITS)) : 0u;
             }
+            if (full) return;   // the counters will be scanned: nothing to queue any more
             uint64_t fm[U];
             uint32_t found = 0;
 #pragma unroll
@@ -828,6 +830,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
             uint32_t base = 0;
             if (lane == 0) base = atomicAdd(&q_count, found);
             base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            full = base + found > FILTER_QUEUE;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const uint32_t pos = base + (uint32_t)__builtin_popcountll(fm[u] & ((1ull << lane) - 1));
@@ -896,46 +899,52 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
         flush_tally(base_sh, hits);
         return;
     }
-    // queue overflow: scan the counters
-    uint32_t nz = 0;
-    for (uint32_t i = tid; i < words; i += T) {
-        const uint32_t x = cnt[i];
-        if (x) {
-#pragma unroll
-            for (uint32_t j = 0; j < PER; ++j) nz += ((x >> (j * BITS)) & MASK) != 0;
+    // Queue overflow: scan the counters.  A wave takes 64 consecutive words at a time and its keys leave side by side: one thread walked
+    // its words and stored key after key before, a memory request each (128 query sets of 128 probed buckets with 11 000 of a slab's
+    // 32 768 documents hit: 177 -> 114 us).
+    const uint32_t trips = (words + T - 1) / T;
+    auto word_at = [&](uint32_t trip) {
+        const uint32_t i = (trip * WAVES + wave) * 64 + lane;
+        return i < words ? cnt[i] : 0u;
+    };
+    uint32_t nz = 0;   // of the thread, then of the wave
+    for (uint32_t trip = 0; trip < trips; ++trip) {
+        const uint32_t x = word_at(trip);
+        if constexpr (W == 4) {
+            nz += x != 0;
+        } else {   // the top bit of every field that is not zero
+            constexpr uint32_t TOP = W == 1 ? 0x80808080u : 0x80008000u;
+            nz += (uint32_t)__builtin_popcount((((x & ~TOP) + ~TOP) | x) & TOP);
         }
     }
-    uint32_t incl = nz;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t y = __shfl_up(incl, o, 64);
-        if ((int)lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[wave] = incl;
+    for (int o = 32; o > 0; o >>= 1) nz += (uint32_t)__shfl_xor((int)nz, o, 64);
+    if (lane == 0) wsum[wave] = nz;
     __syncthreads();
     if (tid == 0) {
         uint32_t total = 0;
         for (int w = 0; w < (int)WAVES; ++w) total += wsum[w];
         base_sh = total ? atomicAdd(&cursor[b], total) : 0;
+        q_count = total;
     }
-    uint32_t before = 0;
-    for (uint32_t w = 0; w < wave; ++w) before += wsum[w];
+    uint32_t at = 0;
+    for (uint32_t w = 0; w < wave; ++w) at += wsum[w];
     __syncthreads();
-    KT* dst = lists + (uint64_t)b * list_stride + base_sh + before + incl - nz;
-    for (uint32_t i = tid; i < words; i += T) {
-        const uint32_t x = cnt[i];
-        if (x) {
+    KT* dst = lists + (uint64_t)b * list_stride + base_sh;
+    for (uint32_t trip = 0; trip < trips; ++trip) {
+        const uint32_t x = word_at(trip), i = (trip * WAVES + wave) * 64 + lane;
 #pragma unroll
-            for (uint32_t j = 0; j < PER; ++j) {
-                const uint32_t c = (x >> (j * BITS)) & MASK;
-                if (c) {
-                    *dst++ = (KT)make_key((int32_t)c, doc0 + i * PER + j, id_bits);
-                    tally(c);
-                }
+        for (uint32_t j = 0; j < PER; ++j) {
+            const uint32_t c = (x >> (j * BITS % 32)) & MASK;
+            const uint64_t some = __ballot(c != 0);
+            if (c) {
+                dst[at + (uint32_t)__builtin_popcountll(some & ((1ull << lane) - 1))] = (KT)make_key((int32_t)c, doc0 + i * PER + j, id_bits);
+                tally(c);
             }
+            at += (uint32_t)__builtin_popcountll(some);
         }
     }
-    flush_tally(base_sh, hits);  // as many keys as first hits
+    flush_tally(base_sh, q_count);
 }
 
 // ---------------------------------------------------------------------------
