@@ -166,11 +166,15 @@ bool is_f16_mfma(const dessert_config_t& c) {
 }
 bool use_mfma(const dessert_index* ix) { return ix->proj_mfma && (is_i8_mfma(ix->cfg) || is_f16_mfma(ix->cfg)); }
 
-// fused / fused_done: a candidate grouping to carry along in the hashing launch when that is the int8 MFMA kernel;
-// *fused_done tells whether it was.
+// Which kernel run_hash would take for vectors X and codes at these addresses carries riders along: the fixed-shape int8 MFMA kernel.
+bool hash_carries(const dessert_index* ix, const void* X, const void* codes) {
+    if (ix->cfg.dtype != DESSERT_I8 || !use_mfma(ix) || (uintptr_t)X % 16 || (uintptr_t)codes % 16) return false;
+    return ix->hash_algo == DESSERT_HASH_MFMA || (ix->hash_algo == DESSERT_HASH_AUTO && !ix->proj_any);
+}
+
+// riders: for hash_carries() only
 dessert_status_t run_hash(const dessert_index* ix, const void* X, uint64_t n, uint8_t* codes,
-                          const CandOrderArgs* fused = nullptr, bool* fused_done = nullptr) {
-    if (fused_done) *fused_done = false;
+                          const HashRiders* riders = nullptr) {
     if (n == 0) return DESSERT_OK;
     int algo = ix->hash_algo;
     bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)codes % 16 == 0);
@@ -190,10 +194,8 @@ dessert_status_t run_hash(const dessert_index* ix, const void* X, uint64_t n, ui
                                         "L in {8,16,32})");
         if (!aligned) return fail(DESSERT_EINVAL, "MFMA hashing needs 16-byte aligned vectors and codes");
         if (ix->cfg.dtype == DESSERT_I8) {
-            const bool fuse = fused && fused->ranges <= hash_mfma_fused_ranges(ix->cfg.d, ix->cfg.L, ix->cfg.C);
             HIP_TRY(launch_hash_mfma_i8((const int8_t*)X, n, ix->cfg.d, ix->cfg.L, ix->cfg.C, ix->proj_mfma, codes,
-                                        fuse ? fused : nullptr, ix->stream));
-            if (fuse && fused_done) *fused_done = true;
+                                        riders && riders->any() ? riders : nullptr, ix->stream));
         }
         else
             HIP_TRY(launch_hash_mfma_f16(X, n, ix->cfg.d, ix->cfg.L, ix->cfg.C, ix->proj_mfma, codes, ix->stream));
@@ -352,10 +354,11 @@ bool stream_capturing(const dessert_index* ix) {
 }
 
 // Shared body of dessert_search (k > 0), dessert_scores (k == 0) and dessert_search_noalloc, after the batch has
-// been checked.  cand_off: host offsets, read only when the candidate lists have unequal lengths.
+// been checked.  cand_off: host offsets, read only when the candidate lists have unequal lengths.  hashed: the query codes are in the
+// workspace already, and the candidates are not to be grouped.
 dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_vectors, uint32_t B,
                              const uint32_t* cand_ids, const uint64_t* cand_off, uint32_t k, void* workspace,
-                             size_t workspace_bytes, int32_t* scores_out, uint32_t* out_ids, int32_t* out_scores) {
+                             size_t workspace_bytes, int32_t* scores_out, uint32_t* out_ids, int32_t* out_scores, bool hashed = false) {
     dessert_status_t st = DESSERT_OK;
     if (B == 0) return DESSERT_OK;
     if (ix->transform != DESSERT_SCORE_RAW_COUNTS && bt.max_q_len > 16383)
@@ -430,7 +433,7 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
         ms.pending = true;
     }
 
-    ScoreArgs sa{};
+    ScoreBatch sa{};
     sa.codes = ix->codes; sa.offsets = ix->offsets; sa.n_docs = ix->n_docs;
     sa.L = ix->cfg.L; sa.C = ix->cfg.C; sa.code_bytes = code_width(ix->cfg);
     sa.qcodes = qcodes; sa.q_off = d_q_off; sa.q_uniform = bt.q_uniform; sa.n_queries = B; sa.max_q_len = bt.max_q_len;
@@ -461,18 +464,36 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     // grouped by document id range (with fewer than 8 lists the one workgroup per list of the grouping costs more
     // than the scoring gains).  The grouping rides in the hashing launch when that is the int8 MFMA kernel.
     CandOrderArgs oa{};
-    bool grouping = (any_tables || (algo == DESSERT_SCORE_MASKLUT && score_masklut_supported(ix->cfg.L, ix->cfg.C))) &&
+    bool grouping = !hashed && (any_tables || (algo == DESSERT_SCORE_MASKLUT && score_masklut_supported(ix->cfg.L, ix->cfg.C))) &&
                     cand_ids && B >= 8 && bt.max_scored >= score_order_min() && order_space(ix, B, bt.total_scored);
     if (grouping) {
         const uint32_t fused_ranges = hash_mfma_fused_ranges(ix->cfg.d, ix->cfg.L, ix->cfg.C);
         grouping = cand_order_plan(cand_ids, sa.cand_off, sa.cand_uniform, B, bt.max_scored, ix->n_docs,
                                    fused_ranges >= 32 ? fused_ranges : 4096, (uint32_t*)(ws + w.order), &oa);
     }
-    bool grouped = false;
-    st = run_hash(ix, q_vectors, bt.total_q, qcodes, grouping ? &oa : nullptr, &grouped);
-    if (st != DESSERT_OK) return st;
-    if (grouping && !grouped) HIP_TRY(launch_cand_order(oa, ix->stream));
     if (grouping) sa.order = oa.order;
+    if (!hashed) {
+        HashRiders riders{};
+        const bool carries = bt.total_q && hash_carries(ix, q_vectors, qcodes);
+        const bool carry_order = carries && grouping && oa.ranges <= hash_mfma_fused_ranges(ix->cfg.d, ix->cfg.L, ix->cfg.C);
+        if (carry_order) riders.order = oa;
+        if (carries && !(sa.sigma_mean && algo == DESSERT_SCORE_MASKLUT && !mean_on_masklut)) {   // scores that partial sums are added to
+            bool adds = false;
+            if (algo == DESSERT_SCORE_MASKLUT && score_masklut_supported(ix->cfg.L, ix->cfg.C))
+                HIP_TRY(launch_score_masklut(sa, ix->stream, nullptr, 0, &adds));
+            else if (any_tables)
+                HIP_TRY(launch_score_maskany(sa, ix->stream, nullptr, 0, &adds));
+            const uint64_t slots = cand_ids ? bt.total_scored : (uint64_t)B * ix->n_docs;
+            if (adds && slots <= (1u << 20)) {
+                riders.zero = scores;
+                riders.zero_words = slots;
+                sa.zeroed = true;
+            }
+        }
+        st = run_hash(ix, q_vectors, bt.total_q, qcodes, &riders);
+        if (st != DESSERT_OK) return st;
+        if (grouping && !carry_order) HIP_TRY(launch_cand_order(oa, ix->stream));
+    }
     if (timed) { HIP_TRY(hipEventRecord(tsp->ev[1], ix->stream)); tsp->hash = true; }
     if (algo == DESSERT_SCORE_MASKLUT) {
         if (sa.sigma_mean && !mean_on_masklut)
@@ -1029,7 +1050,8 @@ struct FilterWorkspace {
 // At most this many query sets in a call: the list selection runs in its two-launch form (launch_topk_lists)
 constexpr uint32_t FILTER_FEW_LISTS = 64;
 // max_q: vectors of the longest query set
-FilterWorkspace carve_filter(const dessert_index* ix, uint32_t B, uint64_t total_q, uint32_t max_q, uint32_t probe) {
+// wide_rows: see filter_hist_plan; a workspace without room for them is accepted
+FilterWorkspace carve_filter(const dessert_index* ix, uint32_t B, uint64_t total_q, uint32_t max_q, uint32_t probe, bool wide_rows = true) {
     FilterWorkspace w{};
     size_t p = 0;
     // probe selection: per-range lists for small probe counts, else the full distance matrix
@@ -1037,7 +1059,7 @@ FilterWorkspace carve_filter(const dessert_index* ix, uint32_t B, uint64_t total
     w.dist = p;      p += align_up(pl.ranges ? pl.list_bytes : (size_t)total_q * filter_tiles(ix->f_K) * 32 * 4, 256);
     w.probe_ids = p; p += align_up((size_t)total_q * probe * 4, 256);
     w.q_off = p;     p += align_up(((size_t)B + 1) * 4, 256);
-    w.cursor = p;    p += align_up(filter_hist_plan(B, max_q * probe, ix->n_docs, ix->f_sub).words * 4, 256);  // list lengths + count histograms
+    w.cursor = p;    p += align_up(filter_hist_plan(B, max_q * probe, ix->n_docs, ix->f_sub, wide_rows).words * 4, 256);  // list lengths + count histograms
     w.emit_plan = p; p += align_up((size_t)FILTER_FEW_LISTS * TOPK_LISTS_EMIT_WORDS * 4, 256);
     // a query set hits at most (its vectors * probe) buckets of at most f_max_bucket documents each
     uint64_t hit = (uint64_t)max_q * probe * ix->f_max_bucket;
@@ -1057,11 +1079,12 @@ size_t dessert_filter_workspace_bytes(const dessert_index_t* ix, uint32_t n_quer
 
 namespace {
 // Body of dessert_filter_query.  ordered = false: the filter_k documents of a query set are written in no particular
-// order (dessert_filter_search only needs the set).
+// order (dessert_filter_search only needs the set).  qcodes: nullptr, or where to hash the query vectors to on the way (hash_carries): the
+// join of the probe lists rides in that launch.
 dessert_status_t filter_query_impl(const dessert_index_t* cix, const void* q_vectors_dev,
                                    const uint32_t* q_lengths_host, uint32_t n_queries, uint32_t filter_probe,
                                    uint32_t filter_k, void* workspace_dev, size_t workspace_bytes,
-                                   uint32_t* out_ids_dev, int32_t* out_counts_dev, bool ordered) {
+                                   uint32_t* out_ids_dev, int32_t* out_counts_dev, bool ordered, uint8_t* qcodes = nullptr) {
     dessert_index* ix = const_cast<dessert_index*>(cix);
     if (!ix) return fail(DESSERT_EINVAL, "index is NULL");
     if (!ix->f_built) return fail(DESSERT_ESTATE, "dessert_filter_build has not been called");
@@ -1087,6 +1110,8 @@ dessert_status_t filter_query_impl(const dessert_index_t* cix, const void* q_vec
     const uint64_t total_q = q_off[n_queries];
     if ((uint64_t)max_q * filter_probe > 0x7FFFFFFEull) return fail(DESSERT_EINVAL, "count range too large");
     FilterWorkspace w = carve_filter(ix, n_queries, total_q, max_q, filter_probe);
+    const bool wide_rows = workspace_bytes >= w.total;
+    if (!wide_rows) w = carve_filter(ix, n_queries, total_q, max_q, filter_probe, false);
     if (workspace_bytes < w.total)
         return fail(DESSERT_EINVAL, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, w.total);
     DeviceGuard guard(ix->cfg.device);
@@ -1104,22 +1129,32 @@ dessert_status_t filter_query_impl(const dessert_index_t* cix, const void* q_vec
         if (st != DESSERT_OK) return st;
     }
     const FilterProbePlan pl = filter_probe_plan(total_q, ix->f_K, filter_probe);
-    const FilterHistPlan hp = filter_hist_plan(n_queries, max_q * filter_probe, ix->n_docs, ix->f_sub);
+    const FilterHistPlan hp = filter_hist_plan(n_queries, max_q * filter_probe, ix->n_docs, ix->f_sub, wide_rows);
     // A few query vectors (one query set, the unit of the paper's latency figures): the chain is bound by its launches, so
     // the probe GEMM also clears the counting kernel's list lengths: one launch fewer.
     const uint64_t zero_words = filter_count_zero_words(hp, n_queries);
     const bool gemm_clears = pl.ranges && total_q <= 512 && zero_words <= 4096;
+    HashRiders riders{};
+    if (qcodes && !pl.ranges) {
+        const dessert_status_t st = run_hash(ix, q_vectors_dev, total_q, qcodes);
+        if (st != DESSERT_OK) return st;
+    }
     if (pl.ranges) {
         HIP_TRY(launch_filter_probe_lists((const int8_t*)q_vectors_dev, total_q, ix->cfg.d, ix->f_K, ix->f_cent,
                                           ix->f_table, filter_probe, pl, (int64_t*)dist, probe_ids, ix->stream,
-                                          gemm_clears ? cursor : nullptr, gemm_clears ? (uint32_t)zero_words : 0u));
+                                          gemm_clears ? cursor : nullptr, gemm_clears ? (uint32_t)zero_words : 0u,
+                                          qcodes ? &riders.merge : nullptr));
+        if (qcodes) {
+            const dessert_status_t st = run_hash(ix, q_vectors_dev, total_q, qcodes, &riders);
+            if (st != DESSERT_OK) return st;
+        }
     } else {
         HIP_TRY(launch_filter_distances((const int8_t*)q_vectors_dev, total_q, ix->cfg.d, ix->f_K, ix->f_cent,
                                         ix->f_table, dist, ix->stream));
         HIP_TRY(launch_filter_probe(dist, total_q, ix->f_K, filter_probe, probe_ids, ix->stream));
     }
     HIP_TRY(launch_filter_count(probe_ids, total_q, filter_probe, max_q * filter_probe, d_q_off, q_uniform, n_queries,
-                                ix->f_sub_off, ix->f_sub, ix->f_bucket_docs, ix->n_docs, lists, w.list_stride, cursor,
+                                ix->f_sub_off, ix->f_sub, ix->f_bucket_docs, ix->n_docs, hp, lists, w.list_stride, cursor,
                                 ix->stream, gemm_clears));
     HIP_TRY(launch_topk_lists(lists, w.list_stride, cursor, n_queries, filter_k, max_q * filter_probe,
                               ix->n_docs ? ix->n_docs - 1 : 0, (ix->n_docs && total_q) ? &hp : nullptr, out_ids_dev,
@@ -1133,10 +1168,10 @@ struct ChainWorkspace {
     size_t filter, filter_bytes, ids, counts, search, search_bytes, total;
 };
 ChainWorkspace carve_chain(const dessert_index* ix, uint32_t B, uint64_t total_q, uint32_t max_q, uint32_t probe,
-                           uint32_t filter_k, uint32_t k) {
+                           uint32_t filter_k, uint32_t k, bool wide_rows = true) {
     ChainWorkspace w{};
     size_t p = 0;
-    w.filter_bytes = carve_filter(ix, B, total_q, max_q, probe).total;
+    w.filter_bytes = carve_filter(ix, B, total_q, max_q, probe, wide_rows).total;
     w.filter = p;  p += align_up(w.filter_bytes, 256);
     w.ids = p;     p += align_up((size_t)B * filter_k * 4, 256);
     w.counts = p;  p += align_up((size_t)B * filter_k * 4, 256);
@@ -1181,14 +1216,20 @@ dessert_status_t dessert_filter_search(const dessert_index_t* ix, const void* q_
         total_q += q_lengths_host[b];
         if (q_lengths_host[b] > max_q) max_q = q_lengths_host[b];
     }
-    const ChainWorkspace w = carve_chain(ix, n_queries, total_q, max_q, filter_probe, filter_k, k);
+    ChainWorkspace w = carve_chain(ix, n_queries, total_q, max_q, filter_probe, filter_k, k);
+    if (workspace_bytes < w.total) w = carve_chain(ix, n_queries, total_q, max_q, filter_probe, filter_k, k, false);
     if (workspace_bytes < w.total)
         return fail(DESSERT_EINVAL, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, w.total);
     char* ws = (char*)workspace_dev;
     uint32_t* cand = (uint32_t*)(ws + w.ids);
+    // Few or short lists are not grouped by range of document id (search_impl), and the query vectors can be hashed while the probe lists
+    // are joined: a launch less.  (Otherwise the hashing launch, after the filter, carries the grouping.)
+    const Workspace sw = carve(ix, n_queries, total_q, (uint64_t)n_queries * filter_k, filter_k, k, true);
+    uint8_t* qcodes = (uint8_t*)ws + w.search + sw.qcodes;
+    const bool hash_early = (n_queries < 8 || filter_k < score_order_min()) && hash_carries(ix, q_vectors_dev, qcodes);
     // the candidates go straight into the scoring, which does not care about their order: the filter skips its sort
     dessert_status_t st = filter_query_impl(ix, q_vectors_dev, q_lengths_host, n_queries, filter_probe, filter_k, ws + w.filter,
-                                            w.filter_bytes, cand, (int32_t*)(ws + w.counts), false);
+                                            w.filter_bytes, cand, (int32_t*)(ws + w.counts), false, hash_early ? qcodes : nullptr);
     if (st != DESSERT_OK) return st;
     // lists of equal length filter_k (unused slots hold 0xFFFFFFFF, which the scoring marks -1 and the top-k skips)
     Batch bt;
@@ -1197,7 +1238,7 @@ dessert_status_t dessert_filter_search(const dessert_index_t* ix, const void* q_
     bt.max_scored = bt.cand_uniform = filter_k;
     bt.total_scored = (uint64_t)n_queries * filter_k;
     return search_impl(const_cast<dessert_index*>(ix), bt, q_vectors_dev, n_queries, cand, nullptr, k, ws + w.search,
-                       w.search_bytes, nullptr, out_ids_dev, out_scores_dev);
+                       w.search_bytes, nullptr, out_ids_dev, out_scores_dev, hash_early);
 }
 
 dessert_status_t dessert_enable_timing(dessert_index_t* ix, int enable) {

@@ -6,6 +6,7 @@
 // |x|^2 is common to all centroids, argmin_k |x - c_k|^2 = argmax_k (2 x.c_k - |c_k|^2): the
 // dense part is an int8 GEMM (vectors x centroids) on v_mfma_i32_32x32x32_i8, exact in int32.
 #include "filter_common.hpp"
+#include "hash_riders.hpp"
 #include "kernels.hpp"
 #include "topk_select.hpp"
 
@@ -81,19 +82,6 @@ __global__ __launch_bounds__(256) void filter_prep_kernel(const int8_t* __restri
 // waves the d = 128 build of MODE 0 spills three registers, 16 bytes of scratch per lane; the figures are with them.)  4.2M vectors x
 // 16 384 centroids, d = 128: 8.7 -> 7.4 ms = 2.4 POP/s, the share of nominal that a large bf16 matrix product reaches here.
 // Four probes of 4096 vectors in 32 768 centroids 116 -> 54 us (32-bit sorted keys; 64-bit list inserts per row before).
-constexpr int64_t LIST_EMPTY = INT64_MIN;
-
-template <int P>
-__device__ __forceinline__ void list_insert(int64_t (&best)[P], int64_t x) {
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        const bool gt = x > best[i];
-        const int64_t lo = gt ? best[i] : x;
-        best[i] = gt ? x : best[i];
-        x = lo;
-    }
-}
-
 // Waves per SIMD that the registers leave room for: 32*NT vectors as fragments (4*KS*NT), two accumulator sets, a tile's constants
 constexpr int gemm_min_waves(int KS, int NT, int MODE) { return KS >= 8 ? 2 : KS * NT >= 8 || MODE > 1 ? 3 : 4; }
 
@@ -433,65 +421,11 @@ __global__ __launch_bounds__(WAVES * 64) void filter_assign_few_kernel(const int
     }
 }
 
-// one probe per vector: one wave per vector, lanes stride over its per_vec entries, wave maximum
-__global__ __launch_bounds__(256) void filter_merge1_kernel(const int64_t* __restrict__ lists, uint64_t n,
-                                                            uint32_t per_vec, uint32_t* __restrict__ probe_ids) {
-    const uint32_t lane = threadIdx.x & 63;
-    const uint64_t v = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (v >= n) return;
-    const int64_t* src = lists + v * per_vec;
-    int64_t best = LIST_EMPTY;
-    for (uint32_t i = lane; i < per_vec; i += 64) {
-        const int64_t e = src[i];
-        best = e > best ? e : best;
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const int64_t other = __shfl_xor((long long)best, o, 64);
-        best = other > best ? other : best;
-    }
-    if (lane == 0) probe_ids[v] = best == LIST_EMPTY ? 0xFFFFFFFFu : ~(uint32_t)best;
-}
-
-// the `probe` best entries of a vector's per_vec list entries, closest first: one wave per vector.  Lanes stride over the
-// entries and keep sorted lists of their own, then the wave's largest head is taken P times (entries differ: they end in their
-// centroid's id).  Bound: the round trips of one pass over the entries; 4096 vectors x 512 entries, 4 probes: 96 -> 7 us
-// (one thread walked a vector's entries before, uncoalesced and with 16 workgroups in all).
+// the probe lists joined in a launch of its own (hash_riders.hpp)
 template <int P>
-__global__ __launch_bounds__(256) void filter_merge_kernel(const int64_t* __restrict__ lists, uint64_t n,
-                                                           uint32_t per_vec, uint32_t probe,
-                                                           uint32_t* __restrict__ probe_ids) {
-    const uint32_t lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void filter_merge_kernel(ProbeMergeArgs a) {
     const uint64_t v = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (v >= n) return;
-    int64_t best[P];
-#pragma unroll
-    for (int i = 0; i < P; ++i) best[i] = LIST_EMPTY;
-    const int64_t* src = lists + v * per_vec;
-    constexpr uint32_t U = 4;   // loads in flight
-    for (uint32_t i = lane; i < per_vec; i += 64 * U) {
-        int64_t e[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) e[u] = i + 64 * u < per_vec ? src[i + 64 * u] : LIST_EMPTY;
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u)
-            if (e[u] > best[P - 1]) list_insert<P>(best, e[u]);
-    }
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        int64_t top = best[0];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const int64_t other = __shfl_xor((long long)top, o, 64);
-            top = other > top ? other : top;
-        }
-        if (lane == 0 && (uint32_t)i < probe) probe_ids[v * probe + i] = top == LIST_EMPTY ? 0xFFFFFFFFu : ~(uint32_t)top;
-        if (best[0] == top) {   // the lane that holds it moves up
-#pragma unroll
-            for (int j = 0; j + 1 < P; ++j) best[j] = best[j + 1];
-            best[P - 1] = LIST_EMPTY;
-        }
-    }
+    if (v < a.n) probe_merge<P>(a, v, threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------
@@ -705,10 +639,10 @@ __global__ void filter_zero_kernel(int32_t* __restrict__ p, uint64_t n) {
 // Only if the queue overflows (more than FILTER_QUEUE distinct documents of one slab hit) are the counters
 // scanned instead.
 // first-hit queue entries per workgroup (positions within the slab: QT = u16, or u32 for slabs over 65536 documents).
-// 3712: with a slab of 32768 one-byte counters and the 128-bin histogram the workgroup then needs just under 40 KB
+// 3712: with a slab of 32768 one-byte counters and the histogram below the workgroup then needs just under 40 KB
 // of LDS and four fit a CU.
 constexpr uint32_t FILTER_QUEUE = 3712;
-constexpr uint32_t FILTER_HSMALL = 128;  // bins of the per-workgroup histogram of counts
+constexpr uint32_t FILTER_HSMALL = 136;  // bins of the per-workgroup histogram of counts: room for those of 32 query vectors x 4 probes, 130
 
 template <int W, int T, typename QT, typename KT>
 __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restrict__ probe_ids, uint32_t probe,
@@ -755,7 +689,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
     // Histogram of the emitted keys' score fields (bin = count + 1) for the selection that follows.  Nearly every
     // document is hit once: a thread counts those in a register; the workgroup gathers its counts in a small LDS
     // histogram.  segs != nullptr: this workgroup's histogram and the run of the list it writes are stored as they
-    // are, hist[b][slab][bins] and segs[b][slab][2] (at most FILTER_HSMALL bins).  Else the occupied bins are added to
+    // are, hist[b][slab][bins] and segs[b][slab][2] (counts that fit FILTER_HSMALL bins).  Else the occupied bins are added to
     // the query set's histogram hist[b][bins] (a handful of global atomics per workgroup; one per key made this kernel
     // four times slower: they all go to the same few addresses).
     __shared__ uint32_t hsmall[FILTER_HSMALL];
@@ -778,7 +712,7 @@ __global__ __launch_bounds__(T) void filter_count_kernel(const uint32_t* __restr
         if (lane == 0 && ones) atomicAdd(&hsmall[2], ones);
         __syncthreads();
         if (segs) {
-            if (tid < hist_bins) my_hist[tid] = hsmall[tid];
+            for (uint32_t i = tid; i < hist_bins; i += T) my_hist[i] = i < FILTER_HSMALL ? hsmall[i] : 0;
             if (tid == 0) {
                 uint32_t* sg = segs + ((size_t)b * gridDim.x + blockIdx.x) * 2;
                 sg[0] = list_start;
@@ -1253,40 +1187,34 @@ FilterProbePlan filter_probe_plan(uint64_t n, uint32_t K, uint32_t probe) {
     return pl;
 }
 
+template <int P>
+static hipError_t launch_probe_gemm(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
+                                    const FilterProbePlan& pl, int64_t* lists, hipStream_t stream, uint32_t* zero, uint32_t zero_words) {
+    return pl.nt == 2 ? launch_gemm<2, P>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
+                      : launch_gemm<1, P>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
+}
+
 hipError_t launch_filter_probe_lists(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
                                      uint32_t probe, const FilterProbePlan& pl, int64_t* lists, uint32_t* probe_ids,
-                                     hipStream_t stream, uint32_t* zero, uint32_t zero_words) {
+                                     hipStream_t stream, uint32_t* zero, uint32_t zero_words, ProbeMergeArgs* merge) {
+    if (merge) *merge = ProbeMergeArgs{};
     if (n == 0) return hipSuccess;
     if (pl.ranges == 0 || probe > K || pl.width != list_width(probe)) return hipErrorInvalidValue;
-    hipError_t e;
-    const uint32_t per_vec = pl.ranges * 2 * pl.width;
-    const dim3 mgrid((unsigned)((n + 3) / 4)), mblock(256);
-    switch (pl.width) {
-        case 1:
-            e = pl.nt == 2 ? launch_gemm<2, 1>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
-                           : launch_gemm<1, 1>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(filter_merge1_kernel, mgrid, mblock, 0, stream, lists, n, per_vec, probe_ids);
-            break;
-        case 2:
-            e = pl.nt == 2 ? launch_gemm<2, 2>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
-                           : launch_gemm<1, 2>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(filter_merge_kernel<2>, mgrid, mblock, 0, stream, lists, n, per_vec, probe, probe_ids);
-            break;
-        case 4:
-            e = pl.nt == 2 ? launch_gemm<2, 4>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
-                           : launch_gemm<1, 4>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(filter_merge_kernel<4>, mgrid, mblock, 0, stream, lists, n, per_vec, probe, probe_ids);
-            break;
-        default:
-            e = pl.nt == 2 ? launch_gemm<2, 8>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words)
-                           : launch_gemm<1, 8>(X, n, d, K, Cp, T2, pl.ranges, pl.tiles_per_range, zero, nullptr, lists, stream, zero_words);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(filter_merge_kernel<8>, mgrid, mblock, 0, stream, lists, n, per_vec, probe, probe_ids);
-            break;
+    const hipError_t e = pl.width == 1   ? launch_probe_gemm<1>(X, n, d, K, Cp, T2, pl, lists, stream, zero, zero_words)
+                         : pl.width == 2 ? launch_probe_gemm<2>(X, n, d, K, Cp, T2, pl, lists, stream, zero, zero_words)
+                         : pl.width == 4 ? launch_probe_gemm<4>(X, n, d, K, Cp, T2, pl, lists, stream, zero, zero_words)
+                                         : launch_probe_gemm<8>(X, n, d, K, Cp, T2, pl, lists, stream, zero, zero_words);
+    if (e != hipSuccess) return e;
+    const ProbeMergeArgs args{lists, n, pl.ranges * 2 * pl.width, probe, pl.width, probe_ids};
+    if (merge) {
+        *merge = args;
+        return hipSuccess;
     }
+    const dim3 mgrid((unsigned)((n + 3) / 4)), mblock(256);
+    if (pl.width == 1) hipLaunchKernelGGL(filter_merge_kernel<1>, mgrid, mblock, 0, stream, args);
+    else if (pl.width == 2) hipLaunchKernelGGL(filter_merge_kernel<2>, mgrid, mblock, 0, stream, args);
+    else if (pl.width == 4) hipLaunchKernelGGL(filter_merge_kernel<4>, mgrid, mblock, 0, stream, args);
+    else hipLaunchKernelGGL(filter_merge_kernel<8>, mgrid, mblock, 0, stream, args);
     return hipGetLastError();
 }
 
@@ -1354,7 +1282,7 @@ static hipError_t launch_filter_count_t(dim3 grid, size_t lds, hipStream_t strea
     return hipGetLastError();
 }
 
-FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t n_docs, FilterSubPlan sp) {
+FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t n_docs, FilterSubPlan sp, bool wide_rows) {
     FilterHistPlan hp{};
     hp.counter_bytes = max_pairs <= 255 ? 1 : max_pairs <= 65535 ? 2 : 4;  // a count is at most the number of probed buckets
     // A slab is one sub-bucket range of documents when its counters fit (32768 documents: 32 KB of LDS with
@@ -1366,7 +1294,9 @@ FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t
     const uint64_t slabs = slab_docs ? (n_docs + slab_docs - 1) / slab_docs : 0;
     hp.slabs = slabs > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)slabs;
     hp.bins = n_docs ? leading_score_bins(max_pairs, n_docs - 1) : 0;
-    hp.rows = hp.bins != 0 && hp.bins <= FILTER_HSMALL && hp.slabs <= 1024;  // one thread per slab in the selection
+    // One thread per slab in the selection.  Without rows it makes a pass over the whole list per digit of the id: 128 query sets of
+    // 128 probed buckets (counts up to 128, 256 bins of which 130 occur), 180 000 keys each, 70 -> 51 us.
+    hp.rows = hp.bins != 0 && (hp.bins <= 128 || (wide_rows && hp.bins <= 256 && max_pairs + 2 <= FILTER_HSMALL)) && hp.slabs <= 1024;
     hp.hist_off = ((size_t)n_queries + 63) / 64 * 64;
     const size_t hist_words = hp.rows ? (size_t)n_queries * hp.slabs * hp.bins : (size_t)n_queries * hp.bins;
     hp.seg_off = hp.hist_off + hist_words;
@@ -1378,11 +1308,10 @@ uint64_t filter_count_zero_words(const FilterHistPlan& hp, uint32_t n_queries) {
 
 hipError_t launch_filter_count(const uint32_t* probe_ids, uint64_t total_q, uint32_t probe, uint32_t max_pairs,
                                const uint32_t* q_off, uint32_t q_uniform, uint32_t n_queries, const uint32_t* sub_off,
-                               FilterSubPlan sp, const uint32_t* bucket_docs, uint64_t n_docs, uint64_t* lists,
+                               FilterSubPlan sp, const uint32_t* bucket_docs, uint64_t n_docs, const FilterHistPlan& hp, uint64_t* lists,
                                uint64_t list_stride, uint32_t* cursor, hipStream_t stream, bool zeroed) {
     if (n_queries == 0) return hipSuccess;
     if (n_queries > 65535 || n_docs > 0xFFFFFFFEull) return hipErrorInvalidValue;
-    const FilterHistPlan hp = filter_hist_plan(n_queries, max_pairs, n_docs, sp);
     const uint32_t hist_bins = hp.bins;
     uint32_t* hist = hist_bins ? cursor + hp.hist_off : nullptr;
     uint32_t* segs = hp.rows ? cursor + hp.seg_off : nullptr;

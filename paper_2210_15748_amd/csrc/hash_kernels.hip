@@ -123,17 +123,19 @@ hipError_t launch_hash_scalar(const void* X, uint32_t dtype, uint64_t n, uint32_
 // 16-bit codes; or a matrix over 64 KB: d = 256 from 32 bytes of code row on) the tables are hashed in groups, one launch
 // per group: `codes` then points at the group's first byte of row 0, Rp at the group's matrix, and row_bytes (bytes from
 // one vector's codes to the next) is the full row.  The vectors are read once per group.
-// FUSED: the workgroups from hash_blocks on do not hash; workgroup hash_blocks + b groups candidate list b by
-// document id range (cand_order.hpp), with the LDS that holds R otherwise as its bins.
+// FUSED: the workgroups from hash_blocks on do not hash but carry out the riders (hash_riders.hpp), in the order of that struct; a grouping
+// has its bins in the LDS that holds R otherwise.
 // Threads per workgroup: a 64 KB matrix lets a CU hold two workgroups, and with four waves each the MFMA, the sign packing
 // and the loads of only two waves per SIMD do not overlap enough; eight waves share such a matrix.
 constexpr int mfma_threads(int KS, int LT) { return LT * KS * 1024 >= 64 * 1024 ? 512 : 256; }
+
+struct NoRiders {};
 
 template <int KS, int LT, int NT, bool WIDE, bool FUSED>
 __global__ __launch_bounds__(mfma_threads(KS, LT)) void hash_mfma_i8_kernel(const int8_t* __restrict__ X, uint64_t n,
                                                            const v4i* __restrict__ Rp, uint32_t cmask,
                                                            uint8_t* __restrict__ codes, uint32_t row_bytes,
-                                                           uint32_t hash_blocks, CandOrderArgs fused) {
+                                                           uint32_t hash_blocks, std::conditional_t<FUSED, HashRiders, NoRiders> riders) {
     constexpr int D = KS * 32;
     constexpr int L = LT * 4;   // bytes per code row
     constexpr int OW = LT / 2;  // output dwords per lane (half a code row)
@@ -143,7 +145,19 @@ __global__ __launch_bounds__(mfma_threads(KS, LT)) void hash_mfma_i8_kernel(cons
     if constexpr (FUSED) {
         if (blockIdx.x >= hash_blocks) {
             __shared__ uint32_t wave_sum[WAVES];
-            cand_order_body<T>(fused, blockIdx.x - hash_blocks, reinterpret_cast<uint32_t*>(sR), wave_sum);
+            uint32_t job = blockIdx.x - hash_blocks;
+            if (job < riders.order.n_lists) {
+                cand_order_body<T>(riders.order, job, reinterpret_cast<uint32_t*>(sR), wave_sum);
+                return;
+            }
+            job -= riders.order.n_lists;
+            const uint32_t zero_wgs = (uint32_t)((riders.zero_words + RIDER_ZERO_PER_WG - 1) / RIDER_ZERO_PER_WG);
+            if (job < zero_wgs) {
+                const uint64_t at = (uint64_t)job * RIDER_ZERO_PER_WG;
+                for (uint32_t i = threadIdx.x; i < RIDER_ZERO_PER_WG && at + i < riders.zero_words; i += T) riders.zero[at + i] = 0;
+                return;
+            }
+            probe_merge_any(riders.merge, (uint64_t)(job - zero_wgs) * WAVES + (threadIdx.x >> 6), threadIdx.x & 63);
             return;
         }
     }
@@ -319,7 +333,7 @@ hipError_t launch_repack_proj_i8(const int8_t* R, uint32_t d, uint32_t L, uint32
 
 template <int KS, int LT>
 static hipError_t launch_mfma_t(const int8_t* X, uint64_t n, uint32_t C, const void* Rp, uint8_t* codes, uint32_t row_bytes,
-                                const CandOrderArgs* fused, hipStream_t stream) {
+                                const HashRiders* riders, hipStream_t stream) {
     constexpr int NT = 2;
     constexpr int T = mfma_threads(KS, LT), WAVES = T / 64;
     const uint64_t n_tiles = (n + 32 * NT - 1) / (32 * NT);
@@ -329,23 +343,25 @@ static hipError_t launch_mfma_t(const int8_t* X, uint64_t n, uint32_t C, const v
     if (blocks > 16384 / WAVES) blocks = 16384 / WAVES;
     size_t lds = (size_t)LT * KS * 64 * 16;
     const uint32_t cmask = (1u << C) - 1u;
-    if (fused) {
-        if ((size_t)fused->ranges * 4 > lds || blocks + fused->n_lists > 0x7fffffffull) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)(blocks + fused->n_lists));
+    if (riders) {
+        const uint64_t jobs = riders->order.n_lists + (riders->zero_words + RIDER_ZERO_PER_WG - 1) / RIDER_ZERO_PER_WG +
+                              (riders->merge.lists ? (riders->merge.n + WAVES - 1) / WAVES : 0);
+        if ((riders->order.n_lists && (size_t)riders->order.ranges * 4 > lds) || blocks + jobs > 0x7fffffffull) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)(blocks + jobs));
         if (C <= 8)
             hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, false, true>), grid, dim3(T), lds, stream, X, n,
-                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *fused);
+                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *riders);
         else
             hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, true, true>), grid, dim3(T), lds, stream, X, n,
-                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *fused);
+                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *riders);
         return hipGetLastError();
     }
     if (C <= 8)
         hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, false, false>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
-                           n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, CandOrderArgs{});
+                           n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, NoRiders{});
     else
         hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, true, false>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
-                           n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, CandOrderArgs{});
+                           n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, NoRiders{});
     return hipGetLastError();
 }
 
@@ -359,7 +375,7 @@ uint32_t hash_mfma_fused_ranges(uint32_t d, uint32_t L, uint32_t C) {
 }
 
 hipError_t launch_hash_mfma_i8(const int8_t* X, uint64_t n, uint32_t d, uint32_t L, uint32_t C, const void* Rp,
-                               uint8_t* codes, const CandOrderArgs* fused, hipStream_t stream) {
+                               uint8_t* codes, const HashRiders* riders, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if (!hash_mfma_supported(d, L, C)) return hipErrorInvalidValue;
     const uint32_t Lg = group_tables(d, L, C), groups = L / Lg;
@@ -369,10 +385,10 @@ hipError_t launch_hash_mfma_i8(const int8_t* X, uint64_t n, uint32_t d, uint32_t
     for (uint32_t grp = 0; grp < groups; ++grp) {
         const void* Rg = (const char*)Rp + (size_t)grp * group_proj_bytes(d, Lg, C);
         uint8_t* cg = codes + (size_t)grp * Lg * code_bytes;
-        const CandOrderArgs* fg = grp == 0 ? fused : nullptr;   // the candidate grouping rides in the first launch
+        const HashRiders* rg = grp == 0 ? riders : nullptr;   // they ride in the first launch
         hipError_t e = hipErrorInvalidValue;
 #define DESSERT_MFMA_CASE(KS_, LT_) \
-    if (d == KS_ * 32 && lt == LT_) e = launch_mfma_t<KS_, LT_>(X, n, C, Rg, cg, row_bytes, fg, stream);
+    if (d == KS_ * 32 && lt == LT_) e = launch_mfma_t<KS_, LT_>(X, n, C, Rg, cg, row_bytes, rg, stream);
         DESSERT_MFMA_CASE(2, 2)
         DESSERT_MFMA_CASE(2, 4)
         DESSERT_MFMA_CASE(2, 8)

@@ -5,7 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "cand_order.hpp"
+#include "hash_riders.hpp"
 
 namespace dessert {
 
@@ -17,12 +17,11 @@ hipError_t launch_rademacher(uint64_t seed, uint32_t P, uint32_t d, int8_t* R, h
 size_t mfma_proj_bytes(uint32_t d, uint32_t L, uint32_t C);
 hipError_t launch_repack_proj_i8(const int8_t* R, uint32_t d, uint32_t L, uint32_t C, void* Rp, hipStream_t stream);
 bool hash_mfma_supported(uint32_t d, uint32_t L, uint32_t C);
-// fused: nullptr, or a candidate grouping (cand_order_plan with max_ranges = hash_mfma_fused_ranges) that extra
-// workgroups of the same launch carry out beside the hashing (a search hashes few vectors: both are short, latency-bound
-// jobs, and one launch instead of two saves a kernel boundary on the stream).
+// riders: nullptr, or jobs that extra workgroups of the same launch carry out (a grouping made by cand_order_plan with max_ranges =
+// hash_mfma_fused_ranges).
 uint32_t hash_mfma_fused_ranges(uint32_t d, uint32_t L, uint32_t C);
 hipError_t launch_hash_mfma_i8(const int8_t* X, uint64_t n, uint32_t d, uint32_t L, uint32_t C, const void* Rp,
-                               uint8_t* codes, const CandOrderArgs* fused, hipStream_t stream);
+                               uint8_t* codes, const HashRiders* riders, hipStream_t stream);
 
 // fp16 vectors x fp32 Gaussian projections on fp16 MFMA (projection matrix split hi + lo).
 size_t mfma_f16_proj_bytes(uint32_t d, uint32_t L);
@@ -55,33 +54,38 @@ hipError_t launch_read_probe(const void* buf, size_t bytes, hipStream_t stream);
 hipError_t launch_mix_probe(const void* in, void* out, size_t out_bytes, hipStream_t stream);
 
 // ---- scoring (Alg. 2: collision counts, sigma = max, A = sum) ---------------
-struct ScoreArgs {
+struct ScoreArgs {   // the kernels' argument: 8 bytes more cost ten sets x 1000 documents 0.2 of 15.6 us, 56 fewer saved as much
     const uint8_t* codes;       // [V][L] codes of code_bytes bytes each
-    uint32_t code_bytes;        // 1 (C <= 8) or 2
     const uint64_t* offsets;    // [n_docs+1]
     uint64_t n_docs;
-    uint32_t L, C;
     const uint8_t* qcodes;      // [total_q][L], same code width
     const uint32_t* q_off;      // dev [B+1]; unused when q_uniform != 0
     uint32_t q_uniform;         // != 0: every query set has this many vectors (q_off[b] = b * q_uniform)
     uint32_t n_queries;
     uint32_t max_q_len;
-    uint64_t chunks, chunk_pairs;  // chunks of 32 query vectors in all sets together, and pairs of chunks of one set (launch heuristics only)
-    bool four_sets;             // workgroups may take four query sets
+    uint32_t L;
     const uint32_t* cand_ids;   // dev or nullptr
     const uint64_t* cand_off;   // dev [B+1] (candidate mode); unused when cand_uniform != 0
     uint64_t cand_uniform;      // != 0: every candidate list has this many ids
     const uint32_t* order;      // dev [total_cand] or nullptr: per list, its slots grouped by document id range
                                 // (launch_cand_order); the mask-table kernel then takes a list's slots in that order
-    uint64_t max_scored;        // largest number of documents scored by one query set
-    uint64_t total_scored;      // all output slots (candidate mode: sum of the list lengths)
-    uint64_t n_vectors;         // vectors in the index (launch heuristics only)
     int32_t* scores;            // out: candidate mode [total_cand], else [B][n_docs]
     const uint32_t* remap;      // dev [L+1] fixed-point phi per collision count (Eq. 1, Sec. 4.1 examples), or nullptr: raw counts
+    const uint32_t* q_weights;  // dev [total_q] Q16 weights of the outer sum (Sec. 4.2), or nullptr
     uint32_t sigma_mean;        // != 0: sigma = rounded mean of remap[count] over the document's vectors (else the max)
+};
+// What the launches of the scoring kernels know besides (not a kernel argument).
+struct ScoreBatch : ScoreArgs {
+    uint32_t code_bytes;        // 1 (C <= 8) or 2
+    uint32_t C;
     uint32_t phi_identity;      // != 0: remap[count] = 65536 / L * count exactly (phi = identity and L a power of two); the
                                 // mask-table kernel then forms the mean from sums of counts
-    const uint32_t* q_weights;  // dev [total_q] Q16 weights of the outer sum (Sec. 4.2), or nullptr
+    uint64_t max_scored;        // largest number of documents scored by one query set
+    uint64_t total_scored;      // all output slots (candidate mode: sum of the list lengths)
+    uint64_t n_vectors;         // vectors in the index
+    uint64_t chunks, chunk_pairs;  // chunks of 32 query vectors in all sets together, and pairs of chunks of one set
+    bool four_sets;             // workgroups may take four query sets
+    bool zeroed;                // the scores are clear already, where the launch would clear them
 };
 // first query vector / first candidate slot of query set b (b may be n_queries: one past the end)
 __device__ inline uint32_t q_begin(const ScoreArgs& a, uint32_t b) { return a.q_uniform ? b * a.q_uniform : a.q_off[b]; }
@@ -90,7 +94,7 @@ __device__ inline uint64_t cand_begin(const ScoreArgs& a, uint32_t b) {
 }
 // desc (optional, desc_len bytes): receives the name of the kernel instantiation that was launched, spelled as a
 // profiler prints it ("" when nothing was launched).
-hipError_t launch_score_bytecmp(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
+hipError_t launch_score_bytecmp(const ScoreBatch& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
 // Candidate lists gathered from all over the code array: order[list start + p] = the slots of a list grouped by
 // range of document id (a counting sort over the leading id bits; the order inside a range is unspecified).
 // Workgroups that take the same run of positions of different lists then read neighbouring parts of the code array
@@ -110,13 +114,14 @@ hipError_t launch_check_cand_ids(const uint32_t* cand_ids, uint64_t n, uint64_t 
 bool score_masklut_supported(uint32_t L, uint32_t C);
 // longest document (in vectors) for which the mask-table kernel can form sigma = mean (32-bit numerators)
 constexpr uint64_t MASKLUT_MEAN_MAX_LEN = 65535;
-hipError_t launch_score_masklut(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
+// adds: nullptr, or only tell whether the launch adds partial sums to scores that have to be clear (nothing is launched then).
+hipError_t launch_score_masklut(const ScoreBatch& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0, bool* adds = nullptr);
 // The same method at any number of tables whose masks (4 * L * 2^C bytes) fit 128 KB of LDS, for every transform; sigma = mean
 // when score_maskany_mean_fits(longest document, largest phi).  The fixed-size kernel above is the faster one where it exists.
 bool score_maskany_supported(uint32_t L, uint32_t C);
 bool score_maskany_mean_fits(uint64_t max_len, uint32_t phi_max);
-bool score_maskany_pays(const ScoreArgs& a);   // the faster one of it and launch_score_bytecmp, as far as sizes tell
-hipError_t launch_score_maskany(const ScoreArgs& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0);
+bool score_maskany_pays(const ScoreBatch& a);   // the faster one of it and launch_score_bytecmp, as far as sizes tell
+hipError_t launch_score_maskany(const ScoreBatch& a, hipStream_t stream, char* desc = nullptr, size_t desc_len = 0, bool* adds = nullptr);
 
 // ---- candidate filter (Sec. 5 "Filtering") ---------------------------------------------
 bool filter_supported(uint32_t d);
@@ -152,9 +157,10 @@ struct FilterProbePlan {
 };
 FilterProbePlan filter_probe_plan(uint64_t n, uint32_t K, uint32_t probe);
 // zero / zero_words: words the launch also clears (nullptr / 0: none), for the kernel that follows it.
+// merge: nullptr, or where to leave what joins the lists: the caller then sees to it (HashRiders).
 hipError_t launch_filter_probe_lists(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
                                      uint32_t probe, const FilterProbePlan& plan, int64_t* lists, uint32_t* probe_ids,
-                                     hipStream_t stream, uint32_t* zero = nullptr, uint32_t zero_words = 0);
+                                     hipStream_t stream, uint32_t* zero = nullptr, uint32_t zero_words = 0, ProbeMergeArgs* merge = nullptr);
 // A bucket is stored as S sub-buckets by document range (sub-bucket s of centroid c holds the bucket's documents
 // with id >> sub_shift == s), so that a query-side workgroup that counts one range of documents reads only that
 // part of every bucket it probes.  sub_off [K*S+1] are the sub-bucket starts in bucket_docs; bucket_off[c] = sub_off[c*S].
@@ -173,7 +179,7 @@ hipError_t launch_filter_probe(const int32_t* dist, uint64_t total_q, uint32_t K
 // selection that follows skip passes over the lists (launch_topk_lists takes the same plan):
 //   rows: per (query set, slab of documents) the histogram of the slab's keys by score field [B][slabs][bins] and the
 //         slab's run within the list [B][slabs][2] (plain stores by the workgroup that owns the slab); or
-//   one histogram per query set [B][bins], added up with atomics (more than 128 bins or very many slabs); or nothing
+//   one histogram per query set [B][bins], added up with atomics (larger counts or very many slabs); or nothing
 //   (score field wider than a digit of the selection).
 struct FilterHistPlan {
     uint32_t bins;    // 0: no histogram
@@ -182,7 +188,8 @@ struct FilterHistPlan {
     bool rows;
     size_t hist_off, seg_off, words;  // in u32 words from the start of the array
 };
-FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t n_docs, FilterSubPlan sp);
+// wide_rows = false: rows up to 128 bins only, which takes less room for counts of 127 and 128.
+FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t n_docs, FilterSubPlan sp, bool wide_rows = true);
 // Per query set: one key (count, id) per document that at least one probed bucket holds, lists[b][0..cursor[b]).
 // max_pairs bounds (vectors of a query set) * probe, i.e. the largest possible count.  cursor: filter_hist_plan().words
 // u32 words (see above).
@@ -191,7 +198,7 @@ FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t
 uint64_t filter_count_zero_words(const FilterHistPlan& hp, uint32_t n_queries);
 hipError_t launch_filter_count(const uint32_t* probe_ids, uint64_t total_q, uint32_t probe, uint32_t max_pairs,
                                const uint32_t* q_off, uint32_t q_uniform, uint32_t n_queries, const uint32_t* sub_off,
-                               FilterSubPlan sp, const uint32_t* bucket_docs, uint64_t n_docs, uint64_t* lists,
+                               FilterSubPlan sp, const uint32_t* bucket_docs, uint64_t n_docs, const FilterHistPlan& hp, uint64_t* lists,
                                uint64_t list_stride, uint32_t* cursor /*out*/, hipStream_t stream, bool zeroed = false);
 
 // ---- top-k (Alg. 2 last line, k best instead of argmax) ---------------------

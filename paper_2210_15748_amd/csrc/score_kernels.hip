@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void score_bytecmp_kernel(ScoreArgs a) {
     }
 }
 
-hipError_t launch_score_bytecmp(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+hipError_t launch_score_bytecmp(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len) {
     if (desc && desc_len) desc[0] = 0;
     if (a.n_queries == 0 || a.max_scored == 0) return hipSuccess;
     if ((a.code_bytes != 1 && a.code_bytes != 2) || (a.L * a.code_bytes) % 4) return hipErrorInvalidValue;
@@ -1372,7 +1372,7 @@ static uint32_t masklut_resident() {
 }
 
 template <int L, int CB, int CW>
-static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len, bool* adds) {
     // two query sets per workgroup when every document is scored for every set and the paired table (8 bytes per entry)
     // is at most 32 KB, or 64 KB with at most 32 tables (512 threads share it then; the offsets still fit the 16-bit
     // immediate of an LDS read).  With one set per workgroup those shapes are bound by LDS: half the arithmetic per read.
@@ -1478,7 +1478,11 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     }
     const uint64_t gyz = (uint64_t)gy * gz;
     if (gyz > 65535) return hipErrorInvalidValue;
-    if (gz > 1) {  // partial sums are added into the scores
+    if (adds) {
+        *adds = gz > 1;
+        return hipSuccess;
+    }
+    if (gz > 1 && !a.zeroed) {  // partial sums are added into the scores
         const uint64_t n = a.cand_ids ? a.total_scored : (uint64_t)a.n_queries * a.n_docs;
         hipError_t e = launch_fill_zero(a.scores, n, stream);
         if (e != hipSuccess) return e;
@@ -1547,15 +1551,16 @@ static hipError_t launch_masklut_t(const ScoreArgs& a, hipStream_t stream, char*
     return hipGetLastError();
 }
 
-hipError_t launch_score_masklut(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+hipError_t launch_score_masklut(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len, bool* adds) {
     if (desc && desc_len) desc[0] = 0;
+    if (adds) *adds = false;
     if (a.n_queries == 0 || a.max_scored == 0) return hipSuccess;
     if (!score_masklut_supported(a.L, a.C) || a.code_bytes != (a.C > 8 ? 2u : 1u)) return hipErrorInvalidValue;
     // a tabulated phi of the maximum, or the mean of the counts themselves (phi = identity)
     if ((a.sigma_mean && !a.phi_identity) || (a.q_weights && !a.remap)) return hipErrorInvalidValue;
     const uint32_t cb = a.C <= 6 ? 6 : a.C;
 #define DESSERT_LUT_CASE(L_, CB_, CW_) \
-    if (a.L == L_ && cb == CB_) return launch_masklut_t<L_, CB_, CW_>(a, stream, desc, desc_len);
+    if (a.L == L_ && cb == CB_) return launch_masklut_t<L_, CB_, CW_>(a, stream, desc, desc_len, adds);
     DESSERT_LUT_CASE(8, 6, 1) DESSERT_LUT_CASE(8, 7, 1) DESSERT_LUT_CASE(8, 8, 1)
     DESSERT_LUT_CASE(16, 6, 1) DESSERT_LUT_CASE(16, 7, 1) DESSERT_LUT_CASE(16, 8, 1)
     DESSERT_LUT_CASE(32, 6, 1) DESSERT_LUT_CASE(32, 7, 1) DESSERT_LUT_CASE(32, 8, 1)
@@ -1587,7 +1592,7 @@ static uint32_t maskany_threads(size_t table) { return table <= 24 * 1024 ? 256 
 // other side 8 sets of 32 x 20 000 documents, L = 32 5040 and 147; raw counts, 64 sets of one vector x 1500 documents of
 // 120 and L = 96 888 and 350.  The rule compares estimates in ns, fitted to both kernels' times over nine (L, C), 1 to 8000 documents of
 // 1 to 3000 vectors and 1 to 64 sets of 1 to 64 (2656 pairs of times: slower by more than 10 % in 2 % of them, at worst 2.3 times).
-bool score_maskany_pays(const ScoreArgs& a) {
+bool score_maskany_pays(const ScoreBatch& a) {
     const double m = a.n_docs ? (double)((a.n_vectors + a.n_docs - 1) / a.n_docs) : 1.0;   // mean of the index, also for lists
     const double docs = (double)a.total_scored, q = a.max_q_len;
     const size_t table = ((size_t)a.L << a.C) * 4;
@@ -1604,7 +1609,7 @@ bool score_maskany_pays(const ScoreArgs& a) {
 }
 
 template <int NG, int CW>
-static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+static hipError_t launch_maskany_t(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len, bool* adds) {
     const size_t table = ((size_t)a.L << a.C) * 4, lds = table + ((size_t)a.L + 1) * 4;
     uint32_t T = maskany_threads(table);
     // a small batch: more workgroups matter more than what a CU could hold of them (2 sets x 1452 documents, 48 KB table 52.3 -> 48.7 us
@@ -1629,7 +1634,11 @@ static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char*
         gz = 1;
         gy = a.n_queries;
     }
-    if (gz > 1) {
+    if (adds) {
+        *adds = gz > 1;
+        return hipSuccess;
+    }
+    if (gz > 1 && !a.zeroed) {
         hipError_t e = launch_fill_zero(a.scores, a.cand_ids ? a.total_scored : (uint64_t)a.n_queries * a.n_docs, stream);
         if (e != hipSuccess) return e;
     }
@@ -1654,20 +1663,21 @@ static hipError_t launch_maskany_t(const ScoreArgs& a, hipStream_t stream, char*
     return hipGetLastError();
 }
 
-hipError_t launch_score_maskany(const ScoreArgs& a, hipStream_t stream, char* desc, size_t desc_len) {
+hipError_t launch_score_maskany(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len, bool* adds) {
     if (desc && desc_len) desc[0] = 0;
+    if (adds) *adds = false;
     if (a.n_queries == 0 || a.max_scored == 0) return hipSuccess;
     if (!score_maskany_supported(a.L, a.C) || a.code_bytes != (a.C > 8 ? 2u : 1u)) return hipErrorInvalidValue;
     if ((a.sigma_mean || a.q_weights) && !a.remap) return hipErrorInvalidValue;
     if (a.code_bytes == 1) {
-        if (a.L <= 16) return launch_maskany_t<1, 1>(a, stream, desc, desc_len);
-        if (a.L <= 32) return launch_maskany_t<2, 1>(a, stream, desc, desc_len);
-        if (a.L <= 64) return launch_maskany_t<4, 1>(a, stream, desc, desc_len);
-        return launch_maskany_t<8, 1>(a, stream, desc, desc_len);
+        if (a.L <= 16) return launch_maskany_t<1, 1>(a, stream, desc, desc_len, adds);
+        if (a.L <= 32) return launch_maskany_t<2, 1>(a, stream, desc, desc_len, adds);
+        if (a.L <= 64) return launch_maskany_t<4, 1>(a, stream, desc, desc_len, adds);
+        return launch_maskany_t<8, 1>(a, stream, desc, desc_len, adds);
     }
-    if (a.L <= 16) return launch_maskany_t<1, 2>(a, stream, desc, desc_len);
-    if (a.L <= 32) return launch_maskany_t<2, 2>(a, stream, desc, desc_len);
-    return launch_maskany_t<4, 2>(a, stream, desc, desc_len);   // 64 tables of 512 entries fill the largest table
+    if (a.L <= 16) return launch_maskany_t<1, 2>(a, stream, desc, desc_len, adds);
+    if (a.L <= 32) return launch_maskany_t<2, 2>(a, stream, desc, desc_len, adds);
+    return launch_maskany_t<4, 2>(a, stream, desc, desc_len, adds);   // 64 tables of 512 entries fill the largest table
 }
 
 }  // namespace dessert
