@@ -336,7 +336,8 @@ struct LutBlockMeta {
 // 5 / 6 / 7 = the forms 0 / 1 / 2 over chunk pairs (W = 2, one query set per workgroup): the two masks of an entry are those of
 // two successive chunks of the same set, for sets of more than 32 vectors: the codes are read once for 64 query vectors, with one
 // address and one 8-byte LDS read per table, and one sum is stored.  The last chunk of an odd number runs a loop that uses the first
-// masks only.  (Instantiations of their own: with the choice made at run time the forms for two sets lost 3 to 11 % where
+// masks only.  With W = 4, four successive chunks (8 tables; every entry's masks are used, those of chunks a set lacks are zero).
+// (Instantiations of their own: with the choice made at run time the forms for two sets lost 3 to 11 % where
 // documents or query sets are short, L = 64, C = 6, 16 000 documents of one vector, 64 sets of 8: 118 -> 129 us.)
 // 64 lists of 4096 of 300 000 documents, 48 vectors: L = 32, C = 7 214 -> 184 us, C = 8 253 -> 181, L = 16, C = 8 160 -> 115; 1000
 // documents of 256 vectors against 16 sets of 256, L = 8, C = 9: 68 -> 38 us (LDS-bound: half the reads).
@@ -383,14 +384,14 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
     // chunk pairs: W = 2, but both masks of an entry belong to one query set, to its chunks c and c + 1 of 32 vectors
     constexpr bool chunk_pairs = REMAP >= MASKLUT_CHUNK_PAIRS;
     constexpr int FORM = chunk_pairs ? REMAP - MASKLUT_CHUNK_PAIRS : REMAP;
-    static_assert(!chunk_pairs || (W == 2 && FORM <= 2), "chunk pairs: two masks per entry, sigma = max");
+    static_assert(!chunk_pairs || (W >= 2 && FORM <= 2), "chunk pairs: two masks per entry, sigma = max");
     const uint32_t gz = SPLIT ? gz_arg : 1u;
-    constexpr uint32_t chunk_step = chunk_pairs ? 64u : 32u;
+    constexpr uint32_t chunk_step = chunk_pairs ? 32u * W : 32u;
     constexpr int T = masklut_threads(L, CB, CW, W);
     constexpr int LW = L * CW / 4;  // dwords per code row
     constexpr int STRIDE = 1 << CB;
     constexpr int P = ilog2_ceil(L + 1);  // planes needed for counts 0..L
-    constexpr int G = (W >= 2 && L <= 32) ? 4 : 8;
+    constexpr int G = (W >= 2 && L <= 32 && !(chunk_pairs && W == 4)) ? 4 : 8;   // chunk fours: long documents
     constexpr int DOCS_PER_WAVE = 64 / G;
     constexpr bool MEAN = FORM >= 3;
     constexpr bool WEIGHTED = FORM == 2 || FORM == 4;
@@ -559,7 +560,7 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
         asm volatile("" : "+v"(rot_swap));
     }
     for (uint32_t c0 = c_first; c0 < max_len; c0 += gz * chunk_step) {  // chunks of 32 query vectors
-        const bool second = chunk_pairs && c0 < q_len[W - 1];  // false: a set's odd last chunk, the entries' first masks alone
+        const bool second = chunk_pairs && W == 2 && c0 < q_len[W - 1];  // false: a set's odd last chunk, the entries' first masks alone
         if (c0 != c_first) {  // the first chunk's table was built above
             __syncthreads();  // previous chunk's readers are done
             zero_table();
@@ -917,11 +918,11 @@ __global__ __launch_bounds__(masklut_threads(L, CB, CW, W), masklut_min_waves(L,
                     score = (int32_t)part;
                 }
                 if constexpr (chunk_pairs) {
-                    if (w == 0) {
+                    score += first_score;
+                    if (w + 1 < W) {
                         first_score = score;
                         continue;
                     }
-                    score += first_score;
                 }
                 constexpr bool one_set = W == 1 || chunk_pairs;
                 if (valid && sub == 0 && (chunk_pairs || (b0 + w < a.n_queries && c0 < q_len[w]))) {
@@ -1418,10 +1419,13 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
     while (dpb > dpb_min && ((a.max_scored + dpb - 1) / dpb) * gy < 4096) dpb /= 2;
     uint64_t bx = (a.max_scored + dpb - 1) / dpb;
     if (bx > 0x7fffffffull || a.n_queries > 65535) return hipErrorInvalidValue;
+    // transform form of the kernel: raw counts, tabulated phi of the maximum (weighted or not), mean of the counts
+    const int remap = a.sigma_mean ? (a.q_weights ? 4 : 3) : a.q_weights ? 2 : a.remap ? 1 : 0;
     // long query sets on a grid that is still small: split the 32-vector chunks over gz workgroups
     const uint32_t chunks = (a.max_q_len + 31) / 32;
     uint32_t gz = 1;
-    bool cp = false;
+    bool cp = false, cf = false;
+    constexpr bool FOUR_CHUNKS_OK = L == 8 && PAIR_BYTES <= 32 * 1024;
     if (chunk_pairs_pay && (!pair || bx * gy < 2048)) {
         // one query set per workgroup and, when that leaves the chip short of workgroups, its pairs of chunks split over gz of them.
         // Not when even that is a small grid (one short list): then single chunks split, twice the workgroups
@@ -1431,7 +1435,21 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
         while (d2 > cp_docs && ((a.max_scored + d2 - 1) / d2) * a.n_queries < 4096) d2 /= 2;
         const uint64_t bx2 = (a.max_scored + d2 - 1) / d2;
         const uint32_t units = (chunks + 1) / 2;
-        if (bx2 * a.n_queries * units * (cp_threads / 256) >= pairs_min_grid) {
+        // Chunk fours with 8 tables, for sets of equal numbers of chunks, four or more: a 16-byte entry holds four chunks' masks, and the LDS
+        // reads that bound this form conflict less.  Eight lanes to a document, since there are few of them and they are long.  1000 documents
+        // of m vectors, C = log2 m + 1, sets of m, a search: m = 256 16 sets 43 -> 38 us, 8 sets 45 -> 26; m = 128 16 sets 26 -> 20; m = 512 (C = 8)
+        // 8 sets 67 -> 58.  Not for a grid of 64 workgroups (one set, m = 512, 27 -> 35), and not where the last four would be one chunk.
+        if (FOUR_CHUNKS_OK && remap == 0 && a.four_sets && chunks >= 4 && chunks % 4 != 1 && a.chunks == (uint64_t)chunks * a.n_queries &&
+            mean_len >= 64 && ((a.max_scored + 63) / 64) * a.n_queries * ((chunks + 3) / 4) >= 100) {
+            cf = true;
+            pair = false;
+            const uint32_t fours = (chunks + 3) / 4;
+            dpb = LUT_DOCS;
+            while (dpb > 64 && ((a.max_scored + dpb - 1) / dpb) * a.n_queries < 2048) dpb /= 2;
+            bx = (a.max_scored + dpb - 1) / dpb;
+            gy = a.n_queries;
+            if (fours > 1 && bx * gy < 1024) gz = std::min(fours, (uint32_t)((1024 + bx * gy - 1) / (bx * gy)));
+        } else if (bx2 * a.n_queries * units * (cp_threads / 256) >= pairs_min_grid) {
             cp = true;
             pair = false;
             dpb = d2;
@@ -1443,7 +1461,7 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
             }
         }
     }
-    if (!cp && chunks > 1 && bx * gy < 2048) {
+    if (!cp && !cf && chunks > 1 && bx * gy < 2048) {
         pair = false;  // single chunks of one query set per workgroup
         gy = a.n_queries;
         gz = (uint32_t)((2048 + bx * gy - 1) / (bx * gy));
@@ -1466,7 +1484,7 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
     // 13).  A search over 60 000 documents for 5 sets, L = 32, C = 7 133 -> 107 us, C = 8 182 -> 114; 30 000 for 33 sets, L = 16, C = 9
     // 300 -> 157, L = 64, C = 6 533 -> 455; 5000 for 62, L = 128, C = 6 575 -> 433.  Lists with 128 tables too (64 of 4096, C = 6 548 -> 420), other lists
     // not: they are bound by gathered reads, which small blocks spread better, and lists of unequal length make no rounds.
-    if ((!a.cand_ids || L == 128) && gz == 1 && !cp && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= 128) {
+    if ((!a.cand_ids || L == 128) && gz == 1 && !cp && !cf && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= 128) {
         // slots: of an XCD, which takes every 8th block (below)
         const uint64_t slots = 32ull * (four ? masklut_resident<L, CB, CW, 4>() : pair ? masklut_resident<L, CB, CW, 2>() : masklut_resident<L, CB, CW, 1>());
         const uint64_t docs_max = masklut_docs(four ? 4 : 1);
@@ -1498,13 +1516,19 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
             gy_linear = (uint32_t)gyz;
         }
     }
-    // transform form of the kernel: raw counts, tabulated phi of the maximum (weighted or not), mean of the counts
-    const int remap = a.sigma_mean ? (a.q_weights ? 4 : 3) : a.q_weights ? 2 : a.remap ? 1 : 0;
     // the instantiation as a profiler prints it
     if (desc)
-        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, cp ? MASKLUT_CHUNK_PAIRS + remap : remap,
-                 four ? 4 : (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
+        snprintf(desc, desc_len, "score_masklut_kernel<%d, %d, %d, %d, %d, %s>", L, CB, CW, cp || cf ? MASKLUT_CHUNK_PAIRS + remap : remap,
+                 four || cf ? 4 : (pair || cp) ? 2 : 1, gz > 1 ? "true" : "false");
     using Kernel = void (*)(ScoreArgs, uint32_t, uint32_t, uint32_t);
+    if constexpr (FOUR_CHUNKS_OK) {
+        if (cf) {
+            const Kernel kern5 = gz > 1 ? score_masklut_kernel<L, CB, CW, MASKLUT_CHUNK_PAIRS, 4, true>
+                                        : score_masklut_kernel<L, CB, CW, MASKLUT_CHUNK_PAIRS, 4, false>;
+            hipLaunchKernelGGL(kern5, grid, dim3(masklut_threads(L, CB, CW, 4)), 0, stream, a, dpb, gy_linear, gz);
+            return hipGetLastError();
+        }
+    }
     if constexpr (CHUNK_PAIRS_OK) {
         if (cp) {
             constexpr int CP = MASKLUT_CHUNK_PAIRS;

@@ -64,3 +64,44 @@ def test_four_sets(L, Cb, n_sets, q, form):
     else:
         want = orc.scores_general(dc, off, qc, orc.PHI_EQ1, orc.SIGMA_MAX, weights=w[qo[b]:qo[b + 1]], eq1_C=Cb)
     assert np.array_equal(got[dz.SCORE_AUTO][b], want)
+
+
+# four chunks of one set per workgroup: 8 tables, sets of four and more chunks, the last four of two, three or four of them; long documents,
+# some empty or short; every document scored and lists with empty slots; one call with the chunks split over workgroups
+@pytest.mark.parametrize("lists", [False, True])
+@pytest.mark.parametrize("n_sets,q,want", [(8, 100, True), (16, 128, True), (16, 224, True), (8, 256, True), (60, 190, True), (16, 160, False), (2, 128, False)])
+@pytest.mark.parametrize("Cb", [5, 7, 8, 9])
+def test_four_chunks(Cb, n_sets, q, want, lists):
+    print("[case]", Cb, n_sets, q, lists, flush=True)
+    rng = np.random.default_rng(Cb * 1000 + q + n_sets)
+    d, L, n_docs = 64, 8, 900
+    lens = rng.integers(50, 110, n_docs)
+    lens[:6] = [0, 1, 260, 7, 0, 65]
+    lens[-1] = 0
+    pool = rng.integers(-100, 101, (9, d))
+    near = lambda n, s: np.clip(pool[rng.integers(0, 9, n)] + rng.integers(-s, s + 1, (n, d)), -127, 127).astype(np.int8)
+    X, Q = near(int(lens.sum()), 25), near(n_sets * q, 20)
+    R = (rng.integers(0, 2, (L * Cb, d)) * 2 - 1).astype(np.int8)
+    ix = dz.create(d, L, Cb, proj=torch.from_numpy(R).to(DEV))
+    dz.build_index(ix, torch.from_numpy(X).to(DEV), lens)
+    kw, sel = {}, [None] * n_sets
+    if lists:
+        sizes = rng.integers(700, 1001, n_sets)
+        sizes[-1] = 1000
+        sel = [rng.integers(0, n_docs, n).astype(np.uint32) for n in sizes]
+        for c in sel:
+            c[rng.random(len(c)) < 0.02] = 0xFFFFFFFF
+        kw = dict(cand_ids=torch.from_numpy(np.concatenate(sel).view(np.int32)).to(DEV), cand_offsets=np.concatenate([[0], np.cumsum(sizes)]))
+    got = {}
+    for algo in (dz.SCORE_AUTO, dz.SCORE_MASKLUT):
+        dz.set_algo(ix, dz.HASH_AUTO, algo)
+        got[algo] = dz.scores(ix, torch.from_numpy(Q).to(DEV), np.full(n_sets, q), **kw).cpu().numpy().reshape(-1)
+        assert (launched(ix) == 4) == (want and algo == dz.SCORE_AUTO), dz.last_score_kernel(ix)
+    assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_MASKLUT])
+    b, off = n_sets - 1, np.concatenate([[0], np.cumsum(lens)])
+    dc, qc = orc.hash_i8(X, R, L, Cb), orc.hash_i8(Q[b * q:], R, L, Cb)
+    ids = None if sel[b] is None else np.where(sel[b] == 0xFFFFFFFF, 0, sel[b]).astype(np.int64)
+    expect = orc.scores(dc, off, qc, ids)
+    if ids is not None:
+        expect = np.where(sel[b] == 0xFFFFFFFF, -1, expect)
+    assert np.array_equal(got[dz.SCORE_AUTO][-len(expect):], expect)
