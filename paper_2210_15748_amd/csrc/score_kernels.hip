@@ -1356,6 +1356,14 @@ bool score_masklut_supported(uint32_t L, uint32_t C) {
     return (L == 8 && C <= 11) || (L == 16 && C <= 10) || (L == 32 && C == 9);
 }
 
+// Documents per workgroup, docs_min to docs_max, so that the workgroups (gy for each block of documents) make whole rounds over the slots
+// of an XCD, which takes every 8th block.
+static uint32_t whole_round_docs(uint64_t docs, uint64_t gy, uint64_t slots, uint64_t docs_max, uint32_t docs_min) {
+    uint64_t rounds = ((docs + docs_max - 1) / docs_max * gy + 8 * slots - 1) / (8 * slots), most;
+    while ((most = rounds * slots / gy * 8) == 0 || (docs + most - 1) / most > docs_max) ++rounds;
+    return std::max((uint32_t)((docs + most - 1) / most), docs_min);
+}
+
 // workgroups of the forms for one, two and four sets that a CU holds at a time
 template <int L, int CB, int CW, int W>
 static uint32_t masklut_resident() {
@@ -1488,10 +1496,7 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
         // slots: of an XCD, which takes every 8th block (below)
         const uint64_t slots = 32ull * (four ? masklut_resident<L, CB, CW, 4>() : pair ? masklut_resident<L, CB, CW, 2>() : masklut_resident<L, CB, CW, 1>());
         const uint64_t docs_max = masklut_docs(four ? 4 : 1);
-        uint64_t rounds = ((a.max_scored + docs_max - 1) / docs_max * gy + 8 * slots - 1) / (8 * slots), most;
-        while ((most = rounds * slots / gy * 8) == 0 || (a.max_scored + most - 1) / most > docs_max) ++rounds;
-        const uint32_t docs_min = four && dpb_min < 128 ? 128 : dpb_min;
-        dpb = std::max((uint32_t)((a.max_scored + most - 1) / most), docs_min);
+        dpb = whole_round_docs(a.max_scored, gy, slots, docs_max, four && dpb_min < 128 ? 128 : dpb_min);
         bx = (a.max_scored + dpb - 1) / dpb;
     }
     const uint64_t gyz = (uint64_t)gy * gz;
@@ -1632,6 +1637,20 @@ bool score_maskany_pays(const ScoreBatch& a) {
     return mask_ns <= cmp_ns;
 }
 
+// workgroups of T threads and lds bytes that a CU holds at a time: what the registers leave room for, asked for 256 threads, and the LDS
+template <int NG, int CW>
+static uint32_t maskany_resident(bool mean, uint32_t T, size_t lds) {
+    auto ask = [](const void* kernel) {
+        int n = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, 0) == hipSuccess && n > 0 ? (uint32_t)n : 4u;
+    };
+    static const uint32_t of_max = ask((const void*)score_bytecmp_kernel_masks<NG, CW, false>);
+    static const uint32_t of_mean = ask((const void*)score_bytecmp_kernel_masks<NG, CW, true>);
+    const uint32_t by_registers = (mean ? of_mean : of_max) * 256 / T;
+    const uint32_t by_lds = (uint32_t)(160 * 1024 / (lds + sizeof(LutBlockMeta<>)));
+    return std::max(1u, std::min(by_registers, by_lds));
+}
+
 template <int NG, int CW>
 static hipError_t launch_maskany_t(const ScoreBatch& a, hipStream_t stream, char* desc, size_t desc_len, bool* adds) {
     const size_t table = ((size_t)a.L << a.C) * 4, lds = table + ((size_t)a.L + 1) * 4;
@@ -1643,7 +1662,7 @@ static hipError_t launch_maskany_t(const ScoreBatch& a, hipStream_t stream, char
     const uint32_t wave_docs = T / 64 * 8;   // one run of 8 documents per wave
     uint32_t dpb = LUT_DOCS;
     while (dpb > wave_docs && ((a.max_scored + dpb - 1) / dpb) * a.n_queries < 4096) dpb /= 2;
-    const uint64_t bx = (a.max_scored + dpb - 1) / dpb;
+    uint64_t bx = (a.max_scored + dpb - 1) / dpb;
     if (bx > 0x7fffffffull || a.n_queries > 65535) return hipErrorInvalidValue;
     // long query sets on a small grid: chunks of 32 query vectors dealt to gz workgroups that add into zeroed scores
     const uint32_t chunks = (a.max_q_len + 31) / 32;
@@ -1657,6 +1676,13 @@ static hipError_t launch_maskany_t(const ScoreBatch& a, hipStream_t stream, char
     if (gy > 65535) {
         gz = 1;
         gy = a.n_queries;
+    }
+    // Whole rounds over the chip as in launch_masklut_t: 8 sets x 20 000 documents, mean of the sigmoid, L = 32, C = 7 148 -> 121 us, raw counts,
+    // L = 48, C = 7 172 -> 140; 2 sets, L = 96, C = 8 165 -> 111, but with smaller tables more workgroups are the faster ones there (L = 48 53 -> 59).
+    if (!a.cand_ids && gz == 1 && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= (T == 1024 ? 128 : 256)) {
+        const uint64_t slots = 32ull * maskany_resident<NG, CW>(a.sigma_mean, T, lds);   // of an XCD, as in launch_masklut_t
+        dpb = whole_round_docs(a.max_scored, gy, slots, LUT_DOCS, wave_docs > 64 ? wave_docs : 64);
+        bx = (a.max_scored + dpb - 1) / dpb;
     }
     if (adds) {
         *adds = gz > 1;

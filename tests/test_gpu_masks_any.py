@@ -133,3 +133,26 @@ def test_which_kernel_takes_a_few_query_vectors(L, Cb, N, m, n_sets, q, transfor
         mask_kernel = dz.last_score_kernel(ix).startswith("score_bytecmp_kernel_masks<")
         assert mask_kernel == (masks and algo == dz.SCORE_AUTO), dz.last_score_kernel(ix)
     assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_BYTECMP])
+
+
+# grids that make whole rounds over the chip: block sizes that are no power of two, a last block that is not full, tables of every thread count
+@pytest.mark.parametrize("transform", [dz.SCORE_RAW_COUNTS, dz.SCORE_MEAN_SIGMOID_Q16])
+@pytest.mark.parametrize("L,Cb,n_docs,n_sets", [(12, 5, 22_003, 3), (24, 7, 17_001, 4), (36, 6, 66_001, 1), (96, 7, 13_005, 5), (96, 8, 33_001, 1), (24, 9, 17_003, 4)])
+def test_whole_rounds(L, Cb, n_docs, n_sets, transform):
+    print("[case]", L, Cb, n_docs, n_sets, transform, flush=True)
+    rng = np.random.default_rng(L + n_docs)
+    lens = rng.integers(0, 4, n_docs)
+    lens[:4], lens[-2:] = [0, 300, 1, 9], [17, 0]
+    pool = rng.integers(-100, 101, (9, 64))
+    near = lambda n, s: np.clip(pool[rng.integers(0, 9, n)] + rng.integers(-s, s + 1, (n, 64)), -127, 127).astype(np.int8)
+    ix = dz.create(64, L, Cb, seed=3)
+    dz.build_index(ix, torch.from_numpy(near(int(lens.sum()), 25)).to(DEV), lens)
+    dz.set_score_transform(ix, transform)
+    q_lens = rng.integers(20, 33, n_sets)
+    Q = torch.from_numpy(near(int(q_lens.sum()), 20)).to(DEV)
+    got = {}
+    for algo in (dz.SCORE_AUTO, dz.SCORE_BYTECMP):
+        dz.set_algo(ix, dz.HASH_AUTO, algo)
+        got[algo] = dz.scores(ix, Q, q_lens).cpu().numpy()
+        assert dz.last_score_kernel(ix).startswith("score_bytecmp_kernel_masks") == (algo == dz.SCORE_AUTO), dz.last_score_kernel(ix)
+    assert np.array_equal(got[dz.SCORE_AUTO], got[dz.SCORE_BYTECMP])
