@@ -43,7 +43,7 @@ VALU_PEAK_TLOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # 256 CUs x 4 SIMDs x 16 lanes x
 MFMA_F16_PEAK_TFLOPS = 2500.0
 
 
-def masklut_lane_ops(L: int, paired: bool) -> int:
+def masklut_lane_ops(L: int, sets: int) -> int:
     """Lane-operations the mask-table method needs per (document vector, 32 query vectors): table addresses, the
     carry-save adder tree that sums L one-bit-per-query masks into bit planes, and the bit-sliced running maximum."""
     fa = ha = 0
@@ -53,7 +53,7 @@ def masklut_lane_ops(L: int, paired: bool) -> int:
         ha += 1 if n % 2 == 0 else 0
         n //= 2
     planes = L.bit_length()           # counts 0..L
-    return (L // 2 if paired else L) + 2 * fa + 2 * ha + 2 * planes
+    return L // sets + 2 * fa + 2 * ha + 2 * planes   # sets: query sets that share an address
 
 
 def log(*a):
@@ -323,10 +323,9 @@ def main() -> int:
                 else "document vectors drawn without replacement",
                 "kmeans_ms": None if kmeans_ms is None else round(kmeans_ms, 2),
                 "bucket_entries": int(b_off[-1].item()), "build_ms": round(f_build_ms, 2),
-                "build_roofline": {"bound": "mfma", "kernel": "filter_gemm_kernel (vectors x centroids, int8)",
-                                   "achieved": round(gemm_ops / (f_build_ms * 1e-3) / 1e12, 1), "peak": 5000.0,
-                                   "unit": "TOP/s", "frac": round(gemm_ops / (f_build_ms * 1e-3) / 1e12 / 5000.0, 4),
-                                   "note": "whole dessert_filter_build call (GEMM + argmin + bucket build) over the GEMM's operations"},
+                "build_all_pairs": {"equivalent": round(gemm_ops / (f_build_ms * 1e-3) / 1e12, 1), "unit": "TOP/s",
+                                    "note": "operations of comparing every vector with every centroid over the whole dessert_filter_build "
+                                            "call; assignment by groups of centroids leaves most of them out, so this is no utilisation"},
                 "filter_probe": f_probe, "filter_k": f_k, "query_ms_per_batch": round(f_query_ms, 4),
                 "queries_per_s": round(B / (f_query_ms * 1e-3), 1),
                 "filter_then_search_ms_per_batch": round(chain_ms, 4),
@@ -375,11 +374,11 @@ def main() -> int:
     else:
         # every document for every query set: the codes are shared by the query sets of a batch (HBM is idle) and
         # the kernel is bound by the vector ALU.  Algorithmic work = lane-operations of the bit-sliced count per
-        # (document vector, chunk of 32 query vectors): one address per table (half when two query sets share the
+        # (document vector, chunk of 32 query vectors): one address per table (a half or a quarter when two or four query sets share the
         # lookups), two per full/half adder of the carry-save tree, two per plane of the running maximum.
-        # (whether two query sets shared the lookups is read off the instantiation the launch picked: its fifth parameter)
+        # (how many query sets shared the lookups is read off the instantiation the launch picked: its fifth parameter)
         inst = score_kernel[score_kernel.find("<") + 1:score_kernel.rfind(">")].split(",") if "masklut" in score_kernel else []
-        ops_unit = masklut_lane_ops(p.L, paired=(len(inst) == 6 and inst[4].strip() == "2"))
+        ops_unit = masklut_lane_ops(p.L, sets=int(inst[4]) if len(inst) == 6 else 1)
         chunks = (p.q_len + 31) // 32
         lane_ops = w.n_vectors * B * chunks * ops_unit
         achieved = lane_ops / (score_ms * 1e-3) / 1e12
