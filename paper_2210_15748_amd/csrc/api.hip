@@ -1226,7 +1226,8 @@ dessert_status_t dessert_filter_search(const dessert_index_t* ix, const void* q_
     // are joined: a launch less.  (Otherwise the hashing launch, after the filter, carries the grouping.)
     const Workspace sw = carve(ix, n_queries, total_q, (uint64_t)n_queries * filter_k, filter_k, k, true);
     uint8_t* qcodes = (uint8_t*)ws + w.search + sw.qcodes;
-    const bool hash_early = (n_queries < 8 || filter_k < score_order_min()) && hash_carries(ix, q_vectors_dev, qcodes);
+    // Not under dessert_enable_timing: the hashing has to lie between the events of its stage.
+    const bool hash_early = !ix->timing && (n_queries < 8 || filter_k < score_order_min()) && hash_carries(ix, q_vectors_dev, qcodes);
     // the candidates go straight into the scoring, which does not care about their order: the filter skips its sort
     dessert_status_t st = filter_query_impl(ix, q_vectors_dev, q_lengths_host, n_queries, filter_probe, filter_k, ws + w.filter,
                                             w.filter_bytes, cand, (int32_t*)(ws + w.counts), false, hash_early ? qcodes : nullptr);
