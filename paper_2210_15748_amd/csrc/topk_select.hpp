@@ -227,6 +227,10 @@ __device__ void bitonic_sort_lds(uint64_t* a, uint32_t npad) {
         for (uint32_t stride = size >> 1; stride > 0;) {
             const bool local = by_wave && 2 * stride <= seg;
             if (!(local && prev_local)) {
+                // The wait is written out because the compiler leaves it out of the barrier here: the loop's first trip has nothing to
+                // wait for, and it drops the wait for the trips that follow too.  (Waves then read keys that others were still writing: one list in
+                // some 1000 of 172 keys lost a few of them.)
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __syncthreads();
             } else {
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
