@@ -243,6 +243,7 @@ struct Batch {
     uint32_t max_q_len = 0;
     uint32_t q_uniform = 0;      // common query-set length, 0 if they differ
     uint64_t cand_uniform = 0;   // common candidate-list length, 0 if they differ (or no candidates)
+    bool padded_lists = false;   // the lists are a filter's, which may have found fewer documents
 };
 
 // Asynchronous upload of a small host array through one of the handle's pinned staging slots (a slot is reused
@@ -443,6 +444,8 @@ dessert_status_t search_impl(dessert_index* ix, const Batch& bt, const void* q_v
     sa.four_sets = ix->score_algo == DESSERT_SCORE_AUTO;
     sa.cand_ids = cand_ids; sa.cand_off = cand_ids ? d_cand_off : nullptr; sa.cand_uniform = cand_ids ? bt.cand_uniform : 0;
     sa.max_scored = bt.max_scored; sa.total_scored = bt.total_scored; sa.n_vectors = ix->n_vectors; sa.scores = scores;
+    sa.equal_docs = ix->max_len * ix->n_docs == ix->n_vectors;
+    sa.padded_lists = bt.padded_lists;
     sa.remap = ix->transform != DESSERT_SCORE_RAW_COUNTS ? ix->remap : nullptr;
     sa.sigma_mean = ix->transform >= DESSERT_SCORE_MEAN_IDENTITY_Q16 ? 1u : 0u;
     // phi = identity with L a power of two: the table is 65536 / L * count exactly
@@ -1237,6 +1240,7 @@ dessert_status_t dessert_filter_search(const dessert_index_t* ix, const void* q_
     st = check_batch(ix, q_vectors_dev, q_lengths_host, n_queries, nullptr, nullptr, &bt);
     if (st != DESSERT_OK) return st;
     bt.max_scored = bt.cand_uniform = filter_k;
+    bt.padded_lists = true;
     bt.total_scored = (uint64_t)n_queries * filter_k;
     return search_impl(const_cast<dessert_index*>(ix), bt, q_vectors_dev, n_queries, cand, nullptr, k, ws + w.search,
                        w.search_bytes, nullptr, out_ids_dev, out_scores_dev, hash_early);

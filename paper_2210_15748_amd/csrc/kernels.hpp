@@ -83,6 +83,8 @@ struct ScoreBatch : ScoreArgs {
     uint64_t max_scored;        // largest number of documents scored by one query set
     uint64_t total_scored;      // all output slots (candidate mode: sum of the list lengths)
     uint64_t n_vectors;         // vectors in the index
+    bool equal_docs;            // all documents have the same length
+    bool padded_lists;          // candidate lists end in empty slots
     uint64_t chunks, chunk_pairs;  // chunks of 32 query vectors in all sets together, and pairs of chunks of one set
     bool four_sets;             // workgroups may take four query sets
     bool zeroed;                // the scores are clear already, where the launch would clear them

@@ -3,6 +3,7 @@
 //     score(Q,S) = sum_{q in Q} max_{x in S} #{ t : code_t(q) == code_t(x) }.
 // Scores are raw integer counts (no division by L, no remap of Eq. 1).
 #include "kernels.hpp"
+#include "score_blocks.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -1356,14 +1357,6 @@ bool score_masklut_supported(uint32_t L, uint32_t C) {
     return (L == 8 && C <= 11) || (L == 16 && C <= 10) || (L == 32 && C == 9);
 }
 
-// Documents per workgroup, docs_min to docs_max, so that the workgroups (gy for each block of documents) make whole rounds over the slots
-// of an XCD, which takes every 8th block.
-static uint32_t whole_round_docs(uint64_t docs, uint64_t gy, uint64_t slots, uint64_t docs_max, uint32_t docs_min) {
-    uint64_t rounds = ((docs + docs_max - 1) / docs_max * gy + 8 * slots - 1) / (8 * slots), most;
-    while ((most = rounds * slots / gy * 8) == 0 || (docs + most - 1) / most > docs_max) ++rounds;
-    return std::max((uint32_t)((docs + most - 1) / most), docs_min);
-}
-
 // workgroups of the forms for one, two and four sets that a CU holds at a time
 template <int L, int CB, int CW, int W>
 static uint32_t masklut_resident() {
@@ -1486,17 +1479,22 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
     const bool four = FOUR_OK && pair && a.four_sets && !a.q_weights && a.chunks == (uint64_t)chunks * a.n_queries &&
                       (a.n_queries + 3) / 4 * 91 <= (a.n_queries + 1) / 2 * 50 &&
                       (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * ((a.n_queries + 3) / 4) >= 256;
-    if (four) gy = (a.n_queries + 3) / 4;
-    // Every document scored: as many documents per workgroup as make whole rounds over the chip, where the smallest blocks did (to have
-    // 4096 workgroups) or the largest, and the chip then waited for a last round that few of them fill (12.2 rounds take as long as
-    // 13).  A search over 60 000 documents for 5 sets, L = 32, C = 7 133 -> 107 us, C = 8 182 -> 114; 30 000 for 33 sets, L = 16, C = 9
-    // 300 -> 157, L = 64, C = 6 533 -> 455; 5000 for 62, L = 128, C = 6 575 -> 433.  Lists with 128 tables too (64 of 4096, C = 6 548 -> 420), other lists
-    // not: they are bound by gathered reads, which small blocks spread better, and lists of unequal length make no rounds.
-    if ((!a.cand_ids || L == 128) && gz == 1 && !cp && !cf && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= 128) {
+    if (four) {
+        gy = (a.n_queries + 3) / 4;
+        dpb = std::max(dpb, 128u);   // a run of documents for every wave
+        bx = (a.max_scored + dpb - 1) / dpb;
+    }
+    // As many documents per workgroup as make whole rounds over the chip where that pays (score_blocks.hpp).  Of lists, only those of equal
+    // length and full, with 128 tables (276 batches, C = 4 to 8, 1 to 250 lists of 512 to 16 384: documents of unequal length 0.82 of the time on
+    // average and at most 1.01, but lists of unequal length up to 1.39, and a filter's list that is mostly empty 1.93): other lists are bound by
+    // gathered reads, which small blocks spread better.
+    if ((!a.cand_ids || (L == 128 && a.cand_uniform && !a.padded_lists)) && gz == 1 && !cp && !cf &&
+        (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= 128 &&
+        whole_rounds_pay((uint64_t)(L << CB) * 4 * (four ? 4 : pair ? 2 : 1), dpb * mean_len * L * CW, a.equal_docs,
+                         a.chunks == (uint64_t)chunks * a.n_queries, false)) {
         // slots: of an XCD, which takes every 8th block (below)
         const uint64_t slots = 32ull * (four ? masklut_resident<L, CB, CW, 4>() : pair ? masklut_resident<L, CB, CW, 2>() : masklut_resident<L, CB, CW, 1>());
-        const uint64_t docs_max = masklut_docs(four ? 4 : 1);
-        dpb = whole_round_docs(a.max_scored, gy, slots, docs_max, four && dpb_min < 128 ? 128 : dpb_min);
+        dpb = std::max(dpb, whole_round_docs(a.max_scored, gy, slots, masklut_docs(four ? 4 : 1), dpb_min));
         bx = (a.max_scored + dpb - 1) / dpb;
     }
     const uint64_t gyz = (uint64_t)gy * gz;
@@ -1677,11 +1675,12 @@ static hipError_t launch_maskany_t(const ScoreBatch& a, hipStream_t stream, char
         gz = 1;
         gy = a.n_queries;
     }
-    // Whole rounds over the chip as in launch_masklut_t: 8 sets x 20 000 documents, mean of the sigmoid, L = 32, C = 7 148 -> 121 us, raw counts,
-    // L = 48, C = 7 172 -> 140; 2 sets, L = 96, C = 8 165 -> 111, but with smaller tables more workgroups are the faster ones there (L = 48 53 -> 59).
-    if (!a.cand_ids && gz == 1 && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= (T == 1024 ? 128 : 256)) {
+    // whole rounds over the chip as in launch_masklut_t
+    const uint64_t mean_len = a.n_docs ? (a.n_vectors + a.n_docs - 1) / a.n_docs : 1;
+    if (!a.cand_ids && gz == 1 && (a.max_scored + LUT_DOCS - 1) / LUT_DOCS * gy >= (T == 1024 ? 128 : 256) &&
+        whole_rounds_pay(table, dpb * mean_len * a.L * CW, a.equal_docs, a.chunks == (uint64_t)chunks * a.n_queries, true)) {
         const uint64_t slots = 32ull * maskany_resident<NG, CW>(a.sigma_mean, T, lds);   // of an XCD, as in launch_masklut_t
-        dpb = whole_round_docs(a.max_scored, gy, slots, LUT_DOCS, wave_docs > 64 ? wave_docs : 64);
+        dpb = std::max(dpb, whole_round_docs(a.max_scored, gy, slots, LUT_DOCS, wave_docs > 64 ? wave_docs : 64));
         bx = (a.max_scored + dpb - 1) / dpb;
     }
     if (adds) {
