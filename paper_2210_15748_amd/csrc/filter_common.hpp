@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "group_cost.hpp"
+
 namespace dessert {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -24,22 +26,6 @@ __device__ __forceinline__ int32_t med3_i32(int32_t x, int32_t y, int32_t z) {
     int32_t r;
     asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
     return r;
-}
-
-// Assignment by groups of centroids (filter_groups.hip): what its launches tell each other.
-constexpr uint32_t GROUP_TRIAL = 4096;   // vectors that tell whether the groups pay
-struct GroupCtl {
-    uint32_t groups;    // groups of centroids
-    uint32_t radius2;   // largest squared distance of a centroid from its group's leader
-    uint32_t easy;      // vectors of the trial that need one group only
-    uint32_t rest;      // vectors left to a comparison with every centroid
-};
-__host__ __device__ inline uint32_t groups_room(uint32_t K) { return K / 3; }   // more groups are not made
-// Groups in vain: too many of them, or too many vectors near to more than one.  Reading a group per vector and the list of the rest cost
-// something too, hence 0.7 and not 1.
-__device__ __forceinline__ bool groups_pay(const GroupCtl& c, uint32_t K) {
-    if (c.groups == 0 || c.groups > groups_room(K)) return false;
-    return (uint64_t)(GROUP_TRIAL - c.easy) * K + (uint64_t)GROUP_TRIAL * c.groups <= (uint64_t)GROUP_TRIAL * K / 10 * 7;
 }
 
 }  // namespace dessert

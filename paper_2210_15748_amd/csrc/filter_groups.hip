@@ -52,7 +52,7 @@ __global__ __launch_bounds__(1024) void group_near_kernel(const int8_t* __restri
     const int col = lane & 31, g = lane >> 5;
     const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
     for (uint32_t i = block * 1024 + threadIdx.x; i < K; i += gridDim.x * gridDim.y * 1024) size[i] = 0;
-    if (block == 0 && threadIdx.x == 0) *ctl = GroupCtl{0, 0, 0, 0};
+    if (block == 0 && threadIdx.x == 0) *ctl = GroupCtl{};
     const uint64_t v = (uint64_t)(blockIdx.x * 32 + col) * n / GROUP_SAMPLE;
     const v4i* src = (const v4i*)(X + v * D + g * 16);
     v4i b[KS];
@@ -332,7 +332,7 @@ __device__ __forceinline__ void best_of(int64_t& key) {
 // accumulators themselves: the row, and the best of the other rows of that tile, are looked for once at the end.  (Both kept by row and tile
 // all along: two operations more per accumulator, and the vector ALU, not the matrix cores, bounds the loop.)  h = x.c - ceil(|c|^2 / 2)
 // gives |x - c|^2 = |x|^2 - 2 h - (0 or 1), which is as good as exact here: the larger for the closest leader, the smaller for the others.
-// trial: only counts the vectors that need one group, among trial vectors taken evenly.
+// trial: only counts the vectors that need one group, and its members, among trial vectors taken evenly.
 // Bound: both halves alike, the loop over the leaders by matrix cores and vector ALU in turn, the members by the CU's 64 bytes a cycle
 // from L2 (17 rows a vector).  4.2M vectors of 128 dimensions, 1024 leaders of 16 384 centroids: 0.89 ms, of which 0.55 and 0.65 by themselves;
 // comparing with every centroid takes 7.4 ms.
@@ -454,7 +454,13 @@ __global__ __launch_bounds__(256, KS >= 8 ? 2 : 3) void group_assign_kernel(cons
         const bool one = __fsqrt_rn((float)(xx - 2 * sec - 1)) > __fsqrt_rn((float)(xx - 2 * val)) + radius + 0.0625f && end - start <= max_group;
         const uint64_t easy = __ballot(mine && one), rest = __ballot(mine && !one);
         if (trial) {
-            if (lane == 0 && easy) atomicAdd(&ctl->easy, (uint32_t)__builtin_popcountll(easy));
+            uint32_t members = mine && one ? end - start : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) members += (uint32_t)__shfl_xor((int)members, o, 64);
+            if (lane == 0 && easy) {
+                atomicAdd(&ctl->easy, (uint32_t)__builtin_popcountll(easy));
+                atomicAdd(&ctl->members, members);
+            }
             continue;
         }
         if (g == 0) s_run[wave][nt * 32 + col] = mine && one ? make_uint2(start, end) : make_uint2(0, 0);
@@ -560,8 +566,7 @@ hipError_t launch_groups(const int8_t* X, uint64_t n, uint32_t K, const v4i* Cp,
     int2* meta = (int2*)(base + w.meta);
     v4i *rows = (v4i*)(base + w.rows), *Lp = (v4i*)(base + w.Lp);
     const uint32_t tiles = filter_tiles(K);
-    // a group costs its members one by one: past K / 64 of them the comparison with every centroid is no dearer
-    const uint32_t max_group = K / 64;
+    const uint32_t max_group = groups_largest(K);
     const uint64_t blocks = (n + 128 * NT - 1) / (128 * NT);
     if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
     hipLaunchKernelGGL(group_near_kernel<KS>, dim3(GROUP_SAMPLE / 32, GROUP_PARTS), dim3(1024), 0, stream, X, n, Cp, W, tiles, K, near, size, ctl);

@@ -139,7 +139,7 @@ bool filter_groups_pay_from(uint32_t K);   // numbers of centroids for which the
 bool filter_groups_try(uint64_t n, uint32_t d, uint32_t K);
 size_t filter_group_bytes(uint32_t K, uint32_t d);
 // assign[v] of the vectors that one group decides; the others go to list, their number and what decides how to go on to the GroupCtl at
-// the start of buffer (filter_common.hpp).
+// the start of buffer (group_cost.hpp).
 hipError_t launch_group_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2, void* buffer,
                                uint32_t* assign, uint32_t* list, hipStream_t stream);
 hipError_t launch_filter_distances(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
