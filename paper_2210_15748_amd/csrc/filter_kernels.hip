@@ -78,8 +78,9 @@ __global__ __launch_bounds__(256) void filter_prep_kernel(const int8_t* __restri
 // Bound: matrix cores.  Column tiles are multiplied one after the other, each while the one before is compared: two accumulator
 // sets instead of one per column tile (202 -> 168 VGPRs at d = 128, three waves per SIMD instead of two).  With 512 tiles
 // 38 % of the tiles can improve some lane of a wave, so what such a tile costs matters: 16 shifts and 8 maxima (parity and
-// tie-break come out of the row's constant with the shift; about 64 operations when they were computed per row).  (Held to three
-// waves the d = 128 build of MODE 0 spills three registers, 16 bytes of scratch per lane; the figures are with them.)  4.2M vectors x
+// tie-break come out of the row's constant with the shift; about 64 operations when they were computed per row).  (No registers are spilled: where a list
+// gives the vectors, their places are made anew at the end, see there; d = 256, 500 000 vectors, 16 384 centroids with 24 bytes of scratch a
+// lane 1.05 of the time.)  4.2M vectors x
 // 16 384 centroids, d = 128: 8.7 -> 7.4 ms = 2.4 POP/s, the share of nominal that a large bf16 matrix product reaches here.
 // Four probes of 4096 vectors in 32 768 centroids 116 -> 54 us (32-bit sorted keys; 64-bit list inserts per row before).
 // Waves per SIMD that the registers leave room for: 32*NT vectors as fragments (4*KS*NT), two accumulator sets, a tile's constants
@@ -287,6 +288,10 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
         if (in_chunk) fold(t_end - in_chunk);
     }
     if constexpr (MODE == 0) {
+        // the vectors' places anew from the thread: where the list gives them the compiler keeps their addresses all along otherwise, and spills
+        uint32_t thread = threadIdx.x;
+        if constexpr (REST) asm volatile("" : "+v"(thread));
+        const uint64_t first = ((uint64_t)blockIdx.x * 4 + thread / 64) * (32 * NT) + (thread & 31);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             int32_t val = best_key[nt] >> 4;
@@ -294,7 +299,7 @@ __global__ __launch_bounds__(256, gemm_min_waves(KS, NT, MODE)) void filter_gemm
             int32_t oval = __shfl_xor(val, 32, 64);
             uint32_t oc = (uint32_t)__shfl_xor((int)c, 32, 64);
             if (oval > val || (oval == val && oc < c)) c = oc;
-            const uint64_t v = v0 + nt * 32 + col;
+            const uint64_t v = first + nt * 32;
             if (g == 0 && v < n) assign[REST && rest.list ? rest.list[v] : v] = c;
         }
     } else if constexpr (MODE > 0) {
