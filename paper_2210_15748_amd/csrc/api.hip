@@ -972,7 +972,7 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
     ix->f_sub = sub;
     HIP_TRY(launch_filter_prep(centroids_dev, n_centroids, ix->cfg.d, ix->f_cent, ix->f_table, ix->stream));
     HIP_TRY(launch_filter_assign((const int8_t*)vectors_dev, ix->n_vectors, ix->cfg.d, n_centroids, ix->f_cent,
-                                 ix->f_table, assign_dev, ix->f_groups, bucket_docs_dev, ix->stream));
+                                 ix->f_table, assign_dev, ix->f_groups, bucket_docs_dev, 0, ix->stream));
     HIP_TRY(launch_filter_buckets(assign_dev, ix->offsets, ix->n_docs, n_centroids, ix->f_sub, ix->f_cursor, ix->f_sub_off,
                                   bucket_offsets_dev, bucket_docs_dev, ix->stream));
     {   // the largest bucket bounds how many documents one query set can hit (sizes the query workspace)
@@ -1038,7 +1038,7 @@ dessert_status_t dessert_filter_kmeans(const dessert_index_t* ix, const int8_t* 
         HIP_TRY(launch_filter_prep(centroids_dev, n_centroids, ix->cfg.d, ws + w.cent, ws + w.table, ix->stream));
         // the list of an assignment by groups lies where the order of the update step goes afterwards
         HIP_TRY(launch_filter_assign(sample_dev, n_sample, ix->cfg.d, n_centroids, ws + w.cent, ws + w.table, assign,
-                                     workspace_bytes >= w.total ? ws + w.groups : nullptr, (uint32_t*)(ws + w.order), ix->stream));
+                                     workspace_bytes >= w.total ? ws + w.groups : nullptr, (uint32_t*)(ws + w.order), it, ix->stream));
         HIP_TRY(launch_kmeans_update(sample_dev, n_sample, ix->cfg.d, assign, n_centroids, (int32_t*)(ws + w.sums),
                                      (uint32_t*)(ws + w.counts), centroids_dev,
                                      workspace_bytes >= w.ordered ? (uint32_t*)(ws + w.order) : nullptr, ix->stream));

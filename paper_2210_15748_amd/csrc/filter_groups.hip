@@ -13,14 +13,15 @@
 // data, few vectors are near to two.  So the width follows the vectors: sqrt(3) times the median distance of a vector
 // from its closest centroid, over a sample.  (Mixture of 1024 centres, 4096 to 16 384 centroids, before and after rounds of k-means: 0 to
 // 2 % of the vectors are left over, 1010 to 1036 groups; at sqrt(2) 1 to 7 %, at sqrt(1.5) 6 to 45 %.)  Where the data have no clusters the
-// groups are too many or the rest is too large; a trial on 4096 vectors tells that on the device, and everything goes the old way.
+// groups are too many or the rest is too large; a trial on 4096 vectors tells that on the device, and everything goes the old way: in a
+// training also the next rounds, without another trial.
 #include "filter_common.hpp"
 #include "kernels.hpp"
 
 namespace dessert {
 
 constexpr uint32_t GROUP_SAMPLE = 512;   // vectors whose median distance sets the groups' width
-constexpr uint32_t GROUP_PARTS = 8;      // of the centroids, looked through side by side for that sample
+constexpr uint32_t GROUP_PARTS = 16;     // of the centroids, looked through side by side for that sample
 
 namespace {
 
@@ -42,15 +43,25 @@ __device__ __forceinline__ int32_t dot16(v4i a, v4i b, int32_t s) {
 // Squared distance from GROUP_SAMPLE vectors, taken evenly, to the closest centroid of each of GROUP_PARTS parts of the tiles; clears the
 // counters for the launches that follow.  A workgroup's 16 waves hold the same 32 vectors and take every 16th tile of a part.  Bound:
 // latency (the parts are there because one CU takes 16 us to read 2 MB of centroids: 38 us in one part, 8 in eight).
+// before: what the round before left, or nullptr; where its groups did not pay, all launches of this one end at once.
 template <int KS>
 __global__ __launch_bounds__(1024) void group_near_kernel(const int8_t* __restrict__ X, uint64_t n, const v4i* __restrict__ Cp,
                                                           const v4i* __restrict__ W, uint32_t tiles, uint32_t K, uint32_t* __restrict__ near,
-                                                          uint32_t* __restrict__ size, GroupCtl* __restrict__ ctl) {
+                                                          uint32_t* __restrict__ size, GroupCtl* __restrict__ ctl,
+                                                          const GroupCtl* __restrict__ before) {
     constexpr int D = KS * 32;
     __shared__ int32_t s_val[16][32];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, g = lane >> 5;
     const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
+    if (before && !groups_pay(*before, K)) {
+        if (block == 0 && threadIdx.x == 0) {
+            GroupCtl none{};
+            none.skip = 1;
+            *ctl = none;
+        }
+        return;
+    }
     for (uint32_t i = block * 1024 + threadIdx.x; i < K; i += gridDim.x * gridDim.y * 1024) size[i] = 0;
     if (block == 0 && threadIdx.x == 0) *ctl = GroupCtl{};
     const uint64_t v = (uint64_t)(blockIdx.x * 32 + col) * n / GROUP_SAMPLE;
@@ -97,10 +108,12 @@ __global__ __launch_bounds__(1024) void group_near_kernel(const int8_t* __restri
 // the same 64 centroids (32 at d = 256) and take every 8th tile up to their own (a centroid is within tau of itself), 32 tiles between
 // two looks at what has been found: lower tiles come first, so the walk ends once every centroid has its leader.  16 384 centroids
 // around 1024 centres, d = 128: 40 us, the few walks that find a leader late or not at all.
+// looks != 0: only counts, by so many workgroups spread over the centroids, how many lead themselves (groups_hopeless).
 template <int KS>
 __global__ __launch_bounds__(512) void group_leader_kernel(const v4i* __restrict__ Cp, const v4i* __restrict__ W, uint32_t tiles, uint32_t K,
                                                            const uint32_t* __restrict__ near, uint32_t* __restrict__ leader,
-                                                           uint32_t* __restrict__ member, uint32_t* __restrict__ size, GroupCtl* __restrict__ ctl) {
+                                                           uint32_t* __restrict__ member, uint32_t* __restrict__ size, GroupCtl* __restrict__ ctl,
+                                                           uint32_t looks) {
     constexpr int NT = KS == 8 ? 1 : 2;
     constexpr uint32_t WAVES = 8, ROUND = 4 * WAVES;
     static_assert(GROUP_SAMPLE == WAVES * 64, "a thread per vector of the sample");
@@ -108,13 +121,25 @@ __global__ __launch_bounds__(512) void group_leader_kernel(const v4i* __restrict
     __shared__ unsigned long long s_found[32 * NT];   // (id, value) of the lowest so far
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, g = lane >> 5;
+    if (ctl->skip || (!looks && groups_hopeless(ctl->led, ctl->alone))) return;   // as the launches before left it
+    const uint32_t* words = (const uint32_t*)W;
+    v4i b[NT][KS];
+    int32_t norm[NT];
+    const uint32_t all = (tiles + NT - 1) / NT;   // workgroups for every centroid; the longest walks start first
+    const uint32_t first = (all - 1 - (looks ? blockIdx.x * all / looks : blockIdx.x)) * NT;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const uint32_t tile = first + nt < tiles ? first + nt : tiles - 1;
+        norm[nt] = norm_of(words[word_at(tile * 32 + col)]);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) b[nt][ks] = Cp[((size_t)tile * KS + ks) * 64 + lane];
+    }
     uint32_t mine = near[threadIdx.x];
     for (uint32_t p = 1; p < GROUP_PARTS; ++p) {
         const uint32_t x = near[p * GROUP_SAMPLE + threadIdx.x];
         mine = x < mine ? x : mine;
     }
     s_near[threadIdx.x] = mine;
-    const uint32_t first = (gridDim.x - 1 - blockIdx.x) * NT;   // the longest walks start first
     const uint32_t end = first + NT < tiles ? first + NT : tiles;
     if (threadIdx.x < 32 * NT) s_found[threadIdx.x] = first * 32 + threadIdx.x < K ? ~0ull : 0ull;
     __syncthreads();
@@ -129,16 +154,9 @@ __global__ __launch_bounds__(512) void group_leader_kernel(const v4i* __restrict
         if (below <= GROUP_SAMPLE / 2) median |= bit;
     }
     const int32_t tau = median < (1u << 21) ? 3 * (int32_t)median : 1 << 22;
-    const uint32_t* words = (const uint32_t*)W;
-    v4i b[NT][KS];
-    int32_t least[NT];   // a value must reach it
+    int32_t least[NT];   // a value must reach it: above -2^24, where rows past K are
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const uint32_t tile = first + nt < tiles ? first + nt : tiles - 1;
-        least[nt] = norm_of(words[word_at(tile * 32 + col)]) - tau;   // above -2^24, where rows past K are
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) b[nt][ks] = Cp[((size_t)tile * KS + ks) * 64 + lane];
-    }
+    for (int nt = 0; nt < NT; ++nt) least[nt] = norm[nt] - tau;
     v4i a[KS], row[4], a_next[KS], row_next[4];
     auto load = [&](uint32_t tile, v4i (&frag)[KS], v4i (&consts)[4]) {
 #pragma unroll
@@ -190,6 +208,14 @@ __global__ __launch_bounds__(512) void group_leader_kernel(const v4i* __restrict
     uint32_t d2 = 0;
     if (threadIdx.x < 32 * NT && c < K) {   // lanes of the first wave
         const uint32_t l = (uint32_t)(s_found[threadIdx.x] >> 32);   // at most c
+        if (looks) {
+            const uint64_t alone = __ballot(l == c), led = __ballot(true);
+            if (threadIdx.x == 0) {
+                atomicAdd(&ctl->led, (uint32_t)__builtin_popcountll(led));
+                atomicAdd(&ctl->alone, (uint32_t)__builtin_popcountll(alone));
+            }
+            return;
+        }
         leader[c] = l;
         // The centroid's number within its group.  Lanes that share the first lane's leader take theirs together: in data without clusters
         // there are few groups, and an atomic to the same word as others takes 11 ns.
@@ -212,10 +238,12 @@ __global__ __launch_bounds__(512) void group_leader_kernel(const v4i* __restrict
 }
 
 // One workgroup: group numbers in order of their leaders, starts[group] = members of the groups before it, and size[leader] becomes the
-// same start.  No more than room groups are written.
+// same start.  No more than room groups are written; none where the leaders were not all looked for.  A thread's 16 sizes come in four
+// reads (in 16 the lines that each wave asks for, one a lane, took 4 of 10 us for 16 384 centroids); size has room for whole reads.
 __global__ __launch_bounds__(1024) void group_starts_kernel(uint32_t* __restrict__ size, uint32_t K, uint32_t room, uint32_t* __restrict__ leads,
                                                             uint32_t* __restrict__ starts, GroupCtl* __restrict__ ctl) {
     __shared__ uint64_t wsum[16];
+    if (ctl->skip || groups_hopeless(ctl->led, ctl->alone)) return;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint64_t carry = 0;   // groups in the high word, members in the low one
     for (uint32_t base = 0; base < K; base += 1024 * 16) {
@@ -223,8 +251,14 @@ __global__ __launch_bounds__(1024) void group_starts_kernel(uint32_t* __restrict
         const uint32_t first = base + tid * 16;
         uint64_t sum = 0;
 #pragma unroll
+        for (uint32_t i = 0; i < 16; i += 4) {
+            uint4 four = make_uint4(0, 0, 0, 0);
+            if (first + i < K) four = *(const uint4*)(size + first + i);
+            x[i] = four.x; x[i + 1] = four.y; x[i + 2] = four.z; x[i + 3] = four.w;
+        }
+#pragma unroll
         for (uint32_t i = 0; i < 16; ++i) {
-            x[i] = first + i < K ? size[first + i] : 0;
+            if (first + i >= K) x[i] = 0;
             sum += ((uint64_t)(x[i] != 0) << 32) | x[i];
         }
         uint64_t incl = sum;
@@ -273,7 +307,7 @@ __global__ __launch_bounds__(256) void group_fill_kernel(const v4i* __restrict__
                                                          int32_t* __restrict__ Lw) {
     constexpr uint32_t LPV = KS * 2;   // lanes to a centroid: 16-byte pieces of a row
     const uint32_t groups = ctl->groups;
-    if (groups > room) return;
+    if (groups == 0 || groups > room) return;
     const uint32_t sub = threadIdx.x & (LPV - 1);
     const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
     for (uint32_t i = first; i < K * LPV; i += stride) {
@@ -347,7 +381,7 @@ __global__ __launch_bounds__(256, KS >= 8 ? 2 : 3) void group_assign_kernel(cons
     __shared__ v4i sW[2][TG * 8];
     __shared__ uint2 s_run[4][32 * NT];   // the members of a vector's group; none: start = end
     const GroupCtl now = *ctl;
-    if (trial ? now.groups > groups_room(K) : !groups_pay(now, K)) return;   // the same for every thread of the launch
+    if (trial ? now.groups == 0 || now.groups > groups_room(K) : !groups_pay(now, K)) return;   // the same for every thread of the launch
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, g = lane >> 5;
     const uint64_t v0 = ((uint64_t)blockIdx.x * 4 + wave) * (32 * NT);
@@ -539,7 +573,7 @@ GroupLayout group_layout(uint32_t K, uint32_t d) {
         return at;
     };
     w.room = groups_room(K);
-    w.ctl = take(sizeof(GroupCtl));
+    w.ctl = take(2 * sizeof(GroupCtl));   // of this round of k-means and the one before, in turn
     w.near = take((size_t)GROUP_PARTS * GROUP_SAMPLE * 4);
     w.leader = take((size_t)K * 4);
     w.member = take((size_t)K * 4);
@@ -556,10 +590,11 @@ GroupLayout group_layout(uint32_t K, uint32_t d) {
 
 template <int KS, int NT>
 hipError_t launch_groups(const int8_t* X, uint64_t n, uint32_t K, const v4i* Cp, const v4i* W, void* buffer, uint32_t* assign, uint32_t* list,
-                         hipStream_t stream) {
+                         uint32_t round, hipStream_t stream) {
     const GroupLayout w = group_layout(K, KS * 32);
     char* base = (char*)buffer;
-    GroupCtl* ctl = (GroupCtl*)(base + w.ctl);
+    GroupCtl* ctl = (GroupCtl*)(base + w.ctl) + (round & 1);
+    const GroupCtl* before = round % GROUP_RETRY ? (GroupCtl*)(base + w.ctl) + (~round & 1) : nullptr;
     uint32_t *near = (uint32_t*)(base + w.near), *leader = (uint32_t*)(base + w.leader), *member = (uint32_t*)(base + w.member), *size = (uint32_t*)(base + w.size);
     uint32_t *leads = (uint32_t*)(base + w.leads), *starts = (uint32_t*)(base + w.starts);
     int32_t* Lw = (int32_t*)(base + w.Lw);
@@ -569,8 +604,12 @@ hipError_t launch_groups(const int8_t* X, uint64_t n, uint32_t K, const v4i* Cp,
     const uint32_t max_group = groups_largest(K);
     const uint64_t blocks = (n + 128 * NT - 1) / (128 * NT);
     if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(group_near_kernel<KS>, dim3(GROUP_SAMPLE / 32, GROUP_PARTS), dim3(1024), 0, stream, X, n, Cp, W, tiles, K, near, size, ctl);
-    hipLaunchKernelGGL(group_leader_kernel<KS>, dim3(KS == 8 ? tiles : (tiles + 1) / 2), dim3(512), 0, stream, Cp, W, tiles, K, near, leader, member, size, ctl);
+    hipLaunchKernelGGL(group_near_kernel<KS>, dim3(GROUP_SAMPLE / 32, GROUP_PARTS), dim3(1024), 0, stream, X, n, Cp, W, tiles, K, near, size, ctl, before);
+    auto leaders = [&](uint32_t workgroups, uint32_t looks) {
+        hipLaunchKernelGGL(group_leader_kernel<KS>, dim3(workgroups), dim3(512), 0, stream, Cp, W, tiles, K, near, leader, member, size, ctl, looks);
+    };
+    if (K >= GROUP_MANY) leaders(GROUP_LOOKS, GROUP_LOOKS);
+    leaders(KS == 8 ? tiles : (tiles + 1) / 2, 0);
     hipLaunchKernelGGL(group_starts_kernel, dim3(1), dim3(1024), 0, stream, size, K, w.room, leads, starts, ctl);
     hipLaunchKernelGGL(group_fill_kernel<KS>, dim3(512), dim3(256), 0, stream, Cp, (const uint32_t*)W, K, w.room, leader, member, size, leads, ctl,
                        rows, meta, Lp, Lw);
@@ -585,11 +624,13 @@ hipError_t launch_groups(const int8_t* X, uint64_t n, uint32_t K, const v4i* Cp,
 
 size_t filter_group_bytes(uint32_t K, uint32_t d) { return group_layout(K, d).total; }
 
+const GroupCtl* group_ctl(const void* buffer, uint32_t round) { return (const GroupCtl*)buffer + (round & 1); }
+
 hipError_t launch_group_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2, void* buffer,
-                               uint32_t* assign, uint32_t* list, hipStream_t stream) {
-    if (d == 64) return launch_groups<2, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, stream);
-    if (d == 128) return launch_groups<4, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, stream);
-    if (d == 256) return launch_groups<8, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, stream);
+                               uint32_t* assign, uint32_t* list, uint32_t round, hipStream_t stream) {
+    if (d == 64) return launch_groups<2, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, round, stream);
+    if (d == 128) return launch_groups<4, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, round, stream);
+    if (d == 256) return launch_groups<8, 2>(X, n, K, (const v4i*)Cp, (const v4i*)T2, buffer, assign, list, round, stream);
     return hipErrorInvalidValue;
 }
 

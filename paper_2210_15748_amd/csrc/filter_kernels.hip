@@ -1122,8 +1122,10 @@ static hipError_t launch_rest(const int8_t* X, uint64_t n, uint32_t K, const voi
 // for the eight launches.  Measured where it helps, vectors around 1024 centres (time of a k-means round against the comparison with
 // every centroid, first and later rounds): d = 128, K = 4096, 500 000 vectors 0.94, 1.05; 1.5M 0.66, 0.71; K = 6000, 170 000 0.77, 0.76;
 // K = 8192, 170 000 0.67, 0.68; K = 16 384, 500 000 0.37, 0.37, 1.5M 0.26, 0.24; K = 3000, 1.5M 1.14, 1.06.  d = 64 and 256 lie on the same line in
-// n * d: 500 000 vectors, K = 6000 0.98, 0.66 and 0.55, 0.53.  Where it does not help, vectors from all directions, the launches that find
-// that out cost 40 to 60 us (130 at d = 256, K = 16 384): 500 000 vectors, d = 128, K = 8192 1.08, K = 16 384 1.05.
+// n * d: 500 000 vectors, K = 6000 0.98, 0.66 and 0.55, 0.53.  Where it does not help, the launches that find
+// that out cost the first of eight rounds 32 to 55 us, up to 100 where groups form that vectors lie between, and the others 15: eight rounds of
+// 500 000 vectors, d = 128, from all directions K = 16 384 1.014, K = 8192 1.026, mixture of 1024 wide clusters 1.021, 1.041, 64 narrow ones 1.014,
+// 1.031; 170 000 vectors, K = 8192 1.05 to 1.07; one round alone 1.03 to 1.09, 170 000 vectors up to 1.2; 600 000 vectors, K = 65 536, one round 1.00 to 1.04.
 bool filter_groups_pay_from(uint32_t K) { return K >= 4096; }
 bool filter_groups_try(uint64_t n, uint32_t d, uint32_t K) {
     return filter_shape(d) && n > assign_few_max(d) && n <= 0xFFFFFFFFull && filter_groups_pay_from(K) && n >= 8ull * K &&
@@ -1131,11 +1133,11 @@ bool filter_groups_try(uint64_t n, uint32_t d, uint32_t K) {
 }
 
 hipError_t launch_filter_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
-                                uint32_t* assign, void* groups, uint32_t* list, hipStream_t stream) {
+                                uint32_t* assign, void* groups, uint32_t* list, uint32_t round, hipStream_t stream) {
     if (groups && list && filter_groups_try(n, d, K)) {
-        const hipError_t e = launch_group_assign(X, n, d, K, Cp, T2, groups, assign, list, stream);
+        const hipError_t e = launch_group_assign(X, n, d, K, Cp, T2, groups, assign, list, round, stream);
         if (e != hipSuccess) return e;
-        const Rest rest{(const GroupCtl*)groups, list, 65536};
+        const Rest rest{group_ctl(groups, round), list, 65536};
         if (d == 64) return launch_rest<2>(X, n, K, Cp, T2, assign, rest, stream);
         if (d == 128) return launch_rest<4>(X, n, K, Cp, T2, assign, rest, stream);
         return launch_rest<8>(X, n, K, Cp, T2, assign, rest, stream);

@@ -132,16 +132,19 @@ size_t filter_centroid_bytes(uint32_t K, uint32_t d);   // MFMA-ordered centroid
 size_t filter_table_bytes(uint32_t K);                  // per-row key constants
 hipError_t launch_filter_prep(const int8_t* Cn, uint32_t K, uint32_t d, void* Cp, void* T2, hipStream_t stream);
 // groups / list: nullptr, or filter_group_bytes(K, d) bytes (256-byte aligned) and n words of scratch, with which large assignments go by
-// groups of centroids (filter_groups_try says which sizes; the results are the same).
+// groups of centroids (filter_groups_try says which sizes; the results are the same).  round: of a training, whose rounds go through the same
+// scratch one after the other, from 0 on.
 hipError_t launch_filter_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
-                                uint32_t* assign, void* groups, uint32_t* list, hipStream_t stream);
+                                uint32_t* assign, void* groups, uint32_t* list, uint32_t round, hipStream_t stream);
 bool filter_groups_pay_from(uint32_t K);   // numbers of centroids for which they are tried at all
 bool filter_groups_try(uint64_t n, uint32_t d, uint32_t K);
 size_t filter_group_bytes(uint32_t K, uint32_t d);
 // assign[v] of the vectors that one group decides; the others go to list, their number and what decides how to go on to the GroupCtl at
-// the start of buffer (group_cost.hpp).
+// the start of buffer (group_ctl; group_cost.hpp).
 hipError_t launch_group_assign(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2, void* buffer,
-                               uint32_t* assign, uint32_t* list, hipStream_t stream);
+                               uint32_t* assign, uint32_t* list, uint32_t round, hipStream_t stream);
+struct GroupCtl;
+const GroupCtl* group_ctl(const void* buffer, uint32_t round);
 hipError_t launch_filter_distances(const int8_t* X, uint64_t n, uint32_t d, uint32_t K, const void* Cp, const void* T2,
                                    int32_t* out /*[n][filter_tiles(K)*32]*/, hipStream_t stream);
 // Update step of Lloyd's k-means: per-cluster coordinate sums and counts of the assigned vectors, then the rounded means

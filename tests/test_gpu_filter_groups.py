@@ -101,3 +101,41 @@ def test_kmeans_with_and_without_room_for_groups(d, K, n):
         assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 3, ws.data_ptr(), nbytes) == dz.OK
         got.append(cent)
     assert torch.equal(got[0], got[1])
+
+
+# Many centroids that lead only themselves: some look for their leaders first, from 32 768 centroids on.  Vectors lie close to centroids, so that the
+# groups are narrow; apart: all centroids alone, half: every other one beside the one before; no groups are made then.  few: one in four alone
+@pytest.mark.parametrize("kind", ["apart", "half", "few"])
+@pytest.mark.parametrize("d,K,n", [(64, 40_003, 320_100), (256, 32_768, 262_200)])
+def test_assignment_where_centroids_lead_themselves(kind, d, K, n):
+    say(f"centroids that lead themselves: {kind} d={d} K={K} n={n}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + K)
+    C = vectors(K, d, None, g)
+    step = {"apart": 1, "half": 2, "few": 4}[kind]
+    base = C[torch.arange(K, device=DEV) // step * step].int()
+    C = (base + torch.randint(-1, 2, (K, d), generator=g, device=DEV)).clamp(-127, 127).to(torch.int8)
+    X = (C[torch.randint(0, K, (n,), generator=g, device=DEV)].int() + torch.randint(-2, 3, (n, d), generator=g, device=DEV)).clamp(-127, 127).to(torch.int8)
+    assign, _, _ = dz.filter_build(handle(d, n), C, X)
+    want = closest(X, C)
+    assert torch.equal(assign, want), f"{int((assign != want).sum())} of {n} vectors"
+
+
+# Rounds of k-means after one whose groups did not pay: they are not tried again until the eighth after
+@pytest.mark.parametrize("clusters", [0, 20, 500])
+@pytest.mark.parametrize("d,K,n", [(128, 8192, 170_000), (256, 8200, 82_001)])
+def test_rounds_of_kmeans_with_and_without_room_for_groups(clusters, d, K, n):
+    say(f"rounds of k-means by groups: clusters={clusters} d={d} K={K} n={n}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d + K + clusters)
+    X = vectors(n, d, torch.randn(clusters, d, generator=g, device=DEV) / math.sqrt(d) if clusters else None, g)
+    start = X[torch.randint(0, n, (K,), generator=g, device=DEV)].contiguous()
+    ix = handle(d, 64)
+    full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
+    got = []
+    for nbytes in (full, full - 256):
+        ws = torch.randint(0, 256, (full,), generator=g, device=DEV, dtype=torch.uint8)   # what it holds from before does not matter
+        cent = start.clone()
+        assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 10, ws.data_ptr(), nbytes) == dz.OK
+        got.append(cent)
+    assert torch.equal(got[0], got[1])

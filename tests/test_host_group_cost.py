@@ -17,6 +17,7 @@ extern "C" int pays(uint32_t groups, uint32_t easy, uint32_t members, uint32_t K
     c.members = members;
     return dessert::groups_pay(c, K);
 }
+extern "C" int hopeless(uint32_t led, uint32_t alone) { return dessert::groups_hopeless(led, alone); }
 extern "C" uint32_t largest(uint32_t K) { return dessert::groups_largest(K); }
 extern "C" uint32_t room(uint32_t K) { return dessert::groups_room(K); }
 """
@@ -59,3 +60,9 @@ def test_a_group_never_costs_a_vector_more_than_every_centroid(rule, K):
     assert 56 * m <= 80 * m <= 1.1 * K
     assert TRIAL * m < 1 << 32
     assert not rule.pays(0, TRIAL, 0, K) and not rule.pays(rule.room(K) + 1, TRIAL, TRIAL, K)
+
+
+def test_when_leaders_are_not_looked_for(rule):
+    assert not rule.hopeless(0, 0)                                            # nothing known: fewer centroids than GROUP_MANY
+    assert rule.hopeless(8192, 8192) and rule.hopeless(4096, 4096 * 2 // 5)   # 1.24 of the time, see group_cost.hpp
+    assert not rule.hopeless(8192, 8192 // 4)
