@@ -594,7 +594,7 @@ hipError_t launch_groups(const int8_t* X, uint64_t n, uint32_t K, const v4i* Cp,
     const GroupLayout w = group_layout(K, KS * 32);
     char* base = (char*)buffer;
     GroupCtl* ctl = (GroupCtl*)(base + w.ctl) + (round & 1);
-    const GroupCtl* before = round % GROUP_RETRY ? (GroupCtl*)(base + w.ctl) + (~round & 1) : nullptr;
+    const GroupCtl* before = group_round_tries(round) ? nullptr : (GroupCtl*)(base + w.ctl) + (~round & 1);
     uint32_t *near = (uint32_t*)(base + w.near), *leader = (uint32_t*)(base + w.leader), *member = (uint32_t*)(base + w.member), *size = (uint32_t*)(base + w.size);
     uint32_t *leads = (uint32_t*)(base + w.leads), *starts = (uint32_t*)(base + w.starts);
     int32_t* Lw = (int32_t*)(base + w.Lw);

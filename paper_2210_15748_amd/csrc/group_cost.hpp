@@ -37,7 +37,8 @@ constexpr bool groups_pay(const GroupCtl& c, uint32_t K) {
 constexpr uint32_t GROUP_MANY = 32768;
 constexpr uint32_t GROUP_LOOKS = 128;   // workgroups
 constexpr bool groups_hopeless(uint32_t led, uint32_t alone) { return (uint64_t)alone * 10 > (uint64_t)led * 3; }
-// Rounds of k-means: where the groups of one did not pay, those of the next few are not made.
-constexpr uint32_t GROUP_RETRY = 8;
+// Rounds of k-means: where the groups of one did not pay, those of the next are not made.  Of every eight the first two always try: after the
+// first the centroids are means instead of vectors, which can change what pays.
+constexpr bool group_round_tries(uint32_t round) { return round % 8 < 2; }
 
 }  // namespace dessert

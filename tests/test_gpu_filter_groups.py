@@ -121,7 +121,7 @@ def test_assignment_where_centroids_lead_themselves(kind, d, K, n):
     assert torch.equal(assign, want), f"{int((assign != want).sum())} of {n} vectors"
 
 
-# Rounds of k-means after one whose groups did not pay: they are not tried again until the eighth after
+# Rounds of k-means after one whose groups did not pay: of every eight only the first two try in any case
 @pytest.mark.parametrize("clusters", [0, 20, 500])
 @pytest.mark.parametrize("d,K,n", [(128, 8192, 170_000), (256, 8200, 82_001)])
 def test_rounds_of_kmeans_with_and_without_room_for_groups(clusters, d, K, n):
