@@ -266,7 +266,10 @@ dessert_status_t dessert_set_debug(dessert_index_t *index, int enable);
  * The two bucket arrays must stay alive while dessert_filter_query is used.  This call waits for the
  * stream at its end (it reads the bucket sizes back: the largest one sizes the query workspace).  The
  * library's own filter buffers are allocated by the first call and kept while n_centroids and the
- * number of documents' id ranges stay the same: such a later call allocates and frees nothing.
+ * number of documents' id ranges stay the same: such a later call allocates and frees nothing.  (Large
+ * collections with 4096 centroids and more take scratch beside them, about 1.4 * d + 40 bytes per
+ * centroid, kept with them; a call allocates or frees it when the number of vectors comes to need it or
+ * no longer does, and does without it when there is no memory for it.)
  *
  * dessert_filter_query: for each query vector the filter_probe closest centroids; every document gets
  * one count per (query vector, probed centroid) pair whose bucket holds it; per query set the

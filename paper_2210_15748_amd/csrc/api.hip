@@ -95,6 +95,7 @@ struct dessert_index {
     void* f_table = nullptr;
     uint32_t* f_cursor = nullptr;
     void* f_groups = nullptr;                 // scratch of assignments by groups of centroids; nullptr: they are not tried
+    size_t f_groups_bytes = 0;
     uint32_t* f_sub_off = nullptr;   // [K*S+1] sub-bucket starts (library-owned)
     FilterSubPlan f_sub{1, 15};
     uint32_t f_K = 0;
@@ -951,8 +952,6 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
         if (ix->f_table) (void)hipFree(ix->f_table);
         if (ix->f_cursor) (void)hipFree(ix->f_cursor);
         if (ix->f_sub_off) (void)hipFree(ix->f_sub_off);
-        if (ix->f_groups) (void)hipFree(ix->f_groups);
-        ix->f_groups = nullptr;
         ix->f_cent = ix->f_table = nullptr;
         ix->f_cursor = ix->f_sub_off = nullptr;
         ix->f_alloc_K = 0;
@@ -962,12 +961,23 @@ dessert_status_t dessert_filter_build(dessert_index_t* ix, const int8_t* centroi
         if (e == hipSuccess) e = hipMalloc((void**)&ix->f_cursor, filter_cursor_bytes(n_sub));
         if (e == hipSuccess) e = hipMalloc((void**)&ix->f_sub_off, (n_sub + 1) * 4);
         if (e != hipSuccess) return fail(DESSERT_ENOMEM, "hipMalloc(filter state): %s", hipGetErrorString(e));
-        if (filter_groups_pay_from(n_centroids) && hipMalloc(&ix->f_groups, filter_group_bytes(n_centroids, ix->cfg.d)) != hipSuccess) {
+        ix->f_alloc_K = n_centroids;
+        ix->f_alloc_sub = n_sub;
+    }
+    // scratch of an assignment by groups, held only for sizes that use it
+    const size_t groups = filter_groups_try(ix->n_vectors, ix->cfg.d, n_centroids) ? filter_group_bytes(n_centroids, ix->cfg.d) : 0;
+    if (ix->f_groups_bytes != groups) {
+        if (ix->f_groups) {
+            HIP_TRY(hipStreamSynchronize(ix->stream));
+            (void)hipFree(ix->f_groups);
+            ix->f_groups = nullptr;
+        }
+        ix->f_groups_bytes = 0;
+        if (groups && hipMalloc(&ix->f_groups, groups) != hipSuccess) {
             ix->f_groups = nullptr;   // the build does without
             (void)hipGetLastError();
         }
-        ix->f_alloc_K = n_centroids;
-        ix->f_alloc_sub = n_sub;
+        if (ix->f_groups) ix->f_groups_bytes = groups;
     }
     ix->f_sub = sub;
     HIP_TRY(launch_filter_prep(centroids_dev, n_centroids, ix->cfg.d, ix->f_cent, ix->f_table, ix->stream));
