@@ -11,14 +11,14 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# 4 probes for sets of up to 31, 32, 33 and 34 vectors: 126, 130, 134 and 138 bins, of which rows hold 136 at most.  A set of equal vectors reaches
-# the largest count.  A workspace without room for the wide rows is accepted; a timed call hashes in its own stage.
+# 126, 130, 134, 138 and 254 to 257 bins, of which rows hold 256 at most (and the last two cases count to 255, a byte's largest, and beyond).  A
+# set of equal vectors reaches the largest count.  A workspace without room for the wide rows is accepted; a timed call hashes in its own stage.
 @pytest.mark.parametrize("n_sets", [2, 9])
-@pytest.mark.parametrize("max_q", [31, 32, 33, 34])
-def test_counts_of_four_probes(max_q, n_sets):
-    print("[case]", max_q, n_sets, flush=True)
+@pytest.mark.parametrize("max_q,probe", [(31, 4), (32, 4), (33, 4), (34, 4), (63, 4), (127, 2), (255, 1), (128, 2)])
+def test_counts_of_several_probes(max_q, probe, n_sets):
+    print("[case]", max_q, probe, n_sets, flush=True)
     rng = np.random.default_rng(max_q)
-    d, K, L, Cb, n_docs, probe, filter_k, k = 128, 37, 32, 7, 70_001, 4, 600, 50
+    d, K, L, Cb, n_docs, filter_k, k = 128, 37, 32, 7, 70_001, 600, 50
     lens = rng.integers(0, 5, n_docs)
     lens[:3], lens[-2:] = [150, 0, 150], [150, 0]
     off = np.concatenate([[0], np.cumsum(lens)])
@@ -38,10 +38,13 @@ def test_counts_of_four_probes(max_q, n_sets):
     obo, obd = orc.inverted_index(orc.assign_centroids(X, Cn), off, K)
     dc, qc = orc.hash_i8(X, R, L, Cb), orc.hash_i8(Q, R, L, Cb)
     ids, cnt = (t.cpu().numpy() for t in dz.filter_query(ix, Qd, q_lens, probe, filter_k))
-    assert cnt[0].max() == 4 * max_q
+    assert cnt[0].max() == probe * max_q
     full = int(dz.lib().dessert_filter_search_workspace_bytes(ix.handle, n_sets, int(qo[-1]), max_q, probe, filter_k, k))
     got = []
-    for nbytes in (full, full - 256) if max_q in (32, 33) else (full,):
+    wide = 128 < probe * max_q + 2 <= 256
+    if wide:   # a row of 256 counters per set and slab of 32 768 documents
+        assert full - int(dz.lib().dessert_filter_search_workspace_bytes(ix.handle, n_sets, int(qo[-1]), 31, 4, filter_k, k)) >= n_sets * 3 * 128 * 4
+    for nbytes in (full, full - 256) if wide else (full,):
         for timed in (False, True):
             ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device=DEV)
             dz.enable_timing(ix, timed)
