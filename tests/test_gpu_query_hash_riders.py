@@ -42,8 +42,9 @@ def test_counts_of_several_probes(max_q, probe, n_sets):
     full = int(dz.lib().dessert_filter_search_workspace_bytes(ix.handle, n_sets, int(qo[-1]), max_q, probe, filter_k, k))
     got = []
     wide = 128 < probe * max_q + 2 <= 256
-    if wide:   # a row of 256 counters per set and slab of 32 768 documents
-        assert full - int(dz.lib().dessert_filter_search_workspace_bytes(ix.handle, n_sets, int(qo[-1]), 31, 4, filter_k, k)) >= n_sets * 3 * 128 * 4
+    if wide:   # rows of 256 counters per set and slab of 32 768 documents, not of 128
+        narrow = dz.lib().dessert_filter_search_workspace_bytes(ix.handle, n_sets, int(qo[-1]), 126 // probe, probe, filter_k, k)
+        assert full - int(narrow) >= n_sets * 3 * 128 * 4
     for nbytes in (full, full - 256) if wide else (full,):
         for timed in (False, True):
             ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device=DEV)
