@@ -123,26 +123,30 @@ hipError_t launch_hash_scalar(const void* X, uint32_t dtype, uint64_t n, uint32_
 // 16-bit codes; or a matrix over 64 KB: d = 256 from 32 bytes of code row on) the tables are hashed in groups, one launch
 // per group: `codes` then points at the group's first byte of row 0, Rp at the group's matrix, and row_bytes (bytes from
 // one vector's codes to the next) is the full row.  The vectors are read once per group.
-// FUSED: the workgroups from hash_blocks on do not hash but carry out the riders (hash_riders.hpp), in the order of that struct; a grouping
-// has its bins in the LDS that holds R otherwise.
+// RIDERS: the workgroups from hash_blocks on do not hash but carry out riders (hash_riders.hpp), of either kind in instantiations of their own
+// (the join holds lists of keys in registers: with both in one kernel 128 dimensions and 16 tables took 128 of them where the grouping needs
+// 88, and at 32 tables a launch that carries a grouping of 128 lists of 8192 took 14.5 us instead of 14.1, of 256 lists of 4096 10.2 instead of 9.8);
+// a grouping has its bins in the LDS that holds R otherwise.
 // Threads per workgroup: a 64 KB matrix lets a CU hold two workgroups, and with four waves each the MFMA, the sign packing
 // and the loads of only two waves per SIMD do not overlap enough; eight waves share such a matrix.
 constexpr int mfma_threads(int KS, int LT) { return LT * KS * 1024 >= 64 * 1024 ? 512 : 256; }
 
 struct NoRiders {};
 
-template <int KS, int LT, int NT, bool WIDE, bool FUSED>
+constexpr int RIDERS_NONE = 0, RIDERS_LISTS = 1, RIDERS_MERGE = 2;   // none; a grouping and words to clear; a join of probe lists
+
+template <int KS, int LT, int NT, bool WIDE, int RIDERS>
 __global__ __launch_bounds__(mfma_threads(KS, LT)) void hash_mfma_i8_kernel(const int8_t* __restrict__ X, uint64_t n,
                                                            const v4i* __restrict__ Rp, uint32_t cmask,
                                                            uint8_t* __restrict__ codes, uint32_t row_bytes,
-                                                           uint32_t hash_blocks, std::conditional_t<FUSED, HashRiders, NoRiders> riders) {
+                                                           uint32_t hash_blocks, std::conditional_t<RIDERS != RIDERS_NONE, HashRiders, NoRiders> riders) {
     constexpr int D = KS * 32;
     constexpr int L = LT * 4;   // bytes per code row
     constexpr int OW = LT / 2;  // output dwords per lane (half a code row)
     constexpr int T = mfma_threads(KS, LT);
     constexpr int WAVES = T / 64;
     extern __shared__ v4i sR[];
-    if constexpr (FUSED) {
+    if constexpr (RIDERS == RIDERS_LISTS) {
         if (blockIdx.x >= hash_blocks) {
             __shared__ uint32_t wave_sum[WAVES];
             uint32_t job = blockIdx.x - hash_blocks;
@@ -151,13 +155,13 @@ __global__ __launch_bounds__(mfma_threads(KS, LT)) void hash_mfma_i8_kernel(cons
                 return;
             }
             job -= riders.order.n_lists;
-            const uint32_t zero_wgs = (uint32_t)((riders.zero_words + RIDER_ZERO_PER_WG - 1) / RIDER_ZERO_PER_WG);
-            if (job < zero_wgs) {
-                const uint64_t at = (uint64_t)job * RIDER_ZERO_PER_WG;
-                for (uint32_t i = threadIdx.x; i < RIDER_ZERO_PER_WG && at + i < riders.zero_words; i += T) riders.zero[at + i] = 0;
-                return;
-            }
-            probe_merge_any(riders.merge, (uint64_t)(job - zero_wgs) * WAVES + (threadIdx.x >> 6), threadIdx.x & 63);
+            const uint64_t at = (uint64_t)job * RIDER_ZERO_PER_WG;
+            for (uint32_t i = threadIdx.x; i < RIDER_ZERO_PER_WG && at + i < riders.zero_words; i += T) riders.zero[at + i] = 0;
+            return;
+        }
+    } else if constexpr (RIDERS == RIDERS_MERGE) {
+        if (blockIdx.x >= hash_blocks) {
+            probe_merge_any(riders.merge, (uint64_t)(blockIdx.x - hash_blocks) * WAVES + (threadIdx.x >> 6), threadIdx.x & 63);
             return;
         }
     }
@@ -343,24 +347,24 @@ static hipError_t launch_mfma_t(const int8_t* X, uint64_t n, uint32_t C, const v
     if (blocks > 16384 / WAVES) blocks = 16384 / WAVES;
     size_t lds = (size_t)LT * KS * 64 * 16;
     const uint32_t cmask = (1u << C) - 1u;
+    using Kernel = void (*)(const int8_t*, uint64_t, const v4i*, uint32_t, uint8_t*, uint32_t, uint32_t, HashRiders);
     if (riders) {
-        const uint64_t jobs = riders->order.n_lists + (riders->zero_words + RIDER_ZERO_PER_WG - 1) / RIDER_ZERO_PER_WG +
-                              (riders->merge.lists ? (riders->merge.n + WAVES - 1) / WAVES : 0);
+        const bool merge = riders->merge.lists != nullptr;
+        if (merge && (riders->order.n_lists || riders->zero_words)) return hipErrorInvalidValue;   // one kind to a launch
+        const uint64_t jobs = merge ? (riders->merge.n + WAVES - 1) / WAVES
+                                    : riders->order.n_lists + (riders->zero_words + RIDER_ZERO_PER_WG - 1) / RIDER_ZERO_PER_WG;
         if ((riders->order.n_lists && (size_t)riders->order.ranges * 4 > lds) || blocks + jobs > 0x7fffffffull) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)(blocks + jobs));
-        if (C <= 8)
-            hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, false, true>), grid, dim3(T), lds, stream, X, n,
-                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *riders);
-        else
-            hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, true, true>), grid, dim3(T), lds, stream, X, n,
-                               (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, *riders);
+        const Kernel kern = C <= 8 ? (merge ? hash_mfma_i8_kernel<KS, LT, NT, false, RIDERS_MERGE> : hash_mfma_i8_kernel<KS, LT, NT, false, RIDERS_LISTS>)
+                                   : (merge ? hash_mfma_i8_kernel<KS, LT, NT, true, RIDERS_MERGE> : hash_mfma_i8_kernel<KS, LT, NT, true, RIDERS_LISTS>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(blocks + jobs)), dim3(T), lds, stream, X, n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks,
+                           *riders);
         return hipGetLastError();
     }
     if (C <= 8)
-        hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, false, false>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
+        hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, false, RIDERS_NONE>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
                            n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, NoRiders{});
     else
-        hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, true, false>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
+        hipLaunchKernelGGL((hash_mfma_i8_kernel<KS, LT, NT, true, RIDERS_NONE>), dim3((unsigned)blocks), dim3(T), lds, stream, X,
                            n, (const v4i*)Rp, cmask, codes, row_bytes, (uint32_t)blocks, NoRiders{});
     return hipGetLastError();
 }

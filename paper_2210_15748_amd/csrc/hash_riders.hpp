@@ -72,9 +72,9 @@ __device__ inline void probe_merge_any(const ProbeMergeArgs& a, uint64_t v, uint
     else probe_merge<8>(a, v, lane);
 }
 
-struct HashRiders {
+struct HashRiders {   // a grouping and words to clear, or a join
     CandOrderArgs order;     // n_lists = 0: none.  A workgroup per list
-    int32_t* zero;           // words to clear (scores that partial sums are added to): ZERO_PER_WG to a workgroup
+    int32_t* zero;           // words to clear (scores that partial sums are added to): RIDER_ZERO_PER_WG to a workgroup
     uint64_t zero_words;
     ProbeMergeArgs merge;    // a wave per query vector
     bool any() const { return order.n_lists || zero_words || merge.lists; }

@@ -36,3 +36,14 @@ def test_comparing_with_every_centroid_spills_nothing(resources):
     kernels = {k: v for k, v in resources("filter_kernels").items() if re.search(r"filter_gemm_kernelILi\dELi4ELi0ELb", k)}
     assert len(kernels) == 6                                   # three widths, all vectors or those of a list
     assert {k: v for k, v in kernels.items() if v[1]} == {}
+
+
+def test_riders_leave_the_hashing_its_registers(resources):
+    """A launch that carries a grouping of candidate lists along keeps as many waves to a CU as the hashing alone."""
+    kernels = resources("hash_kernels")
+    shape = re.compile(r"hash_mfma_i8_kernelILi(\d)ELi(\d+)ELi2ELb([01])ELi(\d)EE")
+    table = {m.groups(): v[0] for k, v in kernels.items() if (m := shape.search(k))}
+    assert table
+    for (ks, lt, wide, riders), registers in table.items():
+        if riders == "1":
+            assert registers <= table[ks, lt, wide, "0"], (ks, lt, wide)
