@@ -84,23 +84,46 @@ def test_assignment_by_groups(kind, d, K, n):
     assert torch.equal(torch.sort(got).values, pairs)
 
 
+def without_groups(n, d, K):
+    """Bytes of a k-means workspace before the scratch for groups: assignment, sums, counts, the centroids' copies in tiles of 32 with their
+    constants, the vectors' order."""
+    up, rows = lambda x: (x + 255) // 256 * 256, (K + 31) // 32 * 32
+    return up(4 * n) + up(4 * K * d) + up(4 * K) + up(rows * d) + up(4 * rows) + up(4 * n)
+
+
+# What the launches decided stands at the start of the scratch: groups, radius, the trial's vectors that needed one group of 4096, the members of
+# those, vectors left over.  partly: as above, one round only (the centroids move to the vectors), enough left over for the kernel for many vectors
+# at d = 64 and 128.  all directions: one group of everything, or too many
+@pytest.mark.parametrize("kind,rounds", [("clusters", 1), ("clusters", 3), ("partly", 1), ("all directions", 1)])
 @pytest.mark.parametrize("d,K,n", [(128, 8192, 170_000), (64, 8223, 320_003), (256, 8200, 82_001)])
-def test_kmeans_with_and_without_room_for_groups(d, K, n):
-    say(f"k-means by groups: d={d} K={K} n={n}")
+def test_kmeans_with_and_without_room_for_groups(d, K, n, kind, rounds):
+    say(f"k-means by groups: {kind} {rounds} d={d} K={K} n={n}")
     g = torch.Generator(device=DEV)
     g.manual_seed(d + K)
-    X = vectors(n, d, torch.randn(500, d, generator=g, device=DEV) / math.sqrt(d), g)
+    X = vectors(n, d, None if kind == "all directions" else torch.randn(500, d, generator=g, device=DEV) / math.sqrt(d), g)
     start = X[torch.randint(0, n, (K,), generator=g, device=DEV)].contiguous()
+    if kind == "partly":
+        X[: int(0.45 * n)] = vectors(int(0.45 * n), d, torch.randn(900, d, generator=g, device=DEV) / math.sqrt(d), g)
+        X = X[torch.randperm(n, generator=g, device=DEV)].contiguous()
     ix = handle(d, 64)
-    full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
-    assert full > 4 * n + K * d, "the workspace has no room for groups: these sizes do not reach them"
+    full, before = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K)), without_groups(n, d, K)
+    assert full >= before + K * d + K // 3 * d, "the workspace has no room for groups: these sizes do not reach them"
     got = []
     for nbytes in (full, full - 256):   # a workspace without room for the groups is accepted
         ws = torch.empty(full, dtype=torch.uint8, device=DEV)
         cent = start.clone()
-        assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 3, ws.data_ptr(), nbytes) == dz.OK
+        assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, rounds, ws.data_ptr(), nbytes) == dz.OK
         got.append(cent)
+        if nbytes == full:
+            groups, _, easy, members, rest = ws[before:before + 20].view(torch.int32).tolist()
+            say("decided:", groups, easy, members, rest)
     assert torch.equal(got[0], got[1])
+    if kind == "clusters":
+        assert 100 < groups <= K // 3 and easy > 3000 and easy <= members < 4096 * (K // 75) and rest < 65536 and rest < n // 4
+    elif kind == "partly":
+        assert 100 < groups <= K // 3 and easy > 1500 and 0.4 * n < rest < 0.6 * n and (rest > 65536) == (d < 256)
+    else:
+        assert rest == 0 and (easy == 0 or groups > K // 3)
 
 
 # Many centroids that lead only themselves: some look for their leaders first, from 32 768 centroids on.  Vectors lie close to centroids, so that the

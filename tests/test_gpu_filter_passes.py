@@ -117,15 +117,30 @@ def test_kmeans_update_of_large_samples(d, n, K):
     X = (pool[torch.randint(0, 50, (n,), generator=g, device=DEV)] + torch.randint(-8, 9, (n, d), generator=g, device=DEV)).clamp(-128, 127).to(torch.int8)
     C = X[torch.randperm(n, generator=g, device=DEV)[:K]].contiguous()
     full = int(dz.lib().dessert_filter_kmeans_workspace_bytes(ix.handle, n, K))
-    order = (n * 4 + 255) // 256 * 256
+    up = lambda x: (x + 255) // 256 * 256
+    rows = (K + 31) // 32 * 32                          # the centroids' copies come in tiles of 32
+    least = up(4 * n) + up(4 * K * d) + up(4 * K) + up(rows * d) + up(4 * rows)   # assignment, sums, counts, centroids, their constants
+    order = up(4 * n)
+    assert full >= least + order                        # and what assignments by groups take, where they are tried
     got = []
-    for nbytes in (full, full - order):
+    for nbytes in (full, least + order - 256, least):   # with the order, without
         ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
         cent = C.clone()
         assert dz.lib().dessert_filter_kmeans(ix.handle, X.data_ptr(), n, cent.data_ptr(), K, 1, ws.data_ptr(), nbytes) == dz.OK
         got.append(cent.cpu().numpy())
-    assert np.array_equal(got[0], got[1])
-    # and the rounded means of a few clusters, from the assignments of the oracle's definition
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+    # the rounded means from an assignment and sums of their own: values below 2^24, exact in fp32
+    norm, Ct = (C.int() ** 2).sum(1), C.float().t().contiguous()
+    sums, counts = torch.zeros(K, d, dtype=torch.int64, device=DEV), torch.zeros(K, dtype=torch.int64, device=DEV)
+    for x in X.split(16384):
+        value = 2 * (x.float() @ Ct).int() - norm
+        first = torch.where(value == value.max(dim=1, keepdim=True).values, torch.arange(K, device=DEV, dtype=torch.int32), K).min(dim=1).values.long()
+        sums.index_add_(0, first, x.long())
+        counts.index_add_(0, first, torch.ones_like(first))
+    some = counts.clamp(min=1)[:, None]
+    means = torch.where(counts[:, None] > 0, (2 * sums + some).div(2 * some, rounding_mode="floor"), C.long())
+    assert np.array_equal(got[0], means.to(torch.int8).cpu().numpy())
+    # and of a few clusters, from the assignments of the oracle's definition
     if K <= 100:
         first = torch.arange(K, device=DEV)                                  # ties to the lower id
         near = lambda x: (128 * (2 * x @ C.double().T - (C.double() ** 2).sum(1)) - first).argmax(1)
