@@ -327,7 +327,9 @@ dessert_status_t dessert_filter_search(const dessert_index_t *index, const void 
  * dessert_get_timing waits for the chosen call's last event and writes
  * milliseconds: ms[0] hashing (a search: query preparation, i.e. hashing and the ordering of long
  * candidate lists), ms[1] scoring, ms[2] top-k, ms[3] whole call;
- * stages that did not run give 0.  calls_back = 0 is the most recent timed call. */
+ * stages that did not run give 0.  calls_back = 0 is the most recent timed call.  With timing on,
+ * dessert_filter_search hashes its query vectors in a launch of its own after the filter, where it may otherwise
+ * hash them beside the join of the probe lists: such a call takes a few microseconds more, and its stages are those of that form. */
 dessert_status_t dessert_enable_timing(dessert_index_t *index, int enable);
 dessert_status_t dessert_get_timing(dessert_index_t *index, uint32_t calls_back, float ms[4]);
 
