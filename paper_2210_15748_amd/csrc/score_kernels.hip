@@ -1440,6 +1440,7 @@ static hipError_t launch_masklut_t(const ScoreBatch& a, hipStream_t stream, char
         // reads that bound this form conflict less.  Eight lanes to a document, since there are few of them and they are long.  1000 documents
         // of m vectors, C = log2 m + 1, sets of m, a search: m = 256 16 sets 43 -> 38 us, 8 sets 45 -> 26; m = 128 16 sets 26 -> 20; m = 512 (C = 8)
         // 8 sets 67 -> 58.  Not for a grid of 64 workgroups (one set, m = 512, 27 -> 35), and not where the last four would be one chunk.
+        // (16 tables and tabulated maxima, where such entries would fit too, have not been measured and stay with pairs.)
         if (FOUR_CHUNKS_OK && remap == 0 && a.four_sets && chunks >= 4 && chunks % 4 != 1 && a.chunks == (uint64_t)chunks * a.n_queries &&
             mean_len >= 64 && ((a.max_scored + 63) / 64) * a.n_queries * ((chunks + 3) / 4) >= 100) {
             cf = true;
