@@ -193,7 +193,7 @@ struct FilterHistPlan {
     bool rows;
     size_t hist_off, seg_off, words;  // in u32 words from the start of the array
 };
-// wide_rows = false: rows up to 128 bins only, which takes less room for counts of 127 and 128.
+// wide_rows = false: rows up to 128 bins only, which takes less room for counts from 127 on.
 FilterHistPlan filter_hist_plan(uint32_t n_queries, uint32_t max_pairs, uint64_t n_docs, FilterSubPlan sp, bool wide_rows = true);
 // Per query set: one key (count, id) per document that at least one probed bucket holds, lists[b][0..cursor[b]).
 // max_pairs bounds (vectors of a query set) * probe, i.e. the largest possible count.  cursor: filter_hist_plan().words
