@@ -108,6 +108,7 @@ typedef struct {
  * f_1..f_L of Sec. 3 are fixed from here on.  With a Gaussian matrix the call may wait for the stream (the matrix is looked over
  * once, to choose the hashing kernel). */
 dessert_status_t dessert_create(const dessert_config_t *config, dessert_index_t **out);
+/* Waits for the handle's stream; may be called while another stream is captured, which goes on. */
 void dessert_destroy(dessert_index_t *index);
 
 /* Copy the projection matrix in use ([L*C][d], int8 or float) to proj_out_dev. */

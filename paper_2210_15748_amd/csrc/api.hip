@@ -668,7 +668,11 @@ dessert_status_t dessert_create(const dessert_config_t* c, dessert_index_t** out
 void dessert_destroy(dessert_index_t* ix) {
     if (!ix) return;
     DeviceGuard guard(ix->cfg.device);
-    (void)hipStreamSynchronize(ix->stream);
+    // A capture that is under way, on whatever stream: in its mode hipFree would be refused here, and the refusal would spoil the capture.  (A
+    // program that collects garbage may drop a handle in the middle of one.)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    if (!stream_capturing(ix)) (void)hipStreamSynchronize(ix->stream);
     if (ix->copy_stream) {
         (void)hipStreamSynchronize(ix->copy_stream);
         (void)hipStreamDestroy(ix->copy_stream);
@@ -693,6 +697,7 @@ void dessert_destroy(dessert_index_t* ix) {
         if (m.host) (void)hipHostFree(m.host);
         if (m.done) (void)hipEventDestroy(m.done);
     }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     delete ix;
 }
 
